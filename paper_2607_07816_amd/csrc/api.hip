@@ -39,13 +39,31 @@ u64 ceil_div(u64 a, u64 b) { return (a + b - 1) / b; }
 
 struct Layout {
     u64 ctl, ctl_save, keys[3], amps[3], side_key, side_w, side_amp, sub_key, sub_w, h1, h2, h2w, h3, best, rcount, rprefix, rtotal, look_comp,
-        t_above, t_side, t_off, tctr, dU, sub_cnt, wpart, sbins, gate, total;
+        t_above, t_side, t_off, w_all, w_kept, bd[2], tctr, dU, sub_cnt, wpart, sbins, gate, total;
 };
 
 // tiles of the LDS-tiled passes (2048 terms each) and the side-buffer entries:
 // one slab of 2048 << m entries per tile, m <= 3
 u64 tiled_tiles(u64 cap) { return (cap + 2047) / 2048 + 1; }
 u64 side_capacity(u64 cap) { return tiled_tiles(cap) * (2048ull << 3); }
+
+// bucket bits of a state of at most n terms: a bucket holds 32 to 64 terms of
+// a full state, so that a wave's share (four buckets) is one or two hundred
+// and the four runs a wave reads are at least 256 bytes long
+int bucket_bits(u64 n)
+{
+    int lg = 0;
+    while ((1ull << lg) < n && lg < 63) ++lg;
+    return std::max(lg - 6, STS_BKT_DIMS);
+}
+
+// largest state that is kept in bucket order (32-bit term indices, and bucket
+// tables of at most 2^22 entries)
+constexpr u64 kBucketMax = 1ull << 28;
+// and the smallest that a gate step puts there: below, the sort passes are
+// one or two short launches
+constexpr u64 kBucketMin = 1024;
+constexpr int kSlabShift = 10; // entries of a share's slab (log2): four per term of a share of 256
 
 Layout make_layout(u64 cap, int prec)
 {
@@ -79,9 +97,14 @@ Layout make_layout(u64 cap, int prec)
     L.rprefix = take(2048 * tiles * 8);
     L.rtotal = take(2048 * 8);
     L.look_comp = take(gtiles * 8);
-    L.t_above = take(ttiles * 4 * 4); // up to 4 slabs per tile
-    L.t_side = take(ttiles * 4 * 4);
-    L.t_off = take(ttiles * 8);
+    const u64 buckets = cap <= kBucketMax ? 1ull << bucket_bits(cap) : 0;
+    const u64 slabs = std::max(ttiles * 4, buckets / 4); // up to 4 slabs per tile
+    L.t_above = take(slabs * 4);
+    L.t_side = take(slabs * 4);
+    L.t_off = take(std::max(ttiles, buckets / 16) * 8);
+    L.w_all = take(buckets);  // a word per share of four buckets
+    L.w_kept = take(buckets);
+    for (int i = 0; i < 2; ++i) L.bd[i] = take(buckets * sizeof(uint2));
     L.tctr = take(16 * 4);
     L.dU = take(kULen * 8 + kULen * 4); // U in FP64, then its FP32 rounding
     L.sub_cnt = take((STS_SUB_REGIONS + 1) * 128);
@@ -147,6 +170,12 @@ struct sts_ctx {
     u64 *rprefix = nullptr, *rtotal = nullptr, *look_comp = nullptr;
     u32 *t_above = nullptr, *t_side = nullptr;
     u64 *t_off = nullptr;
+    u32 *w_all = nullptr, *w_kept = nullptr;
+    uint2 *bd[2] = {nullptr, nullptr}; // bucket tables
+    bool bucketed = false;  // the state in buffer cur is in bucket order:
+    int hb = 0, bdc = 0;    // 2^hb buckets, table bd[bdc]
+    bool bkt_pending = false; // the pending gate is a bucketed step
+    int prev_m = 0, prev_q[2] = {0, 0}; // the qubits of the last bucketed step
     u32 *tctr = nullptr;
     double *dU = nullptr;
     u32 *sub_cnt = nullptr;
@@ -277,6 +306,11 @@ PassBufs pass_bufs(sts_ctx *c, int in, int out)
     b.t_above = c->t_above;
     b.t_side = c->t_side;
     b.t_off = c->t_off;
+    b.w_all = c->w_all;
+    b.w_kept = c->w_kept;
+    b.bd_in = c->bd[c->bdc];
+    b.bd_out = c->bd[c->bdc ^ 1];
+    b.slab_shift = kSlabShift;
     b.tile_ctr = c->tctr + 4;
     b.wpart = c->wpart;
     b.sbins = c->sbins;
@@ -330,6 +364,9 @@ void bind_layout(sts_ctx *c, const Layout &L)
     c->t_above = (u32 *)(c->mem + L.t_above);
     c->t_side = (u32 *)(c->mem + L.t_side);
     c->t_off = (u64 *)(c->mem + L.t_off);
+    c->w_all = (u32 *)(c->mem + L.w_all);
+    c->w_kept = (u32 *)(c->mem + L.w_kept);
+    for (int i = 0; i < 2; ++i) c->bd[i] = (uint2 *)(c->mem + L.bd[i]);
     c->tctr = (u32 *)(c->mem + L.tctr);
     c->dU = (double *)(c->mem + L.dU);
     c->sub_cnt = (u32 *)(c->mem + L.sub_cnt);
@@ -368,7 +405,7 @@ sts_status refuse_step(sts_ctx *c)
 {
     STS_TRY(c, hipMemcpyAsync(c->ctl, c->ctl_save, sizeof(DevCtl), hipMemcpyDeviceToDevice, c->stream));
     STS_TRY(c, hipStreamSynchronize(c->stream));
-    c->pending = false;
+    c->pending = c->bkt_pending = false;
     return STS_E_CAPACITY;
 }
 
@@ -418,10 +455,109 @@ sts_status sort_state(sts_ctx *c, const u64 *notmask, int *sorted, int *hb_out)
     return STS_OK;
 }
 
+// whether a gate of m qubits on the current state is a bucketed step
+bool use_buckets(const sts_ctx *c, int m)
+{
+    return m <= 2 && c->cap <= kBucketMax && c->n_bound >= kBucketMin;
+}
+
+// whether the state's buckets suit its size bound: neither so few that a
+// share overflows a wave's tables nor so many that they hold a handful
+bool buckets_suit(const sts_ctx *c)
+{
+    const int ideal = bucket_bits(c->n_bound);
+    return c->bucketed && c->hb >= ideal - 1 && c->hb <= ideal + 2;
+}
+
+// the size bound after a gate of m qubits and the cut that follows it
+u64 bound_after(const sts_ctx *c, int m)
+{
+    const u64 cb = sat_shl(c->n_bound, m);
+    return std::min(c->K ? std::min<u64>(c->K, cb) : cb, c->cap);
+}
+
+// the kernel description's part that depends on the state's order: the
+// bucket geometry, or the sort's bucket bits
+void place_gate(const sts_ctx *c, GateArg *g, const int *qubits)
+{
+    if (use_buckets(c, g->m)) {
+        const int hb = buckets_suit(c) ? c->hb : bucket_bits(c->n_bound);
+        const int delta = std::min(std::max(bucket_bits(bound_after(c, g->m)) - hb, 0), 4);
+        g->bkt = bkt_plan(hb, delta, g->m, qubits, c->prev_m, c->prev_q);
+    } else {
+        g->hb = sts_radix_bits(sort_shape(c)) * sort_passes(c); // the bucket bits the sort uses
+    }
+}
+
+// put the state in bucket order unless it is (sorting by the bucket hash's
+// top digits: one 11-bit pass while that is enough and the passes are short)
+sts_status bucketize(sts_ctx *c)
+{
+    if (buckets_suit(c)) return STS_OK;
+    const int hb = bucket_bits(c->n_bound);
+    const int shape = hb <= 11 ? STS_RADIX_11x8 : STS_RADIX_8x16;
+    const int bits = sts_radix_bits(shape);
+    const int npass = (hb + bits - 1) / bits;
+    const int tiles = (int)std::max<u64>(ceil_div(c->n_bound, sts_radix_tile(shape)), 1);
+    const int a = (c->cur + 1) % 3, b = (c->cur + 2) % 3;
+    int src = c->cur, dst = a;
+    for (int p = 0; p < npass; ++p) {
+        for (int what = 0; what < 3; ++what) {
+            const int kind = what == 0 ? STS_K_RADIX_HIST : (what == 1 ? STS_K_RADIX_SCAN : STS_K_RADIX_PASS);
+            STS_LAUNCH(c, kind, launch_radix(what, shape, c->prec, c->keys[src], c->amps[src], c->keys[dst],
+                                             c->amps[dst], &c->ctl->cnt[src], &c->ctl->cnt[dst], nullptr,
+                                             64 - bits * npass + bits * p, c->rcount, c->rprefix, c->rtotal,
+                                             c->tiles_cap, tiles, c->stream));
+        }
+        src = dst;
+        dst = dst == a ? b : a;
+    }
+    STS_LAUNCH(c, STS_K_RADIX_SCAN,
+               launch_bucket_bounds(c->keys[src], &c->ctl->cnt[src], c->n_bound, hb, c->bd[c->bdc], c->stream));
+    c->cur = src;
+    c->hb = hb;
+    c->bucketed = true;
+    return STS_OK;
+}
+
+int bucket_tiles(const sts_ctx *c) { return 1 << (c->gate.bkt.hb - STS_BKT_DIMS); }
+
+int bucket_hist_groups(const sts_ctx *c)
+{
+    return std::min(bucket_tiles(c), bucket_hist_capacity(c->prec, c->gate.m));
+}
+
+// the passes that write the pending bucketed step's survivors to buffer dst
+sts_status bucket_write(sts_ctx *c, const PassBufs &b, int dst, u64 bound)
+{
+    const int tiles = bucket_tiles(c);
+    STS_LAUNCH(c, STS_K_GROUP_EXTRACT, launch_bucket_pass(STS_BKT_COUNT, c->prec, c->gate.m, b, tiles, c->stream));
+    STS_LAUNCH(c, STS_K_TILE_KEPT, launch_bucket_kept(b, tiles, c->stream));
+    STS_LAUNCH(c, STS_K_GROUP_EMIT, launch_bucket_pass(STS_BKT_EMIT, c->prec, c->gate.m, b, tiles, c->stream));
+    c->cur = dst;
+    c->n_bound = bound;
+    c->hb = c->gate.bkt.hb + c->gate.bkt.delta;
+    c->bdc ^= 1;
+    c->bucketed = true;
+    c->bkt_pending = c->pending = false;
+    c->prev_m = c->gate.m;
+    for (int t = 0; t < c->gate.m; ++t) c->prev_q[t] = c->gate.q[t];
+    return STS_OK;
+}
+
 // number of nonzero candidates of the pending gate (synchronises)
 sts_status count_candidates(sts_ctx *c, u64 *count)
 {
     PassBufs b = pass_bufs(c, c->cur, -1);
+    if (c->bkt_pending) {
+        STS_LAUNCH(c, STS_K_GROUP_HIST,
+                   launch_bucket_pass(STS_BKT_HIST, c->prec, c->gate.m, b, bucket_tiles(c), c->stream));
+        STS_LAUNCH(c, STS_K_PICK1, launch_pick1(b, 0, 1, 0, c->stream));
+        const sts_status st = sync_ctl(c);
+        if (st != STS_OK) return st;
+        *count = c->hctl->cand_all;
+        return STS_OK;
+    }
     const bool tiled = use_tiles(c, c->gate.m);
     const int G = hist_groups(c->prec, c->n_bound, c->gate.m, tiled);
     STS_LAUNCH(c, STS_K_GROUP_HIST, launch_group_hist(c->prec, c->gate, b, G, tiled, c->stream));
@@ -443,7 +579,7 @@ sts_status materialise(sts_ctx *c)
         const sts_status st = count_candidates(c, &count);
         if (st != STS_OK) return st;
         if (count > c->cap) {
-            c->pending = false; // drop the gate: the sorted input is the state before it
+            c->pending = c->bkt_pending = false; // drop the gate: the sorted input is the state before it
             return STS_E_CAPACITY;
         }
         bound = count;
@@ -451,6 +587,7 @@ sts_status materialise(sts_ctx *c)
     const int dst = (c->cur + 1) % 3;
     PassBufs b = pass_bufs(c, c->cur, dst);
     b.materialise = 1;
+    if (c->bkt_pending) return bucket_write(c, b, dst, std::min(bound, c->cap));
     if (use_tiles(c, c->gate.m)) {
         const int tt = (int)std::max<u64>(ceil_div(c->n_bound, 2048), 1);
         STS_LAUNCH(c, STS_K_GROUP_EXTRACT,
@@ -465,6 +602,7 @@ sts_status materialise(sts_ctx *c)
     }
     c->cur = dst;
     c->n_bound = std::min(bound, c->cap);
+    c->bucketed = false;
     c->pending = false;
     return STS_OK;
 }
@@ -657,9 +795,17 @@ sts_status sts_apply_gate(sts_ctx *c, int m, const int *qubits, const double *U)
         g.uptr_f = reinterpret_cast<const float *>(c->dU + nd);
     }
     int sorted = c->cur, hb = 8;
-    g.hb = sts_radix_bits(sort_shape(c)) * sort_passes(c); // the bucket bits the sort below uses
+    place_gate(c, &g, qubits);
     STS_TRY(c, launch_set_gate(g, c->dgate, c->stream));
     c->gate_dev = c->dgate;
+    if (use_buckets(c, m)) {
+        st = bucketize(c);
+        if (st != STS_OK) return st;
+        c->gate = g;
+        c->pending = c->bkt_pending = true;
+        return STS_OK;
+    }
+    c->bucketed = false;
     st = sort_state(c, &c->dgate->notmask, &sorted, &hb);
     if (st != STS_OK) return st;
     c->cur = sorted;
@@ -668,10 +814,45 @@ sts_status sts_apply_gate(sts_ctx *c, int m, const int *qubits, const double *U)
     return STS_OK;
 }
 
+static sts_status truncate_buckets(sts_ctx *c)
+{
+    const u64 cb = sat_shl(c->n_bound, c->gate.m);
+    const int out = (c->cur + 1) % 3;
+    PassBufs b = pass_bufs(c, c->cur, out);
+    const int m = c->gate.m, tiles = bucket_tiles(c), G = bucket_hist_groups(c);
+    u64 nb = c->K ? std::min<u64>(c->K, cb) : cb;
+    sts_status st = STS_OK;
+    const bool out_risk = nb > c->cap; // a cut limited by p-mass alone may keep more than cap terms
+    if (out_risk) {
+        st = save_ctl(c);
+        if (st != STS_OK) return st;
+    }
+    if (c->n_bound >= STS_SAMPLE_MIN)
+        STS_LAUNCH(c, STS_K_SAMPLE, launch_bucket_pass(STS_BKT_SAMPLE, c->prec, m, b, tiles, c->stream));
+    b.predict = 1;
+    STS_LAUNCH(c, STS_K_GROUP_HIST, launch_bucket_pass(STS_BKT_HIST, c->prec, m, b, tiles, c->stream));
+    b.predict = 0;
+    STS_LAUNCH(c, STS_K_PICK1, launch_pick1(b, G, 0, 2, c->stream));
+    STS_LAUNCH(c, STS_K_GROUP_EXTRACT, launch_bucket_pass(STS_BKT_EXTRACT, c->prec, m, b, tiles, c->stream));
+    const int sg = (int)std::min<u64>(std::max<u64>(ceil_div(std::min(cb, c->scap), 256), 1), STS_SIDE_GROUPS);
+    STS_LAUNCH(c, STS_K_SIDE_HIST, launch_side_hist(b, c->h2, sg, c->stream));
+    STS_LAUNCH(c, STS_K_SIDE_EXTRACT, launch_side_extract(b, std::max(sg, (tiles + 3) / 4), c->stream));
+    STS_LAUNCH(c, STS_K_FINAL, launch_final(b, c->stream));
+    if (out_risk) {
+        st = sync_ctl(c);
+        if (st != STS_OK) return st;
+        const u64 L = c->hctl->keep_all ? c->hctl->n_cand : c->hctl->L;
+        if (L > c->cap) return refuse_step(c);
+        nb = L;
+    }
+    return bucket_write(c, b, out, nb);
+}
+
 sts_status sts_truncate(sts_ctx *c)
 {
     sts_status st = check_live(c);
     if (st != STS_OK) return st;
+    if (c->pending && c->bkt_pending) return truncate_buckets(c);
     if (!c->pending) {
         c->gate = identity_gate();
         c->gate_dev = c->dgate_id;
@@ -748,6 +929,7 @@ sts_status sts_truncate(sts_ctx *c)
     }
     c->cur = out;
     c->n_bound = nb;
+    c->bucketed = false;
     c->pending = false;
     return STS_OK;
 }
@@ -849,7 +1031,8 @@ sts_status sts_load_terms(sts_ctx *c, uint64_t n, const uint64_t *keys, const do
     for (u64 i = 1; i < n; ++i)
         if (sk[i] == sk[i - 1]) return STS_E_ARG;
     // the state is replaced: any pending gate is dropped
-    c->pending = false;
+    c->pending = c->bkt_pending = false;
+    c->bucketed = false;
     if (n) {
         STS_TRY(c, hipMemcpyAsync(c->keys[c->cur], keys, n * 8, hipMemcpyHostToDevice, c->stream));
         if (c->prec == STS_C128) {
@@ -1017,6 +1200,10 @@ struct StepGraph {
     hipGraphNode_t set_node;
     int cur_after;
     u64 nb_after;
+    bool bucketed;       // the state's order before the step, and after
+    int hb, bdc;
+    bool bucketed_after;
+    int hb_after, bdc_after;
 };
 
 struct StepGraphs {
@@ -1060,12 +1247,17 @@ sts_status step_replayed(sts_ctx *c, StepGraphs *gs, int m, const int *qubits, c
     }
     StepGraph *hit = nullptr;
     for (auto &e : gs->v)
-        if (e.m == m && e.cur == c->cur && e.nb == c->n_bound) hit = &e;
+        if (e.m == m && e.cur == c->cur && e.nb == c->n_bound && e.bucketed == c->bucketed &&
+            e.bdc == c->bdc && (!e.bucketed || e.hb == c->hb))
+            hit = &e;
     if (!hit) {
         StepGraph e{};
         e.m = m;
         e.cur = c->cur;
         e.nb = c->n_bound;
+        e.bucketed = c->bucketed;
+        e.hb = c->hb;
+        e.bdc = c->bdc;
         STS_TRY(c, hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
         st = sts_apply_gate(c, m, qubits, U);
         if (st == STS_OK) st = sts_truncate(c);
@@ -1079,6 +1271,9 @@ sts_status step_replayed(sts_ctx *c, StepGraphs *gs, int m, const int *qubits, c
         e.graph = graph;
         e.cur_after = c->cur;
         e.nb_after = c->n_bound;
+        e.bucketed_after = c->bucketed;
+        e.hb_after = c->hb;
+        e.bdc_after = c->bdc;
         // the one launch that writes the gate
         size_t nn = 0;
         hipError_t he = hipGraphGetNodes(graph, nullptr, &nn);
@@ -1106,7 +1301,11 @@ sts_status step_replayed(sts_ctx *c, StepGraphs *gs, int m, const int *qubits, c
     // replay with the new gate: the same bucket bits (same size bound)
     GateArg g;
     fill_gate(&g, m, qubits, U);
-    g.hb = sts_radix_bits(sort_shape(c)) * sort_passes(c);
+    place_gate(c, &g, qubits);
+    if (use_buckets(c, m)) {
+        c->prev_m = m;
+        for (int t = 0; t < m; ++t) c->prev_q[t] = qubits[t];
+    }
     GateArg *dst = c->dgate;
     void *args[2] = {&g, &dst};
     hipKernelNodeParams p{};
@@ -1120,6 +1319,9 @@ sts_status step_replayed(sts_ctx *c, StepGraphs *gs, int m, const int *qubits, c
     STS_TRY(c, hipGraphLaunch(hit->exec, c->stream));
     c->cur = hit->cur_after;
     c->n_bound = hit->nb_after;
+    c->bucketed = hit->bucketed_after;
+    c->hb = hit->hb_after;
+    c->bdc = hit->bdc_after;
     c->gate = g;
     c->gate_dev = c->dgate;
     c->pending = false;

@@ -1,0 +1,129 @@
+// bucket.hip - bucketed gate steps: dispatch by precision, the survivor
+// counts and offsets, and the bucket table of a freshly ordered state.
+#include <algorithm>
+
+#include "kernels.h"
+
+hipError_t bucket_c128_pass(int kind, int m, const PassBufs &b, int tiles, hipStream_t s);
+hipError_t bucket_c64_pass(int kind, int m, const PassBufs &b, int tiles, hipStream_t s);
+int bucket_c128_capacity(int m);
+int bucket_c64_capacity(int m);
+
+namespace {
+
+constexpr int KT = 1024;
+
+// The survivors of every share and the output offset of every tile. When the
+// window held the cut, a share's survivors are its entries above the window
+// and those of the window ranked at or above the threshold term (16 lanes per
+// share, a wave per tile); when nothing is cut, all its candidates; otherwise
+// the counting pass has them. The last workgroup scans the tiles' sums.
+__global__ void __launch_bounds__(KT) k_bkt_kept(PassBufs b)
+{
+    __shared__ u32 s_flag;
+    __shared__ u64 s_scratch[KT / 64];
+    constexpr int UN = 4;
+    DevCtl *ctl = b.ctl;
+    const u32 ntiles = 1u << (b.gate->bkt.hb - STS_BKT_DIMS);
+    const u64 thr_w = ctl->thr_wbits, thr_k = ctl->thr_key;
+    const int shift = ctl->side_slab_shift;
+    const bool all = !b.materialise && ctl->keep_all, hit = !b.materialise && !ctl->keep_all && ctl->pred_hit;
+    const u32 lane = (u32)sts_lane(), sub = lane >> 4, l16 = lane & 15u;
+    for (u32 tile = blockIdx.x * (KT / 64) + (threadIdx.x >> 6); tile < ntiles; tile += gridDim.x * (KT / 64)) {
+        const u32 sl = (tile << 2) + sub;
+        u32 c = 0;
+        if (hit) {
+            const u32 ns = b.t_side[sl];
+            const u64 base = (u64)sl << shift;
+            for (u32 i0 = l16; i0 < ns; i0 += UN * 16) {
+                u64 w[UN], k[UN];
+#pragma unroll
+                for (int r = 0; r < UN; ++r) {
+                    const u32 i = i0 + 16u * (u32)r;
+                    w[r] = b.side_w[base + (i < ns ? i : 0u)];
+                    k[r] = b.side_key[base + (i < ns ? i : 0u)];
+                }
+#pragma unroll
+                for (int r = 0; r < UN; ++r) {
+                    const u32 i = i0 + 16u * (u32)r;
+                    c += (i < ns && (w[r] > thr_w || (w[r] == thr_w && k[r] <= thr_k))) ? 1u : 0u;
+                }
+            }
+            if (l16 == 0) c += b.t_above[sl];
+#pragma unroll
+            for (int d = 8; d > 0; d >>= 1) c += __shfl_xor(c, d, 64);
+        } else {
+            c = all ? b.w_all[sl] : b.w_kept[sl];
+        }
+        if (l16 == 0 && (hit || all)) b.w_kept[sl] = c;
+        c += __shfl_xor(c, 16, 64);
+        c += __shfl_xor(c, 32, 64);
+        if (lane == 0) b.t_off[tile] = c;
+    }
+    if (!sts_last_block(&ctl->done[3], &s_flag)) return;
+    constexpr int CH = 16;
+    u64 carry = 0;
+    for (u32 t0 = 0; t0 < ntiles; t0 += KT * CH) {
+        const u32 lo = t0 + threadIdx.x * CH;
+        u64 v[CH], sum = 0;
+#pragma unroll
+        for (int k = 0; k < CH; ++k) v[k] = lo + k < ntiles ? ld_agent(&b.t_off[lo + k]) : 0ull;
+#pragma unroll
+        for (int k = 0; k < CH; ++k) sum += v[k];
+        u64 total;
+        u64 run = block_excl_scan<u64, KT>(sum, s_scratch, &total) + carry;
+#pragma unroll
+        for (int k = 0; k < CH; ++k) {
+            if (lo + k < ntiles) st_agent(&b.t_off[lo + k], run);
+            run += v[k];
+        }
+        carry += total;
+    }
+    if (threadIdx.x == 0) {
+        *b.n_out = carry;
+        if (carry > b.out_cap) atomicOr(&ctl->flags, STS_F_OUT_OVERFLOW);
+    }
+}
+
+// bd[b] = (first, one past the last) term of bucket b; cleared before
+__global__ void __launch_bounds__(256) k_bkt_bounds(const u64 *__restrict__ keys, const u64 *n_in, int hb, uint2 *bd)
+{
+    const u64 n = *n_in;
+    const auto bucket = [&](u64 key) { // the top hb bits of the hash
+        u32 v = 0;
+        for (int i = 0; i < hb; ++i) v |= sts_parity(key, k_lin_masks[32 - hb + i]) << i;
+        return v;
+    };
+    for (u64 i = (u64)blockIdx.x * 256 + threadIdx.x; i < n; i += (u64)gridDim.x * 256) {
+        const u32 b1 = bucket(keys[i]);
+        const bool first = i == 0 || bucket(keys[i - 1]) != b1;
+        const bool last = i + 1 == n || bucket(keys[i + 1]) != b1;
+        if (first) bd[b1].x = (u32)i;
+        if (last) bd[b1].y = (u32)i + 1;
+    }
+}
+
+} // namespace
+
+int bucket_hist_capacity(int prec, int m) { return prec == 0 ? bucket_c128_capacity(m) : bucket_c64_capacity(m); }
+
+hipError_t launch_bucket_pass(int kind, int prec, int m, const PassBufs &b, int tiles, hipStream_t s)
+{
+    return prec == 0 ? bucket_c128_pass(kind, m, b, tiles, s) : bucket_c64_pass(kind, m, b, tiles, s);
+}
+
+hipError_t launch_bucket_kept(const PassBufs &b, int tiles, hipStream_t s)
+{
+    const int grid = std::max(1, std::min((tiles + KT / 64 - 1) / (KT / 64), 256));
+    hipLaunchKernelGGL(k_bkt_kept, dim3(grid), dim3(KT), 0, s, b);
+    return hipGetLastError();
+}
+
+hipError_t launch_bucket_bounds(const u64 *keys, const u64 *n_in, u64 n_bound, int hb, uint2 *bd, hipStream_t s)
+{
+    hipError_t e = launch_fill_zero(reinterpret_cast<u64 *>(bd), 1ull << hb, s);
+    if (e != hipSuccess) return e;
+    const u64 grid = std::max<u64>(1, std::min<u64>((n_bound + 255) / 256, 4096));
+    hipLaunchKernelGGL(k_bkt_bounds, dim3((unsigned)grid), dim3(256), 0, s, keys, n_in, hb, bd);
+    return hipGetLastError();
+}

@@ -1,0 +1,20 @@
+// bucket_c128.hip - instantiations of the bucketed gate step (bucket_impl.h) for
+// double2 amplitudes; compiled as a unit of its own so the library builds in
+// parallel.
+#include <algorithm>
+
+#include "bucket_impl.h"
+
+hipError_t bucket_c128_pass(int kind, int m, const PassBufs &b, int tiles, hipStream_t s)
+{
+    switch (m) {
+    case 1: return sts_bucket::launch_m<double2, 1>(kind, b, tiles, s);
+    case 2: return sts_bucket::launch_m<double2, 2>(kind, b, tiles, s);
+    }
+    return hipErrorInvalidValue;
+}
+
+int bucket_c128_capacity(int m)
+{
+    return m == 1 ? sts_bucket::hist_capacity_b<double2, 1>() : sts_bucket::hist_capacity_b<double2, 2>();
+}

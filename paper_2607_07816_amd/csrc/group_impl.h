@@ -1028,114 +1028,102 @@ __global__ void __launch_bounds__(STS_WG, M >= 4 ? 3 : 5) k_tile_hist(const Gate
 // previous cut the pass does nothing (the histogram pass then predicts
 // nothing).
 // ---------------------------------------------------------------------------
-template <typename AT, int M>
-__global__ void __launch_bounds__(STS_WG) k_tile_sample(const GateArg *__restrict__ gp, PassBufs b)
+// a sampling workgroup's bins and totals
+struct SampleSmem {
+    u32 c[STS_SW_NB];
+    float m[STS_SW_NB];
+    u64 scan_c[STS_WG / 64];
+    double scan_m[STS_WG / 64];
+    u32 flag, hit, cab, inputs;
+    float mab, mbe;
+};
+
+// a thread's candidates outside the bins
+struct SampleAcc {
+    u32 c_above = 0;
+    float m_above = 0.f, m_below = 0.f;
+};
+
+// clear the bins (the caller's barrier follows)
+__device__ __forceinline__ void sample_begin(SampleSmem &s)
 {
-    const GateArg &g = *gp;
-    stage_gate<AT, M>(g);
-    constexpr int SPAN = STS_SAMPLE_SPAN; // inputs per workgroup, from a tile's start
-    __shared__ TileSmem<AT> s;
-    __shared__ u32 s_c[STS_SW_NB];
-    __shared__ float s_m[STS_SW_NB];
-    __shared__ u64 s_scan_c[STS_WG / 64];
-    __shared__ double s_scan_m[STS_WG / 64];
-    __shared__ u32 s_flag, s_hit, s_cab;
-    __shared__ float s_mab, s_mbe;
     static_assert(STS_SW_NB == STS_WG, "one bin per thread in the last workgroup");
-    DevCtl *ctl = b.ctl;
-    const u64 n = *b.n_in; // loaded with the control word, before the test
-    const int e_prev = ctl->e_pred;
-    if (e_prev < 0) return; // uniform: nothing to centre the bins on
-    const int e_lo = e_prev - STS_SW_EXPS / 2; // exponent field of bin row 0
-    s_c[threadIdx.x] = 0;
-    s_m[threadIdx.x] = 0.f;
+    s.c[threadIdx.x] = 0;
+    s.m[threadIdx.x] = 0.f;
     if (threadIdx.x == 0) {
-        s_cab = 0;
-        s_mab = 0.f;
-        s_mbe = 0.f;
+        s.cab = 0;
+        s.inputs = 0;
+        s.mab = 0.f;
+        s.mbe = 0.f;
     }
-    const u64 *keys = b.keys;
-    const AT *amps = (const AT *)b.amps;
-    const u64 ntiles = (n + TT_TG - 1) / TT_TG;
-    const u64 stride = ntiles > gridDim.x ? ntiles / gridDim.x : 1;
-    const u64 tile = (u64)blockIdx.x * stride;
-    // STS_SW_BANKS copies of the bins, workgroup w adding to copy w %
-    // STS_SW_BANKS: atomics on one address from every workgroup would queue
-    // behind each other
+}
+
+__device__ __forceinline__ void sample_add(SampleSmem &s, SampleAcc &a, u64 wb, int e_lo)
+{
+    const float w = (float)__longlong_as_double((long long)wb);
+    const int row = (int)(wb >> 52) - e_lo;
+    if (row >= STS_SW_EXPS) {
+        ++a.c_above;
+        a.m_above += w;
+    } else if (row < 0) {
+        a.m_below += w;
+    } else {
+        const int f = (row << STS_SW_FB) | (int)((wb >> (52 - STS_SW_FB)) & ((1u << STS_SW_FB) - 1));
+        atomicAdd(&s.c[f], 1u);
+        atomicAdd(&s.m[f], w);
+    }
+}
+
+// add the workgroup's bins to one of STS_SW_BANKS copies in device memory
+// (atomics on one address from every workgroup would queue behind each
+// other); `inputs`: the inputs this thread speaks for. Workgroup totals of
+// the out-of-range parts (wave sums, then LDS), then one global atomic per
+// non-empty bin and per total, on the workgroup's bank.
+__device__ __forceinline__ void sample_flush(SampleSmem &s, SampleAcc &a, const PassBufs &b, u32 inputs)
+{
     const int bank = (int)(blockIdx.x % STS_SW_BANKS);
     u32 *gc = reinterpret_cast<u32 *>(b.sbins);                                   // [bank][bin] counts
     float *gm = reinterpret_cast<float *>(b.sbins + STS_SW_BANKS * STS_SW_NB / 2); // [bank][bin] masses
     // per bank: [0] inputs sampled, [1] count above the bins, [2] (float) mass
     // above, [3] (float) mass below
-    u64 *gt = b.sbins + STS_SW_BANKS * STS_SW_NB;
-    __syncthreads();
-    if (tile < ntiles) {
-        const u64 base = tile * TT_TG;
-        const u64 end = base + SPAN < n ? base + SPAN : n;
-        const u64 lo = base > (u64)TT_H ? base - TT_H : 0;
-        const u64 hi = end + TT_H < n ? end + TT_H : n;
-        stage_tile<AT, M>(s, g, keys, amps, lo, hi);
-        __syncthreads();
-        u32 c_above = 0;
-        float m_above = 0.f, m_below = 0.f;
-#pragma unroll 1
-        for (int k = 0; k < SPAN / STS_WG; ++k) {
-            const u64 e = base + (u64)k * STS_WG + threadIdx.x;
-            Group<AT, M> G;
-            tile_group<AT, M>(s, g, keys, amps, lo, hi, n, e < end ? e : n, G);
-#pragma unroll OutUnroll<AT, M>::value
-            for (int i = 0; i < (1 << M); ++i) {
-                const AT o = group_out<AT, M>(g, G, i);
-                if (!G.present || !nonzero(o)) continue;
-                const u64 wb = weight_bits(o);
-                const float w = (float)__longlong_as_double((long long)wb);
-                const int row = (int)(wb >> 52) - e_lo;
-                if (row >= STS_SW_EXPS) {
-                    ++c_above;
-                    m_above += w;
-                } else if (row < 0) {
-                    m_below += w;
-                } else {
-                    const int f = (row << STS_SW_FB) | (int)((wb >> (52 - STS_SW_FB)) & ((1u << STS_SW_FB) - 1));
-                    atomicAdd(&s_c[f], 1u);
-                    atomicAdd(&s_m[f], w);
-                }
-            }
-        }
-        // workgroup totals of the out-of-range parts (wave sums, then LDS),
-        // then one global atomic per non-empty bin and per total, on the
-        // workgroup's bank
+    u64 *bt = b.sbins + STS_SW_BANKS * STS_SW_NB + 4 * bank;
 #pragma unroll
-        for (int d = 32; d > 0; d >>= 1) {
-            c_above += __shfl_xor(c_above, d, 64);
-            m_above += __shfl_xor(m_above, d, 64);
-            m_below += __shfl_xor(m_below, d, 64);
-        }
-        if ((threadIdx.x & 63) == 0) {
-            atomicAdd(&s_cab, c_above);
-            atomicAdd(&s_mab, m_above);
-            atomicAdd(&s_mbe, m_below);
-        }
-        __syncthreads();
-        const u32 cb = s_c[threadIdx.x];
-        if (cb) {
-            atomicAdd(&gc[bank * STS_SW_NB + threadIdx.x], cb);
-            atomicAdd(&gm[bank * STS_SW_NB + threadIdx.x], s_m[threadIdx.x]);
-        }
-        u64 *bt = gt + 4 * bank;
-        if (threadIdx.x == 0) {
-            atomicAdd(&bt[0], end > base ? end - base : 0ull);
-            if (s_cab) {
-                atomicAdd(&bt[1], (u64)s_cab);
-                atomicAdd(reinterpret_cast<float *>(&bt[2]), s_mab);
-            }
-            if (s_mbe != 0.f) atomicAdd(reinterpret_cast<float *>(&bt[3]), s_mbe);
-        }
+    for (int d = 32; d > 0; d >>= 1) {
+        a.c_above += __shfl_xor(a.c_above, d, 64);
+        a.m_above += __shfl_xor(a.m_above, d, 64);
+        a.m_below += __shfl_xor(a.m_below, d, 64);
     }
-    if (!sts_last_block(&ctl->done[2], &s_flag)) return;
+    if (inputs) atomicAdd(&s.inputs, inputs);
+    if ((threadIdx.x & 63) == 0) {
+        atomicAdd(&s.cab, a.c_above);
+        atomicAdd(&s.mab, a.m_above);
+        atomicAdd(&s.mbe, a.m_below);
+    }
+    __syncthreads();
+    const u32 cb = s.c[threadIdx.x];
+    if (cb) {
+        atomicAdd(&gc[bank * STS_SW_NB + threadIdx.x], cb);
+        atomicAdd(&gm[bank * STS_SW_NB + threadIdx.x], s.m[threadIdx.x]);
+    }
+    if (threadIdx.x == 0) {
+        if (s.inputs) atomicAdd(&bt[0], (u64)s.inputs);
+        if (s.cab) {
+            atomicAdd(&bt[1], (u64)s.cab);
+            atomicAdd(reinterpret_cast<float *>(&bt[2]), s.mab);
+        }
+        if (s.mbe != 0.f) atomicAdd(reinterpret_cast<float *>(&bt[3]), s.mbe);
+    }
+}
 
-    // the last workgroup: thread t owns bin STS_SW_NB-1-t, so rank order
-    // (weight descending) is thread order
+// the last workgroup: the window from the sample of a state of n terms
+__device__ __forceinline__ void sample_finish(SampleSmem &s, const PassBufs &b, int e_lo, u64 n)
+{
+    DevCtl *ctl = b.ctl;
+    const u32 *gc = reinterpret_cast<const u32 *>(b.sbins);
+    const float *gm = reinterpret_cast<const float *>(b.sbins + STS_SW_BANKS * STS_SW_NB / 2);
+    const u64 *gt = b.sbins + STS_SW_BANKS * STS_SW_NB;
+    // thread t owns bin STS_SW_NB-1-t, so rank order (weight descending) is
+    // thread order
     const int t = threadIdx.x;
     const int f = STS_SW_NB - 1 - t;
     u32 c = 0;
@@ -1143,7 +1131,7 @@ __global__ void __launch_bounds__(STS_WG) k_tile_sample(const GateArg *__restric
 #pragma unroll
     for (int k = 0; k < STS_SW_BANKS; ++k) {
         c += ld_agent(&gc[k * STS_SW_NB + f]);
-        m += (double)__int_as_float((int)ld_agent(reinterpret_cast<u32 *>(&gm[k * STS_SW_NB + f])));
+        m += (double)__int_as_float((int)ld_agent(reinterpret_cast<const u32 *>(&gm[k * STS_SW_NB + f])));
     }
     u64 sampled = 0, c_above = 0;
     double m_above = 0.0, m_below = 0.0;
@@ -1157,8 +1145,8 @@ __global__ void __launch_bounds__(STS_WG) k_tile_sample(const GateArg *__restric
     }
     u64 ctot;
     double mtot;
-    const u64 cex = block_excl_scan<u64, STS_WG>((u64)c, s_scan_c, &ctot) + c_above;
-    const double mex = block_excl_scan<double, STS_WG>(m, s_scan_m, &mtot) + m_above;
+    const u64 cex = block_excl_scan<u64, STS_WG>((u64)c, s.scan_c, &ctot) + c_above;
+    const double mex = block_excl_scan<double, STS_WG>(m, s.scan_m, &mtot) + m_above;
     mtot += m_above + m_below;
     const u64 K = ctl->K;
     const double p = ctl->p;
@@ -1167,14 +1155,14 @@ __global__ void __launch_bounds__(STS_WG) k_tile_sample(const GateArg *__restric
     // sample; the mass target is p of the sample's own total
     const double kt = K > 0 && sampled > 0 ? (double)K * (double)sampled / (double)n : 0.0;
     const double mt = p * mtot;
-    if (t == 0) s_hit = 0xffffffffu;
+    if (t == 0) s.hit = 0xffffffffu;
     __syncthreads();
     const bool met_above = (K > 0 && (double)c_above >= kt) || (p_on && m_above >= mt);
     const bool met = c && ((K > 0 && (double)(cex + c) >= kt) || (p_on && mex + m >= mt));
-    if (sampled > 0 && !met_above && met) atomicMin(&s_hit, (u32)t);
+    if (sampled > 0 && !met_above && met) atomicMin(&s.hit, (u32)t);
     __syncthreads();
     if (t == 0) {
-        const u32 r = s_hit;
+        const u32 r = s.hit;
         if (r == 0xffffffffu) {
             ctl->w_mode = 0;
         } else {
@@ -1190,6 +1178,54 @@ __global__ void __launch_bounds__(STS_WG) k_tile_sample(const GateArg *__restric
         }
     }
     for (int i = t; i < STS_SW_BANKS * (STS_SW_NB + 4); i += STS_WG) st_agent(&b.sbins[i], 0ull);
+}
+
+template <typename AT, int M>
+__global__ void __launch_bounds__(STS_WG) k_tile_sample(const GateArg *__restrict__ gp, PassBufs b)
+{
+    const GateArg &g = *gp;
+    stage_gate<AT, M>(g);
+    constexpr int SPAN = STS_SAMPLE_SPAN; // inputs per workgroup, from a tile's start
+    __shared__ TileSmem<AT> s;
+    __shared__ SampleSmem ss;
+    DevCtl *ctl = b.ctl;
+    const u64 n = *b.n_in; // loaded with the control word, before the test
+    const int e_prev = ctl->e_pred;
+    if (e_prev < 0) return; // uniform: nothing to centre the bins on
+    const int e_lo = e_prev - STS_SW_EXPS / 2; // exponent field of bin row 0
+    sample_begin(ss);
+    const u64 *keys = b.keys;
+    const AT *amps = (const AT *)b.amps;
+    const u64 ntiles = (n + TT_TG - 1) / TT_TG;
+    const u64 stride = ntiles > gridDim.x ? ntiles / gridDim.x : 1;
+    const u64 tile = (u64)blockIdx.x * stride;
+    SampleAcc acc;
+    u32 inputs = 0;
+    __syncthreads();
+    if (tile < ntiles) {
+        const u64 base = tile * TT_TG;
+        const u64 end = base + SPAN < n ? base + SPAN : n;
+        const u64 lo = base > (u64)TT_H ? base - TT_H : 0;
+        const u64 hi = end + TT_H < n ? end + TT_H : n;
+        stage_tile<AT, M>(s, g, keys, amps, lo, hi);
+        __syncthreads();
+        if (threadIdx.x == 0) inputs = (u32)(end - base);
+#pragma unroll 1
+        for (int k = 0; k < SPAN / STS_WG; ++k) {
+            const u64 e = base + (u64)k * STS_WG + threadIdx.x;
+            Group<AT, M> G;
+            tile_group<AT, M>(s, g, keys, amps, lo, hi, n, e < end ? e : n, G);
+#pragma unroll OutUnroll<AT, M>::value
+            for (int i = 0; i < (1 << M); ++i) {
+                const AT o = group_out<AT, M>(g, G, i);
+                if (!G.present || !nonzero(o)) continue;
+                sample_add(ss, acc, weight_bits(o), e_lo);
+            }
+        }
+    }
+    sample_flush(ss, acc, b, inputs);
+    if (!sts_last_block(&ctl->done[2], &ss.flag)) return;
+    sample_finish(ss, b, e_lo, n);
 }
 
 // ---------------------------------------------------------------------------

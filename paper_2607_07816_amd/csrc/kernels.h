@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include "common.h"
+#include "linhash.h"
 
 // Gate description passed by value to the grouping kernels. For m <= 3 the
 // matrix travels in the argument block itself (no device copy per gate);
@@ -23,6 +24,7 @@ struct GateArg {
     u64 dep[8];         // dep[i]: pattern i deposited on the gate's qubits (m <= 3)
     const double *uptr; // m >= 4
     const float *uptr_f; // m >= 4: the same rounded to FP32 (nearest-even)
+    BktPlan bkt;         // bucketed steps (m <= 2): where the gate's cosets lie
 };
 
 // Device buffers a grouping pass reads and writes.
@@ -65,6 +67,13 @@ struct PassBufs {
     u64 *wpart;           // [6][STS_MAX_GROUPS]: per histogram workgroup, the count of candidates
                           // above the window and the mantissa sums (>> 26, & (2^26-1)) of those in
                           // the window's exponent; then the count and sums of those inside it
+    // bucketed steps: the input's and the output's bucket tables (first and one past the last
+    // term of each bucket), per share the candidates and the survivors, log2 of a share's slab
+    const uint2 *bd_in;
+    uint2 *bd_out;
+    u32 *w_all;
+    u32 *w_kept;
+    int slab_shift;
     u64 *sbins;           // sampling pass: STS_SW_BANKS x STS_SW_NB counts (u32), as many masses
                           // (float), then 4 totals per bank
 };
@@ -133,6 +142,7 @@ __device__ __forceinline__ u64 slab_at(const TileSlabs &t, u32 j)
 inline int sts_radix_bits(int shape) { return shape >= STS_RADIX_11x16 ? 11 : 8; }
 inline u64 sts_radix_tile(int shape) { return (shape & 1) ? 2048ull : 4096ull; }
 
+// notmask = nullptr sorts by the bucket hash of linhash.h instead of the mixed masked key (shapes 8x16, 11x8)
 // one step of a grouping-sort pass: what = 0 digit counts per tile, 1 their
 // scan (one workgroup per digit), 2 the scatter
 hipError_t launch_radix(int what, int shape, int prec, const u64 *kin, const void *ain, u64 *kout, void *aout,
@@ -160,6 +170,19 @@ hipError_t launch_fill_zero(u64 *p, u64 n, hipStream_t s);
 hipError_t launch_ctl_begin(DevCtl *ctl, u64 K, double p, u64 n_in, hipStream_t s);
 hipError_t launch_terms_out(const u64 *keys, const void *amps, int amp_bytes, const DevCtl *ctl, int slot,
                             u64 *keys_out, void *amps_out, u64 out_cap, u64 *n_out, double *stats, hipStream_t s);
+
+// bucketed steps (bucket_impl.h): gates of 1 and 2 qubits on a state in bucket order
+#define STS_BKT_HIST 0
+#define STS_BKT_SAMPLE 1
+#define STS_BKT_EXTRACT 2
+#define STS_BKT_COUNT 3
+#define STS_BKT_EMIT 4
+hipError_t launch_bucket_pass(int kind, int prec, int m, const PassBufs &b, int tiles, hipStream_t s);
+int bucket_hist_capacity(int prec, int m);
+// survivors per share (when the window held the cut or nothing is cut), then every tile's output offset
+hipError_t launch_bucket_kept(const PassBufs &b, int tiles, hipStream_t s);
+// the bucket table of terms that lie in bucket order
+hipError_t launch_bucket_bounds(const u64 *keys, const u64 *n_in, u64 n_bound, int hb, uint2 *bd, hipStream_t s);
 
 // workgroups to launch for a compaction pass over n terms with an m-qubit
 // gate: m <= 3 uses LDS tiles of 2048 terms, larger

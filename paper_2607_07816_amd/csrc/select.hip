@@ -289,6 +289,8 @@ __global__ void __launch_bounds__(256) k_pick1(PassBufs b, int groups, int peak_
     u64 *h1 = b.h1;
     // the exponent of the window the histogram pass copied (predicted steps)
     const int w_mode = ctl->w_mode;
+    // (predicted = 2: a bucketed step, where a share's slab may have been too small for it)
+    const bool over = predicted == 2 && ctl->w_over != 0;
     const int e_w = predicted ? (w_mode ? ctl->e_w : ctl->e_pred) : -1;
     if (t < 6) s_w[t] = 0;
     if (t == 0) s_fine = 0;
@@ -489,7 +491,7 @@ __global__ void __launch_bounds__(256) k_pick1(PassBufs b, int groups, int peak_
                 bool in_window = false;
                 u64 ca = 0, cw = 0;
                 u128 ma = 0;
-                if (e == e_w) {
+                if (e == e_w && !over) {
                     // the histogram pass counted every candidate above the window;
                     // those in exponents above e are the cnt ranked before this bin
                     ca = s_w[0] - cnt;
@@ -547,6 +549,14 @@ __global__ void __launch_bounds__(256) k_pick1(PassBufs b, int groups, int peak_
             if (lane == 0) {
                 ctl->w2_mode = predicted && w_mode; // the histogram pass binned the window for level 2
                 ctl->w_mode = 0;                     // a window serves one step
+                if (predicted == 2) {
+                    ctl->w_over = 0;
+                    // a missed window: the extraction pass packs its candidates densely
+                    if (hit != 0xffffffffu && !ctl->pred_hit) {
+                        ctl->side_dense = 1;
+                        ctl->side_n = 0;
+                    }
+                }
                 ctl->l2_done = 0;
             }
         }
