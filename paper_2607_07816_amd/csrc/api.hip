@@ -39,7 +39,7 @@ u64 ceil_div(u64 a, u64 b) { return (a + b - 1) / b; }
 
 struct Layout {
     u64 ctl, ctl_save, keys[3], amps[3], side_key, side_w, side_amp, sub_key, sub_w, h1, h2, h2w, h3, best, rcount, rprefix, rtotal, look_comp,
-        t_above, t_side, t_off, w_all, w_kept, bd[2], tctr, dU, sub_cnt, wpart, sbins, gate, total;
+        t_above, t_side, t_off, w_all, w_kept, t_base, bd[2], tctr, dU, sub_cnt, wpart, sbins, gate, total;
 };
 
 // tiles of the LDS-tiled passes (2048 terms each) and the side-buffer entries:
@@ -104,11 +104,12 @@ Layout make_layout(u64 cap, int prec)
     L.t_off = take(std::max(ttiles, buckets / 16) * 8);
     L.w_all = take(buckets);  // a word per share of four buckets
     L.w_kept = take(buckets);
+    L.t_base = take((buckets / 16 / STS_BKT_CHUNK + 1) * 8);
     for (int i = 0; i < 2; ++i) L.bd[i] = take(buckets * sizeof(uint2));
     L.tctr = take(16 * 4);
     L.dU = take(kULen * 8 + kULen * 4); // U in FP64, then its FP32 rounding
     L.sub_cnt = take((STS_SUB_REGIONS + 1) * 128);
-    L.wpart = take(6 * STS_MAX_GROUPS * 8);
+    L.wpart = take(7 * STS_MAX_GROUPS * 8);
     L.sbins = take(STS_SW_BANKS * (STS_SW_NB + 4) * 8);
     L.gate = take(2 * sizeof(GateArg)); // the current gate, and the identity
     L.total = o;
@@ -171,9 +172,11 @@ struct sts_ctx {
     u32 *t_above = nullptr, *t_side = nullptr;
     u64 *t_off = nullptr;
     u32 *w_all = nullptr, *w_kept = nullptr;
+    u64 *t_base = nullptr;
     uint2 *bd[2] = {nullptr, nullptr}; // bucket tables
     bool bucketed = false;  // the state in buffer cur is in bucket order:
     int hb = 0, bdc = 0;    // 2^hb buckets, table bd[bdc]
+    bool one_step = false;    // sts_step_static
     bool bkt_pending = false; // the pending gate is a bucketed step
     int prev_m = 0, prev_q[2] = {0, 0}; // the qubits of the last bucketed step
     u32 *tctr = nullptr;
@@ -308,6 +311,7 @@ PassBufs pass_bufs(sts_ctx *c, int in, int out)
     b.t_off = c->t_off;
     b.w_all = c->w_all;
     b.w_kept = c->w_kept;
+    b.t_base = c->t_base;
     b.bd_in = c->bd[c->bdc];
     b.bd_out = c->bd[c->bdc ^ 1];
     b.slab_shift = kSlabShift;
@@ -366,6 +370,7 @@ void bind_layout(sts_ctx *c, const Layout &L)
     c->t_off = (u64 *)(c->mem + L.t_off);
     c->w_all = (u32 *)(c->mem + L.w_all);
     c->w_kept = (u32 *)(c->mem + L.w_kept);
+    c->t_base = (u64 *)(c->mem + L.t_base);
     for (int i = 0; i < 2; ++i) c->bd[i] = (uint2 *)(c->mem + L.bd[i]);
     c->tctr = (u32 *)(c->mem + L.tctr);
     c->dU = (double *)(c->mem + L.dU);
@@ -456,9 +461,11 @@ sts_status sort_state(sts_ctx *c, const u64 *notmask, int *sorted, int *hb_out)
 }
 
 // whether a gate of m qubits on the current state is a bucketed step
+// (not the one step of sts_step_static: putting its terms in bucket order
+// costs what the sort does, and no later step gains from it)
 bool use_buckets(const sts_ctx *c, int m)
 {
-    return m <= 2 && c->cap <= kBucketMax && c->n_bound >= kBucketMin;
+    return !c->one_step && m <= 2 && c->cap <= kBucketMax && c->n_bound >= kBucketMin;
 }
 
 // whether the state's buckets suit its size bound: neither so few that a
@@ -522,9 +529,9 @@ sts_status bucketize(sts_ctx *c)
 
 int bucket_tiles(const sts_ctx *c) { return 1 << (c->gate.bkt.hb - STS_BKT_DIMS); }
 
-int bucket_hist_groups(const sts_ctx *c)
+int bucket_groups(const sts_ctx *c, bool weigh)
 {
-    return std::min(bucket_tiles(c), bucket_hist_capacity(c->prec, c->gate.m));
+    return bucket_hist_groups(c->prec, c->gate.m, bucket_tiles(c), weigh);
 }
 
 // the passes that write the pending bucketed step's survivors to buffer dst
@@ -533,6 +540,8 @@ sts_status bucket_write(sts_ctx *c, const PassBufs &b, int dst, u64 bound)
     const int tiles = bucket_tiles(c);
     STS_LAUNCH(c, STS_K_GROUP_EXTRACT, launch_bucket_pass(STS_BKT_COUNT, c->prec, c->gate.m, b, tiles, c->stream));
     STS_LAUNCH(c, STS_K_TILE_KEPT, launch_bucket_kept(b, tiles, c->stream));
+    if (!b.materialise)
+        STS_LAUNCH(c, STS_K_GROUP_EMIT, launch_bucket_pass(STS_BKT_COPY, c->prec, c->gate.m, b, tiles, c->stream));
     STS_LAUNCH(c, STS_K_GROUP_EMIT, launch_bucket_pass(STS_BKT_EMIT, c->prec, c->gate.m, b, tiles, c->stream));
     c->cur = dst;
     c->n_bound = bound;
@@ -819,7 +828,7 @@ static sts_status truncate_buckets(sts_ctx *c)
     const u64 cb = sat_shl(c->n_bound, c->gate.m);
     const int out = (c->cur + 1) % 3;
     PassBufs b = pass_bufs(c, c->cur, out);
-    const int m = c->gate.m, tiles = bucket_tiles(c), G = bucket_hist_groups(c);
+    const int m = c->gate.m, tiles = bucket_tiles(c);
     u64 nb = c->K ? std::min<u64>(c->K, cb) : cb;
     sts_status st = STS_OK;
     const bool out_risk = nb > c->cap; // a cut limited by p-mass alone may keep more than cap terms
@@ -827,12 +836,21 @@ static sts_status truncate_buckets(sts_ctx *c)
         st = save_ctl(c);
         if (st != STS_OK) return st;
     }
-    if (c->n_bound >= STS_SAMPLE_MIN)
+    if (c->n_bound >= STS_SAMPLE_MIN) {
+        // a window from a sample; the histogram pass and its pick run only
+        // when it missed
         STS_LAUNCH(c, STS_K_SAMPLE, launch_bucket_pass(STS_BKT_SAMPLE, c->prec, m, b, tiles, c->stream));
-    b.predict = 1;
-    STS_LAUNCH(c, STS_K_GROUP_HIST, launch_bucket_pass(STS_BKT_HIST, c->prec, m, b, tiles, c->stream));
-    b.predict = 0;
-    STS_LAUNCH(c, STS_K_PICK1, launch_pick1(b, G, 0, 2, c->stream));
+        STS_LAUNCH(c, STS_K_GROUP_HIST, launch_bucket_pass(STS_BKT_WEIGH, c->prec, m, b, tiles, c->stream));
+        STS_LAUNCH(c, STS_K_PICK1, launch_pick_window(b, bucket_groups(c, true), c->stream));
+        b.recover = 1;
+        STS_LAUNCH(c, STS_K_GROUP_HIST, launch_bucket_pass(STS_BKT_HIST, c->prec, m, b, tiles, c->stream));
+        STS_LAUNCH(c, STS_K_PICK1, launch_pick1(b, 0, 0, 3, c->stream));
+    } else {
+        b.predict = 1;
+        STS_LAUNCH(c, STS_K_GROUP_HIST, launch_bucket_pass(STS_BKT_HIST, c->prec, m, b, tiles, c->stream));
+        b.predict = 0;
+        STS_LAUNCH(c, STS_K_PICK1, launch_pick1(b, bucket_groups(c, false), 0, 2, c->stream));
+    }
     STS_LAUNCH(c, STS_K_GROUP_EXTRACT, launch_bucket_pass(STS_BKT_EXTRACT, c->prec, m, b, tiles, c->stream));
     const int sg = (int)std::min<u64>(std::max<u64>(ceil_div(std::min(cb, c->scap), 256), 1), STS_SIDE_GROUPS);
     STS_LAUNCH(c, STS_K_SIDE_HIST, launch_side_hist(b, c->h2, sg, c->stream));
@@ -1143,6 +1161,7 @@ sts_status sts_step_static(int n_qubits, uint64_t max_terms, double mass, int pr
     }
     c.cur = 0;
     c.n_bound = n_in;
+    c.one_step = true;
     sts_status st = sts_apply_gate(&c, m, qubits, U);
     if (st != STS_OK) return st;
     st = sts_truncate(&c);

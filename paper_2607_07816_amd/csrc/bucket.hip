@@ -6,8 +6,8 @@
 
 hipError_t bucket_c128_pass(int kind, int m, const PassBufs &b, int tiles, hipStream_t s);
 hipError_t bucket_c64_pass(int kind, int m, const PassBufs &b, int tiles, hipStream_t s);
-int bucket_c128_capacity(int m);
-int bucket_c64_capacity(int m);
+int bucket_c128_groups(int m, int tiles, bool weigh);
+int bucket_c64_groups(int m, int tiles, bool weigh);
 
 namespace {
 
@@ -17,10 +17,13 @@ constexpr int KT = 1024;
 // window held the cut, a share's survivors are its entries above the window
 // and those of the window ranked at or above the threshold term (16 lanes per
 // share, a wave per tile); when nothing is cut, all its candidates; otherwise
-// the counting pass has them. The last workgroup scans the tiles' sums.
+// the counting pass has them. A workgroup has STS_BKT_CHUNK tiles, whose
+// offsets are relative to the chunk's base; the last workgroup scans the
+// chunks' sums.
 __global__ void __launch_bounds__(KT) k_bkt_kept(PassBufs b)
 {
     __shared__ u32 s_flag;
+    __shared__ u32 s_tile[STS_BKT_CHUNK];
     __shared__ u64 s_scratch[KT / 64];
     constexpr int UN = 4;
     DevCtl *ctl = b.ctl;
@@ -29,54 +32,57 @@ __global__ void __launch_bounds__(KT) k_bkt_kept(PassBufs b)
     const int shift = ctl->side_slab_shift;
     const bool all = !b.materialise && ctl->keep_all, hit = !b.materialise && !ctl->keep_all && ctl->pred_hit;
     const u32 lane = (u32)sts_lane(), sub = lane >> 4, l16 = lane & 15u;
-    for (u32 tile = blockIdx.x * (KT / 64) + (threadIdx.x >> 6); tile < ntiles; tile += gridDim.x * (KT / 64)) {
-        const u32 sl = (tile << 2) + sub;
+    const u32 t0 = blockIdx.x * STS_BKT_CHUNK;
+    for (u32 k = threadIdx.x >> 6; k < STS_BKT_CHUNK; k += KT / 64) {
+        const u32 tile = t0 + k;
         u32 c = 0;
-        if (hit) {
-            const u32 ns = b.t_side[sl];
-            const u64 base = (u64)sl << shift;
-            for (u32 i0 = l16; i0 < ns; i0 += UN * 16) {
-                u64 w[UN], k[UN];
+        if (tile < ntiles) {
+            const u32 sl = (tile << 2) + sub;
+            if (hit) {
+                const u32 ns = b.t_side[sl];
+                const u64 base = (u64)sl << shift;
+                if (l16 == 0) c = b.t_above[sl];
+                for (u32 i0 = l16; i0 < ns; i0 += UN * 16) {
+                    u64 w[UN], key[UN];
 #pragma unroll
-                for (int r = 0; r < UN; ++r) {
-                    const u32 i = i0 + 16u * (u32)r;
-                    w[r] = b.side_w[base + (i < ns ? i : 0u)];
-                    k[r] = b.side_key[base + (i < ns ? i : 0u)];
+                    for (int r = 0; r < UN; ++r) {
+                        const u32 i = i0 + 16u * (u32)r;
+                        w[r] = b.side_w[base + (i < ns ? i : 0u)];
+                        key[r] = b.side_key[base + (i < ns ? i : 0u)];
+                    }
+#pragma unroll
+                    for (int r = 0; r < UN; ++r) {
+                        const u32 i = i0 + 16u * (u32)r;
+                        c += (i < ns && (w[r] > thr_w || (w[r] == thr_w && key[r] <= thr_k))) ? 1u : 0u;
+                    }
                 }
 #pragma unroll
-                for (int r = 0; r < UN; ++r) {
-                    const u32 i = i0 + 16u * (u32)r;
-                    c += (i < ns && (w[r] > thr_w || (w[r] == thr_w && k[r] <= thr_k))) ? 1u : 0u;
-                }
+                for (int d = 8; d > 0; d >>= 1) c += __shfl_xor(c, d, 64);
+            } else {
+                c = all ? b.w_all[sl] : b.w_kept[sl];
             }
-            if (l16 == 0) c += b.t_above[sl];
-#pragma unroll
-            for (int d = 8; d > 0; d >>= 1) c += __shfl_xor(c, d, 64);
-        } else {
-            c = all ? b.w_all[sl] : b.w_kept[sl];
+            if (l16 == 0 && (hit || all)) b.w_kept[sl] = c;
+            c += __shfl_xor(c, 16, 64);
+            c += __shfl_xor(c, 32, 64);
         }
-        if (l16 == 0 && (hit || all)) b.w_kept[sl] = c;
-        c += __shfl_xor(c, 16, 64);
-        c += __shfl_xor(c, 32, 64);
-        if (lane == 0) b.t_off[tile] = c;
+        if (lane == 0) s_tile[k] = c;
+    }
+    __syncthreads();
+    if (threadIdx.x < 64) {
+        static_assert(STS_BKT_CHUNK <= 64, "one lane per tile");
+        const u32 c = lane < STS_BKT_CHUNK ? s_tile[lane] : 0u;
+        const u32 inc = wave_incl_scan(c);
+        if (lane < STS_BKT_CHUNK && t0 + lane < ntiles) b.t_off[t0 + lane] = inc - c;
+        if (lane == 63) st_agent(&b.t_base[blockIdx.x], (u64)inc);
     }
     if (!sts_last_block(&ctl->done[3], &s_flag)) return;
-    constexpr int CH = 16;
     u64 carry = 0;
-    for (u32 t0 = 0; t0 < ntiles; t0 += KT * CH) {
-        const u32 lo = t0 + threadIdx.x * CH;
-        u64 v[CH], sum = 0;
-#pragma unroll
-        for (int k = 0; k < CH; ++k) v[k] = lo + k < ntiles ? ld_agent(&b.t_off[lo + k]) : 0ull;
-#pragma unroll
-        for (int k = 0; k < CH; ++k) sum += v[k];
+    for (u32 i0 = 0; i0 < gridDim.x; i0 += KT) {
+        const u32 i = i0 + threadIdx.x;
+        const u64 v = i < gridDim.x ? ld_agent(&b.t_base[i]) : 0ull;
         u64 total;
-        u64 run = block_excl_scan<u64, KT>(sum, s_scratch, &total) + carry;
-#pragma unroll
-        for (int k = 0; k < CH; ++k) {
-            if (lo + k < ntiles) st_agent(&b.t_off[lo + k], run);
-            run += v[k];
-        }
+        const u64 run = block_excl_scan<u64, KT>(v, s_scratch, &total) + carry;
+        if (i < gridDim.x) st_agent(&b.t_base[i], run);
         carry += total;
     }
     if (threadIdx.x == 0) {
@@ -105,7 +111,10 @@ __global__ void __launch_bounds__(256) k_bkt_bounds(const u64 *__restrict__ keys
 
 } // namespace
 
-int bucket_hist_capacity(int prec, int m) { return prec == 0 ? bucket_c128_capacity(m) : bucket_c64_capacity(m); }
+int bucket_hist_groups(int prec, int m, int tiles, bool weigh)
+{
+    return prec == 0 ? bucket_c128_groups(m, tiles, weigh) : bucket_c64_groups(m, tiles, weigh);
+}
 
 hipError_t launch_bucket_pass(int kind, int prec, int m, const PassBufs &b, int tiles, hipStream_t s)
 {
@@ -114,7 +123,7 @@ hipError_t launch_bucket_pass(int kind, int prec, int m, const PassBufs &b, int 
 
 hipError_t launch_bucket_kept(const PassBufs &b, int tiles, hipStream_t s)
 {
-    const int grid = std::max(1, std::min((tiles + KT / 64 - 1) / (KT / 64), 256));
+    const int grid = std::max(1, (tiles + STS_BKT_CHUNK - 1) / STS_BKT_CHUNK);
     hipLaunchKernelGGL(k_bkt_kept, dim3(grid), dim3(KT), 0, s, b);
     return hipGetLastError();
 }

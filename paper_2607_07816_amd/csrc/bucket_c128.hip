@@ -14,7 +14,9 @@ hipError_t bucket_c128_pass(int kind, int m, const PassBufs &b, int tiles, hipSt
     return hipErrorInvalidValue;
 }
 
-int bucket_c128_capacity(int m)
+int bucket_c128_groups(int m, int tiles, bool weigh)
 {
-    return m == 1 ? sts_bucket::hist_capacity_b<double2, 1>() : sts_bucket::hist_capacity_b<double2, 2>();
+    using namespace sts_bucket;
+    if (weigh) return m == 1 ? weigh_grid<double2, 1>(tiles) : weigh_grid<double2, 2>(tiles);
+    return std::min(tiles, m == 1 ? hist_capacity_b<double2, 1>() : hist_capacity_b<double2, 2>());
 }

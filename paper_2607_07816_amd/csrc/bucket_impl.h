@@ -26,11 +26,19 @@ constexpr int BW_ROUNDS = BW_CAP / 64;
 constexpr u32 BW_BINNED = 640;     // larger shares bypass the LDS bins (their sums are bounded by this)
 constexpr int BW_FLUSH = 16;       // tiles between flushes of the LDS bins
 
-template <typename AT> struct BktSmem {
-    AT amp[BW][BW_CAP];
-    u64 key[BW][BW_CAP];
-    unsigned long long slot[BW][BW_SLOTS]; // a group: the staged index + 1 of its member j at bit 16 j
-    unsigned short lead[BW][BW_CAP];       // slots of the groups, in the order they were opened
+// a wave's tables
+template <typename AT> struct WaveSmem {
+    AT amp[BW_CAP];
+    u64 key[BW_CAP];
+    unsigned long long slot[BW_SLOTS]; // a group: the staged index + 1 of its member j at bit 16 j
+    unsigned short lead[BW_CAP];       // from the front: the only member of each group of one; from the end: the
+                                       // slots of the others
+    unsigned short hard[64];
+};
+
+template <typename AT, int NW> struct BktSmem {
+    WaveSmem<AT> w[NW];
+    AT ucol[16]; // U by columns: U[i][j] at [2^m j + i]
 };
 
 // orders a wave's own LDS accesses (which the hardware performs in order)
@@ -40,19 +48,64 @@ __device__ __forceinline__ void wave_sync()
     __builtin_amdgcn_wave_barrier();
 }
 
+// (HIP's __ballot goes through an integer: two more instructions a call)
+__device__ __forceinline__ u64 wballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }
+
 __device__ __forceinline__ u32 uni(u32 v) { return (u32)__builtin_amdgcn_readfirstlane((int)v); }
+
+// what the grouping needs of the gate, read once: through the argument block
+// every use would be a load of its own, since the kernel's stores might
+// change it
+template <int M> struct GateLoc {
+    u64 nm;           // key bits outside the gate
+    u64 bit[M];       // the gate's key bits
+    int q[M];
+};
+
+template <int M> __device__ __forceinline__ GateLoc<M> gate_loc(const GateArg &g)
+{
+    GateLoc<M> l;
+    l.nm = ~0ull;
+#pragma unroll
+    for (int t = 0; t < M; ++t) {
+        l.q[t] = (int)uni((u32)g.q[t]);
+        l.bit[t] = 1ull << l.q[t];
+        l.nm &= ~l.bit[t];
+    }
+    return l;
+}
+
+// a key's pattern on the gate's qubits, and a pattern's key bits
+template <int M> __device__ __forceinline__ u32 pattern_of(const GateLoc<M> &l, u64 key)
+{
+    u32 j = 0;
+#pragma unroll
+    for (int t = 0; t < M; ++t) j |= (u32)((key >> l.q[t]) & 1ull) << t;
+    return j;
+}
+
+template <int M> __device__ __forceinline__ u64 pattern_bits(const GateLoc<M> &l, int i)
+{
+    u64 k = 0;
+#pragma unroll
+    for (int t = 0; t < M; ++t) k |= ((i >> t) & 1) ? l.bit[t] : 0ull;
+    return k;
+}
 
 // the four runs of a wave's share (in scalar registers)
 struct Share {
-    u32 o0, o1, o2, o3; // first term of each run, less its start in the flat index
+    u32 o0, d1, d2, d3; // first term of run 0; what further runs add to it, less their starts in the flat index
     u32 p1, p2, p3, n;  // starts of runs 1..3 in the flat index; terms in all
 };
 
-__device__ __forceinline__ Share load_share(const BktPlan &p, const uint2 *__restrict__ bd, u32 tile, int wv)
+// lane i % 4 reads the bounds of run i
+__device__ __forceinline__ uint2 load_runs(const BktPlan &p, const uint2 *__restrict__ bd, u32 tile, int wv)
 {
-    const u32 lane = (u32)sts_lane();
-    const u32 bucket = bkt_rep(p, tile) ^ bkt_comb(p, (lane & 3u) | ((u32)wv << 2));
-    const uint2 d = bd[bucket];
+    return bd[bkt_rep(p, tile) ^ bkt_comb(p, ((u32)sts_lane() & 3u) | ((u32)wv << 2))];
+}
+
+__device__ __forceinline__ Share share_of(uint2 d)
+{
     u32 beg[4], cnt[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -65,18 +118,21 @@ __device__ __forceinline__ Share load_share(const BktPlan &p, const uint2 *__res
     s.p3 = s.p2 + cnt[2];
     s.n = s.p3 + cnt[3];
     s.o0 = beg[0];
-    s.o1 = beg[1] - s.p1;
-    s.o2 = beg[2] - s.p2;
-    s.o3 = beg[3] - s.p3;
+    s.d1 = beg[1] - s.p1 - beg[0];
+    s.d2 = beg[2] - s.p2 - (beg[1] - s.p1);
+    s.d3 = beg[3] - s.p3 - (beg[2] - s.p2);
     return s;
+}
+
+__device__ __forceinline__ Share load_share(const BktPlan &p, const uint2 *__restrict__ bd, u32 tile, int wv)
+{
+    return share_of(load_runs(p, bd, tile, wv));
 }
 
 __device__ __forceinline__ u32 share_at(const Share &s, u32 j)
 {
-    u32 o = j < s.p1 ? s.o0 : s.o1;
-    o = j < s.p2 ? o : s.o2;
-    o = j < s.p3 ? o : s.o3;
-    return o + j;
+    const u32 d1 = s.d1, d2 = s.d2, d3 = s.d3;
+    return s.o0 + j + (j >= s.p1 ? d1 : 0u) + (j >= s.p2 ? d2 : 0u) + (j >= s.p3 ? d3 : 0u);
 }
 
 __device__ __forceinline__ u32 slot_hash(u64 rest)
@@ -84,38 +140,52 @@ __device__ __forceinline__ u32 slot_hash(u64 rest)
     return ((u32)rest * 0x9e3779b1u + (u32)(rest >> 32) * 0x85ebca6bu) >> 23; // BW_SLOTS = 2^9
 }
 
-// stage the terms of the share (all of them, or those whose second hash has
-// the prefix `pre` of `depth` bits); returns how many there are (more than
-// BW_CAP: not staged)
-template <typename AT>
-__device__ __forceinline__ u32 stage_all(BktSmem<AT> &s, const Share &t, int wv, const u64 *__restrict__ keys,
-                                         const AT *__restrict__ amps)
-{
-    const u32 lane = (u32)sts_lane();
-    u64 kk[BW_ROUNDS];
-    AT aa[BW_ROUNDS];
-#pragma unroll
-    for (int r = 0; r < BW_ROUNDS; ++r) {
-        const u32 j = (u32)r * 64 + lane;
-        if (j < t.n) {
-            const u32 at = share_at(t, j);
-            kk[r] = keys[at];
-            aa[r] = amps[at];
-        }
-    }
-#pragma unroll
-    for (int r = 0; r < BW_ROUNDS; ++r) {
-        const u32 j = (u32)r * 64 + lane;
-        if (j < t.n) {
-            s.key[wv][j] = kk[r];
-            s.amp[wv][j] = aa[r];
-        }
-    }
-    return t.n;
-}
+// the terms of a share of at most BW_CAP, in registers (so that the loads of
+// the next share run while this one is worked on)
+// (scalars: an array of HIP's vector type would be left in scratch memory)
+template <typename AT> struct Staged {
+    u64 k[BW_ROUNDS];
+    typename Scalar<AT>::T x[BW_ROUNDS], y[BW_ROUNDS];
+};
 
 template <typename AT>
-__device__ __noinline__ u32 stage_part(BktSmem<AT> &s, const Share &t, int wv, const u64 *__restrict__ keys,
+__device__ __forceinline__ void stage_load(Staged<AT> &r, const Share &t, const u64 *__restrict__ keys,
+                                           const AT *__restrict__ amps)
+{
+    const u32 lane = (u32)sts_lane();
+#pragma unroll
+    for (int i = 0; i < BW_ROUNDS; ++i) {
+        const u32 j = (u32)i * 64 + lane;
+        if (j < t.n) {
+            const u32 at = share_at(t, j);
+            r.k[i] = keys[at];
+            const AT a = amps[at];
+            r.x[i] = a.x;
+            r.y[i] = a.y;
+        }
+    }
+}
+
+template <typename AT> __device__ __forceinline__ void stage_store(WaveSmem<AT> &s, const Staged<AT> &r, u32 n)
+{
+    const u32 lane = (u32)sts_lane();
+#pragma unroll
+    for (int i = 0; i < BW_ROUNDS; ++i) {
+        const u32 j = (u32)i * 64 + lane;
+        if (j < n) {
+            s.key[j] = r.k[i];
+            AT a;
+            a.x = r.x[i];
+            a.y = r.y[i];
+            s.amp[j] = a;
+        }
+    }
+}
+
+// stage the terms whose second hash has the prefix `pre` of `depth` bits;
+// returns how many there are (more than BW_CAP: not all staged)
+template <typename AT>
+__device__ __forceinline__ u32 stage_part(WaveSmem<AT> &s, const Share &t, const u64 *__restrict__ keys,
                                        const AT *__restrict__ amps, u64 notmask, int depth, u64 pre)
 {
     const u32 lane = (u32)sts_lane();
@@ -130,82 +200,264 @@ __device__ __noinline__ u32 stage_part(BktSmem<AT> &s, const Share &t, int wv, c
             k = keys[at];
             keep = (sts_mix64(k & notmask) >> (64 - depth)) == pre;
         }
-        const u64 m = __ballot(keep);
+        const u64 m = wballot(keep);
         const u32 pos = count + sts_lanes_below(m);
         if (keep && pos < BW_CAP) {
-            s.key[wv][pos] = k;
-            s.amp[wv][pos] = amps[at];
+            s.key[pos] = k;
+            s.amp[pos] = amps[at];
         }
         count += (u32)__popcll(m);
     }
     return count;
 }
 
-// group the `cnt` staged terms: every group gets a slot (open addressing on
-// the masked key) that lists its members; returns the number of groups, their
-// slots in s.lead
+// Group the `cnt` staged terms. Most groups have one member, whose outputs are
+// one column of U each: those are listed (by staged index) from the front of
+// s.lead; the others from its end, by the slot that holds their member list.
+// First every slot counts the terms that hash to it and adds up their
+// indices. A term alone in its slot is a group of one; of two terms in a slot
+// each finds the other from the sum, and they are one group or two; only the
+// terms of fuller slots (a tenth of them at half load) are left to open
+// addressing on the masked key, all in one round as a rule.
 template <typename AT, int M>
-__device__ __forceinline__ u32 build_groups(BktSmem<AT> &s, const GateArg &g, int wv, u32 cnt)
+__device__ __forceinline__ void build_groups(WaveSmem<AT> &s, const GateLoc<M> &g, u32 cnt, u32 &singles, u32 &multis)
 {
     const u32 lane = (u32)sts_lane();
-    const u64 nm = g.notmask;
-    u32 ngroups = 0;
-    for (u32 r0 = 0; r0 < cnt; r0 += 64) {
-        const u32 j = r0 + lane;
-        bool todo = j < cnt, opened = false;
-        u32 sl = 0;
-        u64 rest = 0;
-        unsigned long long mine = 0;
-        if (todo) {
-            const u64 key = s.key[wv][j];
-            rest = key & nm;
-            sl = slot_hash(rest);
-            mine = (unsigned long long)(j + 1) << (16 * extract_bits<M>(key, g));
+    const u64 nm = g.nm;
+    u64 key[BW_ROUNDS], other[BW_ROUNDS];
+    u32 sl[BW_ROUNDS], sum[BW_ROUNDS], mate[BW_ROUNDS];
+    u32 hard = 0; // a bit per round
+    auto word = [&](u32 j, u64 k) { return (unsigned long long)(j + 1) << (16 * pattern_of<M>(g, k)); };
+#pragma unroll
+    for (int r = 0; r < BW_ROUNDS; ++r) {
+        const u32 j = (u32)r * 64 + lane;
+        if (j < cnt) key[r] = s.key[j];
+    }
+#pragma unroll
+    for (int r = 0; r < BW_ROUNDS; ++r) {
+        const u32 j = (u32)r * 64 + lane;
+        if (j < cnt) {
+            sl[r] = slot_hash(key[r] & nm);
+            // indices below 2^9: the sum over all terms stays below 2^16
+            atomicAdd(reinterpret_cast<u32 *>(&s.slot[sl[r]]), 0x10000u + j);
         }
-        while (__ballot(todo)) {
+    }
+    wave_sync();
+#pragma unroll
+    for (int r = 0; r < BW_ROUNDS; ++r) {
+        const u32 j = (u32)r * 64 + lane;
+        sum[r] = 0;
+        if (j < cnt) sum[r] = *reinterpret_cast<const u32 *>(&s.slot[sl[r]]);
+    }
+#pragma unroll
+    for (int r = 0; r < BW_ROUNDS; ++r) {
+        const u32 j = (u32)r * 64 + lane;
+        mate[r] = (sum[r] >> 16) == 2 ? (sum[r] & 0xffffu) - j : j;
+        if (j < cnt) other[r] = s.key[mate[r]];
+    }
+    wave_sync();
+    singles = 0;
+    multis = 0;
+    u32 nhard = 0;
+#pragma unroll
+    for (int r = 0; r < BW_ROUNDS; ++r) {
+        const u32 j = (u32)r * 64 + lane;
+        const bool has = j < cnt;
+        const bool pair = has && mate[r] != j && ((other[r] ^ key[r]) & nm) == 0;
+        const bool one = has && !pair && sum[r] < 0x30000u;
+        const bool left = has && sum[r] >= 0x30000u;
+        const bool lead = pair && j < mate[r];
+        if (has && !pair) s.slot[sl[r]] = 0;
+        if (lead) s.slot[sl[r]] = word(j, key[r]) | word(mate[r], other[r]);
+        const u64 m1 = wballot(one), m2 = wballot(lead), m3 = wballot(left);
+        if (one) s.lead[singles + sts_lanes_below(m1)] = (unsigned short)j;
+        if (lead) s.lead[BW_CAP - 1 - multis - sts_lanes_below(m2)] = (unsigned short)sl[r];
+        if (m3) { // uniform
+            const u32 at = nhard + sts_lanes_below(m3);
+            if (left && at < 64) s.hard[at] = (unsigned short)j;
+            hard |= left ? 1u << r : 0u;
+        }
+        singles += (u32)__popcll(m1);
+        multis += (u32)__popcll(m2);
+        nhard += (u32)__popcll(m3);
+    }
+    wave_sync();
+    // open addressing for term j (when todo), true if it opened its group
+    auto probe = [&](bool todo, u32 j, u64 k, u32 &at) {
+        const u64 rest = k & nm;
+        const unsigned long long mine = word(j, k);
+        bool opened = false;
+        at = slot_hash(rest);
+        while (wballot(todo)) {
             if (todo) {
-                const unsigned long long old = atomicCAS(&s.slot[wv][sl], 0ull, mine);
+                const unsigned long long old = atomicCAS(&s.slot[at], 0ull, mine);
                 if (old == 0) {
                     opened = true;
                     todo = false;
-                } else {
-                    // any member tells the group
+                } else { // any member tells the group
                     const int f = (__ffsll((long long)old) - 1) & ~15;
-                    const u32 o = (u32)((old >> f) & 0xffffu) - 1u;
-                    if ((s.key[wv][o] & nm) == rest) {
-                        atomicOr(&s.slot[wv][sl], mine);
+                    if ((s.key[(u32)((old >> f) & 0xffffu) - 1u] & nm) == rest) {
+                        atomicOr(&s.slot[at], mine);
                         todo = false;
                     } else {
-                        sl = (sl + 1) & (BW_SLOTS - 1);
+                        at = (at + 1) & (BW_SLOTS - 1);
                     }
                 }
             }
         }
-        const u64 m = __ballot(opened);
-        if (opened) s.lead[wv][ngroups + sts_lanes_below(m)] = (unsigned short)sl;
-        ngroups += (u32)__popcll(m);
+        return opened;
+    };
+    if (nhard && nhard <= 64) {
+        const bool has = lane < nhard;
+        const u32 j = has ? s.hard[lane] : 0u;
+        u32 at;
+        const bool opened = probe(has, j, s.key[j], at);
+        wave_sync();
+        bool one = false;
+        if (opened) {
+            const unsigned long long w = s.slot[at];
+            one = (w & ~(0xffffull << ((__ffsll((long long)w) - 1) & ~15))) == 0;
+            if (one) s.slot[at] = 0;
+        }
+        const u64 m1 = wballot(one), m2 = wballot(opened && !one);
+        if (one) s.lead[singles + sts_lanes_below(m1)] = (unsigned short)j;
+        if (opened && !one) s.lead[BW_CAP - 1 - multis - sts_lanes_below(m2)] = (unsigned short)at;
+        singles += (u32)__popcll(m1);
+        multis += (u32)__popcll(m2);
+    } else if (nhard) { // many groups of several members: every group goes by its slot
+#pragma unroll 1
+        for (u32 r = 0; r < BW_ROUNDS; ++r) {
+            const bool has = (hard >> r) & 1u;
+            const u32 j = has ? r * 64 + lane : 0u;
+            u32 at;
+            const bool opened = probe(has, j, s.key[j], at);
+            const u64 m = wballot(opened);
+            if (opened) s.lead[BW_CAP - 1 - multis - sts_lanes_below(m)] = (unsigned short)at;
+            multis += (u32)__popcll(m);
+        }
     }
     wave_sync();
-    return ngroups;
 }
 
-// body(G) for the groups of a share, one per lane (lanes without one have
-// G.present = 0); every lane of the wave takes part
-template <typename AT, int M, typename F>
-__device__ __forceinline__ void share_groups(BktSmem<AT> &s, const GateArg &g, const Share &t, int wv,
-                                             const u64 *__restrict__ keys, const AT *__restrict__ amps, F &&body)
+// body(ox, oy, rest, active) for the groups of a share, one per lane: the new
+// amplitudes of its 2^M patterns (zeros in lanes without a group) and the key
+// bits outside the gate; every lane of the wave takes part
+// (grouped() runs between the grouping and the first call of body)
+template <typename AT, int M, typename F, typename H>
+__device__ __forceinline__ void staged_groups(WaveSmem<AT> &s, const AT *ucol, const GateLoc<M> &g, u32 cnt,
+                                              H &&grouped, F &&body)
 {
+    typedef typename Scalar<AT>::T R;
     const u32 lane = (u32)sts_lane();
+    u32 singles, multis;
+    build_groups<AT, M>(s, g, cnt, singles, multis);
+    grouped();
+    const u32 rs = (singles + 63) >> 6, rm = (multis + 63) >> 6;
+#pragma unroll 1
+    for (u32 r = 0; r < rs + rm; ++r) {
+        R ox[1 << M], oy[1 << M];
+        u64 rest = 0;
+        bool active;
+        if (r < rs) {
+            const u32 q = r * 64 + lane;
+            active = q < singles;
+            AT a;
+            a.x = 0;
+            a.y = 0;
+            u32 j = 0;
+            if (active) {
+                const u32 i = s.lead[q];
+                const u64 key = s.key[i];
+                a = s.amp[i];
+                rest = key & g.nm;
+                j = pattern_of<M>(g, key);
+            }
+            const AT *col = ucol + ((1 << M) * j);
+#pragma unroll
+            for (int i = 0; i < (1 << M); ++i) {
+                const AT u = col[i];
+                if constexpr (sizeof(R) == 4) { // the dense product's terms that are not zero
+                    ox[i] = __builtin_fmaf(-u.y, a.y, u.x * a.x);
+                    oy[i] = __builtin_fmaf(u.y, a.x, u.x * a.y);
+                } else {
+                    ox[i] = (R)0 + (u.x * a.x - u.y * a.y);
+                    oy[i] = (R)0 + (u.x * a.y + u.y * a.x);
+                }
+            }
+        } else {
+            const u32 q = (r - rs) * 64 + lane;
+            active = q < multis;
+            u32 present = 0;
+            R vx[1 << M], vy[1 << M];
+#pragma unroll
+            for (int j = 0; j < (1 << M); ++j) {
+                vx[j] = 0;
+                vy[j] = 0;
+            }
+            if (active) {
+                const u32 sl = s.lead[BW_CAP - 1 - q];
+                const unsigned long long w = s.slot[sl];
+                s.slot[sl] = 0;
+                const int f = (__ffsll((long long)w) - 1) & ~15;
+                rest = s.key[(u32)((w >> f) & 0xffffu) - 1u] & g.nm;
+#pragma unroll
+                for (int j = 0; j < (1 << M); ++j) {
+                    const u32 i = (u32)((w >> (16 * j)) & 0xffffu);
+                    if (i) {
+                        const AT a = s.amp[i - 1];
+                        vx[j] = a.x;
+                        vy[j] = a.y;
+                        present |= 1u << j;
+                    }
+                }
+            }
+            // the product of group_out, with U from LDS (the same address in
+            // every lane)
+#pragma unroll
+            for (int i = 0; i < (1 << M); ++i) {
+                R ar = 0, ai = 0;
+#pragma unroll
+                for (int j = 0; j < (1 << M); ++j) {
+                    const AT u = ucol[(1 << M) * j + i];
+                    if constexpr (sizeof(R) == 4) {
+                        ar = __builtin_fmaf(u.x, vx[j], ar);
+                        ar = __builtin_fmaf(-u.y, vy[j], ar);
+                        ai = __builtin_fmaf(u.x, vy[j], ai);
+                        ai = __builtin_fmaf(u.y, vx[j], ai);
+                    } else {
+                        const R nr = ar + (u.x * vx[j] - u.y * vy[j]);
+                        const R ni = ai + (u.x * vy[j] + u.y * vx[j]);
+                        const bool has = (present >> j) & 1u;
+                        ar = has ? nr : ar;
+                        ai = has ? ni : ai;
+                    }
+                }
+                ox[i] = ar;
+                oy[i] = ai;
+            }
+        }
+        body(ox, oy, rest, active);
+    }
+    wave_sync();
+}
+
+// the groups of a share: of at most BW_CAP terms, already staged; a larger one
+// is staged here in parts
+// (grouped() runs once, after the first grouping)
+template <typename AT, int M, typename F, typename H>
+__device__ __forceinline__ void share_parts(WaveSmem<AT> &s, const AT *ucol, const GateLoc<M> &g, const Share &t,
+                                            const u64 *__restrict__ keys, const AT *__restrict__ amps, H &&grouped,
+                                            F &&body)
+{
+    bool first = true;
     int depth = 0;
     u64 pre = 0;
     if (t.n > BW_CAP)
         while ((t.n >> depth) > BW_CAP * 3 / 4) ++depth;
     for (;;) {
-        u32 cnt;
-        if (depth == 0) {
-            cnt = stage_all<AT>(s, t, wv, keys, amps);
-        } else {
-            cnt = uni(stage_part<AT>(s, t, wv, keys, amps, g.notmask, depth, pre));
+        u32 cnt = t.n;
+        if (depth) {
+            cnt = uni(stage_part<AT>(s, t, keys, amps, g.nm, depth, pre));
             if (cnt > BW_CAP) { // split the prefix (at 64 bits a part is one group)
                 ++depth;
                 pre <<= 1;
@@ -213,32 +465,10 @@ __device__ __forceinline__ void share_groups(BktSmem<AT> &s, const GateArg &g, c
             }
         }
         wave_sync();
-        const u32 ng = build_groups<AT, M>(s, g, wv, cnt);
-#pragma unroll 1
-        for (u32 r0 = 0; r0 < ng; r0 += 64) {
-            const u32 q = r0 + lane;
-            Group<AT, M> G;
-            G.present = 0;
-            G.rest = 0;
-            group_clear<AT, M>(G);
-            if (q < ng) {
-                const u32 sl = s.lead[wv][q];
-                const unsigned long long w = s.slot[wv][sl];
-                s.slot[wv][sl] = 0; // free again for the next part
-                const int f = (__ffsll((long long)w) - 1) & ~15;
-                G.rest = s.key[wv][(u32)((w >> f) & 0xffffu) - 1u] & g.notmask;
-#pragma unroll
-                for (int j = 0; j < (1 << M); ++j) {
-                    const u32 i = (u32)((w >> (16 * j)) & 0xffffu);
-                    if (i) {
-                        G.v[j] = s.amp[wv][i - 1];
-                        G.present |= 1u << j;
-                    }
-                }
-            }
-            body(G);
-        }
-        wave_sync();
+        staged_groups<AT, M>(s, ucol, g, cnt, [&]() {
+            if (first) grouped();
+            first = false;
+        }, body);
         if (depth == 0) break;
         ++pre;
         if (depth < 64 && pre == (1ull << depth)) break;
@@ -246,64 +476,90 @@ __device__ __forceinline__ void share_groups(BktSmem<AT> &s, const GateArg &g, c
     }
 }
 
-template <typename AT> __device__ __forceinline__ void clear_slots(BktSmem<AT> &s)
+template <typename AT, int M, typename F>
+__device__ __forceinline__ void share_groups(WaveSmem<AT> &s, const AT *ucol, const GateLoc<M> &g, const Share &t,
+                                             const u64 *__restrict__ keys, const AT *__restrict__ amps, F &&body)
 {
-    unsigned long long *p = &s.slot[0][0];
-    for (int i = threadIdx.x; i < BW * BW_SLOTS; i += STS_WG) p[i] = 0;
+    if (t.n <= BW_CAP) {
+        Staged<AT> st;
+        stage_load<AT>(st, t, keys, amps);
+        stage_store<AT>(s, st, t.n);
+    }
+    share_parts<AT, M>(s, ucol, g, t, keys, amps, []() {}, body);
+}
+
+// before the first share (the caller's barrier follows)
+template <typename AT, int M, int NW>
+__device__ __forceinline__ void smem_begin(BktSmem<AT, NW> &s, const GateArg &g)
+{
+    typedef typename Scalar<AT>::T R;
+    WaveSmem<AT> &w = s.w[threadIdx.x >> 6];
+    for (int i = sts_lane(); i < BW_SLOTS; i += 64) w.slot[i] = 0;
+    if (threadIdx.x < (1 << (2 * M))) {
+        const int i = (int)threadIdx.x & ((1 << M) - 1), j = (int)threadIdx.x >> M;
+        AT u;
+        u.x = UEntry<R, M>::re(g, i, j);
+        u.y = UEntry<R, M>::im(g, i, j);
+        s.ucol[threadIdx.x] = u;
+    }
 }
 
 __device__ __forceinline__ u32 bkt_tiles(const BktPlan &p) { return 1u << (p.hb - STS_BKT_DIMS); }
 
+// candidates of one output pattern, one per lane, to the wave's slab: the
+// window's from its start, those above it from its end
+struct SlabOut {
+    u32 c_in, c_ab, c_all; // the wave's claims so far, and its candidates (the same in every lane)
+    bool fits;
+};
+
+template <typename AT>
+__device__ __forceinline__ void slab_put(SlabOut &o, u64 *sk, u64 *sw, AT *sa, u32 room, bool inw, bool ab, u64 key,
+                                         u64 wb, const AT &v)
+{
+    const u64 m_ab = wballot(ab), m_in = wballot(inw);
+    const u32 n_ab = (u32)__popcll(m_ab), n_in = (u32)__popcll(m_in);
+    o.fits = o.fits && o.c_in + o.c_ab + n_ab + n_in <= room;
+    if (o.fits && (inw || ab)) {
+        const u32 at = inw ? o.c_in + sts_lanes_below(m_in) : room - 1u - o.c_ab - sts_lanes_below(m_ab);
+        sts_store_at(sk, at * 8u, key);
+        sts_store_at(sa, at * (u32)sizeof(AT), v);
+        if (inw) sts_store_at(sw, at * 8u, wb);
+    }
+    o.c_in += n_in;
+    o.c_ab += n_ab;
+}
+
 // ---------------------------------------------------------------------------
 // histogram pass: exponent histogram with exact mantissa sums of all new
-// weights; the window's candidates and those above it to the wave's slab (2^
-// side_slab_shift entries: the window's from its start, those above from its
-// end); a slab that is too small marks the window as missed. Persistent grid.
+// weights; with b.predict also the candidates of the previous cut's octave
+// and those above it to the wave's slab. A slab that is too small marks the
+// window as missed. Persistent grid. With b.recover it runs only after a
+// sampled window that missed (and copies nothing).
 // ---------------------------------------------------------------------------
 template <typename AT, int M>
-__global__ void __launch_bounds__(STS_WG, 3) k_bkt_hist(const GateArg *__restrict__ gp, PassBufs b)
+__global__ void __launch_bounds__(STS_WG) k_bkt_hist(const GateArg *__restrict__ gp, PassBufs b)
 {
     const GateArg &g = *gp;
-    __shared__ BktSmem<AT> s;
+    const GateLoc<M> gl = gate_loc<M>(g);
+    __shared__ BktSmem<AT, BW> s;
     __shared__ u64 s_hi[TT_SLOTS], s_lo[TT_SLOTS];
     __shared__ u64 s_wacc[6];
-    __shared__ u64 s_w2hi[TT_W2], s_w2lo[TT_W2];
-    clear_slots<AT>(s);
+    DevCtl *ctl = b.ctl;
+    if (b.recover && !ctl->need_full) return; // uniform
+    smem_begin<AT, M, BW>(s, g);
     for (int i = threadIdx.x; i < TT_SLOTS; i += STS_WG) {
         s_hi[i] = 0;
         s_lo[i] = 0;
     }
-    for (int i = threadIdx.x; i < TT_W2; i += STS_WG) {
-        s_w2hi[i] = 0;
-        s_w2lo[i] = 0;
-    }
     if (threadIdx.x < 6) s_wacc[threadIdx.x] = 0;
-    DevCtl *ctl = b.ctl;
     const u64 *keys = b.keys;
     const AT *amps = (const AT *)b.amps;
     const u32 ntiles = bkt_tiles(g.bkt);
-    int e_w = -1;
-    u64 w_lo = 0, w_hi = 0;
-    bool fine = false;
-    if (b.predict) {
-        if (ctl->w_mode) {
-            e_w = ctl->e_w;
-            w_lo = ctl->w_lo;
-            w_hi = ctl->w_hi;
-            fine = true;
-        } else if (ctl->e_pred >= 0) {
-            e_w = ctl->e_pred;
-            w_lo = (u64)e_w << 52;
-            w_hi = w_lo | ((1ull << 52) - 1);
-        }
-    }
+    const int e_w = b.predict ? ctl->e_pred : -1;
     const bool predict = e_w >= 0;
-    const u32 d_lo = (u32)((((1ull << 52) - 1) - (w_hi & ((1ull << 52) - 1))) >> 41);
-    const u32 d_top = 2047u - d_lo;
-    // the window's edges are multiples of 2^47 in the weight bits: the high
-    // words decide
-    const u32 wL = (u32)(w_lo >> 32), wH = (u32)((w_hi + 1) >> 32), wE1 = (u32)(e_w + 1) << 20;
-    u64 ma = 0, mw = 0;
+    const u32 wL = uni((u32)e_w << 20), wH = uni((u32)(e_w + 1) << 20); // the octave, in the weight's high word
+    u64 mw = 0;
     const int shift = b.slab_shift;
     if (predict && blockIdx.x == 0 && threadIdx.x == 0) {
         ctl->side_dense = 0;
@@ -315,6 +571,7 @@ __global__ void __launch_bounds__(STS_WG, 3) k_bkt_hist(const GateArg *__restric
     const int copy = (int)(threadIdx.x % TT_HCOPIES);
     const int e_ref = predict ? e_w : (ctl->e_pred >= 0 ? ctl->e_pred : TT_EBASE + 116);
     const int hot_lo = e_ref - (TT_HOT - 4);
+    u64 ma = 0; // nothing lies above the octave inside its exponent
     __syncthreads();
     int since_flush = 0;
     for (u32 tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
@@ -323,7 +580,6 @@ __global__ void __launch_bounds__(STS_WG, 3) k_bkt_hist(const GateArg *__restric
             __syncthreads();
             flush_bins(b, s_hi, s_lo, hot_lo);
             if (predict) flush_window(s_wacc, ma, mw);
-            if (fine) flush_w2(b, s_w2hi, s_w2lo, d_lo);
             since_flush = 0;
             __syncthreads();
         }
@@ -331,44 +587,23 @@ __global__ void __launch_bounds__(STS_WG, 3) k_bkt_hist(const GateArg *__restric
         const Share sh = load_share(g.bkt, b.bd_in, tile, wv);
         const u32 sl = (tile << 2) + (u32)wv;
         const u64 slab = (u64)sl << shift;
-        const u32 room = 1u << shift;
         const bool direct = sh.n > BW_BINNED;
         u64 *const sk = b.side_key + slab;
         u64 *const sw = b.side_w + slab;
         AT *const sa = (AT *)b.side_amp + slab;
-        u32 c_in = 0, c_ab = 0, c_all = 0;
-        bool fits = true;
-        share_groups<AT, M>(s, g, sh, wv, keys, amps, [&](const Group<AT, M> &G) {
+        SlabOut so = {0, 0, 0, true};
+        share_groups<AT, M>(s.w[wv], s.ucol, gl, sh, keys, amps, [&](const auto &ox, const auto &oy, u64 rest, bool active) {
 #pragma unroll
             for (int i = 0; i < (1 << M); ++i) {
-                const AT o = group_out<AT, M>(g, G, i);
-                const bool cand = G.present && nonzero(o);
+                AT o;
+                o.x = ox[i];
+                o.y = oy[i];
+                const bool cand = active && nonzero(o);
                 const u64 wb = weight_bits(o);
                 const int e_ = (int)(wb >> 52);
-                bool ab = false, inw = false;
+                const u32 hw = (u32)(wb >> 32);
                 if (cand) {
                     const u64 mant = sts_mant(wb);
-                    if (predict) {
-                        const u32 hw = (u32)(wb >> 32);
-                        ab = hw >= wH;
-                        inw = hw >= wL && !ab;
-                        mw += inw ? mant : 0ull;
-                        ma += (ab && hw < wE1) ? mant : 0ull;
-                        if (fine && inw) {
-                            const u32 rel = d_top - ((hw >> 9) & 2047u);
-                            if (rel >= (u32)TT_W2) { // outside the window's bins: cannot happen; fail the step
-                                atomicOr(&ctl->flags, STS_F_UNRESOLVED);
-                            } else if (direct) {
-                                const u32 d = d_lo + rel;
-                                atomicAdd(&b.h2w[d], 1ull);
-                                atomicAdd(&b.h2w[STS_NBIN + d], mant >> 26);
-                                atomicAdd(&b.h2w[2 * STS_NBIN + d], mant & ((1ull << 26) - 1));
-                            } else {
-                                atomicAdd(&s_w2hi[rel], mant >> TT_W2_LOW);
-                                atomicAdd(&s_w2lo[rel], (mant & ((1ull << TT_W2_LOW) - 1)) | (1ull << 44));
-                            }
-                        }
-                    }
                     const int bin = e_ - TT_EBASE;
                     const int hd = e_ - hot_lo;
                     if (!direct && ((unsigned)hd < (unsigned)TT_HOT || (unsigned)bin < (unsigned)TT_NB)) {
@@ -382,49 +617,272 @@ __global__ void __launch_bounds__(STS_WG, 3) k_bkt_hist(const GateArg *__restric
                         atomicAdd(&b.h1[STS_NBIN + e_], mant >> 26);
                         atomicAdd(&b.h1[2 * STS_NBIN + e_], mant & ((1ull << 26) - 1));
                     }
+                    if (predict) mw += e_ == e_w ? mant : 0ull;
                 }
-                c_all += (u32)__popcll(__ballot(cand));
-                if (predict) {
-                    const u64 m_ab = __ballot(ab), m_in = __ballot(inw);
-                    const u32 n_ab = (u32)__popcll(m_ab), n_in = (u32)__popcll(m_in);
-                    fits = fits && c_in + c_ab + n_ab + n_in <= room;
-                    if (fits) {
-                        if (inw) {
-                            const u32 at = c_in + sts_lanes_below(m_in);
-                            sts_store_at(sk, at * 8u, G.rest | deposit_bits<M>((u32)i, g));
-                            sts_store_at(sw, at * 8u, wb);
-                            sts_store_at(sa, at * (u32)sizeof(AT), o);
-                        } else if (ab) {
-                            const u32 at = room - 1u - c_ab - sts_lanes_below(m_ab);
-                            sts_store_at(sk, at * 8u, G.rest | deposit_bits<M>((u32)i, g));
-                            sts_store_at(sa, at * (u32)sizeof(AT), o);
-                        }
-                    }
-                    c_in += n_in;
-                    c_ab += n_ab;
-                }
+                so.c_all += (u32)__popcll(wballot(cand));
+                if (predict)
+                    slab_put<AT>(so, sk, sw, sa, 1u << shift, cand && hw >= wL && hw < wH, cand && hw >= wH,
+                                 rest | pattern_bits<M>(gl, i), wb, o);
             }
             if (direct && predict) flush_window(s_wacc, ma, mw); // the lane sums are bounded for binned shares only
         });
         if (sts_lane() == 0) {
-            b.w_all[sl] = c_all;
+            b.w_all[sl] = so.c_all;
             if (predict) {
-                b.t_above[sl] = c_ab;
-                b.t_side[sl] = c_in;
-                if (!fits) atomicOr(&ctl->w_over, 1u);
-                atomicAdd((unsigned long long *)&s_wacc[0], (unsigned long long)c_ab);
-                atomicAdd((unsigned long long *)&s_wacc[3], (unsigned long long)c_in);
+                b.t_above[sl] = so.c_ab;
+                b.t_side[sl] = so.c_in;
+                if (!so.fits) atomicOr(&ctl->w_over, 1u);
+                atomicAdd((unsigned long long *)&s_wacc[0], (unsigned long long)so.c_ab);
+                atomicAdd((unsigned long long *)&s_wacc[3], (unsigned long long)so.c_in);
             }
         }
     }
     __syncthreads();
     flush_bins(b, s_hi, s_lo, hot_lo);
-    if (fine) flush_w2(b, s_w2hi, s_w2lo, d_lo);
     if (predict) {
         flush_window(s_wacc, ma, mw);
         __syncthreads();
         if (threadIdx.x < 6) b.wpart[threadIdx.x * STS_MAX_GROUPS + blockIdx.x] = s_wacc[threadIdx.x];
     }
+}
+
+// ---------------------------------------------------------------------------
+// weighing pass of a sampled step (large states): the window [w_lo, w_hi] is
+// set, so the exact masses needed are only the total's, the mass above the
+// window and the window's own level-2 bins. The first two are summed in
+// registers: a weight of the exponent fields [L, L + 28), L = e_w - 15, is a
+// multiple of u = 2^(L - 1075) below 2^80 u, and is split exactly into a
+// multiple of 2^40 u (by adding and subtracting 1.5 * 2^92 u) and a rest of
+// at most 2^39 u; sums of up to 2^12 of either stay exact in binary64. Weights
+// of other exponents go to the exponent bins.
+// ---------------------------------------------------------------------------
+struct FineSums {
+    double t1, t2, a1, a2; // total and above the window: the two parts
+};
+
+// add a lane's sums to the workgroup's (LDS, two's complement) and clear them
+__device__ __forceinline__ void flush_fine(u64 *s_acc, FineSums &f, double k1, double k2)
+{
+    const double v[4] = {f.t1 * k1, f.t2 * k2, f.a1 * k1, f.a2 * k2};
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        if (v[i] != 0.0) atomicAdd(&s_acc[i], (u64)(long long)v[i]);
+    f.t1 = f.t2 = f.a1 = f.a2 = 0.0;
+}
+
+// One workgroup per CU, whose waves' tables fill the LDS (16 waves for
+// complex64, 12 for complex128): the pass waits on chains of LDS round trips,
+// and more waves hide more of them. Four waves have one tile.
+template <typename AT> struct WeighWaves {
+    static constexpr int value = sizeof(AT) == 8 ? 16 : 12;
+};
+constexpr int WEIGH_COLD = 64; // exponent fields with LDS bins, from L - 38
+
+template <typename AT, int M>
+__global__ void __launch_bounds__(64 * WeighWaves<AT>::value, 1)
+    k_bkt_weigh(const GateArg *__restrict__ gp, PassBufs b)
+{
+    constexpr int NW = WeighWaves<AT>::value, NT = NW * 64, TPW = NW / 4;
+    const GateArg &g = *gp;
+    const GateLoc<M> gl = gate_loc<M>(g);
+    __shared__ BktSmem<AT, NW> s;
+    __shared__ u64 s_hi[WEIGH_COLD], s_lo[WEIGH_COLD]; // sums of mantissa >> 20; & (2^20 - 1), plus count << 44
+    __shared__ u64 s_w2[TT_W2]; // level-2 bins of the window: sums of the 41 mantissa bits below the bin's,
+    __shared__ u32 s_w2c[TT_W2]; // and counts
+    __shared__ u64 s_acc[7]; // flush_fine's four sums, then candidates: all, above the window, inside it
+    DevCtl *ctl = b.ctl;
+    if (!ctl->w_mode) return; // uniform: no window; the recovering histogram pass does the step
+    smem_begin<AT, M, NW>(s, g);
+    for (int i = threadIdx.x; i < WEIGH_COLD; i += NT) {
+        s_hi[i] = 0;
+        s_lo[i] = 0;
+    }
+    for (int i = threadIdx.x; i < TT_W2; i += NT) {
+        s_w2[i] = 0;
+        s_w2c[i] = 0;
+    }
+    if (threadIdx.x < 7) s_acc[threadIdx.x] = 0;
+    const u64 *keys = b.keys;
+    const AT *amps = (const AT *)b.amps;
+    const u32 ntiles = bkt_tiles(g.bkt);
+    const int e_w = ctl->e_w;
+    const u64 w_lo = ctl->w_lo, w_hi = ctl->w_hi;
+    const u32 d_lo = uni((u32)((((1ull << 52) - 1) - (w_hi & ((1ull << 52) - 1))) >> 41));
+    const u32 d_top = 2047u - d_lo;
+    // the window's edges are multiples of 2^47 in the weight bits: the high
+    // words decide
+    const u32 wL = uni((u32)(w_lo >> 32)), wH = uni((u32)((w_hi + 1) >> 32));
+    const int L = (int)uni((u32)sts_fine_low(e_w));
+    const u32 rL = (u32)L << 20, rN = 28u << 20;
+    const int e_cold = L - 38;
+    const double C = __longlong_as_double((long long)(((u64)(L + 40) << 52) | (1ull << 51)));
+    const double k1 = __longlong_as_double((long long)((u64)(2058 - L) << 52));
+    const double k2 = __longlong_as_double((long long)((u64)(2098 - L) << 52));
+    FineSums f = {0.0, 0.0, 0.0, 0.0};
+    u64 n_all = 0, n_above = 0, n_win = 0; // the wave's totals (the same in every lane)
+    bool over = false;
+    const int shift = b.slab_shift;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        ctl->side_dense = 0;
+        ctl->side_ntiles = (u64)ntiles << 2;
+        ctl->side_slab_shift = shift;
+        ctl->side_spt_log2 = 2;
+    }
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int tw = wv & 3; // the wave's share of its tile
+    auto flush = [&]() {
+        flush_fine(s_acc, f, k1, k2);
+        for (int i = threadIdx.x; i < WEIGH_COLD; i += NT) {
+            const u64 lo = s_lo[i];
+            if (lo >> 44) {
+                const u128 tot = ((u128)s_hi[i] << 20) + (u128)(lo & ((1ull << 44) - 1));
+                const int e = e_cold + i; // counted bins only: a field of the binary64 range
+                atomicAdd(&b.h1[e], lo >> 44);
+                atomicAdd(&b.h1[STS_NBIN + e], (u64)(tot >> 26));
+                atomicAdd(&b.h1[2 * STS_NBIN + e], (u64)tot & ((1ull << 26) - 1));
+            }
+            s_hi[i] = 0;
+            s_lo[i] = 0;
+        }
+        for (int i = threadIdx.x; i < TT_W2; i += NT) {
+            const u32 c = s_w2c[i];
+            if (c) {
+                const u32 d = d_lo + (u32)i;
+                // the bits a bin's mantissas share: the leading one and its top fraction bits
+                const u64 top = ((u64)(2048u | (2047u - d)) << 41);
+                const u128 tot = (u128)top * c + (u128)s_w2[i];
+                atomicAdd(&b.h2w[d], (u64)c);
+                atomicAdd(&b.h2w[STS_NBIN + d], (u64)(tot >> 26));
+                atomicAdd(&b.h2w[2 * STS_NBIN + d], (u64)tot & ((1ull << 26) - 1));
+            }
+            s_w2[i] = 0;
+            s_w2c[i] = 0;
+        }
+    };
+    __syncthreads();
+    // tiles in flight: the terms of this wave's next share are loaded while
+    // the current one is worked on, and the runs of the one after that
+    const u32 step = gridDim.x * TPW;
+    u32 tile = blockIdx.x * TPW + (u32)(wv >> 2);
+    const u32 rounds = (ntiles + step - 1) / step; // the same for every wave: the flushes have barriers
+    auto runs = [&](u32 t) { return load_runs(g.bkt, b.bd_in, t < ntiles ? t : 0u, tw); };
+    Share nx = share_of(runs(tile));
+    if (tile >= ntiles) nx.n = 0;
+    Staged<AT> st;
+    if (nx.n <= BW_CAP) stage_load<AT>(st, nx, keys, amps);
+    uint2 d2 = runs(tile + step);
+    for (u32 it = 0; it < rounds; ++it, tile += step) {
+        if (it && it % BW_FLUSH == 0) {
+            // a lane has added at most 16 * 32 * 4 weights, and the bins at
+            // most 16 * 16 * BW_BINNED * 4
+            __syncthreads();
+            flush();
+            __syncthreads();
+        }
+        const Share sh = nx;
+        if (sh.n <= BW_CAP) stage_store<AT>(s.w[wv], st, sh.n);
+        if (tile >= ntiles) continue;
+        const u32 sl = (tile << 2) + (u32)tw;
+        const u64 slab = (u64)sl << shift;
+        u64 *const sk = b.side_key + slab;
+        u64 *const sw = b.side_w + slab;
+        AT *const sa = (AT *)b.side_amp + slab;
+        const u32 room = 1u << shift;
+        u32 c_in = 0, c_ab = 0, c_all = 0; // the wave's claims so far (the same in every lane)
+        bool fits = true;
+        auto advance = [&]() {
+            nx = share_of(d2);
+            if (tile + step >= ntiles) nx.n = 0;
+            if (nx.n <= BW_CAP) stage_load<AT>(st, nx, keys, amps);
+            d2 = runs(tile + 2 * step);
+        };
+        if (sh.n > BW_BINNED) { // more than the sums are bounded for: the histogram pass takes the step
+            over = true;
+            advance();
+            continue;
+        }
+        share_parts<AT, M>(s.w[wv], s.ucol, gl, sh, keys, amps, advance, [&](const auto &ox, const auto &oy, u64 rest, bool active) {
+#pragma unroll
+            for (int i = 0; i < (1 << M); ++i) {
+                AT o;
+                o.x = ox[i];
+                o.y = oy[i];
+                const u64 wb = weight_bits(o); // 0 in lanes without a group
+                const u32 hw = (u32)(wb >> 32);
+                // (a complex64 weight is zero only when both parts are)
+                const bool cand = sizeof(AT) == 8 ? wb != 0 : nonzero(o);
+                const bool ab = hw >= wH, inw = hw >= wL && !ab;
+                const u64 m_ab = wballot(ab), m_in = wballot(inw), m_c = wballot(cand);
+                const u64 m_far = m_c & wballot(hw - rL >= rN);
+                double w = __longlong_as_double((long long)wb);
+                if (m_far) { // uniform: some weights are too far from the window for the sums
+                    if (cand && hw - rL >= rN) {
+                        w = 0.0;
+                        const int e_ = (int)(wb >> 52), bin = e_ - e_cold;
+                        const u64 mant = sts_mant(wb);
+                        if ((unsigned)bin < (unsigned)WEIGH_COLD) {
+                            atomicAdd(&s_hi[bin], mant >> 20);
+                            atomicAdd(&s_lo[bin], (mant & ((1ull << 20) - 1)) | (1ull << 44));
+                        } else {
+                            atomicAdd(&b.h1[e_], 1ull);
+                            atomicAdd(&b.h1[STS_NBIN + e_], mant >> 26);
+                            atomicAdd(&b.h1[2 * STS_NBIN + e_], mant & ((1ull << 26) - 1));
+                        }
+                    }
+                }
+                const double c1 = (w + C) - C, c2 = w - c1;
+                const double one = ab ? 1.0 : 0.0;
+                f.t1 += c1;
+                f.t2 += c2;
+                f.a1 = __builtin_fma(c1, one, f.a1);
+                f.a2 = __builtin_fma(c2, one, f.a2);
+                if (inw) {
+                    const u32 rel = d_top - ((hw >> 9) & 2047u); // below TT_W2: three sub-bins of 1/32 octave
+                    atomicAdd(&s_w2[rel], wb & ((1ull << 41) - 1));
+                    atomicAdd(&s_w2c[rel], 1u);
+                }
+                c_all += (u32)__popcll(m_c);
+                // to the slab: the window's from its start, those above it from its end
+                const u32 n_ab = (u32)__popcll(m_ab), n_in = (u32)__popcll(m_in);
+                fits = fits && c_in + c_ab + n_ab + n_in <= room;
+                if (fits) {
+                    const u64 key = rest | pattern_bits<M>(gl, i);
+                    if (ab) {
+                        const u32 at = (room - 1u - c_ab - sts_lanes_below(m_ab)) * 8u;
+                        sts_store_at(sk, at, key);
+                        sts_store_at(sa, at * (u32)(sizeof(AT) / 8), o);
+                    }
+                    if (inw) {
+                        const u32 at = (c_in + sts_lanes_below(m_in)) * 8u;
+                        sts_store_at(sk, at, key);
+                        sts_store_at(sw, at, wb);
+                        sts_store_at(sa, at * (u32)(sizeof(AT) / 8), o);
+                    }
+                }
+                c_in += n_in;
+                c_ab += n_ab;
+            }
+        });
+        if (sts_lane() == 0) {
+            b.w_all[sl] = c_all;
+            b.t_above[sl] = c_ab;
+            b.t_side[sl] = c_in;
+        }
+        if (!fits) over = true;
+        n_all += c_all;
+        n_above += c_ab;
+        n_win += c_in;
+    }
+    if (sts_lane() == 0) {
+        if (over) atomicOr(&ctl->w_over, 1u);
+        atomicAdd(&s_acc[4], n_all);
+        atomicAdd(&s_acc[5], n_above);
+        atomicAdd(&s_acc[6], n_win);
+    }
+    __syncthreads();
+    flush();
+    __syncthreads();
+    if (threadIdx.x < 7) b.wpart[threadIdx.x * STS_MAX_GROUPS + blockIdx.x] = s_acc[threadIdx.x];
 }
 
 // ---------------------------------------------------------------------------
@@ -434,12 +892,13 @@ template <typename AT, int M>
 __global__ void __launch_bounds__(STS_WG) k_bkt_sample(const GateArg *__restrict__ gp, PassBufs b)
 {
     const GateArg &g = *gp;
-    __shared__ BktSmem<AT> s;
+    const GateLoc<M> gl = gate_loc<M>(g);
+    __shared__ BktSmem<AT, BW> s;
     __shared__ SampleSmem ss;
     DevCtl *ctl = b.ctl;
     const int e_prev = ctl->e_pred;
     if (e_prev < 0) return; // uniform: nothing to centre the bins on
-    clear_slots<AT>(s);
+    smem_begin<AT, M, BW>(s, g);
     SampleAcc acc;
     sample_begin(ss);
     __syncthreads();
@@ -453,11 +912,13 @@ __global__ void __launch_bounds__(STS_WG) k_bkt_sample(const GateArg *__restrict
         const Share sh = load_share(g.bkt, b.bd_in, tile, wv);
         if (sh.n <= BW_CAP) { // an overfull share is left out of the sample
             seen = sh.n;
-            share_groups<AT, M>(s, g, sh, wv, b.keys, (const AT *)b.amps, [&](const Group<AT, M> &G) {
+            share_groups<AT, M>(s.w[wv], s.ucol, gl, sh, b.keys, (const AT *)b.amps, [&](const auto &ox, const auto &oy, u64 rest, bool active) {
 #pragma unroll
                 for (int i = 0; i < (1 << M); ++i) {
-                    const AT o = group_out<AT, M>(g, G, i);
-                    if (G.present && nonzero(o)) sample_add(ss, acc, weight_bits(o), e_lo);
+                    AT o;
+                    o.x = ox[i];
+                    o.y = oy[i];
+                    if (active && nonzero(o)) sample_add(ss, acc, weight_bits(o), e_lo);
                 }
             });
         }
@@ -476,12 +937,13 @@ template <typename AT, int M>
 __global__ void __launch_bounds__(STS_WG) k_bkt_extract(const GateArg *__restrict__ gp, PassBufs b)
 {
     const GateArg &g = *gp;
-    __shared__ BktSmem<AT> s;
+    const GateLoc<M> gl = gate_loc<M>(g);
+    __shared__ BktSmem<AT, BW> s;
     __shared__ u32 s_cnt[BW];
     __shared__ u64 s_base;
     DevCtl *ctl = b.ctl;
     if (ctl->pred_hit || ctl->keep_all) return; // uniform
-    clear_slots<AT>(s);
+    smem_begin<AT, M, BW>(s, g);
     const int e_star = ctl->e_star;
     const u64 *keys = b.keys;
     const AT *amps = (const AT *)b.amps;
@@ -491,11 +953,13 @@ __global__ void __launch_bounds__(STS_WG) k_bkt_extract(const GateArg *__restric
     for (u32 tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
         const Share sh = load_share(g.bkt, b.bd_in, tile, wv);
         u32 cnt = 0;
-        share_groups<AT, M>(s, g, sh, wv, keys, amps, [&](const Group<AT, M> &G) {
+        share_groups<AT, M>(s.w[wv], s.ucol, gl, sh, keys, amps, [&](const auto &ox, const auto &oy, u64 rest, bool active) {
 #pragma unroll
             for (int i = 0; i < (1 << M); ++i) {
-                const AT o = group_out<AT, M>(g, G, i);
-                cnt += (u32)__popcll(__ballot(G.present && nonzero(o) && (int)(weight_bits(o) >> 52) == e_star));
+                AT o;
+                o.x = ox[i];
+                o.y = oy[i];
+                cnt += (u32)__popcll(wballot(active && nonzero(o) && (int)(weight_bits(o) >> 52) == e_star));
             }
         });
         if (sts_lane() == 0) s_cnt[wv] = cnt;
@@ -504,16 +968,18 @@ __global__ void __launch_bounds__(STS_WG) k_bkt_extract(const GateArg *__restric
         __syncthreads();
         u64 at = s_base;
         for (int w = 0; w < wv; ++w) at += s_cnt[w];
-        share_groups<AT, M>(s, g, sh, wv, keys, amps, [&](const Group<AT, M> &G) {
+        share_groups<AT, M>(s.w[wv], s.ucol, gl, sh, keys, amps, [&](const auto &ox, const auto &oy, u64 rest, bool active) {
 #pragma unroll
             for (int i = 0; i < (1 << M); ++i) {
-                const AT o = group_out<AT, M>(g, G, i);
+                AT o;
+                o.x = ox[i];
+                o.y = oy[i];
                 const u64 wb = weight_bits(o);
-                const bool take = G.present && nonzero(o) && (int)(wb >> 52) == e_star;
-                const u64 m = __ballot(take);
+                const bool take = active && nonzero(o) && (int)(wb >> 52) == e_star;
+                const u64 m = wballot(take);
                 const u64 p = at + sts_lanes_below(m);
                 if (take && p < b.side_cap) {
-                    b.side_key[p] = G.rest | deposit_bits<M>((u32)i, g);
+                    b.side_key[p] = rest | pattern_bits<M>(gl, i);
                     b.side_w[p] = wb;
                 }
                 at += (u64)__popcll(m);
@@ -532,11 +998,12 @@ template <typename AT, int M>
 __global__ void __launch_bounds__(STS_WG) k_bkt_count(const GateArg *__restrict__ gp, PassBufs b)
 {
     const GateArg &g = *gp;
-    __shared__ BktSmem<AT> s;
+    const GateLoc<M> gl = gate_loc<M>(g);
+    __shared__ BktSmem<AT, BW> s;
     DevCtl *ctl = b.ctl;
     const bool all = b.materialise;
     if (!all && (ctl->pred_hit || ctl->keep_all)) return; // uniform
-    clear_slots<AT>(s);
+    smem_begin<AT, M, BW>(s, g);
     const u64 thr_w = ctl->thr_wbits, thr_k = ctl->thr_key;
     const u32 ntiles = bkt_tiles(g.bkt);
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -544,13 +1011,15 @@ __global__ void __launch_bounds__(STS_WG) k_bkt_count(const GateArg *__restrict_
     for (u32 tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
         const Share sh = load_share(g.bkt, b.bd_in, tile, wv);
         u32 cnt = 0;
-        share_groups<AT, M>(s, g, sh, wv, b.keys, (const AT *)b.amps, [&](const Group<AT, M> &G) {
+        share_groups<AT, M>(s.w[wv], s.ucol, gl, sh, b.keys, (const AT *)b.amps, [&](const auto &ox, const auto &oy, u64 rest, bool active) {
 #pragma unroll
             for (int i = 0; i < (1 << M); ++i) {
-                const AT o = group_out<AT, M>(g, G, i);
-                const u64 key = G.rest | deposit_bits<M>((u32)i, g);
+                AT o;
+                o.x = ox[i];
+                o.y = oy[i];
+                const u64 key = rest | pattern_bits<M>(gl, i);
                 cnt += (u32)__popcll(
-                    __ballot(G.present && nonzero(o) && survives<AT>(weight_bits(o), key, all, thr_w, thr_k)));
+                    wballot(active && nonzero(o) && survives<AT>(weight_bits(o), key, all, thr_w, thr_k)));
             }
         });
         if (sts_lane() == 0) b.w_kept[(tile << 2) + (u32)wv] = cnt;
@@ -567,9 +1036,9 @@ constexpr int BW_SUBS = 64; // output buckets of a share, at most 4 << 4
 // far (cnt: the running counts, in LDS); lanes without one take part
 __device__ __forceinline__ u32 sub_rank(bool keep, u32 sub, int bits, u32 *cnt)
 {
-    u64 peers = __ballot(keep);
+    u64 peers = wballot(keep);
     for (int t = 0; t < bits; ++t) {
-        const u64 bb = __ballot((sub >> t) & 1u);
+        const u64 bb = wballot((sub >> t) & 1u);
         peers &= ((sub >> t) & 1u) ? bb : ~bb;
     }
     u32 pre = 0;
@@ -607,140 +1076,193 @@ __device__ __forceinline__ void sub_starts(const BktPlan &p, const PassBufs &b, 
     wave_sync();
 }
 
-template <typename AT, int M>
-__global__ void __launch_bounds__(STS_WG) k_bkt_emit(const GateArg *__restrict__ gp, PassBufs b)
+// a share's first output slot
+__device__ __forceinline__ u32 share_base(const PassBufs &b, u32 tile, int wv)
 {
-    constexpr int UN = 8; // items of a share held in registers
-    const GateArg &g = *gp;
-    __shared__ BktSmem<AT> s;
+    u64 base = b.t_base[tile / STS_BKT_CHUNK] + b.t_off[tile];
+    for (int w = 0; w < wv; ++w) base += b.w_kept[(tile << 2) + (u32)w];
+    return (u32)base;
+}
+
+// when the window held the cut, the survivors are in the wave's slab: all
+// entries above the window, and the window's by the threshold
+template <typename AT>
+__global__ void __launch_bounds__(STS_WG) k_bkt_copy(const GateArg *__restrict__ gp, PassBufs b)
+{
+    constexpr int UN = 8; // items of a share held in registers, per lane
+    const BktPlan &p = gp->bkt;
     __shared__ u32 s_cnt[BW][BW_SUBS];
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const u32 lane = (u32)sts_lane();
     const u32 tile = blockIdx.x;
+    const DevCtl *ctl = b.ctl;
+    const int keep_all = ctl->keep_all, hit = ctl->pred_hit;
+    const u64 thr_w = ctl->thr_wbits, thr_k = ctl->thr_key;
+    const double scale = ctl->scale;
+    const bool rescale = ctl->dropped;
+    const int bits = 2 + p.delta, shift = ctl->side_slab_shift;
+    if (keep_all || !hit) return; // uniform
+    const u32 sl = (tile << 2) + (u32)wv;
+    u32 *cnt = s_cnt[wv];
+    cnt[lane] = 0;
+    const u32 na = uni(b.t_above[sl]), ns = uni(b.t_side[sl]), n = na + ns;
+    const u32 base = uni(share_base(b, tile, wv));
+    wave_sync();
+    const u32 cap = (u32)b.out_cap;
+    u64 *ok = b.out_keys;
+    AT *oa = (AT *)b.out_amps;
+    const u64 slab = (u64)sl << shift;
+    const u64 *sk = b.side_key + slab, *sw = b.side_w + slab;
+    const AT *sa = (const AT *)b.side_amp + slab;
+    const u32 ab0 = (1u << shift) - na; // the entries above the window
+    auto place = [&](u32 j) { return j < na ? ab0 + j : j - na; };
+    if (n <= UN * 64) {
+        u64 kk[UN], ww[UN];
+        AT aa[UN];
+#pragma unroll
+        for (int r = 0; r < UN; ++r) {
+            const u32 j = (u32)r * 64 + lane;
+            ww[r] = ~0ull; // above the window: kept
+            if (j < n) {
+                const u32 i = place(j);
+                kk[r] = __builtin_nontemporal_load(&sk[i]);
+                aa[r].x = __builtin_nontemporal_load(&sa[i].x);
+                aa[r].y = __builtin_nontemporal_load(&sa[i].y);
+                if (j >= na) ww[r] = __builtin_nontemporal_load(&sw[i]);
+            }
+        }
+        u32 pos[UN];
+#pragma unroll
+        for (int r = 0; r < UN; ++r) {
+            pos[r] = ~0u;
+            if ((u32)r * 64 < n) { // uniform
+                const bool keep = (u32)r * 64 + lane < n && survives<AT>(ww[r], kk[r], false, thr_w, thr_k);
+                const u32 sub = keep ? sub_bucket(p, kk[r]) : 0u;
+                const u32 rank = sub_rank(keep, sub, bits, cnt);
+                if (keep) pos[r] = rank | (sub << 26); // ranks are below UN * 64
+            }
+        }
+        wave_sync();
+        sub_starts(p, b, tile, wv, base, cnt);
+#pragma unroll
+        for (int r = 0; r < UN; ++r) {
+            if (pos[r] == ~0u) continue;
+            const u32 at = cnt[pos[r] >> 26] + (pos[r] & ((1u << 26) - 1u));
+            if (at < cap) {
+                ok[at] = kk[r];
+                const AT o = out_amp(aa[r], rescale, scale);
+                __builtin_nontemporal_store(o.x, &oa[at].x);
+                __builtin_nontemporal_store(o.y, &oa[at].y);
+            }
+        }
+        return;
+    }
+    // a large share: count, then place
+    for (int phase = 0; phase < 2; ++phase) {
+        for (u32 j0 = 0; j0 < n; j0 += 64) {
+            const u32 j = j0 + lane;
+            bool keep = false;
+            u64 k = 0;
+            u32 i = 0;
+            if (j < n) {
+                i = place(j);
+                k = sk[i];
+                keep = j < na || survives<AT>(sw[i], k, false, thr_w, thr_k);
+            }
+            const u32 at = sub_rank(keep, keep ? sub_bucket(p, k) : 0u, bits, cnt);
+            if (phase && keep && at < cap) {
+                ok[at] = k;
+                oa[at] = out_amp(sa[i], rescale, scale);
+            }
+        }
+        wave_sync();
+        if (phase == 0) sub_starts(p, b, tile, wv, base, cnt);
+    }
+}
+
+// otherwise (also when nothing is cut) they are computed again
+template <typename AT, int M>
+__global__ void __launch_bounds__(STS_WG) k_bkt_emit(const GateArg *__restrict__ gp, PassBufs b)
+{
+    const GateArg &g = *gp;
+    const BktPlan &p = g.bkt;
+    const GateLoc<M> gl = gate_loc<M>(g);
+    __shared__ BktSmem<AT, BW> s;
+    __shared__ u32 s_cnt[BW][BW_SUBS];
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const DevCtl *ctl = b.ctl;
     const int keep_all = ctl->keep_all, dropped = ctl->dropped, hit = ctl->pred_hit;
     const u64 thr_w = ctl->thr_wbits, thr_k = ctl->thr_key;
     const double scale = ctl->scale;
     const bool all = b.materialise || keep_all;
     const bool rescale = !all && dropped;
-    const BktPlan &p = g.bkt;
+    if (!all && hit) return; // uniform
+    smem_begin<AT, M, BW>(s, g);
+    __syncthreads();
     const int bits = 2 + p.delta;
-    const u32 sl = (tile << 2) + (u32)wv;
-    u32 *cnt = s_cnt[wv];
-    cnt[lane] = 0;
-    u64 base64 = b.t_off[tile];
-    for (int w = 0; w < wv; ++w) base64 += b.w_kept[(tile << 2) + (u32)w];
-    const u32 base = (u32)base64;
-    wave_sync();
-    const u32 cap = (u32)b.out_cap;
+    const u32 cap = (u32)b.out_cap, ntiles = bkt_tiles(p);
     u64 *ok = b.out_keys;
     AT *oa = (AT *)b.out_amps;
-    if (!all && hit) {
-        const int shift = ctl->side_slab_shift;
-        const u32 na = b.t_above[sl], ns = b.t_side[sl], n = na + ns;
-        const u64 slab = (u64)sl << shift;
-        const u64 ab0 = slab + (1ull << shift) - na; // the entries above the window
-        const AT *sa = (const AT *)b.side_amp;
-        auto place = [&](u32 j) { return j < na ? ab0 + j : slab + (j - na); };
-        if (n <= UN * 64) {
-            u64 kk[UN];
-            AT aa[UN];
-            u64 ww[UN];
-#pragma unroll
-            for (int r = 0; r < UN; ++r) {
-                const u32 j = (u32)r * 64 + lane;
-                ww[r] = 0;
-                if (j < n) {
-                    const u64 i = place(j);
-                    kk[r] = __builtin_nontemporal_load(&b.side_key[i]);
-                    aa[r].x = __builtin_nontemporal_load(&sa[i].x);
-                    aa[r].y = __builtin_nontemporal_load(&sa[i].y);
-                    if (j >= na) ww[r] = b.side_w[i];
-                }
-            }
-            u32 pos[UN], sub[UN];
-#pragma unroll
-            for (int r = 0; r < UN; ++r) {
-                const u32 j = (u32)r * 64 + lane;
-                const bool keep = j < n && (j < na || survives<AT>(ww[r], kk[r], false, thr_w, thr_k));
-                sub[r] = keep ? sub_bucket(p, kk[r]) : 0u;
-                pos[r] = sub_rank(keep, sub[r], bits, cnt);
-                if (!keep) sub[r] = ~0u;
-            }
-            wave_sync();
-            sub_starts(p, b, tile, wv, base, cnt);
-#pragma unroll
-            for (int r = 0; r < UN; ++r) {
-                if (sub[r] == ~0u) continue;
-                const u32 at = cnt[sub[r]] + pos[r];
-                if (at < cap) {
-                    ok[at] = kk[r];
-                    const AT o = out_amp(aa[r], rescale, scale);
-                    __builtin_nontemporal_store(o.x, &oa[at].x);
-                    __builtin_nontemporal_store(o.y, &oa[at].y);
-                }
-            }
-            return;
-        }
-        // a large share: count, then place
+    u32 *cnt = s_cnt[wv];
+    for (u32 tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+        cnt[sts_lane()] = 0;
+        const u32 base = uni(share_base(b, tile, wv));
+        wave_sync();
+        const Share sh = load_share(p, b.bd_in, tile, wv);
+#pragma unroll 1
         for (int phase = 0; phase < 2; ++phase) {
-            for (u32 j0 = 0; j0 < n; j0 += 64) {
-                const u32 j = j0 + lane;
-                bool keep = false;
-                u64 k = 0, i = 0;
-                if (j < n) {
-                    i = place(j);
-                    k = b.side_key[i];
-                    keep = j < na || survives<AT>(b.side_w[i], k, false, thr_w, thr_k);
+            share_groups<AT, M>(s.w[wv], s.ucol, gl, sh, b.keys, (const AT *)b.amps,
+                                [&](const auto &ox, const auto &oy, u64 rest, bool active) {
+#pragma unroll
+                for (int i = 0; i < (1 << M); ++i) {
+                    AT o;
+                    o.x = ox[i];
+                    o.y = oy[i];
+                    const u64 key = rest | pattern_bits<M>(gl, i);
+                    const bool keep =
+                        active && nonzero(o) && survives<AT>(weight_bits(o), key, all, thr_w, thr_k);
+                    const u32 at = sub_rank(keep, keep ? sub_bucket(p, key) : 0u, bits, cnt);
+                    if (phase && keep && at < cap) {
+                        ok[at] = key;
+                        oa[at] = out_amp(o, rescale, scale);
+                    }
                 }
-                const u32 at = sub_rank(keep, keep ? sub_bucket(p, k) : 0u, bits, cnt);
-                if (phase && keep && at < cap) {
-                    ok[at] = k;
-                    oa[at] = out_amp(sa[i], rescale, scale);
-                }
-            }
+            });
             wave_sync();
             if (phase == 0) sub_starts(p, b, tile, wv, base, cnt);
         }
-        return;
-    }
-    // recompute
-    clear_slots<AT>(s);
-    __syncthreads();
-    const Share sh = load_share(p, b.bd_in, tile, wv);
-#pragma unroll 1
-    for (int phase = 0; phase < 2; ++phase) {
-        share_groups<AT, M>(s, g, sh, wv, b.keys, (const AT *)b.amps, [&](const Group<AT, M> &G) {
-#pragma unroll
-            for (int i = 0; i < (1 << M); ++i) {
-                const AT o = group_out<AT, M>(g, G, i);
-                const u64 key = G.rest | deposit_bits<M>((u32)i, g);
-                const bool keep =
-                    G.present && nonzero(o) && survives<AT>(weight_bits(o), key, all, thr_w, thr_k);
-                const u32 at = sub_rank(keep, keep ? sub_bucket(p, key) : 0u, bits, cnt);
-                if (phase && keep && at < cap) {
-                    ok[at] = key;
-                    oa[at] = out_amp(o, rescale, scale);
-                }
-            }
-        });
-        if (phase == 0) sub_starts(p, b, tile, wv, base, cnt);
     }
 }
 
 // ---------------------------------------------------------------------------
 // launches
 // ---------------------------------------------------------------------------
+// workgroups of a persistent pass that are resident at once
+template <typename F> int resident_groups(F kernel, int threads)
+{
+    int per_cu = 0, dev = 0, cus = 0;
+    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0);
+    (void)hipGetDevice(&dev);
+    (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    return std::min((per_cu > 0 ? per_cu : 1) * (cus > 0 ? cus : 1), STS_MAX_GROUPS);
+}
+
 template <typename AT, int M> int hist_capacity_b()
 {
-    static const int cap = [] {
-        int per_cu = 0, dev = 0, cus = 0;
-        (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_bkt_hist<AT, M>, STS_WG, 0);
-        (void)hipGetDevice(&dev);
-        (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-        return std::min((per_cu > 0 ? per_cu : 1) * (cus > 0 ? cus : 1), STS_MAX_GROUPS);
-    }();
+    static const int cap = resident_groups(k_bkt_hist<AT, M>, STS_WG);
     return cap;
+}
+
+template <typename AT, int M> int weigh_capacity()
+{
+    static const int cap = resident_groups(k_bkt_weigh<AT, M>, 64 * WeighWaves<AT>::value);
+    return cap;
+}
+
+template <typename AT, int M> int weigh_grid(int tiles)
+{
+    constexpr int per = WeighWaves<AT>::value / 4;
+    return std::min((tiles + per - 1) / per, weigh_capacity<AT, M>());
 }
 
 template <typename AT, int M> hipError_t launch_m(int kind, const PassBufs &b, int tiles, hipStream_t s)
@@ -759,8 +1281,16 @@ template <typename AT, int M> hipError_t launch_m(int kind, const PassBufs &b, i
     case STS_BKT_COUNT:
         hipLaunchKernelGGL((k_bkt_count<AT, M>), dim3(std::min(tiles, cap)), dim3(STS_WG), 0, s, b.gate, b);
         break;
+    case STS_BKT_WEIGH:
+        hipLaunchKernelGGL((k_bkt_weigh<AT, M>), dim3(weigh_grid<AT, M>(tiles)),
+                           dim3(64 * WeighWaves<AT>::value), 0, s,
+                           b.gate, b);
+        break;
+    case STS_BKT_COPY:
+        hipLaunchKernelGGL((k_bkt_copy<AT>), dim3(tiles), dim3(STS_WG), 0, s, b.gate, b);
+        break;
     case STS_BKT_EMIT:
-        hipLaunchKernelGGL((k_bkt_emit<AT, M>), dim3(tiles), dim3(STS_WG), 0, s, b.gate, b);
+        hipLaunchKernelGGL((k_bkt_emit<AT, M>), dim3(std::min(tiles, cap)), dim3(STS_WG), 0, s, b.gate, b);
         break;
     default: return hipErrorInvalidValue;
     }

@@ -66,6 +66,7 @@ struct DevCtl {
     int w_mode;
     int e_w;
     u64 w_lo, w_hi;
+    int need_full;       // bucketed step: the sampled window missed; the histogram pass runs after all
     int level;           // last resolved level
     u64 cnt_before;      // terms ranked before the current subset
     u64 mb_lo, mb_hi;    // mantissa sum (units 2^(max(e*,1)-1075)) ranked before the subset inside e*
@@ -92,6 +93,11 @@ struct DevCtl {
 #define STS_F_OUT_OVERFLOW 2u
 #define STS_F_UNRESOLVED 4u
 #define STS_F_INEXACT 8u
+
+// lowest exponent field whose weights the weighing pass sums in registers
+// (a window is set only where it is at least STS_FINE_MIN - 15: see there)
+#define STS_FINE_MIN 100
+__host__ __device__ inline int sts_fine_low(int e_w) { return e_w - 15; }
 
 // --------------------------------------------------------------------------
 // hashing: a bijective 64-bit mixer (splitmix64 finalisation). Equal hashes

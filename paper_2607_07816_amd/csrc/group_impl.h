@@ -698,8 +698,8 @@ __device__ __forceinline__ void flush_one(const PassBufs &b, int e, u64 hi, u64 
     }
 }
 
-// add the LDS bins to the global exponent histogram and clear them
-__device__ __forceinline__ void flush_bins(const PassBufs &b, u64 *s_hi, u64 *s_lo, int hot_lo)
+// add the LDS bins of single exponents to the global histogram and clear them
+__device__ __forceinline__ void flush_cold(const PassBufs &b, u64 *s_hi, u64 *s_lo)
 {
     for (int i = threadIdx.x; i < TT_NB; i += STS_WG) {
         const u64 hi = s_hi[i], lo = s_lo[i];
@@ -707,6 +707,12 @@ __device__ __forceinline__ void flush_bins(const PassBufs &b, u64 *s_hi, u64 *s_
         s_lo[i] = 0;
         flush_one(b, TT_EBASE + i, hi, lo);
     }
+}
+
+// add the LDS bins to the global exponent histogram and clear them
+__device__ __forceinline__ void flush_bins(const PassBufs &b, u64 *s_hi, u64 *s_lo, int hot_lo)
+{
+    flush_cold(b, s_hi, s_lo);
     if (threadIdx.x < TT_HOT) {
         u64 hi = 0, lo = 0;
         const int at = TT_NB + (int)threadIdx.x * TT_HPER;
@@ -1163,11 +1169,11 @@ __device__ __forceinline__ void sample_finish(SampleSmem &s, const PassBufs &b, 
     __syncthreads();
     if (t == 0) {
         const u32 r = s.hit;
-        if (r == 0xffffffffu) {
+        const int fb = STS_SW_NB - 1 - (int)r;
+        const int ex = e_lo + (fb >> STS_SW_FB);
+        if (r == 0xffffffffu || ex < STS_FINE_MIN || ex > 2000) {
             ctl->w_mode = 0;
         } else {
-            const int fb = STS_SW_NB - 1 - (int)r;
-            const int ex = e_lo + (fb >> STS_SW_FB);
             const int sub = fb & ((1 << STS_SW_FB) - 1);
             const int lo_sub = sub > 0 ? sub - 1 : 0;
             const int hi_sub = sub + 1 < (1 << STS_SW_FB) ? sub + 1 : sub;

@@ -64,7 +64,7 @@ struct PassBufs {
     int copy;             // histogram pass: also keep every candidate above the window, with
                           // the window's amplitudes, in the tile's slab; emit pass: when the
                           // window held the cut, copy the survivors out of the slabs
-    u64 *wpart;           // [6][STS_MAX_GROUPS]: per histogram workgroup, the count of candidates
+    u64 *wpart;           // [7][STS_MAX_GROUPS] (the weighing pass: its sums); histogram passes [6][...]: per histogram workgroup, the count of candidates
                           // above the window and the mantissa sums (>> 26, & (2^26-1)) of those in
                           // the window's exponent; then the count and sums of those inside it
     // bucketed steps: the input's and the output's bucket tables (first and one past the last
@@ -73,7 +73,9 @@ struct PassBufs {
     uint2 *bd_out;
     u32 *w_all;
     u32 *w_kept;
+    u64 *t_base;          // output offset of every STS_BKT_CHUNK tiles (t_off is relative to it)
     int slab_shift;
+    int recover;          // histogram pass: only after a sampled window that missed
     u64 *sbins;           // sampling pass: STS_SW_BANKS x STS_SW_NB counts (u32), as many masses
                           // (float), then 4 totals per bank
 };
@@ -177,8 +179,12 @@ hipError_t launch_terms_out(const u64 *keys, const void *amps, int amp_bytes, co
 #define STS_BKT_EXTRACT 2
 #define STS_BKT_COUNT 3
 #define STS_BKT_EMIT 4
+#define STS_BKT_WEIGH 5
+#define STS_BKT_COPY 6
+#define STS_BKT_CHUNK 32 // tiles whose offsets are relative to one base
 hipError_t launch_bucket_pass(int kind, int prec, int m, const PassBufs &b, int tiles, hipStream_t s);
-int bucket_hist_capacity(int prec, int m);
+int bucket_hist_groups(int prec, int m, int tiles, bool weigh); // workgroups of the histogram or weighing pass
+hipError_t launch_pick_window(const PassBufs &b, int groups, hipStream_t s);
 // survivors per share (when the window held the cut or nothing is cut), then every tile's output offset
 hipError_t launch_bucket_kept(const PassBufs &b, int tiles, hipStream_t s);
 // the bucket table of terms that lie in bucket order

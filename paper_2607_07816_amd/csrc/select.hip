@@ -290,8 +290,11 @@ __global__ void __launch_bounds__(256) k_pick1(PassBufs b, int groups, int peak_
     // the exponent of the window the histogram pass copied (predicted steps)
     const int w_mode = ctl->w_mode;
     // (predicted = 2: a bucketed step, where a share's slab may have been too small for it)
+    // (3: one whose sampled window missed, the histogram pass having run after all)
+    if (predicted == 3 && !ctl->need_full) return; // uniform
+    const bool win = predicted == 1 || predicted == 2;
     const bool over = predicted == 2 && ctl->w_over != 0;
-    const int e_w = predicted ? (w_mode ? ctl->e_w : ctl->e_pred) : -1;
+    const int e_w = win ? (w_mode ? ctl->e_w : ctl->e_pred) : -1;
     if (t < 6) s_w[t] = 0;
     if (t == 0) s_fine = 0;
 
@@ -319,7 +322,7 @@ __global__ void __launch_bounds__(256) k_pick1(PassBufs b, int groups, int peak_
     // (loaded whenever the pass predicted, before the control block says
     // whether a window was copied)
     u64 v[6] = {0, 0, 0, 0, 0, 0};
-    if (predicted) {
+    if (win) {
 #pragma unroll
         for (int r = 0; r < STS_MAX_GROUPS / 256; ++r) { // every load issued before any is used
             const int i = t + 256 * r;
@@ -520,7 +523,7 @@ __global__ void __launch_bounds__(256) k_pick1(PassBufs b, int groups, int peak_
                     }
                 }
                 if (lane < STS_NL) ctl->S_excl.l[lane] = S;
-                if (lane == 0 && in_window && w_mode && predicted) {
+                if (lane == 0 && in_window && w_mode && win) {
                     // the histogram pass binned this window for level 2: the
                     // whole workgroup picks its digit below
                     s_fine = 1;
@@ -547,10 +550,11 @@ __global__ void __launch_bounds__(256) k_pick1(PassBufs b, int groups, int peak_
                 }
             }
             if (lane == 0) {
-                ctl->w2_mode = predicted && w_mode; // the histogram pass binned the window for level 2
+                ctl->w2_mode = win && w_mode; // the histogram pass binned the window for level 2
                 ctl->w_mode = 0;                     // a window serves one step
-                if (predicted == 2) {
+                if (predicted >= 2) {
                     ctl->w_over = 0;
+                    ctl->need_full = 0;
                     // a missed window: the extraction pass packs its candidates densely
                     if (hit != 0xffffffffu && !ctl->pred_hit) {
                         ctl->side_dense = 1;
@@ -582,6 +586,251 @@ __global__ void __launch_bounds__(256) k_pick1(PassBufs b, int groups, int peak_
             }
         }
         for (int i = t; i < 3 * STS_NBIN; i += 256) st_agent(&b.h2w[i], 0ull);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// level 1 and 2 of a sampled bucketed step, from the weighing pass's sums:
+// the exact total W, the exact mass above the window, and the window's level-2
+// bins. Decides exactly whether the window holds the cut; if so picks level 2,
+// if nothing is cut says so, and otherwise asks for the histogram pass.
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ u128 wave_sum128(u128 v)
+{
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) {
+        const u64 lo = __shfl_xor((u64)v, d, 64), hi = __shfl_xor((u64)(v >> 64), d, 64);
+        v += make128(lo, hi);
+    }
+    return v;
+}
+
+__global__ void __launch_bounds__(256) k_pick_window(PassBufs b, int groups)
+{
+    __shared__ unsigned short s_e[STS_NBIN]; // the non-empty exponent bins in rank order
+    __shared__ __attribute__((aligned(16))) u64 s_lo[STS_NBIN];
+    __shared__ u64 s_hi[STS_NBIN];
+    __shared__ u32 s_scan[4];
+    __shared__ u64 s_cnt[4][3];
+    __shared__ u64 s_sum[4][6]; // per wave: total, above, window (low and high words)
+    __shared__ u64 s_part[4][2][64];
+    __shared__ Sub s_sub;
+    __shared__ u32 s_fine, s_hit2;
+    __shared__ u64 s_R_lo, s_R_hi;
+    const int t = threadIdx.x, lane = t & 63, q = t >> 6;
+    DevCtl *ctl = b.ctl;
+    u64 *h1 = b.h1;
+    const int w_mode = ctl->w_mode, e = ctl->e_w;
+    const u32 over = ctl->w_over;
+    const u64 w_hi = ctl->w_hi;
+    if (t == 0) s_fine = 0;
+    __syncthreads(); // the control words are read
+    if (!w_mode || over) { // uniform: the histogram pass has to do the step
+        if (t == 0) {
+            ctl->need_full = 1;
+            ctl->w_mode = 0;
+            ctl->w_over = 0;
+            ctl->w2_mode = 0;
+            ctl->l2_done = 0;
+        }
+        if (w_mode)
+            for (int i = t; i < 3 * STS_NBIN; i += 256) {
+                h1[i] = 0;
+                st_agent(&b.h2w[i], 0ull);
+            }
+        return;
+    }
+    const int L = sts_fine_low(e);
+    // every load issued before any is used: the workgroups' sums,
+    u64 c_all = 0, c_ab = 0, c_in = 0;
+    u128 tot = 0, abv = 0; // units of 2^(L - 1075); the low parts may be negative
+#pragma unroll
+    for (int r = 0; r < STS_MAX_GROUPS / 256; ++r) {
+        const int i = t + 256 * r;
+        if (i < groups) {
+            const u64 *w = b.wpart + i;
+            tot += ((u128)w[0] << 40) + (u128)(__int128)(long long)w[STS_MAX_GROUPS];
+            abv += ((u128)w[2 * STS_MAX_GROUPS] << 40) + (u128)(__int128)(long long)w[3 * STS_MAX_GROUPS];
+            c_all += w[4 * STS_MAX_GROUPS];
+            c_ab += w[5 * STS_MAX_GROUPS];
+            c_in += w[6 * STS_MAX_GROUPS];
+        }
+    }
+    // the window's level-2 bins,
+    const u32 d_lo = (u32)((((1ull << 52) - 1) - (w_hi & ((1ull << 52) - 1))) >> 41);
+    u128 win = 0;
+    if (t < 192 && d_lo + (u32)t < STS_NBIN)
+        win = ((u128)ld_agent(&b.h2w[STS_NBIN + d_lo + t]) << 26) + (u128)ld_agent(&b.h2w[2 * STS_NBIN + d_lo + t]);
+    // and the exponent bins (weights far from the window)
+    u64 c[8], hi[8], lo[8];
+    u32 nz = 0;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        const int f = 2047 - 8 * t - k;
+        c[k] = h1[f];
+        hi[k] = h1[STS_NBIN + f];
+        lo[k] = h1[2 * STS_NBIN + f];
+        nz += c[k] ? 1u : 0u;
+    }
+    u32 nbins;
+    u32 at = block_excl_scan<u32, 256>(nz, s_scan, &nbins);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        if (!c[k]) continue;
+        s_e[at] = (unsigned short)(2047 - 8 * t - k);
+        const u128 ms = ((u128)hi[k] << 26) + (u128)lo[k];
+        s_lo[at] = (u64)ms;
+        s_hi[at] = (u64)(ms >> 64);
+        ++at;
+    }
+    tot = wave_sum128(tot);
+    abv = wave_sum128(abv);
+    win = wave_sum128(win);
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) {
+        c_all += __shfl_xor(c_all, d, 64);
+        c_ab += __shfl_xor(c_ab, d, 64);
+        c_in += __shfl_xor(c_in, d, 64);
+    }
+    if (lane == 0) {
+        s_cnt[q][0] = c_all;
+        s_cnt[q][1] = c_ab;
+        s_cnt[q][2] = c_in;
+        const u128 v[3] = {tot, abv, win};
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            s_sum[q][2 * i] = (u64)v[i];
+            s_sum[q][2 * i + 1] = (u64)(v[i] >> 64);
+        }
+    }
+    __syncthreads();
+    {
+        // the exponent bins in four chunks, one wave each: those above the
+        // register range, then those below
+        const u32 chunk = (nbins + 3) / 4;
+        const u32 j0 = (u32)q * chunk, j1 = j0 + chunk < nbins ? j0 + chunk : nbins;
+        u64 A = 0, B = 0;
+        for (u32 j = j0; j < j1; ++j) {
+            const u64 v = wl_piece(s_lo[j], s_hi[j], unit_bit((int)s_e[j]));
+            if ((int)s_e[j] >= L) A = wl_add(A, v);
+            else B = wl_add(B, v);
+        }
+        s_part[q][0][lane] = A;
+        s_part[q][1][lane] = B;
+    }
+    __syncthreads();
+    if (t < 64) { // one wave decides
+        u64 Sa = 0, W = 0;
+        c_all = c_ab = c_in = 0;
+        tot = abv = win = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            Sa = wl_add(Sa, s_part[i][0][lane]);
+            W = wl_add(W, s_part[i][1][lane]);
+            c_all += s_cnt[i][0];
+            c_ab += s_cnt[i][1];
+            c_in += s_cnt[i][2];
+            tot += make128(s_sum[i][0], s_sum[i][1]);
+            abv += make128(s_sum[i][2], s_sum[i][3]);
+            win += make128(s_sum[i][4], s_sum[i][5]);
+        }
+        W = wl_add(wl_add(W, Sa), wl_piece((u64)tot, (u64)(tot >> 64), unit_bit(L)));
+        Sa = wl_add(Sa, wl_piece((u64)abv, (u64)(abv >> 64), unit_bit(L)));
+        const u64 K = ctl->K;
+        const double p = ctl->p;
+        const bool p_on = p > 0.0 && p < 1.0;
+        u64 T = 0; // p-mass target ceil(p * W), exactly
+        if (p_on) {
+            const u64 pb = sts_dbits(p);
+            const u64 pe = pb >> 52, pf = pb & ((1ull << 52) - 1);
+            T = wl_mul_shr_ceil(W, pe ? (pf | (1ull << 52)) : pf, pe ? (int)(1075 - pe) : 1074);
+        }
+        const bool met_all = (K > 0 && c_all >= K) || (p_on && wl_cmp(W, T) >= 0);
+        const bool met_a = (K > 0 && c_ab >= K) || (p_on && wl_cmp(Sa, T) >= 0);
+        const u64 Sw = wl_add(Sa, wl_piece((u64)win, (u64)(win >> 64), unit_bit(e)));
+        const bool met_w = (K > 0 && c_ab + c_in >= K) || (p_on && wl_cmp(Sw, T) >= 0);
+        const bool hit = !met_a && met_w;
+        const double Wd = wl_to_double(W);
+        u64 R_lo = ~0ull, R_hi = ~0ull; // mass still to reach inside the window, in its units (rounded up)
+        if (p_on && hit) {
+            bool sticky;
+            const u64 r0 = wl_shr(wl_sub(T, Sa), unit_bit(e), &sticky);
+            const bool big = __ballot(lane >= 2 && r0 != 0) != 0;
+            u128 r = ((u128)__shfl(r0, 1, 64) << 64) | (u128)__shfl(r0, 0, 64);
+            if (!big) {
+                if (sticky) r += 1;
+                if (r != 0 || !sticky) {
+                    R_lo = (u64)r;
+                    R_hi = (u64)(r >> 64);
+                }
+            }
+        }
+        if (hit && lane < STS_NL) ctl->S_excl.l[lane] = Sa;
+        if (lane < STS_NL) ctl->T.l[lane] = T;
+        if (lane == 0) {
+            ctl->w_mode = 0;
+            ctl->w2_mode = 0;
+            ctl->l2_done = 0;
+            if (met_all && !hit) {
+                ctl->need_full = 1; // the cut lies elsewhere
+            } else {
+                ctl->cand_all = c_all;
+                ctl->W = Wd;
+                ctl->n_cand = c_all;
+                ctl->tot_steps += 1;
+                ctl->tot_updates += *b.n_in;
+                ctl->tot_cand += c_all;
+                ctl->level = 1;
+                if (!met_all) {
+                    ctl->keep_all = 1;
+                    ctl->dropped = 0;
+                    ctl->L = c_all;
+                    ctl->scale = 1.0;
+                    ctl->S = Wd;
+                    ctl->frac = 1.0;
+                    ctl->pred_hit = 0;
+                    ctl->e_pred = -1;
+                } else {
+                    ctl->keep_all = 0;
+                    ctl->pred_hit = 1;
+                    ctl->e_pred = e;
+                    ctl->e_star = e;
+                    ctl->R_lo = R_lo;
+                    ctl->R_hi = R_hi;
+                    s_fine = 1;
+                    s_sub.cnt_before = c_ab;
+                    s_sub.mb = 0; // S_excl holds all the mass above the window
+                    s_sub.vpre = 0;
+                    s_sub.vshift = 116;
+                    s_sub.count = c_in;
+                    s_R_lo = R_lo;
+                    s_R_hi = R_hi;
+                }
+            }
+        }
+    }
+    __syncthreads();
+    if (nbins)
+        for (int i = t; i < 3 * STS_NBIN; i += 256) h1[i] = 0;
+    if (s_fine) { // uniform: the bin lists above are done with, so their LDS serves the pick
+        const bool ok = pick_digit<256>(b.h2w, b.h2w + STS_NBIN, b.h2w + 2 * STS_NBIN, true, ctl->K,
+                                        make128(s_R_lo, s_R_hi), 11, &s_sub, reinterpret_cast<u128 *>(s_lo), s_hi,
+                                        &s_hit2);
+        if (ok && t <= STS_SUB_REGIONS) st_agent(&b.sub_cnt[t * 32], 0u);
+        if (t == 0) {
+            if (ok) {
+                sub_store(s_sub, ctl);
+                ctl->level = 2;
+                ctl->l2_done = 1;
+            } else {
+                atomicOr(&ctl->flags, STS_F_UNRESOLVED);
+            }
+        }
+    }
+    __syncthreads();
+    if (t < 192 && d_lo + (u32)t < STS_NBIN) {
+#pragma unroll
+        for (int f = 0; f < 3; ++f) st_agent(&b.h2w[f * STS_NBIN + d_lo + t], 0ull);
     }
 }
 
@@ -1267,6 +1516,12 @@ __global__ void __launch_bounds__(256) k_terms_out(const u64 *keys, const void *
 hipError_t launch_pick1(const PassBufs &b, int groups, int peak_only, int predicted, hipStream_t s)
 {
     hipLaunchKernelGGL(k_pick1, dim3(1), dim3(256), 0, s, b, groups, peak_only, predicted);
+    return hipGetLastError();
+}
+
+hipError_t launch_pick_window(const PassBufs &b, int groups, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_pick_window, dim3(1), dim3(256), 0, s, b, groups);
     return hipGetLastError();
 }
 
