@@ -47,14 +47,15 @@ struct Layout {
 u64 tiled_tiles(u64 cap) { return (cap + 2047) / 2048 + 1; }
 u64 side_capacity(u64 cap) { return tiled_tiles(cap) * (2048ull << 3); }
 
-// bucket bits of a state of at most n terms: a bucket holds 32 to 64 terms of
-// a full state, so that a wave's share (four buckets) is one or two hundred
-// and the four runs a wave reads are at least 256 bytes long
+// Bucket bits of a state of at most n terms. A wave's share is four buckets:
+// 128 to 256 terms of a large state, so that its runs are at least 256 bytes
+// long and its rounds of 64 lanes are full; of a state of less than 2^20 terms
+// rather 32 to 64, so that there are shares for every CU's waves.
 int bucket_bits(u64 n)
 {
     int lg = 0;
     while ((1ull << lg) < n && lg < 63) ++lg;
-    return std::max(lg - 6, STS_BKT_DIMS);
+    return std::max(lg <= 18 ? lg - 4 : std::max(14, lg - 6), STS_BKT_DIMS);
 }
 
 // largest state that is kept in bucket order (32-bit term indices, and bucket
@@ -63,7 +64,9 @@ constexpr u64 kBucketMax = 1ull << 28;
 // and the smallest that a gate step puts there: below, the sort passes are
 // one or two short launches
 constexpr u64 kBucketMin = 1024;
-constexpr int kSlabShift = 10; // entries of a share's slab (log2): four per term of a share of 256
+// up to this size bound a step's selection is one workgroup's (k_bkt_select);
+// above, the step samples its window first and spreads the selection
+constexpr u64 kSelectMax = 1ull << 15;
 
 Layout make_layout(u64 cap, int prec)
 {
@@ -314,7 +317,6 @@ PassBufs pass_bufs(sts_ctx *c, int in, int out)
     b.t_base = c->t_base;
     b.bd_in = c->bd[c->bdc];
     b.bd_out = c->bd[c->bdc ^ 1];
-    b.slab_shift = kSlabShift;
     b.tile_ctr = c->tctr + 4;
     b.wpart = c->wpart;
     b.sbins = c->sbins;
@@ -527,6 +529,16 @@ sts_status bucketize(sts_ctx *c)
     return STS_OK;
 }
 
+// entries of a share's slab (log2): the side buffer over the shares, at least
+// four entries per term of a share
+int slab_shift(const sts_ctx *c)
+{
+    const u64 shares = 1ull << (c->gate.bkt.hb - 2);
+    int sh = 0;
+    while (sh < 12 && (shares << (sh + 1)) <= c->scap) ++sh;
+    return sh;
+}
+
 int bucket_tiles(const sts_ctx *c) { return 1 << (c->gate.bkt.hb - STS_BKT_DIMS); }
 
 int bucket_groups(const sts_ctx *c, bool weigh)
@@ -538,9 +550,12 @@ int bucket_groups(const sts_ctx *c, bool weigh)
 sts_status bucket_write(sts_ctx *c, const PassBufs &b, int dst, u64 bound)
 {
     const int tiles = bucket_tiles(c);
-    STS_LAUNCH(c, STS_K_GROUP_EXTRACT, launch_bucket_pass(STS_BKT_COUNT, c->prec, c->gate.m, b, tiles, c->stream));
-    STS_LAUNCH(c, STS_K_TILE_KEPT, launch_bucket_kept(b, tiles, c->stream));
-    if (!b.materialise)
+    if (!b.emit_copies) { // else k_bkt_select has the offsets
+        STS_LAUNCH(c, STS_K_GROUP_EXTRACT,
+                   launch_bucket_pass(STS_BKT_COUNT, c->prec, c->gate.m, b, tiles, c->stream));
+        STS_LAUNCH(c, STS_K_TILE_KEPT, launch_bucket_kept(b, tiles, c->stream));
+    }
+    if (!b.materialise && !b.emit_copies)
         STS_LAUNCH(c, STS_K_GROUP_EMIT, launch_bucket_pass(STS_BKT_COPY, c->prec, c->gate.m, b, tiles, c->stream));
     STS_LAUNCH(c, STS_K_GROUP_EMIT, launch_bucket_pass(STS_BKT_EMIT, c->prec, c->gate.m, b, tiles, c->stream));
     c->cur = dst;
@@ -829,6 +844,7 @@ static sts_status truncate_buckets(sts_ctx *c)
     const int out = (c->cur + 1) % 3;
     PassBufs b = pass_bufs(c, c->cur, out);
     const int m = c->gate.m, tiles = bucket_tiles(c);
+    b.slab_shift = slab_shift(c);
     u64 nb = c->K ? std::min<u64>(c->K, cb) : cb;
     sts_status st = STS_OK;
     const bool out_risk = nb > c->cap; // a cut limited by p-mass alone may keep more than cap terms
@@ -836,7 +852,13 @@ static sts_status truncate_buckets(sts_ctx *c)
         st = save_ctl(c);
         if (st != STS_OK) return st;
     }
-    if (c->n_bound >= STS_SAMPLE_MIN) {
+    const bool small = c->n_bound <= kSelectMax && tiles * 4 <= STS_SEL_SHARES;
+    if (small) {
+        b.predict = 1;
+        STS_LAUNCH(c, STS_K_GROUP_HIST, launch_bucket_pass(STS_BKT_HIST, c->prec, m, b, tiles, c->stream));
+        STS_LAUNCH(c, STS_K_FINAL, launch_bucket_pass(STS_BKT_SELECT, c->prec, m, b, tiles, c->stream));
+        b.emit_copies = 1;
+    } else {
         // a window from a sample; the histogram pass and its pick run only
         // when it missed
         STS_LAUNCH(c, STS_K_SAMPLE, launch_bucket_pass(STS_BKT_SAMPLE, c->prec, m, b, tiles, c->stream));
@@ -845,17 +867,13 @@ static sts_status truncate_buckets(sts_ctx *c)
         b.recover = 1;
         STS_LAUNCH(c, STS_K_GROUP_HIST, launch_bucket_pass(STS_BKT_HIST, c->prec, m, b, tiles, c->stream));
         STS_LAUNCH(c, STS_K_PICK1, launch_pick1(b, 0, 0, 3, c->stream));
-    } else {
-        b.predict = 1;
-        STS_LAUNCH(c, STS_K_GROUP_HIST, launch_bucket_pass(STS_BKT_HIST, c->prec, m, b, tiles, c->stream));
-        b.predict = 0;
-        STS_LAUNCH(c, STS_K_PICK1, launch_pick1(b, bucket_groups(c, false), 0, 2, c->stream));
+        STS_LAUNCH(c, STS_K_GROUP_EXTRACT, launch_bucket_pass(STS_BKT_EXTRACT, c->prec, m, b, tiles, c->stream));
+        const int sg =
+            (int)std::min<u64>(std::max<u64>(ceil_div(std::min(cb, c->scap), 256), 1), STS_SIDE_GROUPS);
+        STS_LAUNCH(c, STS_K_SIDE_HIST, launch_side_hist(b, c->h2, sg, c->stream));
+        STS_LAUNCH(c, STS_K_SIDE_EXTRACT, launch_side_extract(b, std::max(sg, (tiles + 3) / 4), c->stream));
+        STS_LAUNCH(c, STS_K_FINAL, launch_final(b, c->stream));
     }
-    STS_LAUNCH(c, STS_K_GROUP_EXTRACT, launch_bucket_pass(STS_BKT_EXTRACT, c->prec, m, b, tiles, c->stream));
-    const int sg = (int)std::min<u64>(std::max<u64>(ceil_div(std::min(cb, c->scap), 256), 1), STS_SIDE_GROUPS);
-    STS_LAUNCH(c, STS_K_SIDE_HIST, launch_side_hist(b, c->h2, sg, c->stream));
-    STS_LAUNCH(c, STS_K_SIDE_EXTRACT, launch_side_extract(b, std::max(sg, (tiles + 3) / 4), c->stream));
-    STS_LAUNCH(c, STS_K_FINAL, launch_final(b, c->stream));
     if (out_risk) {
         st = sync_ctl(c);
         if (st != STS_OK) return st;

@@ -14,6 +14,7 @@
 // prefix grows until the round fits, so any distribution of keys is handled.
 #pragma once
 #include "group_impl.h"
+#include "select_impl.h"
 
 namespace sts_bucket {
 
@@ -530,12 +531,21 @@ __device__ __forceinline__ void slab_put(SlabOut &o, u64 *sk, u64 *sw, AT *sa, u
     o.c_ab += n_ab;
 }
 
+// lower exponent field of the two octaves a small step's slabs hold: the
+// previous cut's and the one its threshold lies nearer to
+__device__ __forceinline__ int small_window(const DevCtl *ctl)
+{
+    const int e = ctl->e_pred;
+    return e > 0 && !((ctl->thr_wbits >> 51) & 1ull) ? e - 1 : e;
+}
+
 // ---------------------------------------------------------------------------
 // histogram pass: exponent histogram with exact mantissa sums of all new
-// weights; with b.predict also the candidates of the previous cut's octave
-// and those above it to the wave's slab. A slab that is too small marks the
-// window as missed. Persistent grid. With b.recover it runs only after a
-// sampled window that missed (and copies nothing).
+// weights; with b.predict (small states) also the candidates of a window of
+// two octaves and those above it to the wave's slab: the previous cut's octave
+// and the one nearer to the cut. A slab that is too small marks the window as
+// missed. Persistent grid. With b.recover it runs only after a sampled window
+// that missed (and copies nothing).
 // ---------------------------------------------------------------------------
 template <typename AT, int M>
 __global__ void __launch_bounds__(STS_WG) k_bkt_hist(const GateArg *__restrict__ gp, PassBufs b)
@@ -544,7 +554,6 @@ __global__ void __launch_bounds__(STS_WG) k_bkt_hist(const GateArg *__restrict__
     const GateLoc<M> gl = gate_loc<M>(g);
     __shared__ BktSmem<AT, BW> s;
     __shared__ u64 s_hi[TT_SLOTS], s_lo[TT_SLOTS];
-    __shared__ u64 s_wacc[6];
     DevCtl *ctl = b.ctl;
     if (b.recover && !ctl->need_full) return; // uniform
     smem_begin<AT, M, BW>(s, g);
@@ -552,26 +561,18 @@ __global__ void __launch_bounds__(STS_WG) k_bkt_hist(const GateArg *__restrict__
         s_hi[i] = 0;
         s_lo[i] = 0;
     }
-    if (threadIdx.x < 6) s_wacc[threadIdx.x] = 0;
     const u64 *keys = b.keys;
     const AT *amps = (const AT *)b.amps;
     const u32 ntiles = bkt_tiles(g.bkt);
-    const int e_w = b.predict ? ctl->e_pred : -1;
-    const bool predict = e_w >= 0;
-    const u32 wL = uni((u32)e_w << 20), wH = uni((u32)(e_w + 1) << 20); // the octave, in the weight's high word
-    u64 mw = 0;
+    const int e_prev = ctl->e_pred;
+    const bool predict = b.predict;
+    const int e_w = small_window(ctl);
+    // the window, in the weight's high word; without a previous cut, everything
+    const u32 wL = uni(e_prev >= 0 ? (u32)e_w << 20 : 0u), wH = uni(e_prev >= 0 ? (u32)(e_w + 2) << 20 : ~0u);
     const int shift = b.slab_shift;
-    if (predict && blockIdx.x == 0 && threadIdx.x == 0) {
-        ctl->side_dense = 0;
-        ctl->side_ntiles = (u64)ntiles << 2;
-        ctl->side_slab_shift = shift;
-        ctl->side_spt_log2 = 2;
-    }
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int copy = (int)(threadIdx.x % TT_HCOPIES);
-    const int e_ref = predict ? e_w : (ctl->e_pred >= 0 ? ctl->e_pred : TT_EBASE + 116);
-    const int hot_lo = e_ref - (TT_HOT - 4);
-    u64 ma = 0; // nothing lies above the octave inside its exponent
+    const int hot_lo = (e_prev >= 0 ? e_prev : TT_EBASE + 116) - (TT_HOT - 4);
     __syncthreads();
     int since_flush = 0;
     for (u32 tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
@@ -579,7 +580,6 @@ __global__ void __launch_bounds__(STS_WG) k_bkt_hist(const GateArg *__restrict__
             // a tile adds at most 4 * BW_BINNED * 4 candidates to the bins
             __syncthreads();
             flush_bins(b, s_hi, s_lo, hot_lo);
-            if (predict) flush_window(s_wacc, ma, mw);
             since_flush = 0;
             __syncthreads();
         }
@@ -617,14 +617,12 @@ __global__ void __launch_bounds__(STS_WG) k_bkt_hist(const GateArg *__restrict__
                         atomicAdd(&b.h1[STS_NBIN + e_], mant >> 26);
                         atomicAdd(&b.h1[2 * STS_NBIN + e_], mant & ((1ull << 26) - 1));
                     }
-                    if (predict) mw += e_ == e_w ? mant : 0ull;
                 }
                 so.c_all += (u32)__popcll(wballot(cand));
                 if (predict)
                     slab_put<AT>(so, sk, sw, sa, 1u << shift, cand && hw >= wL && hw < wH, cand && hw >= wH,
                                  rest | pattern_bits<M>(gl, i), wb, o);
             }
-            if (direct && predict) flush_window(s_wacc, ma, mw); // the lane sums are bounded for binned shares only
         });
         if (sts_lane() == 0) {
             b.w_all[sl] = so.c_all;
@@ -632,18 +630,11 @@ __global__ void __launch_bounds__(STS_WG) k_bkt_hist(const GateArg *__restrict__
                 b.t_above[sl] = so.c_ab;
                 b.t_side[sl] = so.c_in;
                 if (!so.fits) atomicOr(&ctl->w_over, 1u);
-                atomicAdd((unsigned long long *)&s_wacc[0], (unsigned long long)so.c_ab);
-                atomicAdd((unsigned long long *)&s_wacc[3], (unsigned long long)so.c_in);
             }
         }
     }
     __syncthreads();
     flush_bins(b, s_hi, s_lo, hot_lo);
-    if (predict) {
-        flush_window(s_wacc, ma, mw);
-        __syncthreads();
-        if (threadIdx.x < 6) b.wpart[threadIdx.x * STS_MAX_GROUPS + blockIdx.x] = s_wacc[threadIdx.x];
-    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1087,23 +1078,13 @@ __device__ __forceinline__ u32 share_base(const PassBufs &b, u32 tile, int wv)
 // when the window held the cut, the survivors are in the wave's slab: all
 // entries above the window, and the window's by the threshold
 template <typename AT>
-__global__ void __launch_bounds__(STS_WG) k_bkt_copy(const GateArg *__restrict__ gp, PassBufs b)
+__device__ __forceinline__ void copy_share(const BktPlan &p, const PassBufs &b, u32 tile, int wv, u32 *cnt, u64 thr_w,
+                                           u64 thr_k, bool rescale, double scale)
 {
     constexpr int UN = 8; // items of a share held in registers, per lane
-    const BktPlan &p = gp->bkt;
-    __shared__ u32 s_cnt[BW][BW_SUBS];
-    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const u32 lane = (u32)sts_lane();
-    const u32 tile = blockIdx.x;
-    const DevCtl *ctl = b.ctl;
-    const int keep_all = ctl->keep_all, hit = ctl->pred_hit;
-    const u64 thr_w = ctl->thr_wbits, thr_k = ctl->thr_key;
-    const double scale = ctl->scale;
-    const bool rescale = ctl->dropped;
-    const int bits = 2 + p.delta, shift = ctl->side_slab_shift;
-    if (keep_all || !hit) return; // uniform
+    const int bits = 2 + p.delta, shift = b.slab_shift;
     const u32 sl = (tile << 2) + (u32)wv;
-    u32 *cnt = s_cnt[wv];
     cnt[lane] = 0;
     const u32 na = uni(b.t_above[sl]), ns = uni(b.t_side[sl]), n = na + ns;
     const u32 base = uni(share_base(b, tile, wv));
@@ -1180,6 +1161,17 @@ __global__ void __launch_bounds__(STS_WG) k_bkt_copy(const GateArg *__restrict__
     }
 }
 
+template <typename AT>
+__global__ void __launch_bounds__(STS_WG) k_bkt_copy(const GateArg *__restrict__ gp, PassBufs b)
+{
+    __shared__ u32 s_cnt[BW][BW_SUBS];
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const DevCtl *ctl = b.ctl;
+    const int keep_all = ctl->keep_all, hit = ctl->pred_hit;
+    if (keep_all || !hit) return; // uniform
+    copy_share<AT>(gp->bkt, b, blockIdx.x, wv, s_cnt[wv], ctl->thr_wbits, ctl->thr_key, ctl->dropped, ctl->scale);
+}
+
 // otherwise (also when nothing is cut) they are computed again
 template <typename AT, int M>
 __global__ void __launch_bounds__(STS_WG) k_bkt_emit(const GateArg *__restrict__ gp, PassBufs b)
@@ -1196,11 +1188,16 @@ __global__ void __launch_bounds__(STS_WG) k_bkt_emit(const GateArg *__restrict__
     const double scale = ctl->scale;
     const bool all = b.materialise || keep_all;
     const bool rescale = !all && dropped;
-    if (!all && hit) return; // uniform
+    const u32 cap = (u32)b.out_cap, ntiles = bkt_tiles(p);
+    if (!all && hit) { // uniform: the copy's part (of a small step; else k_bkt_copy does it)
+        if (b.emit_copies)
+            for (u32 tile = blockIdx.x; tile < ntiles; tile += gridDim.x)
+                copy_share<AT>(p, b, tile, wv, s_cnt[wv], thr_w, thr_k, rescale, scale);
+        return;
+    }
     smem_begin<AT, M, BW>(s, g);
     __syncthreads();
     const int bits = 2 + p.delta;
-    const u32 cap = (u32)b.out_cap, ntiles = bkt_tiles(p);
     u64 *ok = b.out_keys;
     AT *oa = (AT *)b.out_amps;
     u32 *cnt = s_cnt[wv];
@@ -1231,6 +1228,199 @@ __global__ void __launch_bounds__(STS_WG) k_bkt_emit(const GateArg *__restrict__
             wave_sync();
             if (phase == 0) sub_starts(p, b, tile, wv, base, cnt);
         }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// The whole selection of a small step (at most SEL_SHARES shares) in one
+// workgroup: the level-1 pick over the exponent bins, the further levels over
+// the slabs' window entries of the cut's exponent, and the survivors' offsets.
+// Several short launches in a chain cost more than one workgroup's pass over
+// some thousands of entries. A window that missed the cut is not recovered by
+// further launches: four waves of this workgroup then compute the candidates
+// again for each pass over them.
+// ---------------------------------------------------------------------------
+constexpr int SEL_NT = 1024;
+
+template <typename AT, int M>
+__global__ void __launch_bounds__(SEL_NT) k_bkt_select(const GateArg *__restrict__ gp, PassBufs b)
+{
+    using namespace sts_select;
+    const GateArg &g = *gp;
+    const GateLoc<M> gl = gate_loc<M>(g);
+    __shared__ BktSmem<AT, BW> s;
+    __shared__ union {
+        Level1Smem<SEL_NT> l1;
+        unsigned char raw[3 * STS_NBIN * sizeof(u64)];
+    } u;
+    __shared__ Level1Cut s_l1;
+    __shared__ CutSmem s_cut;
+    __shared__ Sub s_sub;
+    __shared__ u32 s_kept[STS_SEL_SHARES];
+    __shared__ u64 s_scan[SEL_NT / 64];
+    DevCtl *ctl = b.ctl;
+    const int t = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(t >> 6);
+    const u32 lane = (u32)sts_lane(), l16 = lane & 15u, g16 = (u32)t >> 4;
+    const u32 ntiles = bkt_tiles(g.bkt), nsl = ntiles << 2;
+    const int shift = b.slab_shift;
+    // control words, read before the pick writes any
+    const int e_prev = ctl->e_pred, e_w = small_window(ctl);
+    const u32 over = ctl->w_over;
+    const u64 K = ctl->K;
+    const double l10 = ctl->log10_cum;
+    if (wv < BW) {
+        for (int i = lane; i < BW_SLOTS; i += 64) s.w[wv].slot[i] = 0;
+    }
+    if (t < (1 << (2 * M))) {
+        typedef typename Scalar<AT>::T R;
+        const int i = t & ((1 << M) - 1), j = t >> M;
+        AT v;
+        v.x = UEntry<R, M>::re(g, i, j);
+        v.y = UEntry<R, M>::im(g, i, j);
+        s.ucol[t] = v;
+    }
+    __syncthreads();
+    pick_level1<SEL_NT>(b, 0, 0, 0, u.l1);
+    __syncthreads();
+    if (t < (int)(sizeof(Level1Cut) / sizeof(u64)))
+        reinterpret_cast<u64 *>(&s_l1)[t] = reinterpret_cast<const u64 *>(&u.l1.cut)[t];
+    __syncthreads();
+    const bool all = s_l1.keep_all;
+    const int e = s_l1.e;
+    // the slabs hold every candidate of the cut's exponent and above
+    const bool slabs = !all && !over && (e_prev < 0 || e == e_w || e == e_w + 1);
+    u64 thr_w = 0, thr_k = 0;
+    auto recompute = [&](auto body) { // body(share, weight bits, key, valid) for every candidate
+        if (wv < BW) {
+            for (u32 tile = 0; tile < ntiles; ++tile) {
+                const Share sh = load_share(g.bkt, b.bd_in, tile, wv);
+                share_groups<AT, M>(s.w[wv], s.ucol, gl, sh, b.keys, (const AT *)b.amps,
+                                    [&](const auto &ox, const auto &oy, u64 rest, bool active) {
+#pragma unroll
+                    for (int i = 0; i < (1 << M); ++i) {
+                        AT o;
+                        o.x = ox[i];
+                        o.y = oy[i];
+                        body((tile << 2) + (u32)wv, weight_bits(o), rest | pattern_bits<M>(gl, i),
+                             active && nonzero(o));
+                    }
+                });
+            }
+        }
+    };
+    if (!all) {
+        if (t == 0) {
+            s_sub.cnt_before = s_l1.cnt;
+            s_sub.mb = 0;
+            s_sub.vpre = 0;
+            s_sub.vshift = 116;
+            s_sub.count = s_l1.count;
+        }
+        __syncthreads();
+        auto under = [&](u64 w, u64 k, int vshift, u128 vpre, bool &in) { // V, and whether it is under the prefix
+            const u128 v = rank_key(w, k);
+            in = (v >> vshift) == vpre;
+            return v;
+        };
+        auto each = [&](int vshift, u128 vpre, bool keyed, auto f) {
+            if (!slabs) {
+                recompute([&](u32, u64 w, u64 k, bool valid) {
+                    bool in;
+                    const u128 v = under(w, k, vshift, vpre, in);
+                    if (valid && (int)(w >> 52) == e && in) f(v);
+                });
+                return;
+            }
+            constexpr int UN = 4;
+            const bool key_decides = vshift < 64;
+            for (u32 sl = g16; sl < nsl; sl += SEL_NT / 16) { // 16 lanes a share
+                const u32 ns = b.t_side[sl];
+                const u64 base = (u64)sl << shift;
+                for (u32 i0 = l16; i0 < ns; i0 += 16 * UN) {
+                    u64 w[UN];
+#pragma unroll
+                    for (int r = 0; r < UN; ++r) {
+                        const u32 i = i0 + 16u * (u32)r;
+                        w[r] = i < ns ? b.side_w[base + i] : ~0ull; // no weight has all bits set
+                    }
+#pragma unroll
+                    for (int r = 0; r < UN; ++r) {
+                        if ((int)(w[r] >> 52) != e || w[r] == ~0ull) continue;
+                        bool in;
+                        u128 v = under(w[r], 0, key_decides ? 64 : vshift, key_decides ? vpre >> (64 - vshift) : vpre,
+                                       in);
+                        if (!in) continue;
+                        if (keyed || key_decides) {
+                            v = under(w[r], b.side_key[base + i0 + 16u * (u32)r], vshift, vpre, in);
+                            if (!in) continue;
+                        }
+                        f(v);
+                    }
+                }
+            }
+        };
+        const bool ok = resolve_cut<SEL_NT>(ctl, each, e, K, make128(s_l1.R_lo, s_l1.R_hi), s_sub, u.raw, s_cut,
+                                            s_l1.S, s_l1.total, s_l1.W, l10);
+        if (!ok) { // uniform
+            if (t == 0) atomicOr(&ctl->flags, STS_F_UNRESOLVED);
+            return;
+        }
+        __syncthreads();
+        thr_w = s_cut.thr_w;
+        thr_k = s_cut.thr_k;
+    }
+    // survivors per share
+    if (all || slabs) {
+        for (u32 sl = g16; sl < nsl; sl += SEL_NT / 16) {
+            u32 c = 0;
+            if (all) {
+                c = b.w_all[sl];
+            } else {
+                const u32 ns = b.t_side[sl];
+                const u64 base = (u64)sl << shift;
+                if (l16 == 0) c = b.t_above[sl];
+                for (u32 i = l16; i < ns; i += 16) {
+                    const u64 w = b.side_w[base + i];
+                    c += w > thr_w || (w == thr_w && b.side_key[base + i] <= thr_k) ? 1u : 0u;
+                }
+#pragma unroll
+                for (int d = 8; d > 0; d >>= 1) c += __shfl_xor(c, d, 64);
+            }
+            if (l16 == 0) s_kept[sl] = c;
+        }
+    } else {
+        for (u32 sl = t; sl < nsl; sl += SEL_NT) s_kept[sl] = 0;
+        __syncthreads();
+        recompute([&](u32 sl, u64 w, u64 k, bool valid) {
+            const u64 m = wballot(valid && survives<AT>(w, k, false, thr_w, thr_k));
+            if (lane == 0) s_kept[sl] += (u32)__popcll(m); // the share is this wave's
+        });
+    }
+    __syncthreads();
+    // offsets: one tile per thread
+    u64 carry = 0;
+    for (u32 t0 = 0; t0 < ntiles; t0 += SEL_NT) {
+        const u32 tile = t0 + (u32)t;
+        u32 k[4] = {0, 0, 0, 0};
+        if (tile < ntiles) {
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                k[w] = s_kept[(tile << 2) + w];
+                b.w_kept[(tile << 2) + w] = k[w];
+            }
+        }
+        const u64 sum = (u64)k[0] + k[1] + k[2] + k[3];
+        u64 total;
+        const u64 at = block_excl_scan<u64, SEL_NT>(sum, s_scan, &total) + carry;
+        if (tile < ntiles) b.t_off[tile] = at;
+        if (tile < ntiles && tile % STS_BKT_CHUNK == 0) b.t_base[tile / STS_BKT_CHUNK] = 0;
+        carry += total;
+    }
+    if (t == 0) {
+        *b.n_out = carry;
+        if (carry > b.out_cap) atomicOr(&ctl->flags, STS_F_OUT_OVERFLOW);
+        ctl->w_over = 0;
+        ctl->pred_hit = slabs;
     }
 }
 
@@ -1288,6 +1478,9 @@ template <typename AT, int M> hipError_t launch_m(int kind, const PassBufs &b, i
         break;
     case STS_BKT_COPY:
         hipLaunchKernelGGL((k_bkt_copy<AT>), dim3(tiles), dim3(STS_WG), 0, s, b.gate, b);
+        break;
+    case STS_BKT_SELECT:
+        hipLaunchKernelGGL((k_bkt_select<AT, M>), dim3(1), dim3(SEL_NT), 0, s, b.gate, b);
         break;
     case STS_BKT_EMIT:
         hipLaunchKernelGGL((k_bkt_emit<AT, M>), dim3(std::min(tiles, cap)), dim3(STS_WG), 0, s, b.gate, b);

@@ -75,6 +75,7 @@ struct PassBufs {
     u32 *w_kept;
     u64 *t_base;          // output offset of every STS_BKT_CHUNK tiles (t_off is relative to it)
     int slab_shift;
+    int emit_copies;      // write pass: also copies the survivors when the window held the cut
     int recover;          // histogram pass: only after a sampled window that missed
     u64 *sbins;           // sampling pass: STS_SW_BANKS x STS_SW_NB counts (u32), as many masses
                           // (float), then 4 totals per bank
@@ -181,6 +182,8 @@ hipError_t launch_terms_out(const u64 *keys, const void *amps, int amp_bytes, co
 #define STS_BKT_EMIT 4
 #define STS_BKT_WEIGH 5
 #define STS_BKT_COPY 6
+#define STS_BKT_SELECT 7
+#define STS_SEL_SHARES 2048 // most shares of a step whose selection is one workgroup
 #define STS_BKT_CHUNK 32 // tiles whose offsets are relative to one base
 hipError_t launch_bucket_pass(int kind, int prec, int m, const PassBufs &b, int tiles, hipStream_t s);
 int bucket_hist_groups(int prec, int m, int tiles, bool weigh); // workgroups of the histogram or weighing pass

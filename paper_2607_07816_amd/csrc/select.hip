@@ -20,573 +20,17 @@
 #include <algorithm>
 
 #include "kernels.h"
+#include "select_impl.h"
 
 namespace {
 
-// bit position of the unit 2^(max(e,1)-1075) on the 2^-1074 grid
-__device__ __forceinline__ int unit_bit(int e) { return (e > 0 ? e : 1) - 1; }
+using namespace sts_select;
 
-__device__ __forceinline__ u128 make128(u64 lo, u64 hi) { return ((u128)hi << 64) | lo; }
-
-// ---------------------------------------------------------------------------
-// Exact masses, one wave wide: a number of 64 limbs of 64 bits (units
-// 2^-1074), limb i held by lane i. Every lane of the wave takes part in each
-// operation. Carries between limbs are resolved at once from two ballots: a
-// limb generates a carry (its sum wrapped) or propagates one (its sum is all
-// ones), and the carries into the limbs are the carries of the binary sum
-// (G | P) + G, i.e. ((G | P) + G) ^ (G | P) ^ G.
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ u64 wl_carry_in(bool gen, bool prop)
-{
-    const u64 G = __ballot(gen), P = __ballot(prop);
-    const u64 X = G | P;
-    return (((X + G) ^ X ^ G) >> sts_lane()) & 1ull;
-}
-
-__device__ __forceinline__ u64 wl_add(u64 a, u64 b)
-{
-    const u64 s = a + b;
-    return s + wl_carry_in(s < a, s == ~0ull);
-}
-
-// a - b, a >= b
-__device__ __forceinline__ u64 wl_sub(u64 a, u64 b)
-{
-    const u64 d = a - b;
-    return d - wl_carry_in(a < b, d == 0);
-}
-
-// this lane's limb of v * 2^bit, v < 2^128 given as (lo, hi)
-__device__ __forceinline__ u64 wl_piece(u64 lo, u64 hi, int bit)
-{
-    const int k = sts_lane() - (bit >> 6), off = bit & 63;
-    if (k == 0) return lo << off;
-    if (k == 1) return off ? (hi << off) | (lo >> (64 - off)) : hi;
-    if (k == 2) return off ? hi >> (64 - off) : 0ull;
-    return 0ull;
-}
-
-// sign of a - b
-__device__ __forceinline__ int wl_cmp(u64 a, u64 b)
-{
-    const u64 D = __ballot(a != b);
-    if (!D) return 0;
-    const int top = 63 - __clzll((long long)D);
-    return ((__ballot(a > b) >> top) & 1ull) ? 1 : -1;
-}
-
-// limb `src` of the number (0 outside 0..63); src may differ between lanes
-__device__ __forceinline__ u64 wl_limb(u64 a, int src)
-{
-    const u64 v = __shfl(a, src & 63, 64);
-    return (src >= 0 && src < 64) ? v : 0ull;
-}
-
-// a >> s (s >= 0), and whether any bit below s was set
-__device__ __forceinline__ u64 wl_shr(u64 a, int s, bool *sticky)
-{
-    const int q = s >> 6, r = s & 63, lane = sts_lane();
-    const u64 a0 = wl_limb(a, lane + q), a1 = wl_limb(a, lane + q + 1);
-    const u64 low = lane < q ? a : (lane == q && r ? (a & ((1ull << r) - 1)) : 0ull);
-    *sticky = __ballot(low != 0) != 0;
-    return r ? (a0 >> r) | (a1 << (64 - r)) : a0;
-}
-
-// ceil(a * m / 2^s), m < 2^64
-__device__ __forceinline__ u64 wl_mul_shr_ceil(u64 a, u64 m, int s)
-{
-    const u128 pr = (u128)a * m;
-    const u64 hi_below = __shfl_up((u64)(pr >> 64), 1, 64);
-    const u64 t = wl_add((u64)pr, sts_lane() > 0 ? hi_below : 0ull);
-    bool sticky;
-    const u64 q = wl_shr(t, s, &sticky);
-    return sticky ? wl_add(q, sts_lane() == 0 ? 1ull : 0ull) : q;
-}
-
-// nearest binary64 (ties to even); the result is the same in every lane
-__device__ inline double wl_to_double(u64 a)
-{
-    const u64 NZ = __ballot(a != 0);
-    if (!NZ) return 0.0;
-    const int top = 63 - __clzll((long long)NZ);
-    const u64 L0 = wl_limb(a, top), L1 = wl_limb(a, top - 1), L2 = wl_limb(a, top - 2);
-    const bool below = top >= 3 && (NZ & ((1ull << (top - 2)) - 1)) != 0;
-    const int lz = __clzll((long long)L0);
-    const int h = top * 64 + 63 - lz; // position of the top set bit
-    if (h < 53) return ldexp((double)L0, -1074);
-    const u64 hi = lz ? (L0 << lz) | (L1 >> (64 - lz)) : L0; // bit 63 = bit h
-    const u64 lo = lz ? (L1 << lz) | (L2 >> (64 - lz)) : L1;
-    const bool rest = below || (lz ? (L2 << lz) != 0 : L2 != 0);
-    u64 mant = hi >> 11;
-    const bool guard = (hi >> 10) & 1ull;
-    const bool sticky = (hi & 0x3ffull) != 0 || lo != 0 || rest;
-    int lsb = h - 52;
-    if (guard && (sticky || (mant & 1ull))) {
-        mant += 1;
-        if (mant == (1ull << 53)) {
-            mant >>= 1;
-            lsb += 1;
-        }
-    }
-    return ldexp((double)mant, lsb - 1074);
-}
-
-// Subset of the rank order still holding the cut: the terms of exponent e*
-// whose rank key V has the high part vpre above bit vshift.
-struct Sub {
-    u64 cnt_before; // terms ranked before the subset
-    u128 mb;        // their mantissa sum inside e* (units 2^(max(e*,1)-1075))
-    u128 vpre;
-    int vshift;
-    u64 count;      // terms in the subset
-};
-
-__device__ inline void sub_load(Sub &s, const DevCtl *ctl)
-{
-    s.cnt_before = ctl->cnt_before;
-    s.mb = make128(ctl->mb_lo, ctl->mb_hi);
-    s.vpre = make128(ctl->vpre_lo, ctl->vpre_hi);
-    s.vshift = ctl->vshift;
-    s.count = ctl->sub_count;
-}
-
-__device__ inline void sub_store(const Sub &s, DevCtl *ctl)
-{
-    ctl->cnt_before = s.cnt_before;
-    ctl->mb_lo = (u64)s.mb;
-    ctl->mb_hi = (u64)(s.mb >> 64);
-    ctl->vpre_lo = (u64)s.vpre;
-    ctl->vpre_hi = (u64)(s.vpre >> 64);
-    ctl->vshift = s.vshift;
-    ctl->sub_count = s.count;
-}
-
-// Pick the first digit (ascending = rank order) where the rule is met, over
-// 2048 bins held in (cnt[], hi[], lo[]) - global (agent loads) or LDS - by NT
-// threads, and narrow *sub to it. K, R: the rule (R all ones = no p-mass).
-// Returns false if no digit qualifies.
-// inclusive scan of (count, mass) pairs over a workgroup of NT threads, in
-// place: wave scans, then the wave totals through LDS (one barrier; sc, sm
-// hold NT / 64 entries and are not read again before the caller's next
-// barrier)
-template <int NT>
-__device__ __forceinline__ void block_scan_cm(u64 &c, u128 &m, u64 *sc, u128 *sm)
-{
-    const int lane = sts_lane(), w = (int)threadIdx.x >> 6;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const u64 oc = __shfl_up(c, d, 64);
-        const u64 ol = __shfl_up((u64)m, d, 64), oh = __shfl_up((u64)(m >> 64), d, 64);
-        if (lane >= d) {
-            c += oc;
-            m += make128(ol, oh);
-        }
-    }
-    if (lane == 63) {
-        sc[w] = c;
-        sm[w] = m;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < NT / 64; ++i) {
-        if (i < w) {
-            c += sc[i];
-            m += sm[i];
-        }
-    }
-}
-
-template <int NT>
-__device__ bool pick_digit(const u64 *cntp, const u64 *hip_, const u64 *lop, bool agent, u64 K, u128 R, int dw,
-                           Sub *sub, u128 *s_m, u64 *s_c, u32 *s_hit)
-{
-    constexpr int PER = STS_NBIN / NT;
-    const int t = threadIdx.x;
-    u64 c[PER];
-    u128 ms[PER];
-    u64 cc = 0;
-    u128 mm = 0;
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        const int d = PER * t + k;
-        if (agent) {
-            c[k] = ld_agent(&cntp[d]);
-            ms[k] = ((u128)ld_agent(&hip_[d]) << 26) + (u128)ld_agent(&lop[d]);
-        } else {
-            c[k] = cntp[d];
-            ms[k] = ((u128)hip_[d] << 26) + (u128)lop[d];
-        }
-        cc += c[k];
-        mm += ms[k];
-    }
-    const u64 own_c = cc;
-    const u128 own_m = mm;
-    if (t == 0) *s_hit = 0xffffffffu;
-    block_scan_cm<NT>(cc, mm, s_c, s_m);
-    // exclusive prefix of this thread's bins, from the subset's start
-    u64 cnt = sub->cnt_before + (cc - own_c);
-    u128 m = sub->mb + (mm - own_m);
-    u32 hit = 0xffffffffu;
-    u64 cnt_hit = 0;
-    u128 m_hit = 0;
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        if (hit == 0xffffffffu && c[k]) {
-            const bool hk = K > 0 && cnt + c[k] >= K;
-            const bool hp = m + ms[k] >= R;
-            if (hk || hp) {
-                hit = (u32)(PER * t + k);
-                cnt_hit = cnt;
-                m_hit = m;
-            } else {
-                cnt += c[k];
-                m += ms[k];
-            }
-        }
-    }
-    if (hit != 0xffffffffu) atomicMin(s_hit, hit);
-    __syncthreads();
-    const u32 first = *s_hit;
-    if (first == 0xffffffffu) {
-        __syncthreads();
-        return false;
-    }
-    if (hit == first) {
-        const int k = (int)first - PER * t;
-        sub->vpre = (sub->vpre << dw) | (u128)first;
-        sub->vshift -= dw;
-        sub->cnt_before = cnt_hit;
-        sub->mb = m_hit;
-        sub->count = c[k];
-    }
-    __syncthreads();
-    return true;
-}
-
-// ---------------------------------------------------------------------------
-// level 1: one workgroup of 256 threads. Thread t owns the eight exponent
-// bins 2047-8t .. 2040-8t (descending weight order). The bins that hold
-// candidates are listed in rank order in LDS; one wave then adds their exact
-// masses up (the total W and the p-mass target), and walks them again to the
-// first bin where the rule is met.
-// ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(256) k_pick1(PassBufs b, int groups, int peak_only, int predicted)
 {
-    __shared__ u32 s_e[STS_NBIN];   // the non-empty bins in rank order: exponent field,
-    __shared__ u64 s_c[STS_NBIN];   // count,
-    __shared__ __attribute__((aligned(16))) u64 s_lo[STS_NBIN]; // mantissa sum (low, high words)
-    __shared__ u64 s_hi[STS_NBIN];
-    __shared__ u32 s_scan[4];
-    __shared__ u64 s_bw[4], s_bk[4];
-    __shared__ u64 s_w[6];
-    __shared__ Sub s_sub;   // level 2 of a sampled window that holds the cut
-    __shared__ u32 s_fine, s_hit2;
-    __shared__ u64 s_sub_R_lo, s_sub_R_hi;
-    __shared__ u64 s_chunk[4][64]; // exact mass of each quarter of the bin list (a limb per lane)
-    __shared__ u64 s_chunk_c[4];   // and its count
-    const int t = threadIdx.x;
-    DevCtl *ctl = b.ctl;
-    u64 *h1 = b.h1;
-    // the exponent of the window the histogram pass copied (predicted steps)
-    const int w_mode = ctl->w_mode;
-    // (predicted = 2: a bucketed step, where a share's slab may have been too small for it)
-    // (3: one whose sampled window missed, the histogram pass having run after all)
-    if (predicted == 3 && !ctl->need_full) return; // uniform
-    const bool win = predicted == 1 || predicted == 2;
-    const bool over = predicted == 2 && ctl->w_over != 0;
-    const int e_w = win ? (w_mode ? ctl->e_w : ctl->e_pred) : -1;
-    if (t < 6) s_w[t] = 0;
-    if (t == 0) s_fine = 0;
-
-    // own bins: every load issued before any is used
-    u64 c[8], hi[8], lo[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        const int e = 2047 - 8 * t - k;
-        c[k] = h1[e];
-        hi[k] = h1[STS_NBIN + e];
-        lo[k] = h1[2 * STS_NBIN + e];
-    }
-    // the per-workgroup peaks too (reduced below)
-    constexpr int BPT = (STS_MAX_GROUPS + 255) / 256;
-    u64 bwv[BPT], bkv[BPT];
-#pragma unroll
-    for (int r = 0; r < BPT; ++r) {
-        const int i = t + 256 * r;
-        bwv[r] = i < groups ? b.best[i] : 0ull;
-        bkv[r] = i < groups ? b.best[STS_MAX_GROUPS + i] : ~0ull;
-    }
-    // the window sums of the histogram workgroups: count of candidates above
-    // the window and mantissa sums of those in its exponent, then count and
-    // sums of those inside it
-    // (loaded whenever the pass predicted, before the control block says
-    // whether a window was copied)
-    u64 v[6] = {0, 0, 0, 0, 0, 0};
-    if (win) {
-#pragma unroll
-        for (int r = 0; r < STS_MAX_GROUPS / 256; ++r) { // every load issued before any is used
-            const int i = t + 256 * r;
-            if (i < groups) {
-#pragma unroll
-                for (int f = 0; f < 6; ++f) v[f] += b.wpart[f * STS_MAX_GROUPS + i];
-            }
-        }
-    }
-    if (e_w >= 0) {
-#pragma unroll
-        for (int f = 0; f < 6; ++f) {
-#pragma unroll
-            for (int d = 32; d > 0; d >>= 1) v[f] += __shfl_xor(v[f], d, 64);
-        }
-        __syncthreads(); // s_w cleared
-        if ((t & 63) == 0) {
-#pragma unroll
-            for (int f = 0; f < 6; ++f) atomicAdd((unsigned long long *)&s_w[f], (unsigned long long)v[f]);
-        }
-    }
-    // list the non-empty bins in rank order
-    u32 nz = 0;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) nz += c[k] ? 1u : 0u;
-    u32 nbins;
-    u32 at = block_excl_scan<u32, 256>(nz, s_scan, &nbins);
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        if (!c[k]) continue;
-        s_e[at] = (u32)(2047 - 8 * t - k);
-        s_c[at] = c[k];
-        const u128 ms = ((u128)hi[k] << 26) + (u128)lo[k];
-        s_lo[at] = (u64)ms;
-        s_hi[at] = (u64)(ms >> 64);
-        ++at;
-    }
-    // peak: reduce the per-workgroup bests (written by the identity pass of
-    // sts_peak only)
-    if (peak_only) {
-        u64 bw = 0, bk = ~0ull;
-#pragma unroll
-        for (int r = 0; r < BPT; ++r) {
-            const u64 w = bwv[r], k = bkv[r];
-            if (w > bw || (w == bw && k < bk)) {
-                bw = w;
-                bk = k;
-            }
-        }
-#pragma unroll
-        for (int d = 32; d > 0; d >>= 1) {
-            const u64 ow = __shfl_xor(bw, d, 64);
-            const u64 ok = __shfl_xor(bk, d, 64);
-            if (ow > bw || (ow == bw && ok < bk)) {
-                bw = ow;
-                bk = ok;
-            }
-        }
-        if ((t & 63) == 0) {
-            s_bw[t >> 6] = bw;
-            s_bk[t >> 6] = bk;
-        }
-    }
-    __syncthreads();
-
-    // exact sums of the listed bins in four chunks, one wave each (a chain of
-    // exact additions per bin, a quarter as long as over all bins)
-    const u32 chunk = (nbins + 3) / 4;
-    {
-        const int q = t >> 6;
-        const u32 j0 = (u32)q * chunk, j1 = j0 + chunk < nbins ? j0 + chunk : nbins;
-        u64 C = 0, nc = 0;
-        for (u32 j = j0; j < j1; ++j) {
-            C = wl_add(C, wl_piece(s_lo[j], s_hi[j], unit_bit((int)s_e[j])));
-            nc += s_c[j];
-        }
-        s_chunk[q][t & 63] = C;
-        if ((t & 63) == 0) s_chunk_c[q] = nc;
-    }
-    __syncthreads();
-
-    if (t < 64) { // one wave: the total, the target and the cut's bin
-        const int lane = t;
-        u64 W = 0, total_c = 0;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            W = wl_add(W, s_chunk[q][lane]);
-            total_c += s_chunk_c[q];
-        }
-        const double Wd = wl_to_double(W);
-        if (peak_only) {
-            if (lane == 0) {
-                ctl->cand_all = total_c;
-                ctl->peak_W = Wd;
-                u64 w = s_bw[0], k = s_bk[0];
-                for (int i = 1; i < 4; ++i)
-                    if (s_bw[i] > w || (s_bw[i] == w && s_bk[i] < k)) {
-                        w = s_bw[i];
-                        k = s_bk[i];
-                    }
-                ctl->peak_key = k;
-                ctl->peak_w = (w >> 63) ? __longlong_as_double((long long)(w & ~(1ull << 63))) : 0.0;
-            }
-        } else {
-            const u64 K = ctl->K;
-            const double p = ctl->p;
-            const bool p_on = p > 0.0 && p < 1.0;
-            // p-mass target T = ceil(p * W), exactly
-            u64 T = 0;
-            if (p_on) {
-                const u64 pb = sts_dbits(p);
-                const u64 pe = pb >> 52, pf = pb & ((1ull << 52) - 1);
-                const u64 pm = pe ? (pf | (1ull << 52)) : pf;
-                const int sh = pe ? (int)(1075 - pe) : 1074;
-                T = wl_mul_shr_ceil(W, pm, sh);
-            }
-            if (lane < STS_NL) ctl->T.l[lane] = T;
-            if (lane == 0) {
-                ctl->cand_all = total_c;
-                ctl->W = Wd;
-                ctl->n_cand = total_c;
-                ctl->tot_steps += 1;
-                ctl->tot_updates += *b.n_in;
-                ctl->tot_cand += total_c;
-            }
-            // the first bin in rank order where the rule is met: the first
-            // chunk through which it is met (the rule only grows along the
-            // ranking), then that chunk's bins
-            u64 S = 0, cnt = 0;
-            u32 hit = 0xffffffffu;
-            for (int q = 0; q < 4; ++q) {
-                const u64 inc_q = wl_add(S, s_chunk[q][lane]);
-                const bool met_q = (K > 0 && cnt + s_chunk_c[q] >= K) || (p_on && wl_cmp(inc_q, T) >= 0);
-                if (met_q) {
-                    const u32 j0 = (u32)q * chunk, j1 = j0 + chunk < nbins ? j0 + chunk : nbins;
-                    for (u32 j = j0; j < j1; ++j) {
-                        const u64 inc = wl_add(S, wl_piece(s_lo[j], s_hi[j], unit_bit((int)s_e[j])));
-                        const bool hk = K > 0 && cnt + s_c[j] >= K;
-                        const bool hp = p_on && wl_cmp(inc, T) >= 0;
-                        if (hk || hp) {
-                            hit = j;
-                            break;
-                        }
-                        S = inc;
-                        cnt += s_c[j];
-                    }
-                    break;
-                }
-                S = inc_q;
-                cnt += s_chunk_c[q];
-            }
-            if (hit == 0xffffffffu) {
-                if (lane == 0) {
-                    ctl->keep_all = 1;
-                    ctl->dropped = 0;
-                    ctl->L = total_c;
-                    ctl->scale = 1.0;
-                    ctl->S = Wd;
-                    ctl->frac = 1.0;
-                    ctl->level = 1;
-                    ctl->pred_hit = 0;
-                    ctl->e_pred = -1;
-                }
-            } else {
-                const int e = (int)s_e[hit];
-                const int ub = unit_bit(e);
-                // does the copied window hold the cut? Exactly when the rule is
-                // not met through the candidates above it and is met through it
-                bool in_window = false;
-                u64 ca = 0, cw = 0;
-                u128 ma = 0;
-                if (e == e_w && !over) {
-                    // the histogram pass counted every candidate above the window;
-                    // those in exponents above e are the cnt ranked before this bin
-                    ca = s_w[0] - cnt;
-                    cw = s_w[3];
-                    ma = ((u128)s_w[1] << 26) + (u128)s_w[2];
-                    const u128 mw = ((u128)s_w[4] << 26) + (u128)s_w[5];
-                    const u64 Sa = wl_add(S, wl_piece((u64)ma, (u64)(ma >> 64), ub));
-                    const bool met_a = (K > 0 && cnt + ca >= K) || (p_on && wl_cmp(Sa, T) >= 0);
-                    const u64 Sw = wl_add(Sa, wl_piece((u64)mw, (u64)(mw >> 64), ub));
-                    const bool met_w = (K > 0 && cnt + ca + cw >= K) || (p_on && wl_cmp(Sw, T) >= 0);
-                    in_window = !met_a && met_w;
-                }
-                // remaining mass to reach inside the bin, in its units (rounded up)
-                u64 R_lo = ~0ull, R_hi = ~0ull;
-                if (p_on) {
-                    bool sticky;
-                    const u64 q = wl_shr(wl_sub(T, S), ub, &sticky);
-                    const bool over = __ballot(lane >= 2 && q != 0) != 0;
-                    u128 r = ((u128)__shfl(q, 1, 64) << 64) | (u128)__shfl(q, 0, 64);
-                    if (!over) {
-                        if (sticky) r += 1;
-                        if (r != 0 || !sticky) {
-                            R_lo = (u64)r;
-                            R_hi = (u64)(r >> 64);
-                        }
-                    }
-                }
-                if (lane < STS_NL) ctl->S_excl.l[lane] = S;
-                if (lane == 0 && in_window && w_mode && win) {
-                    // the histogram pass binned this window for level 2: the
-                    // whole workgroup picks its digit below
-                    s_fine = 1;
-                    s_sub.cnt_before = cnt + ca;
-                    s_sub.mb = ma;
-                    s_sub.vpre = 0;
-                    s_sub.vshift = 116;
-                    s_sub.count = cw;
-                    s_sub_R_lo = R_lo;
-                    s_sub_R_hi = R_hi;
-                }
-                if (lane == 0) {
-                    ctl->keep_all = 0;
-                    ctl->pred_hit = in_window ? 1 : 0;
-                    ctl->e_pred = e;
-                    ctl->e_star = e;
-                    ctl->cnt_before = in_window ? cnt + ca : cnt;
-                    ctl->sub_count = in_window ? cw : s_c[hit];
-                    ctl->mb_lo = in_window ? (u64)ma : 0;
-                    ctl->mb_hi = in_window ? (u64)(ma >> 64) : 0;
-                    ctl->level = 1;
-                    ctl->R_lo = R_lo;
-                    ctl->R_hi = R_hi;
-                }
-            }
-            if (lane == 0) {
-                ctl->w2_mode = win && w_mode; // the histogram pass binned the window for level 2
-                ctl->w_mode = 0;                     // a window serves one step
-                if (predicted >= 2) {
-                    ctl->w_over = 0;
-                    ctl->need_full = 0;
-                    // a missed window: the extraction pass packs its candidates densely
-                    if (hit != 0xffffffffu && !ctl->pred_hit) {
-                        ctl->side_dense = 1;
-                        ctl->side_n = 0;
-                    }
-                }
-                ctl->l2_done = 0;
-            }
-        }
-    }
-    __syncthreads();
-    for (int i = t; i < 3 * STS_NBIN; i += 256) h1[i] = 0;
-    if (s_fine) { // uniform
-        // level 2 from the window's bins (the side pass then has nothing to
-        // do); the bin lists above are done with, so their LDS serves the pick
-        const u128 R = make128(s_sub_R_lo, s_sub_R_hi);
-        u128 *s_m = reinterpret_cast<u128 *>(s_lo);
-        u64 *s_c2 = s_hi;
-        const bool ok = pick_digit<256>(b.h2w, b.h2w + STS_NBIN, b.h2w + 2 * STS_NBIN, true, ctl->K, R, 11, &s_sub,
-                                        s_m, s_c2, &s_hit2);
-        if (ok && t <= STS_SUB_REGIONS) st_agent(&b.sub_cnt[t * 32], 0u);
-        if (t == 0) {
-            if (ok) {
-                sub_store(s_sub, ctl);
-                ctl->level = 2;
-                ctl->l2_done = 1;
-            } else {
-                atomicOr(&ctl->flags, STS_F_UNRESOLVED);
-            }
-        }
-        for (int i = t; i < 3 * STS_NBIN; i += 256) st_agent(&b.h2w[i], 0ull);
-    }
+    __shared__ Level1Smem<256> sm;
+    if (predicted == 3 && !b.ctl->need_full) return; // uniform
+    pick_level1<256>(b, groups, peak_only, predicted, sm);
 }
 
 // ---------------------------------------------------------------------------
@@ -907,20 +351,6 @@ __device__ __forceinline__ TileSlabs chunk_of(const SideChunks &c, u64 t)
 // most entries a chunk can hold
 __device__ __forceinline__ u64 chunk_max(const SideChunks &c) { return c.dense ? 8192ull : (1ull << (c.shift + c.spl)); }
 
-// within-exponent rank key: ascending V = descending weight, then ascending key
-__device__ __forceinline__ u128 rank_key(u64 wbits, u64 key)
-{
-    const u64 frac = wbits & ((1ull << 52) - 1);
-    return ((u128)(((1ull << 52) - 1) - frac) << 64) | (u128)key;
-}
-
-__device__ __forceinline__ u64 mant_of_v(u128 v, int e)
-{
-    const u64 frac = ((1ull << 52) - 1) - (u64)(v >> 64);
-    return e ? (frac | (1ull << 52)) : frac;
-}
-
-
 // ---------------------------------------------------------------------------
 // level 2 over the side buffer (many workgroups), pick by the last one
 // ---------------------------------------------------------------------------
@@ -1140,16 +570,9 @@ constexpr int FB = 8; // subset entries a thread of the final workgroup loads at
 
 __global__ void __launch_bounds__(FT) k_final(PassBufs b)
 {
-    // LDS: the level histograms and the sort buffer share one region
-    __shared__ __attribute__((aligned(16))) unsigned char s_raw[STS_SMALL * sizeof(u128)];
-    __shared__ u128 s_m[FT];
-    __shared__ u64 s_c[FT];
-    __shared__ u32 s_hit, s_n;
-    u64 *h_cnt = reinterpret_cast<u64 *>(s_raw);
-    u64 *h_hi = h_cnt + STS_NBIN;
-    u64 *h_lo = h_hi + STS_NBIN;
-    u128 *sv = reinterpret_cast<u128 *>(s_raw);
-    static_assert(3 * STS_NBIN * sizeof(u64) <= STS_SMALL * sizeof(u128), "LDS union");
+    // LDS: the level histograms and the last terms share one region
+    __shared__ __attribute__((aligned(16))) unsigned char s_raw[3 * STS_NBIN * sizeof(u64)];
+    __shared__ CutSmem s_cut;
 
     __shared__ Sub s_sub;
     DevCtl *ctl = b.ctl;
@@ -1203,7 +626,7 @@ __global__ void __launch_bounds__(FT) k_final(PassBufs b)
     // body(V) for every visited entry whose V lies under the prefix: FB
     // entries per thread at a time, their loads in flight together (a loop
     // of one entry at a time waits on a load per entry)
-    auto each_in_subset = [&](int vshift, u128 vpre, auto body) {
+    auto each_in_subset = [&](int vshift, u128 vpre, bool, auto body) {
         for (u64 f0 = t; f0 < n; f0 += (u64)FT * FB) {
             u64 w[FB], k[FB], at[FB];
             bool ok[FB];
@@ -1233,132 +656,15 @@ __global__ void __launch_bounds__(FT) k_final(PassBufs b)
     // next step, whether or not a level is needed
     bool from_h3 = ctl->sub_count <= b.sub_cap;
 
-    // further levels until the subset is small (a level is a pass over the
-    // subset and a block scan; the bitonic sort below costs a barrier per
-    // stage, so levels are the cheaper way down)
-    while (s_sub.count > STS_FINAL_SORT && s_sub.vshift > 0) {
-        const int vshift = s_sub.vshift;
-        const int dw = vshift < 11 ? vshift : 11;
-        const u128 vpre = s_sub.vpre;
-        bool ok;
-        if (from_h3) {
-            ok = pick_digit<FT>(b.h3, b.h3 + STS_NBIN, b.h3 + 2 * STS_NBIN, true, K, R, dw, &s_sub, s_m, s_c,
-                                &s_hit);
-            for (int i = t; i < 3 * STS_NBIN; i += FT) st_agent(&b.h3[i], 0ull);
-            from_h3 = false;
-        } else {
-            for (int i = t; i < 3 * STS_NBIN; i += FT) h_cnt[i] = 0;
-            __syncthreads();
-            each_in_subset(vshift, vpre, [&](const u128 v) {
-                const u32 d = (u32)((v >> (vshift - dw)) & (u128)((1u << dw) - 1));
-                const u64 mant = mant_of_v(v, e);
-                atomicAdd((unsigned long long *)&h_cnt[d], 1ull);
-                atomicAdd((unsigned long long *)&h_hi[d], mant >> 26);
-                atomicAdd((unsigned long long *)&h_lo[d], mant & ((1ull << 26) - 1));
-            });
-            __syncthreads();
-            ok = pick_digit<FT>(h_cnt, h_hi, h_lo, false, K, R, dw, &s_sub, s_m, s_c, &s_hit);
-        }
-        if (!ok) {
-            if (t == 0) atomicOr(&ctl->flags, STS_F_UNRESOLVED);
-            return;
-        }
-    }
-    if (from_h3) // binned, but the subset was small enough already
+    // the first level's pick from those bins, then the levels and the cut
+    bool ok = true;
+    if (from_h3 && s_sub.count > STS_FINAL_SORT && s_sub.vshift > 0)
+        ok = pick_digit<FT>(b.h3, b.h3 + STS_NBIN, b.h3 + 2 * STS_NBIN, true, K, R,
+                            s_sub.vshift < 11 ? s_sub.vshift : 11, &s_sub, s_cut.m, s_cut.c, &s_cut.hit);
+    if (from_h3)
         for (int i = t; i < 3 * STS_NBIN; i += FT) st_agent(&b.h3[i], 0ull);
-
-    // gather the subset and sort it by V
-    const int vshift = s_sub.vshift;
-    const u128 vpre = s_sub.vpre;
-    if (t == 0) s_n = 0;
-    __syncthreads();
-    each_in_subset(vshift, vpre, [&](const u128 v) {
-        const u32 slot = atomicAdd(&s_n, 1u);
-        if (slot < STS_SMALL) sv[slot] = v;
-    });
-    __syncthreads();
-    const u32 m = s_n;
-    if (m == 0 || m > STS_SMALL) {
-        if (t == 0) atomicOr(&ctl->flags, STS_F_UNRESOLVED);
-        return;
-    }
-    u32 P = 1;
-    while (P < m) P <<= 1;
-    for (u32 i = m + t; i < P; i += FT) sv[i] = ~(u128)0;
-    __syncthreads();
-    for (u32 k = 2; k <= P; k <<= 1) {
-        for (u32 j = k >> 1; j > 0; j >>= 1) {
-            for (u32 i = t; i < P; i += FT) {
-                const u32 ixj = i ^ j;
-                if (ixj > i) {
-                    const u128 a = sv[i], c = sv[ixj];
-                    const bool up = (i & k) == 0;
-                    if ((a > c) == up) {
-                        sv[i] = c;
-                        sv[ixj] = a;
-                    }
-                }
-            }
-            __syncthreads();
-        }
-    }
-
-    // exact prefix in rank order: thread t owns elements 4t .. 4t+3
-    constexpr int PER = STS_SMALL / FT;
-    u128 loc[PER];
-    u128 acc = 0;
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        const u32 r = PER * t + k;
-        if (r < m) acc += (u128)mant_of_v(sv[r], e);
-        loc[k] = acc;
-    }
-    if (t == 0) s_hit = 0xffffffffu;
-    u64 none = 0;
-    u128 inc = acc;
-    block_scan_cm<FT>(none, inc, s_c, s_m);
-    const u128 excl = inc - acc;
-    const u64 cb = s_sub.cnt_before;
-    const u128 mb = s_sub.mb;
-    u32 hit = 0xffffffffu;
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        const u32 r = PER * t + k;
-        if (hit == 0xffffffffu && r < m) {
-            const bool hk = K > 0 && cb + r + 1 >= K;
-            const bool hp = mb + excl + loc[k] >= R;
-            if (hk || hp) hit = r;
-        }
-    }
-    if (hit != 0xffffffffu) atomicMin(&s_hit, hit);
-    __syncthreads();
-    const u32 first = s_hit;
-    if (first == 0xffffffffu) {
-        if (t == 0) atomicOr(&ctl->flags, STS_F_UNRESOLVED);
-        return;
-    }
-    if (hit == first) {
-        const int k = (int)first - PER * t;
-        const u128 v = sv[first];
-        const u64 frac = ((1ull << 52) - 1) - (u64)(v >> 64);
-        const u128 mk = mb + excl + loc[k];
-        Big S;
-#pragma unroll
-        for (int i = 0; i < STS_NL; ++i) S.l[i] = s_Sx[i];
-        big_add_shifted(S, (u64)mk, (u64)(mk >> 64), unit_bit(e));
-        const double Sd = big_to_double(S);
-        const u64 L = cb + first + 1;
-        const int dropped = L < s_ncand;
-        ctl->L = L;
-        ctl->thr_wbits = ((u64)e << 52) | frac;
-        ctl->thr_key = (u64)v;
-        ctl->dropped = dropped;
-        ctl->S = Sd;
-        ctl->scale = dropped ? 1.0 / sqrt(Sd) : 1.0;
-        const double frac_kept = Sd / s_W;
-        ctl->frac = frac_kept;
-        if (dropped) ctl->log10_cum = s_l10 + log10(frac_kept);
-    }
+    ok = ok && resolve_cut<FT>(ctl, each_in_subset, e, K, R, s_sub, s_raw, s_cut, s_Sx, s_ncand, s_W, s_l10);
+    if (!ok && t == 0) atomicOr(&ctl->flags, STS_F_UNRESOLVED);
 }
 
 // ---------------------------------------------------------------------------

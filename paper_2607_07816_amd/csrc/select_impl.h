@@ -1,0 +1,714 @@
+// select_impl.h - parts of the cut's selection shared by its kernels: exact
+// masses held by a wave, digit picks, the level-1 pick, and the last levels.
+#pragma once
+#include "kernels.h"
+
+namespace sts_select {
+
+// bit position of the unit 2^(max(e,1)-1075) on the 2^-1074 grid
+__device__ __forceinline__ int unit_bit(int e) { return (e > 0 ? e : 1) - 1; }
+
+__device__ __forceinline__ u128 make128(u64 lo, u64 hi) { return ((u128)hi << 64) | lo; }
+
+// ---------------------------------------------------------------------------
+// Exact masses, one wave wide: a number of 64 limbs of 64 bits (units
+// 2^-1074), limb i held by lane i. Every lane of the wave takes part in each
+// operation. Carries between limbs are resolved at once from two ballots: a
+// limb generates a carry (its sum wrapped) or propagates one (its sum is all
+// ones), and the carries into the limbs are the carries of the binary sum
+// (G | P) + G, i.e. ((G | P) + G) ^ (G | P) ^ G.
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ u64 wl_carry_in(bool gen, bool prop)
+{
+    const u64 G = __ballot(gen), P = __ballot(prop);
+    const u64 X = G | P;
+    return (((X + G) ^ X ^ G) >> sts_lane()) & 1ull;
+}
+
+__device__ __forceinline__ u64 wl_add(u64 a, u64 b)
+{
+    const u64 s = a + b;
+    return s + wl_carry_in(s < a, s == ~0ull);
+}
+
+// a - b, a >= b
+__device__ __forceinline__ u64 wl_sub(u64 a, u64 b)
+{
+    const u64 d = a - b;
+    return d - wl_carry_in(a < b, d == 0);
+}
+
+// this lane's limb of v * 2^bit, v < 2^128 given as (lo, hi)
+__device__ __forceinline__ u64 wl_piece(u64 lo, u64 hi, int bit)
+{
+    const int k = sts_lane() - (bit >> 6), off = bit & 63;
+    if (k == 0) return lo << off;
+    if (k == 1) return off ? (hi << off) | (lo >> (64 - off)) : hi;
+    if (k == 2) return off ? hi >> (64 - off) : 0ull;
+    return 0ull;
+}
+
+// sign of a - b
+__device__ __forceinline__ int wl_cmp(u64 a, u64 b)
+{
+    const u64 D = __ballot(a != b);
+    if (!D) return 0;
+    const int top = 63 - __clzll((long long)D);
+    return ((__ballot(a > b) >> top) & 1ull) ? 1 : -1;
+}
+
+// limb `src` of the number (0 outside 0..63); src may differ between lanes
+__device__ __forceinline__ u64 wl_limb(u64 a, int src)
+{
+    const u64 v = __shfl(a, src & 63, 64);
+    return (src >= 0 && src < 64) ? v : 0ull;
+}
+
+// a >> s (s >= 0), and whether any bit below s was set
+__device__ __forceinline__ u64 wl_shr(u64 a, int s, bool *sticky)
+{
+    const int q = s >> 6, r = s & 63, lane = sts_lane();
+    const u64 a0 = wl_limb(a, lane + q), a1 = wl_limb(a, lane + q + 1);
+    const u64 low = lane < q ? a : (lane == q && r ? (a & ((1ull << r) - 1)) : 0ull);
+    *sticky = __ballot(low != 0) != 0;
+    return r ? (a0 >> r) | (a1 << (64 - r)) : a0;
+}
+
+// ceil(a * m / 2^s), m < 2^64
+__device__ __forceinline__ u64 wl_mul_shr_ceil(u64 a, u64 m, int s)
+{
+    const u128 pr = (u128)a * m;
+    const u64 hi_below = __shfl_up((u64)(pr >> 64), 1, 64);
+    const u64 t = wl_add((u64)pr, sts_lane() > 0 ? hi_below : 0ull);
+    bool sticky;
+    const u64 q = wl_shr(t, s, &sticky);
+    return sticky ? wl_add(q, sts_lane() == 0 ? 1ull : 0ull) : q;
+}
+
+// nearest binary64 (ties to even); the result is the same in every lane
+__device__ inline double wl_to_double(u64 a)
+{
+    const u64 NZ = __ballot(a != 0);
+    if (!NZ) return 0.0;
+    const int top = 63 - __clzll((long long)NZ);
+    const u64 L0 = wl_limb(a, top), L1 = wl_limb(a, top - 1), L2 = wl_limb(a, top - 2);
+    const bool below = top >= 3 && (NZ & ((1ull << (top - 2)) - 1)) != 0;
+    const int lz = __clzll((long long)L0);
+    const int h = top * 64 + 63 - lz; // position of the top set bit
+    if (h < 53) return ldexp((double)L0, -1074);
+    const u64 hi = lz ? (L0 << lz) | (L1 >> (64 - lz)) : L0; // bit 63 = bit h
+    const u64 lo = lz ? (L1 << lz) | (L2 >> (64 - lz)) : L1;
+    const bool rest = below || (lz ? (L2 << lz) != 0 : L2 != 0);
+    u64 mant = hi >> 11;
+    const bool guard = (hi >> 10) & 1ull;
+    const bool sticky = (hi & 0x3ffull) != 0 || lo != 0 || rest;
+    int lsb = h - 52;
+    if (guard && (sticky || (mant & 1ull))) {
+        mant += 1;
+        if (mant == (1ull << 53)) {
+            mant >>= 1;
+            lsb += 1;
+        }
+    }
+    return ldexp((double)mant, lsb - 1074);
+}
+
+// Subset of the rank order still holding the cut: the terms of exponent e*
+// whose rank key V has the high part vpre above bit vshift.
+struct Sub {
+    u64 cnt_before; // terms ranked before the subset
+    u128 mb;        // their mantissa sum inside e* (units 2^(max(e*,1)-1075))
+    u128 vpre;
+    int vshift;
+    u64 count;      // terms in the subset
+};
+
+__device__ inline void sub_load(Sub &s, const DevCtl *ctl)
+{
+    s.cnt_before = ctl->cnt_before;
+    s.mb = make128(ctl->mb_lo, ctl->mb_hi);
+    s.vpre = make128(ctl->vpre_lo, ctl->vpre_hi);
+    s.vshift = ctl->vshift;
+    s.count = ctl->sub_count;
+}
+
+__device__ inline void sub_store(const Sub &s, DevCtl *ctl)
+{
+    ctl->cnt_before = s.cnt_before;
+    ctl->mb_lo = (u64)s.mb;
+    ctl->mb_hi = (u64)(s.mb >> 64);
+    ctl->vpre_lo = (u64)s.vpre;
+    ctl->vpre_hi = (u64)(s.vpre >> 64);
+    ctl->vshift = s.vshift;
+    ctl->sub_count = s.count;
+}
+
+// Pick the first digit (ascending = rank order) where the rule is met, over
+// 2048 bins held in (cnt[], hi[], lo[]) - global (agent loads) or LDS - by NT
+// threads, and narrow *sub to it. K, R: the rule (R all ones = no p-mass).
+// Returns false if no digit qualifies.
+// inclusive scan of (count, mass) pairs over a workgroup of NT threads, in
+// place: wave scans, then the wave totals through LDS (one barrier; sc, sm
+// hold NT / 64 entries and are not read again before the caller's next
+// barrier)
+template <int NT>
+__device__ __forceinline__ void block_scan_cm(u64 &c, u128 &m, u64 *sc, u128 *sm)
+{
+    const int lane = sts_lane(), w = (int)threadIdx.x >> 6;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const u64 oc = __shfl_up(c, d, 64);
+        const u64 ol = __shfl_up((u64)m, d, 64), oh = __shfl_up((u64)(m >> 64), d, 64);
+        if (lane >= d) {
+            c += oc;
+            m += make128(ol, oh);
+        }
+    }
+    if (lane == 63) {
+        sc[w] = c;
+        sm[w] = m;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < NT / 64; ++i) {
+        if (i < w) {
+            c += sc[i];
+            m += sm[i];
+        }
+    }
+}
+
+template <int NT>
+__device__ bool pick_digit(const u64 *cntp, const u64 *hip_, const u64 *lop, bool agent, u64 K, u128 R, int dw,
+                           Sub *sub, u128 *s_m, u64 *s_c, u32 *s_hit)
+{
+    constexpr int PER = STS_NBIN / NT;
+    const int t = threadIdx.x;
+    u64 c[PER];
+    u128 ms[PER];
+    u64 cc = 0;
+    u128 mm = 0;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int d = PER * t + k;
+        if (agent) {
+            c[k] = ld_agent(&cntp[d]);
+            ms[k] = ((u128)ld_agent(&hip_[d]) << 26) + (u128)ld_agent(&lop[d]);
+        } else {
+            c[k] = cntp[d];
+            ms[k] = ((u128)hip_[d] << 26) + (u128)lop[d];
+        }
+        cc += c[k];
+        mm += ms[k];
+    }
+    const u64 own_c = cc;
+    const u128 own_m = mm;
+    if (t == 0) *s_hit = 0xffffffffu;
+    block_scan_cm<NT>(cc, mm, s_c, s_m);
+    // exclusive prefix of this thread's bins, from the subset's start
+    u64 cnt = sub->cnt_before + (cc - own_c);
+    u128 m = sub->mb + (mm - own_m);
+    u32 hit = 0xffffffffu;
+    u64 cnt_hit = 0;
+    u128 m_hit = 0;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        if (hit == 0xffffffffu && c[k]) {
+            const bool hk = K > 0 && cnt + c[k] >= K;
+            const bool hp = m + ms[k] >= R;
+            if (hk || hp) {
+                hit = (u32)(PER * t + k);
+                cnt_hit = cnt;
+                m_hit = m;
+            } else {
+                cnt += c[k];
+                m += ms[k];
+            }
+        }
+    }
+    if (hit != 0xffffffffu) atomicMin(s_hit, hit);
+    __syncthreads();
+    const u32 first = *s_hit;
+    if (first == 0xffffffffu) {
+        __syncthreads();
+        return false;
+    }
+    if (hit == first) {
+        const int k = (int)first - PER * t;
+        sub->vpre = (sub->vpre << dw) | (u128)first;
+        sub->vshift -= dw;
+        sub->cnt_before = cnt_hit;
+        sub->mb = m_hit;
+        sub->count = c[k];
+    }
+    __syncthreads();
+    return true;
+}
+
+// within-exponent rank key: ascending V = descending weight, then ascending key
+__device__ __forceinline__ u128 rank_key(u64 wbits, u64 key)
+{
+    const u64 frac = wbits & ((1ull << 52) - 1);
+    return ((u128)(((1ull << 52) - 1) - frac) << 64) | (u128)key;
+}
+
+__device__ __forceinline__ u64 mant_of_v(u128 v, int e)
+{
+    const u64 frac = ((1ull << 52) - 1) - (u64)(v >> 64);
+    return e ? (frac | (1ull << 52)) : frac;
+}
+
+
+// ---------------------------------------------------------------------------
+// level 1: one workgroup of NT threads. Thread t owns the NB = 2048 / NT
+// exponent bins from 2047 - NB t down (descending weight order). The bins that hold
+// candidates are listed in rank order in LDS; one wave then adds their exact
+// masses up (the total W and the p-mass target), and walks them again to the
+// first bin where the rule is met.
+// ---------------------------------------------------------------------------
+// what the level-1 pick found, for the rest of the same workgroup
+struct Level1Cut {
+    int keep_all;
+    int e;            // exponent field that holds the cut
+    u64 total;        // candidates
+    double W;
+    u64 cnt, count;   // terms ranked before e's, and e's
+    u64 R_lo, R_hi;   // mass to reach inside e, in its units (all ones: off)
+    u64 S[STS_NL];    // exact mass ranked before e's terms
+};
+
+template <int NT> struct Level1Smem {
+    u32 e[STS_NBIN];   // the non-empty bins in rank order: exponent field,
+    u64 c[STS_NBIN];   // count,
+    __attribute__((aligned(16))) u64 lo[STS_NBIN]; // mantissa sum (low, high words)
+    u64 hi[STS_NBIN];
+    u32 scan[NT / 64];
+    u64 bw[NT / 64], bk[NT / 64];
+    u64 w[6];
+    Sub sub;   // level 2 of a sampled window that holds the cut
+    u32 fine, hit2;
+    u64 R_lo, R_hi;
+    u64 chunk[NT / 64][64]; // exact mass of each part of the bin list (a limb per lane)
+    u64 chunk_c[NT / 64];   // and its count
+    Level1Cut cut;
+};
+
+// predicted: 0 no window, 1 a window of the tiled passes, 3 a bucketed step
+// whose histogram pass ran (no window; the side buffer, if the extraction
+// pass fills it, is packed densely)
+template <int NT>
+__device__ void pick_level1(const PassBufs &b, int groups, int peak_only, int predicted, Level1Smem<NT> &sm)
+{
+    constexpr int NB = STS_NBIN / NT, NW = NT / 64;
+    const int t = threadIdx.x;
+    DevCtl *ctl = b.ctl;
+    u64 *h1 = b.h1;
+    // the exponent of the window the histogram pass copied (predicted steps)
+    const int w_mode = ctl->w_mode;
+    const bool win = predicted == 1;
+    const int e_w = win ? (w_mode ? ctl->e_w : ctl->e_pred) : -1;
+    if (t < 6) sm.w[t] = 0;
+    if (t == 0) sm.fine = 0;
+
+    // own bins: every load issued before any is used
+    u64 c[NB], hi[NB], lo[NB];
+#pragma unroll
+    for (int k = 0; k < NB; ++k) {
+        const int e = 2047 - NB * t - k;
+        c[k] = h1[e];
+        hi[k] = h1[STS_NBIN + e];
+        lo[k] = h1[2 * STS_NBIN + e];
+    }
+    // the per-workgroup peaks too (reduced below)
+    constexpr int BPT = (STS_MAX_GROUPS + NT - 1) / NT;
+    u64 bwv[BPT], bkv[BPT];
+#pragma unroll
+    for (int r = 0; r < BPT; ++r) {
+        const int i = t + NT * r;
+        bwv[r] = i < groups ? b.best[i] : 0ull;
+        bkv[r] = i < groups ? b.best[STS_MAX_GROUPS + i] : ~0ull;
+    }
+    // the window sums of the histogram workgroups: count of candidates above
+    // the window and mantissa sums of those in its exponent, then count and
+    // sums of those inside it
+    // (loaded whenever the pass predicted, before the control block says
+    // whether a window was copied)
+    u64 v[6] = {0, 0, 0, 0, 0, 0};
+    if (win) {
+#pragma unroll
+        for (int r = 0; r < STS_MAX_GROUPS / NT; ++r) { // every load issued before any is used
+            const int i = t + NT * r;
+            if (i < groups) {
+#pragma unroll
+                for (int f = 0; f < 6; ++f) v[f] += b.wpart[f * STS_MAX_GROUPS + i];
+            }
+        }
+    }
+    if (e_w >= 0) {
+#pragma unroll
+        for (int f = 0; f < 6; ++f) {
+#pragma unroll
+            for (int d = 32; d > 0; d >>= 1) v[f] += __shfl_xor(v[f], d, 64);
+        }
+        __syncthreads(); // sm.w cleared
+        if ((t & 63) == 0) {
+#pragma unroll
+            for (int f = 0; f < 6; ++f) atomicAdd((unsigned long long *)&sm.w[f], (unsigned long long)v[f]);
+        }
+    }
+    // list the non-empty bins in rank order
+    u32 nz = 0;
+#pragma unroll
+    for (int k = 0; k < NB; ++k) nz += c[k] ? 1u : 0u;
+    u32 nbins;
+    u32 at = block_excl_scan<u32, NT>(nz, sm.scan, &nbins);
+#pragma unroll
+    for (int k = 0; k < NB; ++k) {
+        if (!c[k]) continue;
+        sm.e[at] = (u32)(2047 - NB * t - k);
+        sm.c[at] = c[k];
+        const u128 ms = ((u128)hi[k] << 26) + (u128)lo[k];
+        sm.lo[at] = (u64)ms;
+        sm.hi[at] = (u64)(ms >> 64);
+        ++at;
+    }
+    // peak: reduce the per-workgroup bests (written by the identity pass of
+    // sts_peak only)
+    if (peak_only) {
+        u64 bw = 0, bk = ~0ull;
+#pragma unroll
+        for (int r = 0; r < BPT; ++r) {
+            const u64 w = bwv[r], k = bkv[r];
+            if (w > bw || (w == bw && k < bk)) {
+                bw = w;
+                bk = k;
+            }
+        }
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1) {
+            const u64 ow = __shfl_xor(bw, d, 64);
+            const u64 ok = __shfl_xor(bk, d, 64);
+            if (ow > bw || (ow == bw && ok < bk)) {
+                bw = ow;
+                bk = ok;
+            }
+        }
+        if ((t & 63) == 0) {
+            sm.bw[t >> 6] = bw;
+            sm.bk[t >> 6] = bk;
+        }
+    }
+    __syncthreads();
+
+    // exact sums of the listed bins in NW chunks, one wave each (a chain of
+    // exact additions per bin, that much shorter than over all bins)
+    const u32 chunk = (nbins + NW - 1) / NW;
+    {
+        const int q = t >> 6;
+        const u32 j0 = (u32)q * chunk, j1 = j0 + chunk < nbins ? j0 + chunk : nbins;
+        u64 C = 0, nc = 0;
+        for (u32 j = j0; j < j1; ++j) {
+            C = wl_add(C, wl_piece(sm.lo[j], sm.hi[j], unit_bit((int)sm.e[j])));
+            nc += sm.c[j];
+        }
+        sm.chunk[q][t & 63] = C;
+        if ((t & 63) == 0) sm.chunk_c[q] = nc;
+    }
+    __syncthreads();
+
+    if (t < 64) { // one wave: the total, the target and the cut's bin
+        const int lane = t;
+        u64 W = 0, total_c = 0;
+#pragma unroll
+        for (int q = 0; q < NW; ++q) {
+            W = wl_add(W, sm.chunk[q][lane]);
+            total_c += sm.chunk_c[q];
+        }
+        const double Wd = wl_to_double(W);
+        if (peak_only) {
+            if (lane == 0) {
+                ctl->cand_all = total_c;
+                ctl->peak_W = Wd;
+                u64 w = sm.bw[0], k = sm.bk[0];
+                for (int i = 1; i < NW; ++i)
+                    if (sm.bw[i] > w || (sm.bw[i] == w && sm.bk[i] < k)) {
+                        w = sm.bw[i];
+                        k = sm.bk[i];
+                    }
+                ctl->peak_key = k;
+                ctl->peak_w = (w >> 63) ? __longlong_as_double((long long)(w & ~(1ull << 63))) : 0.0;
+            }
+        } else {
+            const u64 K = ctl->K;
+            const double p = ctl->p;
+            const bool p_on = p > 0.0 && p < 1.0;
+            // p-mass target T = ceil(p * W), exactly
+            u64 T = 0;
+            if (p_on) {
+                const u64 pb = sts_dbits(p);
+                const u64 pe = pb >> 52, pf = pb & ((1ull << 52) - 1);
+                const u64 pm = pe ? (pf | (1ull << 52)) : pf;
+                const int sh = pe ? (int)(1075 - pe) : 1074;
+                T = wl_mul_shr_ceil(W, pm, sh);
+            }
+            if (lane < STS_NL) ctl->T.l[lane] = T;
+            if (lane == 0) {
+                ctl->cand_all = total_c;
+                ctl->W = Wd;
+                ctl->n_cand = total_c;
+                ctl->tot_steps += 1;
+                ctl->tot_updates += *b.n_in;
+                ctl->tot_cand += total_c;
+            }
+            // the first bin in rank order where the rule is met: the first
+            // chunk through which it is met (the rule only grows along the
+            // ranking), then that chunk's bins
+            u64 S = 0, cnt = 0;
+            u32 hit = 0xffffffffu;
+            for (int q = 0; q < NW; ++q) {
+                const u64 inc_q = wl_add(S, sm.chunk[q][lane]);
+                const bool met_q = (K > 0 && cnt + sm.chunk_c[q] >= K) || (p_on && wl_cmp(inc_q, T) >= 0);
+                if (met_q) {
+                    const u32 j0 = (u32)q * chunk, j1 = j0 + chunk < nbins ? j0 + chunk : nbins;
+                    for (u32 j = j0; j < j1; ++j) {
+                        const u64 inc = wl_add(S, wl_piece(sm.lo[j], sm.hi[j], unit_bit((int)sm.e[j])));
+                        const bool hk = K > 0 && cnt + sm.c[j] >= K;
+                        const bool hp = p_on && wl_cmp(inc, T) >= 0;
+                        if (hk || hp) {
+                            hit = j;
+                            break;
+                        }
+                        S = inc;
+                        cnt += sm.c[j];
+                    }
+                    break;
+                }
+                S = inc_q;
+                cnt += sm.chunk_c[q];
+            }
+            if (lane == 0) {
+                sm.cut.keep_all = hit == 0xffffffffu;
+                sm.cut.total = total_c;
+                sm.cut.W = Wd;
+            }
+            if (hit == 0xffffffffu) {
+                if (lane == 0) {
+                    ctl->keep_all = 1;
+                    ctl->dropped = 0;
+                    ctl->L = total_c;
+                    ctl->scale = 1.0;
+                    ctl->S = Wd;
+                    ctl->frac = 1.0;
+                    ctl->level = 1;
+                    ctl->pred_hit = 0;
+                    ctl->e_pred = -1;
+                }
+            } else {
+                const int e = (int)sm.e[hit];
+                const int ub = unit_bit(e);
+                // does the copied window hold the cut? Exactly when the rule is
+                // not met through the candidates above it and is met through it
+                bool in_window = false;
+                u64 ca = 0, cw = 0;
+                u128 ma = 0;
+                if (e == e_w) {
+                    // the histogram pass counted every candidate above the window;
+                    // those in exponents above e are the cnt ranked before this bin
+                    ca = sm.w[0] - cnt;
+                    cw = sm.w[3];
+                    ma = ((u128)sm.w[1] << 26) + (u128)sm.w[2];
+                    const u128 mw = ((u128)sm.w[4] << 26) + (u128)sm.w[5];
+                    const u64 Sa = wl_add(S, wl_piece((u64)ma, (u64)(ma >> 64), ub));
+                    const bool met_a = (K > 0 && cnt + ca >= K) || (p_on && wl_cmp(Sa, T) >= 0);
+                    const u64 Sw = wl_add(Sa, wl_piece((u64)mw, (u64)(mw >> 64), ub));
+                    const bool met_w = (K > 0 && cnt + ca + cw >= K) || (p_on && wl_cmp(Sw, T) >= 0);
+                    in_window = !met_a && met_w;
+                }
+                // remaining mass to reach inside the bin, in its units (rounded up)
+                u64 R_lo = ~0ull, R_hi = ~0ull;
+                if (p_on) {
+                    bool sticky;
+                    const u64 q = wl_shr(wl_sub(T, S), ub, &sticky);
+                    const bool over = __ballot(lane >= 2 && q != 0) != 0;
+                    u128 r = ((u128)__shfl(q, 1, 64) << 64) | (u128)__shfl(q, 0, 64);
+                    if (!over) {
+                        if (sticky) r += 1;
+                        if (r != 0 || !sticky) {
+                            R_lo = (u64)r;
+                            R_hi = (u64)(r >> 64);
+                        }
+                    }
+                }
+                if (lane < STS_NL) {
+                    ctl->S_excl.l[lane] = S;
+                    sm.cut.S[lane] = S;
+                }
+                if (lane == 0) {
+                    sm.cut.e = e;
+                    sm.cut.cnt = cnt;
+                    sm.cut.count = sm.c[hit];
+                    sm.cut.R_lo = R_lo;
+                    sm.cut.R_hi = R_hi;
+                }
+                if (lane == 0 && in_window && w_mode && win) {
+                    // the histogram pass binned this window for level 2: the
+                    // whole workgroup picks its digit below
+                    sm.fine = 1;
+                    sm.sub.cnt_before = cnt + ca;
+                    sm.sub.mb = ma;
+                    sm.sub.vpre = 0;
+                    sm.sub.vshift = 116;
+                    sm.sub.count = cw;
+                    sm.R_lo = R_lo;
+                    sm.R_hi = R_hi;
+                }
+                if (lane == 0) {
+                    ctl->keep_all = 0;
+                    ctl->pred_hit = in_window ? 1 : 0;
+                    ctl->e_pred = e;
+                    ctl->e_star = e;
+                    ctl->cnt_before = in_window ? cnt + ca : cnt;
+                    ctl->sub_count = in_window ? cw : sm.c[hit];
+                    ctl->mb_lo = in_window ? (u64)ma : 0;
+                    ctl->mb_hi = in_window ? (u64)(ma >> 64) : 0;
+                    ctl->level = 1;
+                    ctl->R_lo = R_lo;
+                    ctl->R_hi = R_hi;
+                }
+            }
+            if (lane == 0) {
+                ctl->w2_mode = win && w_mode; // the histogram pass binned the window for level 2
+                ctl->w_mode = 0;                     // a window serves one step
+                if (predicted == 3) {
+                    ctl->w_over = 0;
+                    ctl->need_full = 0;
+                    // a missed window: the extraction pass packs its candidates densely
+                    if (hit != 0xffffffffu && !ctl->pred_hit) {
+                        ctl->side_dense = 1;
+                        ctl->side_n = 0;
+                    }
+                }
+                ctl->l2_done = 0;
+            }
+        }
+    }
+    __syncthreads();
+    for (int i = t; i < 3 * STS_NBIN; i += NT) h1[i] = 0;
+    if (sm.fine) { // uniform
+        // level 2 from the window's bins (the side pass then has nothing to
+        // do); the bin lists above are done with, so their LDS serves the pick
+        const u128 R = make128(sm.R_lo, sm.R_hi);
+        u128 *s_m = reinterpret_cast<u128 *>(sm.lo);
+        u64 *s_c2 = sm.hi;
+        const bool ok = pick_digit<NT>(b.h2w, b.h2w + STS_NBIN, b.h2w + 2 * STS_NBIN, true, ctl->K, R, 11, &sm.sub,
+                                        s_m, s_c2, &sm.hit2);
+        if (ok && t <= STS_SUB_REGIONS) st_agent(&b.sub_cnt[t * 32], 0u);
+        if (t == 0) {
+            if (ok) {
+                sub_store(sm.sub, ctl);
+                ctl->level = 2;
+                ctl->l2_done = 1;
+            } else {
+                atomicOr(&ctl->flags, STS_F_UNRESOLVED);
+            }
+        }
+        for (int i = t; i < 3 * STS_NBIN; i += NT) st_agent(&b.h2w[i], 0ull);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// last levels: narrow s_sub by 11-bit digits of the rank key V until at most
+// STS_FINAL_SORT terms are left, then the exact cut. each(vshift,
+// vpre, keyed, f) calls f(V) for every term of the subset whose V lies under
+// the prefix (all threads take part; V's key half may be 0 unless keyed). raw: STS_NBIN * 24 bytes of LDS. The subset's terms are
+// few by then (a handful as a rule), so every term counts and weighs the ones
+// before it by itself; their mantissas add up below 2^63. Returns false when
+// the cut could not be resolved (an internal inconsistency).
+// ---------------------------------------------------------------------------
+struct CutSmem {
+    u128 m[1024 / 64];
+    u64 c[1024 / 64];
+    u32 hit, n;
+    u64 thr_w, thr_k; // the cut's term
+};
+
+template <int NT, typename E>
+__device__ bool resolve_cut(DevCtl *ctl, E &&each, int e, u64 K, u128 R, Sub &s_sub, unsigned char *raw, CutSmem &sm,
+                            const u64 *s_Sx, u64 ncand, double W, double l10)
+{
+    const int t = threadIdx.x;
+    u64 *h_cnt = reinterpret_cast<u64 *>(raw), *h_hi = h_cnt + STS_NBIN, *h_lo = h_hi + STS_NBIN;
+    u128 *sv = reinterpret_cast<u128 *>(raw);
+    static_assert(NT <= 1024 && STS_FINAL_SORT <= NT, "one term per thread");
+    while (s_sub.count > STS_FINAL_SORT && s_sub.vshift > 0) {
+        const int vshift = s_sub.vshift;
+        const int dw = vshift < 11 ? vshift : 11;
+        const u128 vpre = s_sub.vpre;
+        for (int i = t; i < 3 * STS_NBIN; i += NT) h_cnt[i] = 0;
+        __syncthreads();
+        each(vshift, vpre, vshift - dw < 64, [&](const u128 v) {
+            const u32 d = (u32)((v >> (vshift - dw)) & (u128)((1u << dw) - 1));
+            const u64 mant = mant_of_v(v, e);
+            atomicAdd((unsigned long long *)&h_cnt[d], 1ull);
+            atomicAdd((unsigned long long *)&h_hi[d], mant >> 26);
+            atomicAdd((unsigned long long *)&h_lo[d], mant & ((1ull << 26) - 1));
+        });
+        __syncthreads();
+        if (!pick_digit<NT>(h_cnt, h_hi, h_lo, false, K, R, dw, &s_sub, sm.m, sm.c, &sm.hit)) return false;
+    }
+    const int vshift = s_sub.vshift;
+    const u128 vpre = s_sub.vpre;
+    if (t == 0) {
+        sm.n = 0;
+        sm.hit = 0xffffffffu;
+    }
+    __syncthreads();
+    each(vshift, vpre, true, [&](const u128 v) {
+        const u32 slot = atomicAdd(&sm.n, 1u);
+        if (slot < STS_FINAL_SORT) sv[slot] = v;
+    });
+    __syncthreads();
+    const u32 m = sm.n;
+    if (m == 0 || m > STS_FINAL_SORT) return false;
+    u128 v = 0;
+    u32 rank = 0;
+    u64 mass = 0; // of the terms up to this one
+    bool met = false;
+    if ((u32)t < m) {
+        v = sv[t];
+        for (u32 i = 0; i < m; ++i) {
+            const u128 o = sv[i];
+            rank += o < v ? 1u : 0u;
+            mass += o <= v ? mant_of_v(o, e) : 0ull;
+        }
+        met = (K > 0 && s_sub.cnt_before + rank + 1 >= K) || s_sub.mb + (u128)mass >= R;
+        if (met) atomicMin(&sm.hit, rank);
+    }
+    __syncthreads();
+    if (sm.hit == 0xffffffffu) return false;
+    if (met && rank == sm.hit) {
+        const u64 frac = ((1ull << 52) - 1) - (u64)(v >> 64);
+        const u128 mk = s_sub.mb + (u128)mass;
+        Big S;
+#pragma unroll
+        for (int i = 0; i < STS_NL; ++i) S.l[i] = s_Sx[i];
+        big_add_shifted(S, (u64)mk, (u64)(mk >> 64), unit_bit(e));
+        const double Sd = big_to_double(S);
+        const u64 L = s_sub.cnt_before + rank + 1;
+        const int dropped = L < ncand;
+        ctl->L = L;
+        ctl->thr_wbits = ((u64)e << 52) | frac;
+        ctl->thr_key = (u64)v;
+        sm.thr_w = ((u64)e << 52) | frac;
+        sm.thr_k = (u64)v;
+        ctl->dropped = dropped;
+        ctl->S = Sd;
+        ctl->scale = dropped ? 1.0 / sqrt(Sd) : 1.0;
+        const double frac_kept = Sd / W;
+        ctl->frac = frac_kept;
+        if (dropped) ctl->log10_cum = l10 + log10(frac_kept);
+    }
+    return true;
+}
+
+} // namespace sts_select
