@@ -61,9 +61,6 @@ int bucket_bits(u64 n)
 // largest state that is kept in bucket order (32-bit term indices, and bucket
 // tables of at most 2^22 entries)
 constexpr u64 kBucketMax = 1ull << 28;
-// and the smallest that a gate step puts there: below, the sort passes are
-// one or two short launches
-constexpr u64 kBucketMin = 1024;
 // up to this size bound a step's selection is one workgroup's (k_bkt_select);
 // above, the step samples its window first and spreads the selection
 constexpr u64 kSelectMax = 1ull << 15;
@@ -181,6 +178,7 @@ struct sts_ctx {
     int hb = 0, bdc = 0;    // 2^hb buckets, table bd[bdc]
     bool one_step = false;    // sts_step_static
     bool bkt_pending = false; // the pending gate is a bucketed step
+    bool tiny_pending = false; // or a one-launch step
     int prev_m = 0, prev_q[2] = {0, 0}; // the qubits of the last bucketed step
     u32 *tctr = nullptr;
     double *dU = nullptr;
@@ -462,12 +460,14 @@ sts_status sort_state(sts_ctx *c, const u64 *notmask, int *sorted, int *hb_out)
     return STS_OK;
 }
 
-// whether a gate of m qubits on the current state is a bucketed step
-// (not the one step of sts_step_static: putting its terms in bucket order
+// whether a gate of m qubits on the current state is a one-launch step
+bool use_tiny(const sts_ctx *c, int m) { return m <= 2 && c->n_bound <= STS_TINY_MAX; }
+
+// whether it is a bucketed step (not the one step of sts_step_static: putting its terms in bucket order
 // costs what the sort does, and no later step gains from it)
 bool use_buckets(const sts_ctx *c, int m)
 {
-    return !c->one_step && m <= 2 && c->cap <= kBucketMax && c->n_bound >= kBucketMin;
+    return !c->one_step && m <= 2 && c->cap <= kBucketMax && c->n_bound > STS_TINY_MAX;
 }
 
 // whether the state's buckets suit its size bound: neither so few that a
@@ -489,6 +489,7 @@ u64 bound_after(const sts_ctx *c, int m)
 // bucket geometry, or the sort's bucket bits
 void place_gate(const sts_ctx *c, GateArg *g, const int *qubits)
 {
+    if (use_tiny(c, g->m)) return; // any order will do
     if (use_buckets(c, g->m)) {
         const int hb = buckets_suit(c) ? c->hb : bucket_bits(c->n_bound);
         const int delta = std::min(std::max(bucket_bits(bound_after(c, g->m)) - hb, 0), 4);
@@ -569,6 +570,33 @@ sts_status bucket_write(sts_ctx *c, const PassBufs &b, int dst, u64 bound)
     return STS_OK;
 }
 
+// a one-launch step that may not fit the capacity takes the sorted passes
+// instead, which can be counted first and refused
+sts_status tiny_to_sorted(sts_ctx *c)
+{
+    int hb = 8, sorted = c->cur;
+    c->gate.hb = sts_radix_bits(sort_shape(c)) * sort_passes(c);
+    STS_TRY(c, launch_set_gate(c->gate, c->dgate, c->stream));
+    c->gate_dev = c->dgate;
+    c->bucketed = false;
+    const sts_status st = sort_state(c, &c->dgate->notmask, &sorted, &hb);
+    if (st != STS_OK) return st;
+    c->cur = sorted;
+    c->tiny_pending = false;
+    return STS_OK;
+}
+
+// the pending one-launch step, its result in buffer dst
+sts_status tiny_step(sts_ctx *c, PassBufs &b, int dst, u64 bound)
+{
+    STS_LAUNCH(c, STS_K_FINAL, launch_tiny(c->prec, c->gate, b, c->stream));
+    c->cur = dst;
+    c->n_bound = bound;
+    c->bucketed = false;
+    c->tiny_pending = c->pending = false;
+    return STS_OK;
+}
+
 // number of nonzero candidates of the pending gate (synchronises)
 sts_status count_candidates(sts_ctx *c, u64 *count)
 {
@@ -598,6 +626,16 @@ sts_status materialise(sts_ctx *c)
     if (!c->pending) return STS_OK;
     const u64 cb = sat_shl(c->n_bound, c->gate.m);
     u64 bound = cb;
+    if (c->tiny_pending) {
+        if (cb <= c->cap) {
+            const int dst = (c->cur + 1) % 3;
+            PassBufs b = pass_bufs(c, c->cur, dst);
+            b.materialise = 1;
+            return tiny_step(c, b, dst, cb);
+        }
+        const sts_status st = tiny_to_sorted(c);
+        if (st != STS_OK) return st;
+    }
     if (cb > c->cap) {
         u64 count = 0;
         const sts_status st = count_candidates(c, &count);
@@ -820,6 +858,11 @@ sts_status sts_apply_gate(sts_ctx *c, int m, const int *qubits, const double *U)
     }
     int sorted = c->cur, hb = 8;
     place_gate(c, &g, qubits);
+    if (use_tiny(c, m)) { // the whole step is the next call's one launch
+        c->gate = g;
+        c->pending = c->tiny_pending = true;
+        return STS_OK;
+    }
     STS_TRY(c, launch_set_gate(g, c->dgate, c->stream));
     c->gate_dev = c->dgate;
     if (use_buckets(c, m)) {
@@ -854,8 +897,7 @@ static sts_status truncate_buckets(sts_ctx *c)
     }
     const bool small = c->n_bound <= kSelectMax && tiles * 4 <= STS_SEL_SHARES;
     if (small) {
-        b.predict = 1;
-        STS_LAUNCH(c, STS_K_GROUP_HIST, launch_bucket_pass(STS_BKT_HIST, c->prec, m, b, tiles, c->stream));
+        STS_LAUNCH(c, STS_K_GROUP_HIST, launch_bucket_pass(STS_BKT_SMALL, c->prec, m, b, tiles, c->stream));
         STS_LAUNCH(c, STS_K_FINAL, launch_bucket_pass(STS_BKT_SELECT, c->prec, m, b, tiles, c->stream));
         b.emit_copies = 1;
     } else {
@@ -889,6 +931,17 @@ sts_status sts_truncate(sts_ctx *c)
     sts_status st = check_live(c);
     if (st != STS_OK) return st;
     if (c->pending && c->bkt_pending) return truncate_buckets(c);
+    if (c->pending && c->tiny_pending) {
+        const u64 cb = sat_shl(c->n_bound, c->gate.m);
+        const u64 nb = c->K ? std::min<u64>(c->K, cb) : cb;
+        if (nb <= c->cap) {
+            const int out = (c->cur + 1) % 3;
+            PassBufs b = pass_bufs(c, c->cur, out);
+            return tiny_step(c, b, out, nb);
+        }
+        st = tiny_to_sorted(c); // a cut limited by p-mass alone may keep more than cap terms
+        if (st != STS_OK) return st;
+    }
     if (!c->pending) {
         c->gate = identity_gate();
         c->gate_dev = c->dgate_id;
@@ -1067,7 +1120,7 @@ sts_status sts_load_terms(sts_ctx *c, uint64_t n, const uint64_t *keys, const do
     for (u64 i = 1; i < n; ++i)
         if (sk[i] == sk[i - 1]) return STS_E_ARG;
     // the state is replaced: any pending gate is dropped
-    c->pending = c->bkt_pending = false;
+    c->pending = c->bkt_pending = c->tiny_pending = false;
     c->bucketed = false;
     if (n) {
         STS_TRY(c, hipMemcpyAsync(c->keys[c->cur], keys, n * 8, hipMemcpyHostToDevice, c->stream));
@@ -1320,7 +1373,8 @@ sts_status step_replayed(sts_ctx *c, StepGraphs *gs, int m, const int *qubits, c
             hipGraphNodeType t;
             if (hipGraphNodeGetType(nodes[i], &t) != hipSuccess || t != hipGraphNodeTypeKernel) continue;
             hipKernelNodeParams p{};
-            if (hipGraphKernelNodeGetParams(nodes[i], &p) == hipSuccess && p.func == set_gate_kernel())
+            if (hipGraphKernelNodeGetParams(nodes[i], &p) == hipSuccess &&
+                (p.func == set_gate_kernel() || p.func == tiny_kernel(c->prec, m)))
                 e.set_node = nodes[i];
         }
         if (he == hipSuccess && !e.set_node) he = hipErrorNotFound;
@@ -1343,13 +1397,10 @@ sts_status step_replayed(sts_ctx *c, StepGraphs *gs, int m, const int *qubits, c
         c->prev_m = m;
         for (int t = 0; t < m; ++t) c->prev_q[t] = qubits[t];
     }
-    GateArg *dst = c->dgate;
-    void *args[2] = {&g, &dst};
+    // the node's first argument is the gate; the others stay
     hipKernelNodeParams p{};
-    p.func = const_cast<void *>(set_gate_kernel());
-    p.gridDim = dim3(1);
-    p.blockDim = dim3(64);
-    p.sharedMemBytes = 0;
+    STS_TRY(c, hipGraphKernelNodeGetParams(hit->set_node, &p));
+    void *args[2] = {&g, p.kernelParams[1]};
     p.kernelParams = args;
     p.extra = nullptr;
     STS_TRY(c, hipGraphExecKernelNodeSetParams(hit->exec, hit->set_node, &p));

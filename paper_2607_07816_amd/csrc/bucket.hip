@@ -1,4 +1,4 @@
-// bucket.hip - bucketed gate steps: dispatch by precision, the survivor
+// bucket.hip - bucketed and one-launch gate steps: dispatch by precision, the survivor
 // counts and offsets, and the bucket table of a freshly ordered state.
 #include <algorithm>
 
@@ -6,6 +6,10 @@
 
 hipError_t bucket_c128_pass(int kind, int m, const PassBufs &b, int tiles, hipStream_t s);
 hipError_t bucket_c64_pass(int kind, int m, const PassBufs &b, int tiles, hipStream_t s);
+hipError_t tiny_c128(const GateArg &g, const PassBufs &b, hipStream_t s);
+hipError_t tiny_c64(const GateArg &g, const PassBufs &b, hipStream_t s);
+const void *tiny_c128_kernel(int m);
+const void *tiny_c64_kernel(int m);
 int bucket_c128_groups(int m, int tiles, bool weigh);
 int bucket_c64_groups(int m, int tiles, bool weigh);
 
@@ -115,6 +119,13 @@ int bucket_hist_groups(int prec, int m, int tiles, bool weigh)
 {
     return prec == 0 ? bucket_c128_groups(m, tiles, weigh) : bucket_c64_groups(m, tiles, weigh);
 }
+
+hipError_t launch_tiny(int prec, const GateArg &g, const PassBufs &b, hipStream_t s)
+{
+    return prec == 0 ? tiny_c128(g, b, s) : tiny_c64(g, b, s);
+}
+
+const void *tiny_kernel(int prec, int m) { return prec == 0 ? tiny_c128_kernel(m) : tiny_c64_kernel(m); }
 
 hipError_t launch_bucket_pass(int kind, int prec, int m, const PassBufs &b, int tiles, hipStream_t s)
 {

@@ -489,13 +489,16 @@ __device__ __forceinline__ void share_groups(WaveSmem<AT> &s, const AT *ucol, co
     share_parts<AT, M>(s, ucol, g, t, keys, amps, []() {}, body);
 }
 
-// before the first share (the caller's barrier follows)
+// before the first share (the caller's barrier follows); called by the first
+// NW waves, or by all of a larger workgroup
 template <typename AT, int M, int NW>
 __device__ __forceinline__ void smem_begin(BktSmem<AT, NW> &s, const GateArg &g)
 {
     typedef typename Scalar<AT>::T R;
-    WaveSmem<AT> &w = s.w[threadIdx.x >> 6];
-    for (int i = sts_lane(); i < BW_SLOTS; i += 64) w.slot[i] = 0;
+    if (threadIdx.x < NW * 64) {
+        WaveSmem<AT> &w = s.w[threadIdx.x >> 6];
+        for (int i = sts_lane(); i < BW_SLOTS; i += 64) w.slot[i] = 0;
+    }
     if (threadIdx.x < (1 << (2 * M))) {
         const int i = (int)threadIdx.x & ((1 << M) - 1), j = (int)threadIdx.x >> M;
         AT u;
@@ -531,6 +534,24 @@ __device__ __forceinline__ void slab_put(SlabOut &o, u64 *sk, u64 *sw, AT *sa, u
     o.c_ab += n_ab;
 }
 
+// a candidate's weight to the exponent bins
+__device__ __forceinline__ void bin_weight(const PassBufs &b, u64 *s_hi, u64 *s_lo, int hot_lo, u64 wb, bool direct)
+{
+    const int e = (int)(wb >> 52);
+    const u64 mant = sts_mant(wb);
+    const int bin = e - TT_EBASE, hd = e - hot_lo;
+    if (!direct && ((unsigned)hd < (unsigned)TT_HOT || (unsigned)bin < (unsigned)TT_NB)) {
+        const int f2 = (int)((wb >> 50) & (TT_HSUB - 1)), copy = (int)(threadIdx.x % TT_HCOPIES);
+        const int slot = (unsigned)hd < (unsigned)TT_HOT ? TT_NB + (hd * TT_HSUB + f2) * TT_HCOPIES + copy : bin;
+        atomicAdd(&s_hi[slot], mant >> 26);
+        atomicAdd(&s_lo[slot], (mant & ((1ull << 26) - 1)) | (1ull << 44));
+    } else {
+        atomicAdd(&b.h1[e], 1ull);
+        atomicAdd(&b.h1[STS_NBIN + e], mant >> 26);
+        atomicAdd(&b.h1[2 * STS_NBIN + e], mant & ((1ull << 26) - 1));
+    }
+}
+
 // lower exponent field of the two octaves a small step's slabs hold: the
 // previous cut's and the one its threshold lies nearer to
 __device__ __forceinline__ int small_window(const DevCtl *ctl)
@@ -541,11 +562,8 @@ __device__ __forceinline__ int small_window(const DevCtl *ctl)
 
 // ---------------------------------------------------------------------------
 // histogram pass: exponent histogram with exact mantissa sums of all new
-// weights; with b.predict (small states) also the candidates of a window of
-// two octaves and those above it to the wave's slab: the previous cut's octave
-// and the one nearer to the cut. A slab that is too small marks the window as
-// missed. Persistent grid. With b.recover it runs only after a sampled window
-// that missed (and copies nothing).
+// weights (persistent grid). With b.recover it runs only after a sampled
+// window that missed.
 // ---------------------------------------------------------------------------
 template <typename AT, int M>
 __global__ void __launch_bounds__(STS_WG) k_bkt_hist(const GateArg *__restrict__ gp, PassBufs b)
@@ -561,17 +579,9 @@ __global__ void __launch_bounds__(STS_WG) k_bkt_hist(const GateArg *__restrict__
         s_hi[i] = 0;
         s_lo[i] = 0;
     }
-    const u64 *keys = b.keys;
-    const AT *amps = (const AT *)b.amps;
     const u32 ntiles = bkt_tiles(g.bkt);
     const int e_prev = ctl->e_pred;
-    const bool predict = b.predict;
-    const int e_w = small_window(ctl);
-    // the window, in the weight's high word; without a previous cut, everything
-    const u32 wL = uni(e_prev >= 0 ? (u32)e_w << 20 : 0u), wH = uni(e_prev >= 0 ? (u32)(e_w + 2) << 20 : ~0u);
-    const int shift = b.slab_shift;
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int copy = (int)(threadIdx.x % TT_HCOPIES);
     const int hot_lo = (e_prev >= 0 ? e_prev : TT_EBASE + 116) - (TT_HOT - 4);
     __syncthreads();
     int since_flush = 0;
@@ -585,53 +595,21 @@ __global__ void __launch_bounds__(STS_WG) k_bkt_hist(const GateArg *__restrict__
         }
         ++since_flush;
         const Share sh = load_share(g.bkt, b.bd_in, tile, wv);
-        const u32 sl = (tile << 2) + (u32)wv;
-        const u64 slab = (u64)sl << shift;
         const bool direct = sh.n > BW_BINNED;
-        u64 *const sk = b.side_key + slab;
-        u64 *const sw = b.side_w + slab;
-        AT *const sa = (AT *)b.side_amp + slab;
-        SlabOut so = {0, 0, 0, true};
-        share_groups<AT, M>(s.w[wv], s.ucol, gl, sh, keys, amps, [&](const auto &ox, const auto &oy, u64 rest, bool active) {
+        u32 c_all = 0;
+        share_groups<AT, M>(s.w[wv], s.ucol, gl, sh, b.keys, (const AT *)b.amps,
+                            [&](const auto &ox, const auto &oy, u64 rest, bool active) {
 #pragma unroll
             for (int i = 0; i < (1 << M); ++i) {
                 AT o;
                 o.x = ox[i];
                 o.y = oy[i];
                 const bool cand = active && nonzero(o);
-                const u64 wb = weight_bits(o);
-                const int e_ = (int)(wb >> 52);
-                const u32 hw = (u32)(wb >> 32);
-                if (cand) {
-                    const u64 mant = sts_mant(wb);
-                    const int bin = e_ - TT_EBASE;
-                    const int hd = e_ - hot_lo;
-                    if (!direct && ((unsigned)hd < (unsigned)TT_HOT || (unsigned)bin < (unsigned)TT_NB)) {
-                        const int f2 = (int)((wb >> 50) & (TT_HSUB - 1));
-                        const int slot =
-                            (unsigned)hd < (unsigned)TT_HOT ? TT_NB + (hd * TT_HSUB + f2) * TT_HCOPIES + copy : bin;
-                        atomicAdd(&s_hi[slot], mant >> 26);
-                        atomicAdd(&s_lo[slot], (mant & ((1ull << 26) - 1)) | (1ull << 44));
-                    } else {
-                        atomicAdd(&b.h1[e_], 1ull);
-                        atomicAdd(&b.h1[STS_NBIN + e_], mant >> 26);
-                        atomicAdd(&b.h1[2 * STS_NBIN + e_], mant & ((1ull << 26) - 1));
-                    }
-                }
-                so.c_all += (u32)__popcll(wballot(cand));
-                if (predict)
-                    slab_put<AT>(so, sk, sw, sa, 1u << shift, cand && hw >= wL && hw < wH, cand && hw >= wH,
-                                 rest | pattern_bits<M>(gl, i), wb, o);
+                if (cand) bin_weight(b, s_hi, s_lo, hot_lo, weight_bits(o), direct);
+                c_all += (u32)__popcll(wballot(cand));
             }
         });
-        if (sts_lane() == 0) {
-            b.w_all[sl] = so.c_all;
-            if (predict) {
-                b.t_above[sl] = so.c_ab;
-                b.t_side[sl] = so.c_in;
-                if (!so.fits) atomicOr(&ctl->w_over, 1u);
-            }
-        }
+        if (sts_lane() == 0) b.w_all[(tile << 2) + (u32)wv] = c_all;
     }
     __syncthreads();
     flush_bins(b, s_hi, s_lo, hot_lo);
@@ -1232,32 +1210,43 @@ __global__ void __launch_bounds__(STS_WG) k_bkt_emit(const GateArg *__restrict__
 }
 
 // ---------------------------------------------------------------------------
-// The whole selection of a small step (at most SEL_SHARES shares) in one
-// workgroup: the level-1 pick over the exponent bins, the further levels over
-// the slabs' window entries of the cut's exponent, and the survivors' offsets.
-// Several short launches in a chain cost more than one workgroup's pass over
-// some thousands of entries. A window that missed the cut is not recovered by
-// further launches: four waves of this workgroup then compute the candidates
-// again for each pass over them.
+// Small steps (at most STS_SEL_SHARES shares). The weighing pass bins the
+// weights as the histogram pass does and copies a window of two octaves (of
+// all weights when there is no previous cut) and the candidates above it to
+// the slabs. One workgroup then does the whole selection: the level-1 pick
+// over the exponent bins, the further levels over the slabs' entries of the
+// cut's exponent, and the survivors' offsets. Several short launches in a
+// chain cost more than one workgroup's passes over some thousands of entries.
+// (Selecting in the weighing pass's last workgroup instead of a launch of its
+// own was slower: 48 us instead of 12 + 29 at 4096 terms; the fences of that
+// handover cost more than the launch.) A window that missed the cut is not
+// recovered by further launches either: four waves of the selection then
+// compute the candidates again for each pass over them.
 // ---------------------------------------------------------------------------
 constexpr int SEL_NT = 1024;
+
+struct SelectSmem {
+    union {
+        sts_select::Level1Smem<SEL_NT> l1;
+        unsigned char raw[3 * STS_NBIN * sizeof(u64)];
+    } u;
+    sts_select::Level1Cut l1;
+    sts_select::CutSmem cut;
+    sts_select::Sub sub;
+    u32 kept[STS_SEL_SHARES];
+    u64 scan[SEL_NT / 64];
+};
 
 template <typename AT, int M>
 __global__ void __launch_bounds__(SEL_NT) k_bkt_select(const GateArg *__restrict__ gp, PassBufs b)
 {
     using namespace sts_select;
+    constexpr int NT = SEL_NT;
+    constexpr int UN = 8; // entries in flight per lane
     const GateArg &g = *gp;
     const GateLoc<M> gl = gate_loc<M>(g);
     __shared__ BktSmem<AT, BW> s;
-    __shared__ union {
-        Level1Smem<SEL_NT> l1;
-        unsigned char raw[3 * STS_NBIN * sizeof(u64)];
-    } u;
-    __shared__ Level1Cut s_l1;
-    __shared__ CutSmem s_cut;
-    __shared__ Sub s_sub;
-    __shared__ u32 s_kept[STS_SEL_SHARES];
-    __shared__ u64 s_scan[SEL_NT / 64];
+    __shared__ SelectSmem m;
     DevCtl *ctl = b.ctl;
     const int t = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(t >> 6);
     const u32 lane = (u32)sts_lane(), l16 = lane & 15u, g16 = (u32)t >> 4;
@@ -1266,152 +1255,125 @@ __global__ void __launch_bounds__(SEL_NT) k_bkt_select(const GateArg *__restrict
     // control words, read before the pick writes any
     const int e_prev = ctl->e_pred, e_w = small_window(ctl);
     const u32 over = ctl->w_over;
+    u64 thr_w = 0, thr_k = 0;
     const u64 K = ctl->K;
     const double l10 = ctl->log10_cum;
-    if (wv < BW) {
-        for (int i = lane; i < BW_SLOTS; i += 64) s.w[wv].slot[i] = 0;
-    }
-    if (t < (1 << (2 * M))) {
-        typedef typename Scalar<AT>::T R;
-        const int i = t & ((1 << M) - 1), j = t >> M;
-        AT v;
-        v.x = UEntry<R, M>::re(g, i, j);
-        v.y = UEntry<R, M>::im(g, i, j);
-        s.ucol[t] = v;
-    }
-    __syncthreads();
-    pick_level1<SEL_NT>(b, 0, 0, 0, u.l1);
+    pick_level1<NT>(b, 0, 0, 0, m.u.l1, DeviceBins<NT>{b.h1});
     __syncthreads();
     if (t < (int)(sizeof(Level1Cut) / sizeof(u64)))
-        reinterpret_cast<u64 *>(&s_l1)[t] = reinterpret_cast<const u64 *>(&u.l1.cut)[t];
+        reinterpret_cast<u64 *>(&m.l1)[t] = reinterpret_cast<const u64 *>(&m.u.l1.cut)[t];
+    for (u32 sl = t; sl < nsl; sl += NT) m.kept[sl] = 0;
+    const bool all = m.u.l1.cut.keep_all;
+    if (!all && (over || (e_prev >= 0 && m.u.l1.cut.e != e_w && m.u.l1.cut.e != e_w + 1)))
+        smem_begin<AT, M, BW>(s, g); // uniform: the candidates will be computed again
     __syncthreads();
-    const bool all = s_l1.keep_all;
-    const int e = s_l1.e;
+    const int e = m.l1.e;
     // the slabs hold every candidate of the cut's exponent and above
     const bool slabs = !all && !over && (e_prev < 0 || e == e_w || e == e_w + 1);
-    u64 thr_w = 0, thr_k = 0;
     auto recompute = [&](auto body) { // body(share, weight bits, key, valid) for every candidate
-        if (wv < BW) {
-            for (u32 tile = 0; tile < ntiles; ++tile) {
-                const Share sh = load_share(g.bkt, b.bd_in, tile, wv);
-                share_groups<AT, M>(s.w[wv], s.ucol, gl, sh, b.keys, (const AT *)b.amps,
-                                    [&](const auto &ox, const auto &oy, u64 rest, bool active) {
+        for (u32 sl = (u32)wv; wv < BW && sl < nsl; sl += BW) {
+            const Share sh = load_share(g.bkt, b.bd_in, sl >> 2, (int)(sl & 3u));
+            share_groups<AT, M>(s.w[wv], s.ucol, gl, sh, b.keys, (const AT *)b.amps,
+                                [&](const auto &ox, const auto &oy, u64 rest, bool active) {
 #pragma unroll
-                    for (int i = 0; i < (1 << M); ++i) {
-                        AT o;
-                        o.x = ox[i];
-                        o.y = oy[i];
-                        body((tile << 2) + (u32)wv, weight_bits(o), rest | pattern_bits<M>(gl, i),
-                             active && nonzero(o));
-                    }
-                });
+                for (int i = 0; i < (1 << M); ++i) {
+                    AT o;
+                    o.x = ox[i];
+                    o.y = oy[i];
+                    body(sl, weight_bits(o), rest | pattern_bits<M>(gl, i), active && nonzero(o));
+                }
+            });
+        }
+    };
+    // body(share, w, index, in range) for every window entry, 16 lanes a share
+    auto entries = [&](auto body) {
+        for (u32 sl = g16; sl < nsl; sl += NT / 16) {
+            const u32 ns = b.t_side[sl];
+            const u64 base = (u64)sl << shift;
+            for (u32 i0 = l16; i0 < ns; i0 += 16 * UN) {
+                u64 w[UN];
+#pragma unroll
+                for (int r = 0; r < UN; ++r) {
+                    const u32 i = i0 + 16u * (u32)r;
+                    w[r] = i < ns ? b.side_w[base + i] : ~0ull; // no weight has all bits set
+                }
+#pragma unroll
+                for (int r = 0; r < UN; ++r)
+                    if (w[r] != ~0ull) body(sl, w[r], base + i0 + 16u * (u32)r);
             }
         }
     };
     if (!all) {
         if (t == 0) {
-            s_sub.cnt_before = s_l1.cnt;
-            s_sub.mb = 0;
-            s_sub.vpre = 0;
-            s_sub.vshift = 116;
-            s_sub.count = s_l1.count;
+            m.sub.cnt_before = m.l1.cnt;
+            m.sub.mb = 0;
+            m.sub.vpre = 0;
+            m.sub.vshift = 116;
+            m.sub.count = m.l1.count;
         }
         __syncthreads();
-        auto under = [&](u64 w, u64 k, int vshift, u128 vpre, bool &in) { // V, and whether it is under the prefix
-            const u128 v = rank_key(w, k);
-            in = (v >> vshift) == vpre;
-            return v;
-        };
         auto each = [&](int vshift, u128 vpre, bool keyed, auto f) {
             if (!slabs) {
                 recompute([&](u32, u64 w, u64 k, bool valid) {
-                    bool in;
-                    const u128 v = under(w, k, vshift, vpre, in);
-                    if (valid && (int)(w >> 52) == e && in) f(v);
+                    const u128 v = rank_key(w, k);
+                    if (valid && (int)(w >> 52) == e && (v >> vshift) == vpre) f(v);
                 });
                 return;
             }
-            constexpr int UN = 4;
             const bool key_decides = vshift < 64;
-            for (u32 sl = g16; sl < nsl; sl += SEL_NT / 16) { // 16 lanes a share
-                const u32 ns = b.t_side[sl];
-                const u64 base = (u64)sl << shift;
-                for (u32 i0 = l16; i0 < ns; i0 += 16 * UN) {
-                    u64 w[UN];
-#pragma unroll
-                    for (int r = 0; r < UN; ++r) {
-                        const u32 i = i0 + 16u * (u32)r;
-                        w[r] = i < ns ? b.side_w[base + i] : ~0ull; // no weight has all bits set
-                    }
-#pragma unroll
-                    for (int r = 0; r < UN; ++r) {
-                        if ((int)(w[r] >> 52) != e || w[r] == ~0ull) continue;
-                        bool in;
-                        u128 v = under(w[r], 0, key_decides ? 64 : vshift, key_decides ? vpre >> (64 - vshift) : vpre,
-                                       in);
-                        if (!in) continue;
-                        if (keyed || key_decides) {
-                            v = under(w[r], b.side_key[base + i0 + 16u * (u32)r], vshift, vpre, in);
-                            if (!in) continue;
-                        }
-                        f(v);
-                    }
+            const u64 hi = (u64)(key_decides ? vpre >> (64 - vshift) : vpre); // the prefix's part in the weight
+            const int hsh = key_decides ? 0 : vshift - 64;
+            entries([&](u32, u64 w, u64 i) {
+                const u64 vh = ((1ull << 52) - 1) - (w & ((1ull << 52) - 1));
+                if ((int)(w >> 52) != e || (vh >> hsh) != hi) return;
+                u128 v = (u128)vh << 64;
+                if (keyed || key_decides) {
+                    v |= (u128)b.side_key[i];
+                    if ((v >> vshift) != vpre) return;
                 }
-            }
+                f(v);
+            });
         };
-        const bool ok = resolve_cut<SEL_NT>(ctl, each, e, K, make128(s_l1.R_lo, s_l1.R_hi), s_sub, u.raw, s_cut,
-                                            s_l1.S, s_l1.total, s_l1.W, l10);
+        const bool ok = resolve_cut<NT>(ctl, each, e, K, make128(m.l1.R_lo, m.l1.R_hi), m.sub, m.u.raw, m.cut, m.l1.S,
+                                        m.l1.total, m.l1.W, l10);
         if (!ok) { // uniform
             if (t == 0) atomicOr(&ctl->flags, STS_F_UNRESOLVED);
             return;
         }
         __syncthreads();
-        thr_w = s_cut.thr_w;
-        thr_k = s_cut.thr_k;
+        thr_w = m.cut.thr_w;
+        thr_k = m.cut.thr_k;
     }
     // survivors per share
-    if (all || slabs) {
-        for (u32 sl = g16; sl < nsl; sl += SEL_NT / 16) {
-            u32 c = 0;
-            if (all) {
-                c = b.w_all[sl];
-            } else {
-                const u32 ns = b.t_side[sl];
-                const u64 base = (u64)sl << shift;
-                if (l16 == 0) c = b.t_above[sl];
-                for (u32 i = l16; i < ns; i += 16) {
-                    const u64 w = b.side_w[base + i];
-                    c += w > thr_w || (w == thr_w && b.side_key[base + i] <= thr_k) ? 1u : 0u;
-                }
-#pragma unroll
-                for (int d = 8; d > 0; d >>= 1) c += __shfl_xor(c, d, 64);
-            }
-            if (l16 == 0) s_kept[sl] = c;
-        }
+    if (all) {
+        for (u32 sl = t; sl < nsl; sl += NT) m.kept[sl] = b.w_all[sl];
+    } else if (slabs) {
+        for (u32 sl = t; sl < nsl; sl += NT) atomicAdd(&m.kept[sl], b.t_above[sl]);
+        entries([&](u32 sl, u64 w, u64 i) {
+            if (w > thr_w || (w == thr_w && b.side_key[i] <= thr_k)) atomicAdd(&m.kept[sl], 1u);
+        });
     } else {
-        for (u32 sl = t; sl < nsl; sl += SEL_NT) s_kept[sl] = 0;
-        __syncthreads();
         recompute([&](u32 sl, u64 w, u64 k, bool valid) {
-            const u64 m = wballot(valid && survives<AT>(w, k, false, thr_w, thr_k));
-            if (lane == 0) s_kept[sl] += (u32)__popcll(m); // the share is this wave's
+            const u64 mk = wballot(valid && survives<AT>(w, k, false, thr_w, thr_k));
+            if (lane == 0) m.kept[sl] += (u32)__popcll(mk); // the share is this wave's
         });
     }
     __syncthreads();
     // offsets: one tile per thread
     u64 carry = 0;
-    for (u32 t0 = 0; t0 < ntiles; t0 += SEL_NT) {
+    for (u32 t0 = 0; t0 < ntiles; t0 += NT) {
         const u32 tile = t0 + (u32)t;
         u32 k[4] = {0, 0, 0, 0};
         if (tile < ntiles) {
 #pragma unroll
             for (int w = 0; w < 4; ++w) {
-                k[w] = s_kept[(tile << 2) + w];
+                k[w] = m.kept[(tile << 2) + w];
                 b.w_kept[(tile << 2) + w] = k[w];
             }
         }
         const u64 sum = (u64)k[0] + k[1] + k[2] + k[3];
         u64 total;
-        const u64 at = block_excl_scan<u64, SEL_NT>(sum, s_scan, &total) + carry;
+        const u64 at = block_excl_scan<u64, NT>(sum, m.scan, &total) + carry;
         if (tile < ntiles) b.t_off[tile] = at;
         if (tile < ntiles && tile % STS_BKT_CHUNK == 0) b.t_base[tile / STS_BKT_CHUNK] = 0;
         carry += total;
@@ -1422,6 +1384,67 @@ __global__ void __launch_bounds__(SEL_NT) k_bkt_select(const GateArg *__restrict
         ctl->w_over = 0;
         ctl->pred_hit = slabs;
     }
+}
+
+template <typename AT, int M>
+__global__ void __launch_bounds__(STS_WG) k_bkt_small(const GateArg *__restrict__ gp, PassBufs b)
+{
+    const GateArg &g = *gp;
+    const GateLoc<M> gl = gate_loc<M>(g);
+    __shared__ BktSmem<AT, BW> s;
+    __shared__ u64 s_hi[TT_SLOTS], s_lo[TT_SLOTS];
+    DevCtl *ctl = b.ctl;
+    smem_begin<AT, M, BW>(s, g);
+    for (int i = threadIdx.x; i < TT_SLOTS; i += STS_WG) {
+        s_hi[i] = 0;
+        s_lo[i] = 0;
+    }
+    const u64 *keys = b.keys;
+    const AT *amps = (const AT *)b.amps;
+    const u32 nsl = bkt_tiles(g.bkt) << 2;
+    const int e_prev = ctl->e_pred;
+    const int e_w = small_window(ctl);
+    // the window, in the weight's high word; without a previous cut, everything
+    const u32 wL = uni(e_prev >= 0 ? (u32)e_w << 20 : 0u), wH = uni(e_prev >= 0 ? (u32)(e_w + 2) << 20 : ~0u);
+    const int shift = b.slab_shift;
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int hot_lo = (e_prev >= 0 ? e_prev : TT_EBASE + 116) - (TT_HOT - 4);
+    __syncthreads();
+    // (a wave's shares go to the LDS bins while those stay exact: the grid
+    // gives it a few)
+    for (u32 sl = blockIdx.x * BW + (u32)wv; sl < nsl; sl += gridDim.x * BW) {
+        const Share sh = load_share(g.bkt, b.bd_in, sl >> 2, (int)(sl & 3u));
+        const u64 slab = (u64)sl << shift;
+        const bool direct = sh.n > BW_BINNED;
+        u64 *const sk = b.side_key + slab;
+        u64 *const sw = b.side_w + slab;
+        AT *const sa = (AT *)b.side_amp + slab;
+        SlabOut so = {0, 0, 0, true};
+        share_groups<AT, M>(s.w[wv], s.ucol, gl, sh, keys, amps,
+                            [&](const auto &ox, const auto &oy, u64 rest, bool active) {
+#pragma unroll
+            for (int i = 0; i < (1 << M); ++i) {
+                AT o;
+                o.x = ox[i];
+                o.y = oy[i];
+                const bool cand = active && nonzero(o);
+                const u64 wb = weight_bits(o);
+                const u32 hw = (u32)(wb >> 32);
+                if (cand) bin_weight(b, s_hi, s_lo, hot_lo, wb, direct);
+                so.c_all += (u32)__popcll(wballot(cand));
+                slab_put<AT>(so, sk, sw, sa, 1u << shift, cand && hw >= wL && hw < wH, cand && hw >= wH,
+                             rest | pattern_bits<M>(gl, i), wb, o);
+            }
+        });
+        if (sts_lane() == 0) {
+            b.w_all[sl] = so.c_all;
+            b.t_above[sl] = so.c_ab;
+            b.t_side[sl] = so.c_in;
+            if (!so.fits) atomicOr(&ctl->w_over, 1u);
+        }
+    }
+    __syncthreads();
+    flush_bins(b, s_hi, s_lo, hot_lo);
 }
 
 // ---------------------------------------------------------------------------
@@ -1478,6 +1501,9 @@ template <typename AT, int M> hipError_t launch_m(int kind, const PassBufs &b, i
         break;
     case STS_BKT_COPY:
         hipLaunchKernelGGL((k_bkt_copy<AT>), dim3(tiles), dim3(STS_WG), 0, s, b.gate, b);
+        break;
+    case STS_BKT_SMALL:
+        hipLaunchKernelGGL((k_bkt_small<AT, M>), dim3(std::min(tiles, 256)), dim3(STS_WG), 0, s, b.gate, b);
         break;
     case STS_BKT_SELECT:
         hipLaunchKernelGGL((k_bkt_select<AT, M>), dim3(1), dim3(SEL_NT), 0, s, b.gate, b);

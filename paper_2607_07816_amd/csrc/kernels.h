@@ -174,6 +174,11 @@ hipError_t launch_ctl_begin(DevCtl *ctl, u64 K, double p, u64 n_in, hipStream_t 
 hipError_t launch_terms_out(const u64 *keys, const void *amps, int amp_bytes, const DevCtl *ctl, int slot,
                             u64 *keys_out, void *amps_out, u64 out_cap, u64 *n_out, double *stats, hipStream_t s);
 
+// steps of at most STS_TINY_MAX terms (tiny_impl.h): one launch, the gate passed by value
+#define STS_TINY_MAX 2048
+hipError_t launch_tiny(int prec, const GateArg &g, const PassBufs &b, hipStream_t s);
+const void *tiny_kernel(int prec, int m); // the kernel launch_tiny launches (to find its node in a captured graph)
+
 // bucketed steps (bucket_impl.h): gates of 1 and 2 qubits on a state in bucket order
 #define STS_BKT_HIST 0
 #define STS_BKT_SAMPLE 1
@@ -182,8 +187,9 @@ hipError_t launch_terms_out(const u64 *keys, const void *amps, int amp_bytes, co
 #define STS_BKT_EMIT 4
 #define STS_BKT_WEIGH 5
 #define STS_BKT_COPY 6
-#define STS_BKT_SELECT 7
-#define STS_SEL_SHARES 2048 // most shares of a step whose selection is one workgroup
+#define STS_BKT_SMALL 7
+#define STS_BKT_SELECT 8
+#define STS_SEL_SHARES 1024 // most shares of a step whose selection is one workgroup
 #define STS_BKT_CHUNK 32 // tiles whose offsets are relative to one base
 hipError_t launch_bucket_pass(int kind, int prec, int m, const PassBufs &b, int tiles, hipStream_t s);
 int bucket_hist_groups(int prec, int m, int tiles, bool weigh); // workgroups of the histogram or weighing pass

@@ -30,7 +30,7 @@ __global__ void __launch_bounds__(256) k_pick1(PassBufs b, int groups, int peak_
 {
     __shared__ Level1Smem<256> sm;
     if (predicted == 3 && !b.ctl->need_full) return; // uniform
-    pick_level1<256>(b, groups, peak_only, predicted, sm);
+    pick_level1<256>(b, groups, peak_only, predicted, sm, DeviceBins<256>{b.h1});
 }
 
 // ---------------------------------------------------------------------------

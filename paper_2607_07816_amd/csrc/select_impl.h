@@ -278,7 +278,7 @@ struct Level1Cut {
 };
 
 template <int NT> struct Level1Smem {
-    u32 e[STS_NBIN];   // the non-empty bins in rank order: exponent field,
+    unsigned short e[STS_NBIN]; // the non-empty bins in rank order: exponent field,
     u64 c[STS_NBIN];   // count,
     __attribute__((aligned(16))) u64 lo[STS_NBIN]; // mantissa sum (low, high words)
     u64 hi[STS_NBIN];
@@ -293,16 +293,33 @@ template <int NT> struct Level1Smem {
     Level1Cut cut;
 };
 
+// the exponent bins in device memory
+template <int NT> struct DeviceBins {
+    u64 *h1;
+    __device__ __forceinline__ void load(int e, u64 &c, u64 &hi, u64 &lo) const
+    {
+        c = h1[e];
+        hi = h1[STS_NBIN + e];
+        lo = h1[2 * STS_NBIN + e];
+    }
+    __device__ __forceinline__ void clear(int t) const
+    {
+        for (int i = t; i < 3 * STS_NBIN; i += NT) h1[i] = 0;
+    }
+};
+
 // predicted: 0 no window, 1 a window of the tiled passes, 3 a bucketed step
 // whose histogram pass ran (no window; the side buffer, if the extraction
 // pass fills it, is packed densely)
-template <int NT>
-__device__ void pick_level1(const PassBufs &b, int groups, int peak_only, int predicted, Level1Smem<NT> &sm)
+// bins: load(e, count, mantissa sum >> 26, & (2^26 - 1)) of exponent field e,
+// and clear(t) by every thread when all are read
+template <int NT, typename BINS>
+__device__ void pick_level1(const PassBufs &b, int groups, int peak_only, int predicted, Level1Smem<NT> &sm,
+                            const BINS &bins)
 {
     constexpr int NB = STS_NBIN / NT, NW = NT / 64;
     const int t = threadIdx.x;
     DevCtl *ctl = b.ctl;
-    u64 *h1 = b.h1;
     // the exponent of the window the histogram pass copied (predicted steps)
     const int w_mode = ctl->w_mode;
     const bool win = predicted == 1;
@@ -315,9 +332,7 @@ __device__ void pick_level1(const PassBufs &b, int groups, int peak_only, int pr
 #pragma unroll
     for (int k = 0; k < NB; ++k) {
         const int e = 2047 - NB * t - k;
-        c[k] = h1[e];
-        hi[k] = h1[STS_NBIN + e];
-        lo[k] = h1[2 * STS_NBIN + e];
+        bins.load(e, c[k], hi[k], lo[k]);
     }
     // the per-workgroup peaks too (reduced below)
     constexpr int BPT = (STS_MAX_GROUPS + NT - 1) / NT;
@@ -365,7 +380,7 @@ __device__ void pick_level1(const PassBufs &b, int groups, int peak_only, int pr
 #pragma unroll
     for (int k = 0; k < NB; ++k) {
         if (!c[k]) continue;
-        sm.e[at] = (u32)(2047 - NB * t - k);
+        sm.e[at] = (unsigned short)(2047 - NB * t - k);
         sm.c[at] = c[k];
         const u128 ms = ((u128)hi[k] << 26) + (u128)lo[k];
         sm.lo[at] = (u64)ms;
@@ -593,7 +608,7 @@ __device__ void pick_level1(const PassBufs &b, int groups, int peak_only, int pr
         }
     }
     __syncthreads();
-    for (int i = t; i < 3 * STS_NBIN; i += NT) h1[i] = 0;
+    bins.clear(t);
     if (sm.fine) { // uniform
         // level 2 from the window's bins (the side pass then has nothing to
         // do); the bin lists above are done with, so their LDS serves the pick
@@ -630,6 +645,8 @@ struct CutSmem {
     u64 c[1024 / 64];
     u32 hit, n;
     u64 thr_w, thr_k; // the cut's term
+    double scale;
+    int dropped;
 };
 
 template <int NT, typename E>
@@ -696,14 +713,16 @@ __device__ bool resolve_cut(DevCtl *ctl, E &&each, int e, u64 K, u128 R, Sub &s_
         const double Sd = big_to_double(S);
         const u64 L = s_sub.cnt_before + rank + 1;
         const int dropped = L < ncand;
-        ctl->L = L;
-        ctl->thr_wbits = ((u64)e << 52) | frac;
-        ctl->thr_key = (u64)v;
         sm.thr_w = ((u64)e << 52) | frac;
         sm.thr_k = (u64)v;
+        sm.dropped = dropped;
+        sm.scale = dropped ? 1.0 / sqrt(Sd) : 1.0;
+        ctl->L = L;
+        ctl->thr_wbits = sm.thr_w;
+        ctl->thr_key = sm.thr_k;
         ctl->dropped = dropped;
         ctl->S = Sd;
-        ctl->scale = dropped ? 1.0 / sqrt(Sd) : 1.0;
+        ctl->scale = sm.scale;
         const double frac_kept = Sd / W;
         ctl->frac = frac_kept;
         if (dropped) ctl->log10_cum = l10 + log10(frac_kept);
