@@ -1228,7 +1228,11 @@ constexpr int SEL_NT = 1024;
 struct SelectSmem {
     union {
         sts_select::Level1Smem<SEL_NT> l1;
-        unsigned char raw[3 * STS_NBIN * sizeof(u64)];
+        __attribute__((aligned(16))) unsigned char raw[STS_NBIN * 12];
+        struct {
+            __attribute__((aligned(16))) u128 v[STS_FINAL_SORT];
+            u32 share[STS_FINAL_SORT];
+        } last; // the terms the cut is among, and their shares
     } u;
     sts_select::Level1Cut l1;
     sts_select::CutSmem cut;
@@ -1255,7 +1259,6 @@ __global__ void __launch_bounds__(SEL_NT) k_bkt_select(const GateArg *__restrict
     // control words, read before the pick writes any
     const int e_prev = ctl->e_pred, e_w = small_window(ctl);
     const u32 over = ctl->w_over;
-    u64 thr_w = 0, thr_k = 0;
     const u64 K = ctl->K;
     const double l10 = ctl->log10_cum;
     pick_level1<NT>(b, 0, 0, 0, m.u.l1, DeviceBins<NT>{b.h1});
@@ -1334,29 +1337,80 @@ __global__ void __launch_bounds__(SEL_NT) k_bkt_select(const GateArg *__restrict
                 f(v);
             });
         };
-        const bool ok = resolve_cut<NT>(ctl, each, e, K, make128(m.l1.R_lo, m.l1.R_hi), m.sub, m.u.raw, m.cut, m.l1.S,
-                                        m.l1.total, m.l1.W, l10);
+        const u128 R = make128(m.l1.R_lo, m.l1.R_hi);
+        bool ok = narrow_cut<NT, true>(each, e, K, R, m.sub, m.u.raw, m.cut, STS_FINAL_SORT);
+        const int vshift = m.sub.vshift;
+        const u128 vpre = m.sub.vpre;
+        const u32 count = (u32)m.sub.count;
+        if (t == 0) {
+            m.cut.n = 0;
+            m.cut.hit = 0xffffffffu;
+        }
+        __syncthreads();
+        if (ok && count <= STS_FINAL_SORT) {
+            // list the subset and, in the same pass, count the survivors
+            // ranked before it, share by share
+            auto sort_out = [&](u32 sl, u64 w, u64 k, u32 &before) {
+                const int x = (int)(w >> 52);
+                const u128 p = rank_key(w, k) >> vshift;
+                if (x > e || (x == e && p < vpre)) {
+                    ++before;
+                } else if (x == e && p == vpre) {
+                    const u32 slot = atomicAdd(&m.cut.n, 1u);
+                    if (slot < STS_FINAL_SORT) {
+                        m.u.last.v[slot] = rank_key(w, k);
+                        m.u.last.share[slot] = sl;
+                    }
+                }
+            };
+            if (slabs) {
+                for (u32 sl = g16; sl < nsl; sl += NT / 16) { // 16 lanes a share
+                    const u32 ns = b.t_side[sl];
+                    const u64 base = (u64)sl << shift;
+                    u32 before = l16 == 0 ? b.t_above[sl] : 0u;
+                    for (u32 i0 = l16; i0 < ns; i0 += 16 * UN) {
+                        u64 w[UN];
+#pragma unroll
+                        for (int r = 0; r < UN; ++r) {
+                            const u32 i = i0 + 16u * (u32)r;
+                            w[r] = i < ns ? b.side_w[base + i] : 0ull; // ranked last
+                        }
+#pragma unroll
+                        for (int r = 0; r < UN; ++r) {
+                            // the key only of the terms it could matter for
+                            const bool near = (int)(w[r] >> 52) == e &&
+                                              (vshift < 64 || (rank_key(w[r], 0) >> vshift) == vpre);
+                            const u64 k = near && i0 + 16u * (u32)r < ns ? b.side_key[base + i0 + 16u * (u32)r] : 0ull;
+                            if (i0 + 16u * (u32)r < ns) sort_out(sl, w[r], k, before);
+                        }
+                    }
+#pragma unroll
+                    for (int d = 8; d > 0; d >>= 1) before += __shfl_xor(before, d, 64);
+                    if (l16 == 0) m.kept[sl] = before;
+                }
+            } else {
+                recompute([&](u32 sl, u64 w, u64 k, bool valid) {
+                    u32 before = 0;
+                    if (valid) sort_out(sl, w, k, before);
+                    const u64 mk = wballot(before != 0);
+                    if (lane == 0) m.kept[sl] += (u32)__popcll(mk); // the share is this wave's
+                });
+            }
+            __syncthreads();
+            ok = m.cut.n == count;
+            const u32 rank = rank_cut<NT>(m.u.last.v, count, e, K, R, m.sub, m.cut);
+            ok = ok && m.cut.hit != 0xffffffffu;
+            if (ok && rank <= m.cut.hit) atomicAdd(&m.kept[m.u.last.share[t]], 1u);
+        } else {
+            ok = false; // no subset is larger once every bit of V is fixed
+        }
         if (!ok) { // uniform
             if (t == 0) atomicOr(&ctl->flags, STS_F_UNRESOLVED);
             return;
         }
-        __syncthreads();
-        thr_w = m.cut.thr_w;
-        thr_k = m.cut.thr_k;
-    }
-    // survivors per share
-    if (all) {
-        for (u32 sl = t; sl < nsl; sl += NT) m.kept[sl] = b.w_all[sl];
-    } else if (slabs) {
-        for (u32 sl = t; sl < nsl; sl += NT) atomicAdd(&m.kept[sl], b.t_above[sl]);
-        entries([&](u32 sl, u64 w, u64 i) {
-            if (w > thr_w || (w == thr_w && b.side_key[i] <= thr_k)) atomicAdd(&m.kept[sl], 1u);
-        });
+        if (wv == NT / 64 - 1) finish_cut(ctl, m.cut, e, m.l1.S, m.l1.total, m.l1.W, l10);
     } else {
-        recompute([&](u32 sl, u64 w, u64 k, bool valid) {
-            const u64 mk = wballot(valid && survives<AT>(w, k, false, thr_w, thr_k));
-            if (lane == 0) m.kept[sl] += (u32)__popcll(mk); // the share is this wave's
-        });
+        for (u32 sl = t; sl < nsl; sl += NT) m.kept[sl] = b.w_all[sl];
     }
     __syncthreads();
     // offsets: one tile per thread

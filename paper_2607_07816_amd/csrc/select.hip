@@ -257,7 +257,7 @@ __global__ void __launch_bounds__(256) k_pick_window(PassBufs b, int groups)
     if (nbins)
         for (int i = t; i < 3 * STS_NBIN; i += 256) h1[i] = 0;
     if (s_fine) { // uniform: the bin lists above are done with, so their LDS serves the pick
-        const bool ok = pick_digit<256>(b.h2w, b.h2w + STS_NBIN, b.h2w + 2 * STS_NBIN, true, ctl->K,
+        const bool ok = pick_digit<256>(AgentBins{b.h2w}, ctl->K,
                                         make128(s_R_lo, s_R_hi), 11, &s_sub, reinterpret_cast<u128 *>(s_lo), s_hi,
                                         &s_hit2);
         if (ok && t <= STS_SUB_REGIONS) st_agent(&b.sub_cnt[t * 32], 0u);
@@ -457,7 +457,7 @@ __global__ void __launch_bounds__(256) k_side_hist(PassBufs b, u64 *h2)
         }
         __syncthreads();
         const u128 R = make128(ctl->R_lo, ctl->R_hi);
-        if (pick_digit<256>(hs, hs + STS_NBIN, hs + 2 * STS_NBIN, true, ctl->K, R, 11, &s_sub, s_m, s_c, &s_hit)) {
+        if (pick_digit<256>(AgentBins{hs}, ctl->K, R, 11, &s_sub, s_m, s_c, &s_hit)) {
             if (threadIdx.x <= STS_SUB_REGIONS) st_agent(&b.sub_cnt[threadIdx.x * 32], 0u);
             if (threadIdx.x == 0) {
                 sub_store(s_sub, ctl);
@@ -659,12 +659,16 @@ __global__ void __launch_bounds__(FT) k_final(PassBufs b)
     // the first level's pick from those bins, then the levels and the cut
     bool ok = true;
     if (from_h3 && s_sub.count > STS_FINAL_SORT && s_sub.vshift > 0)
-        ok = pick_digit<FT>(b.h3, b.h3 + STS_NBIN, b.h3 + 2 * STS_NBIN, true, K, R,
+        ok = pick_digit<FT>(AgentBins{b.h3}, K, R,
                             s_sub.vshift < 11 ? s_sub.vshift : 11, &s_sub, s_cut.m, s_cut.c, &s_cut.hit);
     if (from_h3)
         for (int i = t; i < 3 * STS_NBIN; i += FT) st_agent(&b.h3[i], 0ull);
-    ok = ok && resolve_cut<FT>(ctl, each_in_subset, e, K, R, s_sub, s_raw, s_cut, s_Sx, s_ncand, s_W, s_l10);
-    if (!ok && t == 0) atomicOr(&ctl->flags, STS_F_UNRESOLVED);
+    ok = ok && resolve_cut<FT, false>(each_in_subset, e, K, R, s_sub, s_raw, s_cut);
+    if (!ok) {
+        if (t == 0) atomicOr(&ctl->flags, STS_F_UNRESOLVED);
+        return;
+    }
+    if (t < 64) finish_cut(ctl, s_cut, e, s_Sx, s_ncand, s_W, s_l10);
 }
 
 // ---------------------------------------------------------------------------

@@ -178,9 +178,28 @@ __device__ __forceinline__ void block_scan_cm(u64 &c, u128 &m, u64 *sc, u128 *sm
     }
 }
 
-template <int NT>
-__device__ bool pick_digit(const u64 *cntp, const u64 *hip_, const u64 *lop, bool agent, u64 K, u128 R, int dw,
-                           Sub *sub, u128 *s_m, u64 *s_c, u32 *s_hit)
+// bins in three arrays (count, mantissa sum >> 26, & (2^26 - 1)), in device
+// memory that other workgroups wrote (agent loads) or in LDS
+struct AgentBins {
+    const u64 *h;
+    __device__ __forceinline__ void operator()(u32 d, u64 &c, u128 &m) const
+    {
+        c = ld_agent(&h[d]);
+        m = ((u128)ld_agent(&h[STS_NBIN + d]) << 26) + (u128)ld_agent(&h[2 * STS_NBIN + d]);
+    }
+};
+struct WideBins {
+    const u64 *h;
+    __device__ __forceinline__ void operator()(u32 d, u64 &c, u128 &m) const
+    {
+        c = h[d];
+        m = ((u128)h[STS_NBIN + d] << 26) + (u128)h[2 * STS_NBIN + d];
+    }
+};
+
+// bins(d, count, mass): the 2048 bins
+template <int NT, typename BINS>
+__device__ bool pick_digit(const BINS &bins, u64 K, u128 R, int dw, Sub *sub, u128 *s_m, u64 *s_c, u32 *s_hit)
 {
     constexpr int PER = STS_NBIN / NT;
     const int t = threadIdx.x;
@@ -190,14 +209,7 @@ __device__ bool pick_digit(const u64 *cntp, const u64 *hip_, const u64 *lop, boo
     u128 mm = 0;
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
-        const int d = PER * t + k;
-        if (agent) {
-            c[k] = ld_agent(&cntp[d]);
-            ms[k] = ((u128)ld_agent(&hip_[d]) << 26) + (u128)ld_agent(&lop[d]);
-        } else {
-            c[k] = cntp[d];
-            ms[k] = ((u128)hip_[d] << 26) + (u128)lop[d];
-        }
+        bins((u32)(PER * t + k), c[k], ms[k]);
         cc += c[k];
         mm += ms[k];
     }
@@ -288,8 +300,8 @@ template <int NT> struct Level1Smem {
     Sub sub;   // level 2 of a sampled window that holds the cut
     u32 fine, hit2;
     u64 R_lo, R_hi;
-    u64 chunk[NT / 64][64]; // exact mass of each part of the bin list (a limb per lane)
-    u64 chunk_c[NT / 64];   // and its count
+    u64 chunk[4][64]; // exact mass of each quarter of the bin list (a limb per lane)
+    u64 chunk_c[4];   // and its count
     Level1Cut cut;
 };
 
@@ -318,6 +330,7 @@ __device__ void pick_level1(const PassBufs &b, int groups, int peak_only, int pr
                             const BINS &bins)
 {
     constexpr int NB = STS_NBIN / NT, NW = NT / 64;
+    constexpr int NC = 4; // chunks of the bin list
     const int t = threadIdx.x;
     DevCtl *ctl = b.ctl;
     // the exponent of the window the histogram pass copied (predicted steps)
@@ -415,10 +428,11 @@ __device__ void pick_level1(const PassBufs &b, int groups, int peak_only, int pr
     }
     __syncthreads();
 
-    // exact sums of the listed bins in NW chunks, one wave each (a chain of
-    // exact additions per bin, that much shorter than over all bins)
-    const u32 chunk = (nbins + NW - 1) / NW;
-    {
+    // exact sums of the listed bins in four chunks, one wave each (a chain of
+    // exact additions per bin, a quarter as long as over all bins; the wave
+    // that goes on walks the chunks, so that more of them would not pay)
+    const u32 chunk = (nbins + NC - 1) / NC;
+    if (t < 64 * NC) {
         const int q = t >> 6;
         const u32 j0 = (u32)q * chunk, j1 = j0 + chunk < nbins ? j0 + chunk : nbins;
         u64 C = 0, nc = 0;
@@ -435,7 +449,7 @@ __device__ void pick_level1(const PassBufs &b, int groups, int peak_only, int pr
         const int lane = t;
         u64 W = 0, total_c = 0;
 #pragma unroll
-        for (int q = 0; q < NW; ++q) {
+        for (int q = 0; q < NC; ++q) {
             W = wl_add(W, sm.chunk[q][lane]);
             total_c += sm.chunk_c[q];
         }
@@ -480,7 +494,7 @@ __device__ void pick_level1(const PassBufs &b, int groups, int peak_only, int pr
             // ranking), then that chunk's bins
             u64 S = 0, cnt = 0;
             u32 hit = 0xffffffffu;
-            for (int q = 0; q < NW; ++q) {
+            for (int q = 0; q < NC; ++q) {
                 const u64 inc_q = wl_add(S, sm.chunk[q][lane]);
                 const bool met_q = (K > 0 && cnt + sm.chunk_c[q] >= K) || (p_on && wl_cmp(inc_q, T) >= 0);
                 if (met_q) {
@@ -615,7 +629,7 @@ __device__ void pick_level1(const PassBufs &b, int groups, int peak_only, int pr
         const u128 R = make128(sm.R_lo, sm.R_hi);
         u128 *s_m = reinterpret_cast<u128 *>(sm.lo);
         u64 *s_c2 = sm.hi;
-        const bool ok = pick_digit<NT>(b.h2w, b.h2w + STS_NBIN, b.h2w + 2 * STS_NBIN, true, ctl->K, R, 11, &sm.sub,
+        const bool ok = pick_digit<NT>(AgentBins{b.h2w}, ctl->K, R, 11, &sm.sub,
                                         s_m, s_c2, &sm.hit2);
         if (ok && t <= STS_SUB_REGIONS) st_agent(&b.sub_cnt[t * 32], 0u);
         if (t == 0) {
@@ -632,50 +646,156 @@ __device__ void pick_level1(const PassBufs &b, int groups, int peak_only, int pr
 }
 
 // ---------------------------------------------------------------------------
-// last levels: narrow s_sub by 11-bit digits of the rank key V until at most
-// STS_FINAL_SORT terms are left, then the exact cut. each(vshift,
-// vpre, keyed, f) calls f(V) for every term of the subset whose V lies under
-// the prefix (all threads take part; V's key half may be 0 unless keyed). raw: STS_NBIN * 24 bytes of LDS. The subset's terms are
-// few by then (a handful as a rule), so every term counts and weighs the ones
-// before it by itself; their mantissas add up below 2^63. Returns false when
-// the cut could not be resolved (an internal inconsistency).
+// Last levels: narrow `sub` by 11-bit digits of the rank key V until at most
+// STS_FINAL_SORT terms are left, then find the exact cut among them.
+// each(vshift, vpre, keyed, f) calls f(V) for every term of the subset whose V
+// lies under the prefix (all threads take part; V's key half may be 0 unless
+// keyed). raw: STS_NBIN * 24 bytes of LDS, or * 12 when there are so few terms
+// (below 2^22) that 64 bits hold a bin's sum of the 41 mantissa bits that the
+// first level leaves open.
 // ---------------------------------------------------------------------------
 struct CutSmem {
     u128 m[1024 / 64];
     u64 c[1024 / 64];
     u32 hit, n;
-    u64 thr_w, thr_k; // the cut's term
+    u64 thr_w, thr_k;  // the cut's term
+    u64 mk_lo, mk_hi;  // mantissa sum ranked up to it inside its exponent
+    u64 L;
     double scale;
     int dropped;
 };
 
-template <int NT, typename E>
-__device__ bool resolve_cut(DevCtl *ctl, E &&each, int e, u64 K, u128 R, Sub &s_sub, unsigned char *raw, CutSmem &sm,
-                            const u64 *s_Sx, u64 ncand, double W, double l10)
+// mantissa bits shared by the terms of exponent e whose first digit is d
+__device__ __forceinline__ u64 digit_mant(u32 d, int e)
+{
+    return ((u64)(2047u - d) << 41) | (e ? 1ull << 52 : 0ull);
+}
+
+constexpr u64 LOW41 = (1ull << 41) - 1;
+
+// bins of one level: sums of the low 41 mantissa bits, and counts; the high
+// bits come from the bin (first level) or are common to the subset
+struct ThinBins {
+    const u64 *low;
+    const u32 *cnt;
+    int e;
+    bool first;
+    u64 high;
+    __device__ __forceinline__ void operator()(u32 d, u64 &c, u128 &m) const
+    {
+        c = cnt[d];
+        m = (u128)(first ? digit_mant(d, e) : high) * c + (u128)low[d];
+    }
+};
+
+template <int NT, bool THIN, typename E>
+__device__ bool narrow_cut(E &&each, int e, u64 K, u128 R, Sub &sub, unsigned char *raw, CutSmem &sm, u32 enough)
 {
     const int t = threadIdx.x;
-    u64 *h_cnt = reinterpret_cast<u64 *>(raw), *h_hi = h_cnt + STS_NBIN, *h_lo = h_hi + STS_NBIN;
-    u128 *sv = reinterpret_cast<u128 *>(raw);
-    static_assert(NT <= 1024 && STS_FINAL_SORT <= NT, "one term per thread");
-    while (s_sub.count > STS_FINAL_SORT && s_sub.vshift > 0) {
-        const int vshift = s_sub.vshift;
+    u64 *h = reinterpret_cast<u64 *>(raw);
+    u32 *hc = reinterpret_cast<u32 *>(h + STS_NBIN);
+    while (sub.count > enough && sub.vshift > 0) {
+        const int vshift = sub.vshift;
         const int dw = vshift < 11 ? vshift : 11;
-        const u128 vpre = s_sub.vpre;
-        for (int i = t; i < 3 * STS_NBIN; i += NT) h_cnt[i] = 0;
+        const u128 vpre = sub.vpre;
+        for (int i = t; i < (THIN ? STS_NBIN * 3 / 2 : 3 * STS_NBIN); i += NT) h[i] = 0;
         __syncthreads();
         each(vshift, vpre, vshift - dw < 64, [&](const u128 v) {
             const u32 d = (u32)((v >> (vshift - dw)) & (u128)((1u << dw) - 1));
             const u64 mant = mant_of_v(v, e);
-            atomicAdd((unsigned long long *)&h_cnt[d], 1ull);
-            atomicAdd((unsigned long long *)&h_hi[d], mant >> 26);
-            atomicAdd((unsigned long long *)&h_lo[d], mant & ((1ull << 26) - 1));
+            if (THIN) {
+                atomicAdd((unsigned long long *)&h[d], mant & LOW41);
+                atomicAdd(&hc[d], 1u);
+            } else {
+                atomicAdd((unsigned long long *)&h[d], 1ull);
+                atomicAdd((unsigned long long *)&h[STS_NBIN + d], mant >> 26);
+                atomicAdd((unsigned long long *)&h[2 * STS_NBIN + d], mant & ((1ull << 26) - 1));
+            }
         });
         __syncthreads();
-        if (!pick_digit<NT>(h_cnt, h_hi, h_lo, false, K, R, dw, &s_sub, sm.m, sm.c, &sm.hit)) return false;
+        bool ok;
+        if (THIN) {
+            const bool first = vshift == 116;
+            const u64 high = first ? 0ull : digit_mant((u32)(vpre >> (105 - vshift)), e);
+            ok = pick_digit<NT>(ThinBins{h, hc, e, first, high}, K, R, dw, &sub, sm.m, sm.c, &sm.hit);
+        } else {
+            ok = pick_digit<NT>(WideBins{h}, K, R, dw, &sub, sm.m, sm.c, &sm.hit);
+        }
+        if (!ok) return false;
     }
-    const int vshift = s_sub.vshift;
-    const u128 vpre = s_sub.vpre;
-    if (t == 0) {
+    return true;
+}
+
+// the cut among the m <= STS_FINAL_SORT terms listed in sv (a handful as a
+// rule): every term counts and weighs the ones before it by itself; their
+// mantissas add up below 2^63. Returns this thread's rank (m or more: no term)
+template <int NT> __device__ u32 rank_cut(const u128 *sv, u32 m, int e, u64 K, u128 R, const Sub &sub, CutSmem &sm)
+{
+    const u32 t = threadIdx.x;
+    static_assert(STS_FINAL_SORT <= NT, "one term per thread");
+    u128 v = 0;
+    u32 rank = ~0u;
+    u64 mass = 0; // of the terms up to this one
+    bool met = false;
+    if (t < m) {
+        v = sv[t];
+        rank = 0;
+        for (u32 i = 0; i < m; ++i) {
+            const u128 o = sv[i];
+            rank += o < v ? 1u : 0u;
+            mass += o <= v ? mant_of_v(o, e) : 0ull;
+        }
+        met = (K > 0 && sub.cnt_before + rank + 1 >= K) || sub.mb + (u128)mass >= R;
+        if (met) atomicMin(&sm.hit, rank);
+    }
+    __syncthreads();
+    if (met && rank == sm.hit) {
+        const u128 mk = sub.mb + (u128)mass;
+        sm.thr_w = ((u64)e << 52) | (((1ull << 52) - 1) - (u64)(v >> 64));
+        sm.thr_k = (u64)v;
+        sm.mk_lo = (u64)mk;
+        sm.mk_hi = (u64)(mk >> 64);
+        sm.L = sub.cnt_before + rank + 1;
+    }
+    __syncthreads();
+    return rank;
+}
+
+// one wave: the kept mass, the scale and the statistics (S_excl: the exact
+// mass ranked before exponent e's part, one limb per entry)
+__device__ __forceinline__ void finish_cut(DevCtl *ctl, CutSmem &sm, int e, const u64 *S_excl, u64 ncand, double W,
+                                           double l10)
+{
+    const int lane = sts_lane();
+    const u64 x = lane < STS_NL ? S_excl[lane] : 0ull;
+    const double Sd = wl_to_double(wl_add(x, wl_piece(sm.mk_lo, sm.mk_hi, unit_bit(e))));
+    if (lane == 0) {
+        const int dropped = sm.L < ncand;
+        const double scale = dropped ? 1.0 / sqrt(Sd) : 1.0;
+        sm.dropped = dropped;
+        sm.scale = scale;
+        ctl->L = sm.L;
+        ctl->thr_wbits = sm.thr_w;
+        ctl->thr_key = sm.thr_k;
+        ctl->dropped = dropped;
+        ctl->S = Sd;
+        ctl->scale = scale;
+        const double frac_kept = Sd / W;
+        ctl->frac = frac_kept;
+        if (dropped) ctl->log10_cum = l10 + log10(frac_kept);
+    }
+}
+
+// all of it, up to the cut's term in sm (false: the cut could not be resolved,
+// an internal inconsistency); finish_cut by one wave follows
+template <int NT, bool THIN, typename E>
+__device__ bool resolve_cut(E &&each, int e, u64 K, u128 R, Sub &sub, unsigned char *raw, CutSmem &sm)
+{
+    if (!narrow_cut<NT, THIN>(each, e, K, R, sub, raw, sm, STS_FINAL_SORT)) return false;
+    u128 *sv = reinterpret_cast<u128 *>(raw);
+    const int vshift = sub.vshift;
+    const u128 vpre = sub.vpre;
+    if (threadIdx.x == 0) {
         sm.n = 0;
         sm.hit = 0xffffffffu;
     }
@@ -687,47 +807,8 @@ __device__ bool resolve_cut(DevCtl *ctl, E &&each, int e, u64 K, u128 R, Sub &s_
     __syncthreads();
     const u32 m = sm.n;
     if (m == 0 || m > STS_FINAL_SORT) return false;
-    u128 v = 0;
-    u32 rank = 0;
-    u64 mass = 0; // of the terms up to this one
-    bool met = false;
-    if ((u32)t < m) {
-        v = sv[t];
-        for (u32 i = 0; i < m; ++i) {
-            const u128 o = sv[i];
-            rank += o < v ? 1u : 0u;
-            mass += o <= v ? mant_of_v(o, e) : 0ull;
-        }
-        met = (K > 0 && s_sub.cnt_before + rank + 1 >= K) || s_sub.mb + (u128)mass >= R;
-        if (met) atomicMin(&sm.hit, rank);
-    }
-    __syncthreads();
-    if (sm.hit == 0xffffffffu) return false;
-    if (met && rank == sm.hit) {
-        const u64 frac = ((1ull << 52) - 1) - (u64)(v >> 64);
-        const u128 mk = s_sub.mb + (u128)mass;
-        Big S;
-#pragma unroll
-        for (int i = 0; i < STS_NL; ++i) S.l[i] = s_Sx[i];
-        big_add_shifted(S, (u64)mk, (u64)(mk >> 64), unit_bit(e));
-        const double Sd = big_to_double(S);
-        const u64 L = s_sub.cnt_before + rank + 1;
-        const int dropped = L < ncand;
-        sm.thr_w = ((u64)e << 52) | frac;
-        sm.thr_k = (u64)v;
-        sm.dropped = dropped;
-        sm.scale = dropped ? 1.0 / sqrt(Sd) : 1.0;
-        ctl->L = L;
-        ctl->thr_wbits = sm.thr_w;
-        ctl->thr_key = sm.thr_k;
-        ctl->dropped = dropped;
-        ctl->S = Sd;
-        ctl->scale = sm.scale;
-        const double frac_kept = Sd / W;
-        ctl->frac = frac_kept;
-        if (dropped) ctl->log10_cum = l10 + log10(frac_kept);
-    }
-    return true;
+    (void)rank_cut<NT>(sv, m, e, K, R, sub, sm);
+    return sm.hit != 0xffffffffu;
 }
 
 } // namespace sts_select

@@ -41,7 +41,7 @@ template <typename AT> struct TinySmem {
             unsigned long long slot[SLOTS]; // a group: the index + 1 of its member j at bit 16 j
         } g;
         Level1Smem<NT> l1;
-        unsigned char raw[3 * STS_NBIN * sizeof(u64)];
+        __attribute__((aligned(16))) unsigned char raw[STS_NBIN * 12];
     } u;
     u64 hi[STS_NBIN], lo[STS_NBIN];
     Level1Cut l1;
@@ -173,7 +173,6 @@ __global__ void __launch_bounds__(NT) k_tiny(GateArg g, PassBufs b)
         all = s.l1.keep_all;
     }
     const bool cut = !all;
-    double scale = 1.0;
     if (cut) {
         const int e = s.l1.e;
         if (t == 0) {
@@ -195,18 +194,14 @@ __global__ void __launch_bounds__(NT) k_tiny(GateArg g, PassBufs b)
                     if ((v >> vshift) == vpre) f(v);
                 }
         };
-        const bool ok = resolve_cut<NT>(ctl, each, e, K, make128(s.l1.R_lo, s.l1.R_hi), s.sub, s.u.raw, s.cut, s.l1.S,
-                                        s.l1.total, s.l1.W, l10);
-        if (!ok) { // uniform
+        if (!resolve_cut<NT, true>(each, e, K, make128(s.l1.R_lo, s.l1.R_hi), s.sub, s.u.raw, s.cut)) { // uniform
             if (t == 0) atomicOr(&ctl->flags, STS_F_UNRESOLVED);
             return;
         }
-        __syncthreads();
         thr_w = s.cut.thr_w;
         thr_k = s.cut.thr_k;
-        scale = s.cut.scale;
+        if (t >= NT - 64) finish_cut(ctl, s.cut, e, s.l1.S, s.l1.total, s.l1.W, l10);
     }
-    const bool rescale = cut && s.cut.dropped;
     u32 keep = 0;
 #pragma unroll
     for (int r = 0; r < RPT; ++r)
@@ -216,24 +211,28 @@ __global__ void __launch_bounds__(NT) k_tiny(GateArg g, PassBufs b)
             const bool in = ((cand >> (r * NP + p)) & 1u) && (!cut || w > thr_w || (w == thr_w && k <= thr_k));
             keep |= in ? 1u << (r * NP + p) : 0u;
         }
-    u32 base = 0;
+    u32 base = 0, pos[RPT];
 #pragma unroll
     for (int r = 0; r < RPT; ++r) {
-        const u32 mine = (keep >> (r * NP)) & (NP == 32 ? ~0u : (1u << NP) - 1u);
-        u32 tot;
-        u32 pos = base + block_excl_scan<u32, NT>((u32)__popc(mine), s.scan, &tot);
+        u32 tot; // (the scans' barriers also publish the scale)
+        pos[r] = base + block_excl_scan<u32, NT>((u32)__popc((keep >> (r * NP)) & ((1u << NP) - 1u)), s.scan, &tot);
         base += tot;
+    }
+    const bool rescale = cut && s.cut.dropped;
+    const double scale = rescale ? s.cut.scale : 1.0;
+#pragma unroll
+    for (int r = 0; r < RPT; ++r) {
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
-            if (!((mine >> p) & 1u)) continue;
-            if (pos < b.out_cap) {
+            if (!((keep >> (r * NP + p)) & 1u)) continue;
+            if (pos[r] < b.out_cap) {
                 AT o;
                 o.x = ox[r][p];
                 o.y = oy[r][p];
-                b.out_keys[pos] = rest[r] | g.dep[p];
-                ((AT *)b.out_amps)[pos] = out_amp(o, rescale, scale);
+                b.out_keys[pos[r]] = rest[r] | g.dep[p];
+                ((AT *)b.out_amps)[pos[r]] = out_amp(o, rescale, scale);
             }
-            ++pos;
+            ++pos[r];
         }
     }
     if (t == 0) {
