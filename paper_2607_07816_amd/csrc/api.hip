@@ -552,11 +552,12 @@ sts_status bucket_write(sts_ctx *c, const PassBufs &b, int dst, u64 bound)
 {
     const int tiles = bucket_tiles(c);
     if (!b.emit_copies) { // else k_bkt_select has the offsets
-        STS_LAUNCH(c, STS_K_GROUP_EXTRACT,
-                   launch_bucket_pass(STS_BKT_COUNT, c->prec, c->gate.m, b, tiles, c->stream));
+        if (!b.whole)
+            STS_LAUNCH(c, STS_K_GROUP_EXTRACT,
+                       launch_bucket_pass(STS_BKT_COUNT, c->prec, c->gate.m, b, tiles, c->stream));
         STS_LAUNCH(c, STS_K_TILE_KEPT, launch_bucket_kept(b, tiles, c->stream));
     }
-    if (!b.materialise && !b.emit_copies)
+    if (!b.materialise && !b.emit_copies && !b.whole)
         STS_LAUNCH(c, STS_K_GROUP_EMIT, launch_bucket_pass(STS_BKT_COPY, c->prec, c->gate.m, b, tiles, c->stream));
     STS_LAUNCH(c, STS_K_GROUP_EMIT, launch_bucket_pass(STS_BKT_EMIT, c->prec, c->gate.m, b, tiles, c->stream));
     c->cur = dst;
@@ -602,6 +603,7 @@ sts_status count_candidates(sts_ctx *c, u64 *count)
 {
     PassBufs b = pass_bufs(c, c->cur, -1);
     if (c->bkt_pending) {
+        b.whole = 1;
         STS_LAUNCH(c, STS_K_GROUP_HIST,
                    launch_bucket_pass(STS_BKT_HIST, c->prec, c->gate.m, b, bucket_tiles(c), c->stream));
         STS_LAUNCH(c, STS_K_PICK1, launch_pick1(b, 0, 1, 0, c->stream));
@@ -896,6 +898,13 @@ static sts_status truncate_buckets(sts_ctx *c)
         if (st != STS_OK) return st;
     }
     const bool small = c->n_bound <= kSelectMax && tiles * 4 <= STS_SEL_SHARES;
+    if (!small && c->p == 0.0 && c->K && cb < c->K) {
+        // nothing can be cut: the histogram for the statistics, then the write
+        b.whole = 1;
+        STS_LAUNCH(c, STS_K_GROUP_HIST, launch_bucket_pass(STS_BKT_HIST, c->prec, m, b, tiles, c->stream));
+        STS_LAUNCH(c, STS_K_PICK1, launch_pick1(b, 0, 0, 0, c->stream));
+        return bucket_write(c, b, out, nb);
+    }
     if (small) {
         STS_LAUNCH(c, STS_K_GROUP_HIST, launch_bucket_pass(STS_BKT_SMALL, c->prec, m, b, tiles, c->stream));
         STS_LAUNCH(c, STS_K_FINAL, launch_bucket_pass(STS_BKT_SELECT, c->prec, m, b, tiles, c->stream));
@@ -908,11 +917,9 @@ static sts_status truncate_buckets(sts_ctx *c)
         STS_LAUNCH(c, STS_K_PICK1, launch_pick_window(b, bucket_groups(c, true), c->stream));
         b.recover = 1;
         STS_LAUNCH(c, STS_K_GROUP_HIST, launch_bucket_pass(STS_BKT_HIST, c->prec, m, b, tiles, c->stream));
-        STS_LAUNCH(c, STS_K_PICK1, launch_pick1(b, 0, 0, 3, c->stream));
         STS_LAUNCH(c, STS_K_GROUP_EXTRACT, launch_bucket_pass(STS_BKT_EXTRACT, c->prec, m, b, tiles, c->stream));
         const int sg =
             (int)std::min<u64>(std::max<u64>(ceil_div(std::min(cb, c->scap), 256), 1), STS_SIDE_GROUPS);
-        STS_LAUNCH(c, STS_K_SIDE_HIST, launch_side_hist(b, c->h2, sg, c->stream));
         STS_LAUNCH(c, STS_K_SIDE_EXTRACT, launch_side_extract(b, std::max(sg, (tiles + 3) / 4), c->stream));
         STS_LAUNCH(c, STS_K_FINAL, launch_final(b, c->stream));
     }

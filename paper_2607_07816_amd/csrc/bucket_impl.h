@@ -563,7 +563,7 @@ __device__ __forceinline__ int small_window(const DevCtl *ctl)
 // ---------------------------------------------------------------------------
 // histogram pass: exponent histogram with exact mantissa sums of all new
 // weights (persistent grid). With b.recover it runs only after a sampled
-// window that missed.
+// window that missed, and its last workgroup does the level-1 pick.
 // ---------------------------------------------------------------------------
 template <typename AT, int M>
 __global__ void __launch_bounds__(STS_WG) k_bkt_hist(const GateArg *__restrict__ gp, PassBufs b)
@@ -571,7 +571,14 @@ __global__ void __launch_bounds__(STS_WG) k_bkt_hist(const GateArg *__restrict__
     const GateArg &g = *gp;
     const GateLoc<M> gl = gate_loc<M>(g);
     __shared__ BktSmem<AT, BW> s;
-    __shared__ u64 s_hi[TT_SLOTS], s_lo[TT_SLOTS];
+    __shared__ union {
+        struct {
+            u64 hi[TT_SLOTS], lo[TT_SLOTS];
+        } bins;
+        sts_select::Level1Smem<STS_WG> l1;
+    } u;
+    __shared__ u32 s_flag;
+    u64 *const s_hi = u.bins.hi, *const s_lo = u.bins.lo;
     DevCtl *ctl = b.ctl;
     if (b.recover && !ctl->need_full) return; // uniform
     smem_begin<AT, M, BW>(s, g);
@@ -613,6 +620,8 @@ __global__ void __launch_bounds__(STS_WG) k_bkt_hist(const GateArg *__restrict__
     }
     __syncthreads();
     flush_bins(b, s_hi, s_lo, hot_lo);
+    if (!b.recover || !sts_last_block(&ctl->done[0], &s_flag)) return;
+    sts_select::pick_level1<STS_WG>(b, 0, 0, 3, u.l1, sts_select::DeviceBins<STS_WG>{b.h1});
 }
 
 // ---------------------------------------------------------------------------
@@ -900,19 +909,30 @@ __global__ void __launch_bounds__(STS_WG) k_bkt_sample(const GateArg *__restrict
 // ---------------------------------------------------------------------------
 // the passes of a step whose window missed the cut (they exit at once when it
 // held it): the candidates of the cut's exponent to the side buffer, densely
-// packed (one claim per tile), and the survivors per share
+// packed (one claim per tile), with their level-2 bins, picked by the last
+// workgroup; and the survivors per share
 // ---------------------------------------------------------------------------
 template <typename AT, int M>
 __global__ void __launch_bounds__(STS_WG) k_bkt_extract(const GateArg *__restrict__ gp, PassBufs b)
 {
+    using namespace sts_select;
     const GateArg &g = *gp;
     const GateLoc<M> gl = gate_loc<M>(g);
     __shared__ BktSmem<AT, BW> s;
     __shared__ u32 s_cnt[BW];
     __shared__ u64 s_base;
+    __shared__ u64 s_low[STS_NBIN]; // sums of the 41 mantissa bits below the bin's, and counts
+    __shared__ u32 s_num[STS_NBIN];
+    __shared__ CutSmem s_cut;
+    __shared__ Sub s_sub;
+    __shared__ u32 s_flag;
     DevCtl *ctl = b.ctl;
     if (ctl->pred_hit || ctl->keep_all) return; // uniform
     smem_begin<AT, M, BW>(s, g);
+    for (int i = threadIdx.x; i < STS_NBIN; i += STS_WG) {
+        s_low[i] = 0;
+        s_num[i] = 0;
+    }
     const int e_star = ctl->e_star;
     const u64 *keys = b.keys;
     const AT *amps = (const AT *)b.amps;
@@ -922,7 +942,7 @@ __global__ void __launch_bounds__(STS_WG) k_bkt_extract(const GateArg *__restric
     for (u32 tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
         const Share sh = load_share(g.bkt, b.bd_in, tile, wv);
         u32 cnt = 0;
-        share_groups<AT, M>(s.w[wv], s.ucol, gl, sh, keys, amps, [&](const auto &ox, const auto &oy, u64 rest, bool active) {
+        share_groups<AT, M>(s.w[wv], s.ucol, gl, sh, keys, amps, [&](const auto &ox, const auto &oy, u64, bool active) {
 #pragma unroll
             for (int i = 0; i < (1 << M); ++i) {
                 AT o;
@@ -937,7 +957,8 @@ __global__ void __launch_bounds__(STS_WG) k_bkt_extract(const GateArg *__restric
         __syncthreads();
         u64 at = s_base;
         for (int w = 0; w < wv; ++w) at += s_cnt[w];
-        share_groups<AT, M>(s.w[wv], s.ucol, gl, sh, keys, amps, [&](const auto &ox, const auto &oy, u64 rest, bool active) {
+        share_groups<AT, M>(s.w[wv], s.ucol, gl, sh, keys, amps,
+                            [&](const auto &ox, const auto &oy, u64 rest, bool active) {
 #pragma unroll
             for (int i = 0; i < (1 << M); ++i) {
                 AT o;
@@ -950,12 +971,53 @@ __global__ void __launch_bounds__(STS_WG) k_bkt_extract(const GateArg *__restric
                 if (take && p < b.side_cap) {
                     b.side_key[p] = rest | pattern_bits<M>(gl, i);
                     b.side_w[p] = wb;
+                    const u32 d = 2047u - ((u32)(wb >> 41) & 2047u);
+                    const u64 mant = sts_mant(wb);
+                    if (sh.n > (1u << 19)) { // more than a bin of the workgroup holds
+                        atomicAdd(&b.h2w[d], 1ull);
+                        atomicAdd(&b.h2w[STS_NBIN + d], mant >> 26);
+                        atomicAdd(&b.h2w[2 * STS_NBIN + d], mant & ((1ull << 26) - 1));
+                    } else {
+                        atomicAdd(&s_low[d], mant & LOW41);
+                        atomicAdd(&s_num[d], 1u);
+                    }
                 }
                 at += (u64)__popcll(m);
             }
         });
         __syncthreads();
+        for (int i = threadIdx.x; i < STS_NBIN; i += STS_WG) {
+            const u32 c = s_num[i];
+            if (!c) continue;
+            const u128 tot = (u128)digit_mant((u32)i, e_star) * c + (u128)s_low[i];
+            atomicAdd(&b.h2w[i], (u64)c);
+            atomicAdd(&b.h2w[STS_NBIN + i], (u64)(tot >> 26));
+            atomicAdd(&b.h2w[2 * STS_NBIN + i], (u64)tot & ((1ull << 26) - 1));
+            s_low[i] = 0;
+            s_num[i] = 0;
+        }
     }
+    if (!sts_last_block(&ctl->done[1], &s_flag)) return;
+    if (threadIdx.x == 0) {
+        s_sub.cnt_before = ctl->cnt_before;
+        s_sub.mb = 0;
+        s_sub.vpre = 0;
+        s_sub.vshift = 116;
+        s_sub.count = ctl->sub_count;
+    }
+    __syncthreads();
+    const bool ok = pick_digit<STS_WG>(AgentBins{b.h2w}, ctl->K, make128(ctl->R_lo, ctl->R_hi), 11, &s_sub, s_cut.m,
+                                       s_cut.c, &s_cut.hit);
+    if (ok && threadIdx.x <= STS_SUB_REGIONS) st_agent(&b.sub_cnt[threadIdx.x * 32], 0u);
+    if (threadIdx.x == 0) {
+        if (ok) {
+            sub_store(s_sub, ctl);
+            ctl->level = 2;
+        } else {
+            atomicOr(&ctl->flags, STS_F_UNRESOLVED);
+        }
+    }
+    for (int i = threadIdx.x; i < 3 * STS_NBIN; i += STS_WG) st_agent(&b.h2w[i], 0ull);
 }
 
 template <typename AT> __device__ __forceinline__ bool survives(u64 wb, u64 key, bool all, u64 thr_w, u64 thr_k)
@@ -1534,7 +1596,9 @@ template <typename AT, int M> int weigh_grid(int tiles)
 
 template <typename AT, int M> hipError_t launch_m(int kind, const PassBufs &b, int tiles, hipStream_t s)
 {
-    const int cap = hist_capacity_b<AT, M>();
+    // a pass that a truncated step launches in case its window missed is sized
+    // to cost little when it exits at once: one workgroup per CU
+    const int cap = b.materialise || b.whole ? hist_capacity_b<AT, M>() : 256;
     switch (kind) {
     case STS_BKT_HIST:
         hipLaunchKernelGGL((k_bkt_hist<AT, M>), dim3(std::min(tiles, cap)), dim3(STS_WG), 0, s, b.gate, b);

@@ -77,6 +77,7 @@ struct PassBufs {
     int slab_shift;
     int emit_copies;      // write pass: also copies the survivors when the window held the cut
     int recover;          // histogram pass: only after a sampled window that missed
+    int whole;            // the passes launched are known to run
     u64 *sbins;           // sampling pass: STS_SW_BANKS x STS_SW_NB counts (u32), as many masses
                           // (float), then 4 totals per bank
 };

@@ -29,7 +29,6 @@ using namespace sts_select;
 __global__ void __launch_bounds__(256) k_pick1(PassBufs b, int groups, int peak_only, int predicted)
 {
     __shared__ Level1Smem<256> sm;
-    if (predicted == 3 && !b.ctl->need_full) return; // uniform
     pick_level1<256>(b, groups, peak_only, predicted, sm, DeviceBins<256>{b.h1});
 }
 

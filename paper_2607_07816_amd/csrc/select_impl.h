@@ -611,7 +611,7 @@ __device__ void pick_level1(const PassBufs &b, int groups, int peak_only, int pr
                 if (predicted == 3) {
                     ctl->w_over = 0;
                     ctl->need_full = 0;
-                    // a missed window: the extraction pass packs its candidates densely
+                    // the extraction pass packs its candidates densely
                     if (hit != 0xffffffffu && !ctl->pred_hit) {
                         ctl->side_dense = 1;
                         ctl->side_n = 0;
