@@ -225,7 +225,7 @@ class State:
         got = ctypes.c_uint64(0)
         _check(load().sts_read_terms(self._ctx, n, keys.ctypes.data, amps.ctypes.data, ctypes.byref(got)),
                "sts_read_terms")
-        return keys[: got.value].copy(), amps[: got.value].copy()
+        return keys[: got.value], amps[: got.value]
 
     def load_terms(self, keys: np.ndarray, amps: np.ndarray):
         k = np.ascontiguousarray(keys, dtype=np.uint64)

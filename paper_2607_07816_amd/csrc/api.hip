@@ -18,6 +18,7 @@
 // Without a truncation rule (or when the next gate arrives first) step 6
 // alone runs, keeping every nonzero candidate.
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
@@ -448,8 +449,8 @@ sts_status sort_state(sts_ctx *c, const u64 *notmask, int *sorted, int *hb_out)
         const int shift = 64 - hb + bits * p;
         for (int what = 0; what < 3; ++what) {
             const int kind = what == 0 ? STS_K_RADIX_HIST : (what == 1 ? STS_K_RADIX_SCAN : STS_K_RADIX_PASS);
-            STS_LAUNCH(c, kind, launch_radix(what, shape, c->prec, c->keys[src], c->amps[src], c->keys[dst],
-                                             c->amps[dst], &c->ctl->cnt[src], &c->ctl->cnt[dst], notmask, shift,
+            STS_LAUNCH(c, kind, launch_radix(what, STS_SORT_BY_MIX, shape, c->prec, c->keys[src], c->amps[src],
+                                             c->keys[dst], c->amps[dst], &c->ctl->cnt[src], &c->ctl->cnt[dst], notmask, shift,
                                              c->rcount, c->rprefix, c->rtotal, c->tiles_cap, tiles, c->stream));
         }
         src = dst;
@@ -457,6 +458,25 @@ sts_status sort_state(sts_ctx *c, const u64 *notmask, int *sorted, int *hb_out)
     }
     *sorted = src;
     *hb_out = hb;
+    return STS_OK;
+}
+
+// sort n terms by key, from *k and *a through the buffers kb and ab in turn (the
+// input stays as it is unless no pass is needed); *k and *a: where they end up
+sts_status sort_by_key(sts_ctx *c, u64 n, int prec, u64 **k, void **a, std::array<u64 *, 2> kb,
+                       std::array<void *, 2> ab, const u64 *count)
+{
+    const int shape = n <= (1ull << 18) ? STS_RADIX_11x8 : STS_RADIX_8x16;
+    const int bits = sts_radix_bits(shape);
+    const int tiles = (int)ceil_div(n, sts_radix_tile(shape));
+    for (int p = 0; p * bits < c->n_qubits; ++p) {
+        for (int what = 0; what < 3; ++what)
+            STS_TRY(c, launch_radix(what, STS_SORT_BY_KEY, shape, prec, *k, *a, kb[p & 1], ab[p & 1], count,
+                                    &c->ctl->cnt[3], nullptr, p * bits, c->rcount, c->rprefix, c->rtotal,
+                                    c->tiles_cap, tiles, c->stream));
+        *k = kb[p & 1];
+        *a = ab[p & 1];
+    }
     return STS_OK;
 }
 
@@ -514,9 +534,9 @@ sts_status bucketize(sts_ctx *c)
     for (int p = 0; p < npass; ++p) {
         for (int what = 0; what < 3; ++what) {
             const int kind = what == 0 ? STS_K_RADIX_HIST : (what == 1 ? STS_K_RADIX_SCAN : STS_K_RADIX_PASS);
-            STS_LAUNCH(c, kind, launch_radix(what, shape, c->prec, c->keys[src], c->amps[src], c->keys[dst],
-                                             c->amps[dst], &c->ctl->cnt[src], &c->ctl->cnt[dst], nullptr,
-                                             64 - bits * npass + bits * p, c->rcount, c->rprefix, c->rtotal,
+            STS_LAUNCH(c, kind, launch_radix(what, STS_SORT_BY_BUCKET, shape, c->prec, c->keys[src], c->amps[src],
+                                             c->keys[dst], c->amps[dst], &c->ctl->cnt[src], &c->ctl->cnt[dst],
+                                             nullptr, 64 - bits * npass + bits * p, c->rcount, c->rprefix, c->rtotal,
                                              c->tiles_cap, tiles, c->stream));
         }
         src = dst;
@@ -1089,27 +1109,20 @@ sts_status sts_read_terms(sts_ctx *c, uint64_t cap, uint64_t *keys, double *amps
     const u64 cnt = *n;
     if (cnt > cap) return STS_E_CAPACITY;
     if (cnt == 0) return STS_OK;
-    std::vector<u64> k(cnt);
-    STS_TRY(c, hipMemcpyAsync(k.data(), c->keys[c->cur], cnt * 8, hipMemcpyDeviceToHost, c->stream));
-    std::vector<double> a(2 * cnt);
-    std::vector<float> af;
-    if (c->prec == STS_C128) {
-        STS_TRY(c, hipMemcpyAsync(a.data(), c->amps[c->cur], cnt * 16, hipMemcpyDeviceToHost, c->stream));
-    } else {
-        af.resize(2 * cnt);
-        STS_TRY(c, hipMemcpyAsync(af.data(), c->amps[c->cur], cnt * 8, hipMemcpyDeviceToHost, c->stream));
+    // sorted by key on the device, between the two free term buffers
+    u64 *k = c->keys[c->cur];
+    void *a = c->amps[c->cur];
+    st = sort_by_key(c, cnt, c->prec, &k, &a, {c->keys[(c->cur + 1) % 3], c->keys[(c->cur + 2) % 3]},
+                     {c->amps[(c->cur + 1) % 3], c->amps[(c->cur + 2) % 3]}, &c->ctl->cnt[c->cur]);
+    if (st != STS_OK) return st;
+    const void *wide = a;
+    if (c->prec == STS_C64) { // the side buffer has room for the FP64 pairs
+        STS_TRY(c, launch_widen((const float2 *)a, (double2 *)c->side_amp, cnt, c->stream));
+        wide = c->side_amp;
     }
+    STS_TRY(c, hipMemcpyAsync(keys, k, cnt * 8, hipMemcpyDeviceToHost, c->stream));
+    STS_TRY(c, hipMemcpyAsync(amps, wide, cnt * 16, hipMemcpyDeviceToHost, c->stream));
     STS_TRY(c, hipStreamSynchronize(c->stream));
-    if (c->prec == STS_C64)
-        for (u64 i = 0; i < 2 * cnt; ++i) a[i] = (double)af[i];
-    std::vector<u64> order(cnt);
-    for (u64 i = 0; i < cnt; ++i) order[i] = i;
-    std::sort(order.begin(), order.end(), [&](u64 x, u64 y) { return k[x] < k[y]; });
-    for (u64 i = 0; i < cnt; ++i) {
-        keys[i] = k[order[i]];
-        amps[2 * i] = a[2 * order[i]];
-        amps[2 * i + 1] = a[2 * order[i] + 1];
-    }
     return STS_OK;
 }
 
@@ -1120,27 +1133,32 @@ sts_status sts_load_terms(sts_ctx *c, uint64_t n, const uint64_t *keys, const do
     if (n && (!keys || !amps)) return STS_E_ARG;
     if (n > c->cap) return STS_E_CAPACITY;
     const u64 lim = c->n_qubits == 64 ? ~0ull : ((1ull << c->n_qubits) - 1);
-    std::vector<u64> sk(keys, keys + n);
-    for (u64 i = 0; i < n; ++i)
-        if (sk[i] > lim || !std::isfinite(amps[2 * i]) || !std::isfinite(amps[2 * i + 1])) return STS_E_ARG;
-    std::sort(sk.begin(), sk.end());
-    for (u64 i = 1; i < n; ++i)
-        if (sk[i] == sk[i - 1]) return STS_E_ARG;
+    const int dst = (c->cur + 1) % 3; // a free buffer: refused terms change nothing
+    if (n) {
+        // checked on the device: range and finiteness, then (sorted in the
+        // side buffer) that no key comes twice
+        double *wide = c->prec == STS_C128 ? (double *)c->amps[dst] : (double *)c->side_amp;
+        STS_TRY(c, hipMemcpyAsync(c->keys[dst], keys, n * 8, hipMemcpyHostToDevice, c->stream));
+        STS_TRY(c, hipMemcpyAsync(wide, amps, n * 16, hipMemcpyHostToDevice, c->stream));
+        STS_TRY(c, launch_load_check(c->prec, c->keys[dst], wide, n, lim, (float2 *)c->amps[dst], c->ctl, c->stream));
+        STS_TRY(c, launch_set_n(&c->ctl->cnt[dst], n, c->stream));
+        u64 *k = c->keys[dst];
+        void *w = c->keys[dst]; // moved along with the keys, not used
+        st = sort_by_key(c, n, STS_C64, &k, &w, {c->side_key, c->side_key + c->cap}, {c->side_w, c->side_w + c->cap},
+                         &c->ctl->cnt[dst]);
+        if (st != STS_OK) return st;
+        STS_TRY(c, launch_load_unique(k, n, c->ctl, c->stream));
+        st = sync_ctl(c); // also: the caller's arrays have been read
+        if (st != STS_OK) return st;
+        if (c->hctl->load_flags) {
+            STS_TRY(c, hipMemsetAsync(&c->ctl->load_flags, 0, sizeof(u32), c->stream));
+            return STS_E_ARG;
+        }
+    }
     // the state is replaced: any pending gate is dropped
     c->pending = c->bkt_pending = c->tiny_pending = false;
     c->bucketed = false;
-    if (n) {
-        STS_TRY(c, hipMemcpyAsync(c->keys[c->cur], keys, n * 8, hipMemcpyHostToDevice, c->stream));
-        if (c->prec == STS_C128) {
-            STS_TRY(c, hipMemcpyAsync(c->amps[c->cur], amps, n * 16, hipMemcpyHostToDevice, c->stream));
-            STS_TRY(c, hipStreamSynchronize(c->stream));
-        } else {
-            std::vector<float> af(2 * n);
-            for (u64 i = 0; i < 2 * n; ++i) af[i] = (float)amps[i];
-            STS_TRY(c, hipMemcpyAsync(c->amps[c->cur], af.data(), n * 8, hipMemcpyHostToDevice, c->stream));
-            STS_TRY(c, hipStreamSynchronize(c->stream));
-        }
-    }
+    c->cur = dst;
     STS_TRY(c, launch_set_n(&c->ctl->cnt[c->cur], n, c->stream));
     c->n_bound = n;
     return STS_OK;

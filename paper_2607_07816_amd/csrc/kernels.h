@@ -146,10 +146,14 @@ __device__ __forceinline__ u64 slab_at(const TileSlabs &t, u32 j)
 inline int sts_radix_bits(int shape) { return shape >= STS_RADIX_11x16 ? 11 : 8; }
 inline u64 sts_radix_tile(int shape) { return (shape & 1) ? 2048ull : 4096ull; }
 
-// notmask = nullptr sorts by the bucket hash of linhash.h instead of the mixed masked key (shapes 8x16, 11x8)
-// one step of a grouping-sort pass: what = 0 digit counts per tile, 1 their
-// scan (one workgroup per digit), 2 the scatter
-hipError_t launch_radix(int what, int shape, int prec, const u64 *kin, const void *ain, u64 *kout, void *aout,
+// what a sort orders by: the mixed masked key (grouping), the bucket hash of linhash.h, the key
+#define STS_SORT_BY_MIX 0
+#define STS_SORT_BY_BUCKET 1 // (shapes 8x16 and 11x8)
+#define STS_SORT_BY_KEY 2    // (shapes 8x16 and 11x8)
+
+// one step of a sort pass: what = 0 digit counts per tile, 1 their scan (one
+// workgroup per digit), 2 the scatter
+hipError_t launch_radix(int what, int by, int shape, int prec, const u64 *kin, const void *ain, u64 *kout, void *aout,
                         const u64 *n_in, u64 *n_out, const u64 *notmask, int shift, u32 *counts, u64 *prefix,
                         u64 *totals, u64 tiles_cap, int tiles, hipStream_t s);
 
@@ -170,6 +174,13 @@ hipError_t launch_init_state(int prec, u64 *keys, void *amps, u64 *n_out, hipStr
 hipError_t launch_set_n(u64 *n_out, u64 n, hipStream_t s);
 hipError_t launch_set_gate(const GateArg &g, GateArg *dst, hipStream_t s);
 const void *set_gate_kernel(); // the kernel launch_set_gate launches (to find its node in a captured graph)
+// terms from the host: range and finiteness (ctl->load_flags), and FP32 rounding of complex64 amplitudes
+hipError_t launch_load_check(int prec, const u64 *keys, const double *amps, u64 n, u64 limit, float2 *amps32,
+                             DevCtl *ctl, hipStream_t s);
+// ctl->load_flags if two neighbours of the n sorted keys are equal
+hipError_t launch_load_unique(const u64 *sorted, u64 n, DevCtl *ctl, hipStream_t s);
+// n complex64 amplitudes to FP64 pairs
+hipError_t launch_widen(const float2 *in, double2 *out, u64 n, hipStream_t s);
 hipError_t launch_fill_zero(u64 *p, u64 n, hipStream_t s);
 hipError_t launch_ctl_begin(DevCtl *ctl, u64 K, double p, u64 n_in, hipStream_t s);
 hipError_t launch_terms_out(const u64 *keys, const void *amps, int amp_bytes, const DevCtl *ctl, int slot,

@@ -33,15 +33,19 @@
 
 namespace {
 
-// LIN: the bucket hash of linhash.h (32 bits, taken as the top half of 64)
-template <int BITS, bool LIN> __device__ __forceinline__ u32 bucket_digit(u64 key, u64 notmask, int shift)
+// what a sort orders by: the mixed masked key, the bucket hash of linhash.h (32
+// bits, taken as the top half of 64), or the key itself
+constexpr int BY_MIX = STS_SORT_BY_MIX, BY_LIN = STS_SORT_BY_BUCKET, BY_KEY = STS_SORT_BY_KEY;
+
+template <int BITS, int BY> __device__ __forceinline__ u32 bucket_digit(u64 key, u64 notmask, int shift)
 {
-    if constexpr (LIN) return lin_bits<BITS>(key, shift - 32);
+    if constexpr (BY == BY_LIN) return lin_bits<BITS>(key, shift - 32);
+    if constexpr (BY == BY_KEY) return (u32)(key >> shift) & ((1u << BITS) - 1u);
     return (u32)((sts_mix64(key & notmask) >> shift) & ((1u << BITS) - 1u));
 }
 
 // digit counts of one tile, written digit-major: counts[d * tiles_cap + tile]
-template <int BITS, int IT, bool LIN>
+template <int BITS, int IT, int BY>
 __global__ void __launch_bounds__(STS_WG) k_radix_count(const u64 *__restrict__ keys, const u64 *n_in,
                                                          const u64 *gate_notmask, int shift, u32 *__restrict__ counts,
                                                          u64 tiles_cap)
@@ -50,7 +54,7 @@ __global__ void __launch_bounds__(STS_WG) k_radix_count(const u64 *__restrict__ 
     constexpr u64 TILE = (u64)STS_WG * IT;
     __shared__ u32 s_h[ND];
     const u64 n = *n_in;
-    const u64 notmask = LIN ? 0ull : *gate_notmask;
+    const u64 notmask = BY == BY_MIX ? *gate_notmask : 0ull;
     // the state's tiles go to the XCDs in contiguous ranges, so that the
     // counts of neighbouring tiles (adjacent in each digit's row) are written
     // through one L2; workgroups past the state's tiles write zeros
@@ -73,7 +77,7 @@ __global__ void __launch_bounds__(STS_WG) k_radix_count(const u64 *__restrict__ 
 #pragma unroll
     for (int k = 0; k < IT; ++k) {
         const u64 i = base + (u64)k * STS_WG + threadIdx.x;
-        if (i < n) atomicAdd(&s_h[bucket_digit<BITS, LIN>(kk[k], notmask, shift)], 1u);
+        if (i < n) atomicAdd(&s_h[bucket_digit<BITS, BY>(kk[k], notmask, shift)], 1u);
     }
     __syncthreads();
     for (int d = threadIdx.x; d < ND; d += STS_WG) counts[(u64)d * tiles_cap + tile] = s_h[d];
@@ -143,7 +147,7 @@ __global__ void __launch_bounds__(STS_WG) k_radix_scan(const u32 *__restrict__ c
 // complex128), held in one register array per word (an array of HIP's
 // 16-byte vector type would be left in scratch memory). Thread t owns the
 // DPT = 2^BITS / 256 consecutive digits t*DPT .. t*DPT + DPT-1.
-template <int W, int BITS, int IT, bool LIN>
+template <int W, int BITS, int IT, int BY>
 __global__ void __launch_bounds__(STS_WG) k_radix_pass(const u64 *__restrict__ kin, const u64 *__restrict__ ain,
                                                         u64 *__restrict__ kout, u64 *__restrict__ aout,
                                                         const u64 *n_in, u64 *n_out, const u64 *gate_notmask,
@@ -165,7 +169,7 @@ __global__ void __launch_bounds__(STS_WG) k_radix_pass(const u64 *__restrict__ k
     __shared__ dig_t s_dig[TILE];
     __shared__ __attribute__((aligned(16))) unsigned char s_buf[TILE * ESZ];
 
-    const u64 notmask = LIN ? 0ull : *gate_notmask;
+    const u64 notmask = BY == BY_MIX ? *gate_notmask : 0ull;
     const int tid = threadIdx.x;
     const int w = tid >> 6;
     const int lane = tid & 63;
@@ -224,7 +228,7 @@ __global__ void __launch_bounds__(STS_WG) k_radix_pass(const u64 *__restrict__ k
     for (int k = 0; k < IT; ++k) {
         const u64 e = base + (u64)w * (64 * IT) + (u64)k * 64 + lane;
         const bool valid = e < n;
-        const u32 d = valid ? bucket_digit<BITS, LIN>(key[k], notmask, shift) : 0u;
+        const u32 d = valid ? bucket_digit<BITS, BY>(key[k], notmask, shift) : 0u;
         dig[k] = valid ? d : (u32)ND;
         u64 peers = __ballot(valid);
 #pragma unroll
@@ -311,53 +315,55 @@ __global__ void __launch_bounds__(STS_WG) k_radix_pass(const u64 *__restrict__ k
 
 } // namespace
 
-template <int BITS, int IT, bool LIN>
+template <int BITS, int IT, int BY>
 static hipError_t radix_launch(int what, int prec, const u64 *kin, const void *ain, u64 *kout, void *aout, const u64 *n_in,
                         u64 *n_out, const u64 *notmask, int shift, u32 *counts, u64 *prefix, u64 *totals,
                         u64 tiles_cap, int tiles, hipStream_t s)
 {
     static_assert(sizeof(double2) == 2 * sizeof(u64) && sizeof(float2) == sizeof(u64), "amplitude words");
     if (what == 0) {
-        hipLaunchKernelGGL((k_radix_count<BITS, IT, LIN>), dim3(tiles), dim3(STS_WG), 0, s, kin, n_in, notmask, shift,
+        hipLaunchKernelGGL((k_radix_count<BITS, IT, BY>), dim3(tiles), dim3(STS_WG), 0, s, kin, n_in, notmask, shift,
                            counts, tiles_cap);
     } else if (what == 1) {
         hipLaunchKernelGGL(k_radix_scan, dim3(1u << BITS), dim3(STS_WG), 0, s, (const u32 *)counts, prefix, totals,
                            n_in, tiles_cap, (u64)STS_WG * IT);
     } else if (prec == 0) {
-        hipLaunchKernelGGL((k_radix_pass<2, BITS, IT, LIN>), dim3(tiles), dim3(STS_WG), 0, s, kin, (const u64 *)ain, kout,
+        hipLaunchKernelGGL((k_radix_pass<2, BITS, IT, BY>), dim3(tiles), dim3(STS_WG), 0, s, kin, (const u64 *)ain, kout,
                            (u64 *)aout, n_in, n_out, notmask, shift, prefix, totals, tiles_cap);
     } else {
-        hipLaunchKernelGGL((k_radix_pass<1, BITS, IT, LIN>), dim3(tiles), dim3(STS_WG), 0, s, kin, (const u64 *)ain, kout,
+        hipLaunchKernelGGL((k_radix_pass<1, BITS, IT, BY>), dim3(tiles), dim3(STS_WG), 0, s, kin, (const u64 *)ain, kout,
                            (u64 *)aout, n_in, n_out, notmask, shift, prefix, totals, tiles_cap);
     }
     return hipGetLastError();
 }
 
-hipError_t launch_radix(int what, int shape, int prec, const u64 *kin, const void *ain, u64 *kout, void *aout,
+hipError_t launch_radix(int what, int by, int shape, int prec, const u64 *kin, const void *ain, u64 *kout, void *aout,
                         const u64 *n_in, u64 *n_out, const u64 *notmask, int shift, u32 *counts, u64 *prefix,
                         u64 *totals, u64 tiles_cap, int tiles, hipStream_t s)
 {
-    if (!notmask) { // into bucket order
+    if (by != BY_MIX) { // these sorts take two of the shapes
         if (shape == STS_RADIX_8x16)
-            return radix_launch<8, 16, true>(what, prec, kin, ain, kout, aout, n_in, n_out, notmask, shift, counts,
-                                             prefix, totals, tiles_cap, tiles, s);
+            return (by == BY_LIN ? radix_launch<8, 16, BY_LIN> : radix_launch<8, 16, BY_KEY>)(
+                what, prec, kin, ain, kout, aout, n_in, n_out, notmask, shift, counts, prefix, totals, tiles_cap, tiles,
+                s);
         if (shape == STS_RADIX_11x8)
-            return radix_launch<11, 8, true>(what, prec, kin, ain, kout, aout, n_in, n_out, notmask, shift, counts,
-                                             prefix, totals, tiles_cap, tiles, s);
+            return (by == BY_LIN ? radix_launch<11, 8, BY_LIN> : radix_launch<11, 8, BY_KEY>)(
+                what, prec, kin, ain, kout, aout, n_in, n_out, notmask, shift, counts, prefix, totals, tiles_cap, tiles,
+                s);
         return hipErrorInvalidValue;
     }
     switch (shape) {
     case STS_RADIX_8x16:
-        return radix_launch<8, 16, false>(what, prec, kin, ain, kout, aout, n_in, n_out, notmask, shift, counts, prefix,
+        return radix_launch<8, 16, BY_MIX>(what, prec, kin, ain, kout, aout, n_in, n_out, notmask, shift, counts, prefix,
                                    totals, tiles_cap, tiles, s);
     case STS_RADIX_8x8:
-        return radix_launch<8, 8, false>(what, prec, kin, ain, kout, aout, n_in, n_out, notmask, shift, counts, prefix,
+        return radix_launch<8, 8, BY_MIX>(what, prec, kin, ain, kout, aout, n_in, n_out, notmask, shift, counts, prefix,
                                   totals, tiles_cap, tiles, s);
     case STS_RADIX_11x16:
-        return radix_launch<11, 16, false>(what, prec, kin, ain, kout, aout, n_in, n_out, notmask, shift, counts, prefix,
+        return radix_launch<11, 16, BY_MIX>(what, prec, kin, ain, kout, aout, n_in, n_out, notmask, shift, counts, prefix,
                                     totals, tiles_cap, tiles, s);
     case STS_RADIX_11x8:
-        return radix_launch<11, 8, false>(what, prec, kin, ain, kout, aout, n_in, n_out, notmask, shift, counts, prefix,
+        return radix_launch<11, 8, BY_MIX>(what, prec, kin, ain, kout, aout, n_in, n_out, notmask, shift, counts, prefix,
                                    totals, tiles_cap, tiles, s);
     }
     return hipErrorInvalidValue;

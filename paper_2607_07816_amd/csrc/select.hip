@@ -772,6 +772,34 @@ __global__ void __launch_bounds__(64) k_set_gate(GateArg g, GateArg *dst)
     for (u32 i = threadIdx.x; i < sizeof(GateArg) / sizeof(u32); i += 64) d[i] = src[i];
 }
 
+// range and finiteness of n terms from the host; complex64: their amplitudes
+// rounded to FP32 (nearest-even)
+__global__ void __launch_bounds__(256) k_load_check(const u64 *__restrict__ keys, const double2 *__restrict__ amps,
+                                                    u64 n, u64 limit, float2 *amps32, DevCtl *ctl)
+{
+    bool bad = false;
+    for (u64 i = (u64)blockIdx.x * 256 + threadIdx.x; i < n; i += (u64)gridDim.x * 256) {
+        const double2 a = amps[i];
+        bad |= keys[i] > limit || !isfinite(a.x) || !isfinite(a.y);
+        if (amps32) amps32[i] = make_float2((float)a.x, (float)a.y);
+    }
+    if (bad) atomicOr(&ctl->load_flags, 1u);
+}
+
+__global__ void __launch_bounds__(256) k_load_unique(const u64 *__restrict__ keys, u64 n, DevCtl *ctl)
+{
+    bool bad = false;
+    for (u64 i = (u64)blockIdx.x * 256 + threadIdx.x + 1; i < n; i += (u64)gridDim.x * 256)
+        bad |= keys[i] == keys[i - 1];
+    if (bad) atomicOr(&ctl->load_flags, 1u);
+}
+
+__global__ void __launch_bounds__(256) k_widen(const float2 *__restrict__ in, double2 *__restrict__ out, u64 n)
+{
+    for (u64 i = (u64)blockIdx.x * 256 + threadIdx.x; i < n; i += (u64)gridDim.x * 256)
+        out[i] = make_double2((double)in[i].x, (double)in[i].y);
+}
+
 // zero n words (a kernel rather than a memset, so the work can sit in a
 // captured graph)
 __global__ void __launch_bounds__(256) k_fill_zero(u64 *p, u64 n)
@@ -883,6 +911,28 @@ const void *set_gate_kernel() { return reinterpret_cast<const void *>(&k_set_gat
 hipError_t launch_set_n(u64 *n_out, u64 n, hipStream_t s)
 {
     hipLaunchKernelGGL(k_set_n, dim3(1), dim3(1), 0, s, n_out, n);
+    return hipGetLastError();
+}
+
+static dim3 stream_grid(u64 n) { return dim3((unsigned)std::max<u64>(1, std::min<u64>((n + 255) / 256, 2048))); }
+
+hipError_t launch_load_check(int prec, const u64 *keys, const double *amps, u64 n, u64 limit, float2 *amps32,
+                             DevCtl *ctl, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_load_check, stream_grid(n), dim3(256), 0, s, keys, (const double2 *)amps, n, limit,
+                       prec == 0 ? nullptr : amps32, ctl);
+    return hipGetLastError();
+}
+
+hipError_t launch_load_unique(const u64 *sorted, u64 n, DevCtl *ctl, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_load_unique, stream_grid(n), dim3(256), 0, s, sorted, n, ctl);
+    return hipGetLastError();
+}
+
+hipError_t launch_widen(const float2 *in, double2 *out, u64 n, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_widen, stream_grid(n), dim3(256), 0, s, in, out, n);
     return hipGetLastError();
 }
 
