@@ -1282,40 +1282,44 @@ __global__ void __launch_bounds__(STS_WG) k_bkt_emit(const GateArg *__restrict__
 // (Selecting in the weighing pass's last workgroup instead of a launch of its
 // own was slower: 48 us instead of 12 + 29 at 4096 terms; the fences of that
 // handover cost more than the launch.) A window that missed the cut is not
-// recovered by further launches either: four waves of the selection then
-// compute the candidates again for each pass over them.
+// recovered by further launches either: the selection then computes the
+// candidates again and fills the slabs with those of the cut's exponent and
+// above (for every pass over them if a slab cannot hold its share's).
 // ---------------------------------------------------------------------------
-constexpr int SEL_NT = 1024;
+constexpr int SEL_NT = 512;
+constexpr int SEL_S = 32; // shares of which a wave holds up to 64 entries each
 
-struct SelectSmem {
+constexpr int SEL_NW = SEL_NT / 64;
+
+template <typename AT> struct SelectSmem {
     union {
         sts_select::Level1Smem<SEL_NT> l1;
-        __attribute__((aligned(16))) unsigned char raw[STS_NBIN * 12];
-        struct {
-            __attribute__((aligned(16))) u128 v[STS_FINAL_SORT];
-            u32 share[STS_FINAL_SORT];
-        } last; // the terms the cut is among, and their shares
+        BktSmem<AT, SEL_NW> bkt; // when candidates are computed again
     } u;
+    __attribute__((aligned(16))) unsigned char raw[sts_select::THIN_BINS * 12];
     sts_select::Level1Cut l1;
     sts_select::CutSmem cut;
     sts_select::Sub sub;
+    __attribute__((aligned(16))) u128 last[STS_FINAL_SORT]; // the terms the cut is among,
+    u32 last_share[STS_FINAL_SORT];                         // and their shares
     u32 kept[STS_SEL_SHARES];
-    u64 scan[SEL_NT / 64];
+    u32 side[STS_SEL_SHARES]; // window entries of each share's slab
+    u32 full;                 // a slab could not hold them
+    u64 scan[SEL_NW];
 };
 
 template <typename AT, int M>
 __global__ void __launch_bounds__(SEL_NT) k_bkt_select(const GateArg *__restrict__ gp, PassBufs b)
 {
     using namespace sts_select;
-    constexpr int NT = SEL_NT;
-    constexpr int UN = 8; // entries in flight per lane
+    constexpr int NT = SEL_NT, S = SEL_S;
     const GateArg &g = *gp;
     const GateLoc<M> gl = gate_loc<M>(g);
-    __shared__ BktSmem<AT, BW> s;
-    __shared__ SelectSmem m;
+    __shared__ SelectSmem<AT> m;
+    BktSmem<AT, SEL_NW> &s = m.u.bkt;
     DevCtl *ctl = b.ctl;
     const int t = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(t >> 6);
-    const u32 lane = (u32)sts_lane(), l16 = lane & 15u, g16 = (u32)t >> 4;
+    const u32 lane = (u32)sts_lane();
     const u32 ntiles = bkt_tiles(g.bkt), nsl = ntiles << 2;
     const int shift = b.slab_shift;
     // control words, read before the pick writes any
@@ -1323,21 +1327,40 @@ __global__ void __launch_bounds__(SEL_NT) k_bkt_select(const GateArg *__restrict
     const u32 over = ctl->w_over;
     const u64 K = ctl->K;
     const double l10 = ctl->log10_cum;
-    pick_level1<NT>(b, 0, 0, 0, m.u.l1, DeviceBins<NT>{b.h1});
+    // Every load the selection starts with is issued at once: the exponent
+    // bins, the shares' counts, and the first 64 window entries of S shares
+    // per wave, which stay in registers for all passes over the entries
+    const EarlyBins<NT> bins(b.h1);
+    const u32 room = 1u << shift;
+    const u32 sl_own = lane * (NT / 64) + (u32)wv; // the share whose count the lane holds
+    u32 ns0 = lane < (u32)S && sl_own < nsl ? b.t_side[sl_own] : 0u;
+    u64 wa[S];
+#pragma unroll
+    for (int i = 0; i < S; ++i) {
+        const u32 sl = (u32)(i * (NT / 64) + wv);
+        wa[i] = sl < nsl && lane < room ? b.side_w[((u64)sl << shift) + lane] : ~0ull;
+    }
+    for (u32 sl = t; sl < nsl; sl += NT) {
+        m.side[sl] = std::min(b.t_side[sl], room);
+        m.kept[sl] = b.t_above[sl];
+    }
+    for (int i = t; i < THIN_BINS * 3 / 2; i += NT) reinterpret_cast<u64 *>(m.raw)[i] = 0;
+    ns0 = std::min(ns0, room);
+    pick_level1<NT>(b, 0, 0, 0, m.u.l1, bins);
+#pragma unroll
+    for (int i = 0; i < S; ++i)
+        if (lane >= sts_readlane(ns0, i)) wa[i] = ~0ull; // no weight has all bits set
     __syncthreads();
     if (t < (int)(sizeof(Level1Cut) / sizeof(u64)))
         reinterpret_cast<u64 *>(&m.l1)[t] = reinterpret_cast<const u64 *>(&m.u.l1.cut)[t];
-    for (u32 sl = t; sl < nsl; sl += NT) m.kept[sl] = 0;
-    const bool all = m.u.l1.cut.keep_all;
-    if (!all && (over || (e_prev >= 0 && m.u.l1.cut.e != e_w && m.u.l1.cut.e != e_w + 1)))
-        smem_begin<AT, M, BW>(s, g); // uniform: the candidates will be computed again
+    if (t == 0) m.full = over;
     __syncthreads();
+    const bool all = m.l1.keep_all;
     const int e = m.l1.e;
-    // the slabs hold every candidate of the cut's exponent and above
-    const bool slabs = !all && !over && (e_prev < 0 || e == e_w || e == e_w + 1);
-    auto recompute = [&](auto body) { // body(share, weight bits, key, valid) for every candidate
-        for (u32 sl = (u32)wv; wv < BW && sl < nsl; sl += BW) {
+    auto recompute = [&](auto begin, auto body, auto end) { // of every share and candidate
+        for (u32 sl = (u32)wv; sl < nsl; sl += SEL_NW) {
             const Share sh = load_share(g.bkt, b.bd_in, sl >> 2, (int)(sl & 3u));
+            begin(sl);
             share_groups<AT, M>(s.w[wv], s.ucol, gl, sh, b.keys, (const AT *)b.amps,
                                 [&](const auto &ox, const auto &oy, u64 rest, bool active) {
 #pragma unroll
@@ -1345,26 +1368,60 @@ __global__ void __launch_bounds__(SEL_NT) k_bkt_select(const GateArg *__restrict
                     AT o;
                     o.x = ox[i];
                     o.y = oy[i];
-                    body(sl, weight_bits(o), rest | pattern_bits<M>(gl, i), active && nonzero(o));
+                    body(sl, weight_bits(o), rest | pattern_bits<M>(gl, i), o, active && nonzero(o));
                 }
             });
+            end(sl);
         }
     };
-    // body(share, w, index, in range) for every window entry, 16 lanes a share
-    auto entries = [&](auto body) {
-        for (u32 sl = g16; sl < nsl; sl += NT / 16) {
-            const u32 ns = b.t_side[sl];
-            const u64 base = (u64)sl << shift;
-            for (u32 i0 = l16; i0 < ns; i0 += 16 * UN) {
-                u64 w[UN];
+    // whether the slabs hold every candidate of the cut's exponent and above;
+    // when the window missed, they are filled again with those
+    const bool hit = all || e_prev < 0 || e == e_w || e == e_w + 1;
+    if (!hit || over) { // uniform
+        smem_begin<AT, M, SEL_NW>(s, g);
+        __syncthreads();
+    }
+    if (!hit && !over) {
+        SlabOut so;
+        recompute([&](u32) { so = SlabOut{0, 0, 0, true}; },
+                  [&](u32 sl, u64 w, u64 k, const AT &o, bool valid) {
+                      const int x = (int)(w >> 52);
+                      const u64 at = (u64)sl << shift;
+                      slab_put<AT>(so, b.side_key + at, b.side_w + at, (AT *)b.side_amp + at, room, valid && x == e,
+                                   valid && x > e, k, w, o);
+                  },
+                  [&](u32 sl) {
+                      if (lane == 0) {
+                          b.t_above[sl] = m.kept[sl] = so.c_ab;
+                          b.t_side[sl] = so.c_in;
+                          m.side[sl] = std::min(so.c_in, room);
+                          if (!so.fits) m.full = 1;
+                      }
+                  });
+        __threadfence_block();
+        __syncthreads();
+    }
+    const bool slabs = !all && !m.full;
+    // block(first share, first index, counts, w[S]) for 64 window entries of S
+    // shares (NT / 64 apart) at a time: those held in registers, then others.
+    // counts: lane i's is the i-th share's, entries past it have all bits set
+    auto entries = [&](auto block) {
+        for (u32 sl0 = (u32)wv; sl0 < nsl; sl0 += (u32)(S * (NT / 64))) {
+            const u32 sl = sl0 + lane * (NT / 64);
+            const u32 ns = lane < (u32)S && sl < nsl ? m.side[sl] : 0u;
+            for (u32 c0 = 0; wballot(ns > c0); c0 += 64) {
+                u64 w[S];
+                const u32 at = c0 + lane;
+                if (c0 == 0 && sl0 == (u32)wv && hit) {
 #pragma unroll
-                for (int r = 0; r < UN; ++r) {
-                    const u32 i = i0 + 16u * (u32)r;
-                    w[r] = i < ns ? b.side_w[base + i] : ~0ull; // no weight has all bits set
+                    for (int i = 0; i < S; ++i) w[i] = wa[i];
+                } else {
+#pragma unroll
+                    for (int i = 0; i < S; ++i)
+                        w[i] = at < sts_readlane(ns, i)
+                                   ? b.side_w[((u64)(sl0 + (u32)(i * (NT / 64))) << shift) + at] : ~0ull;
                 }
-#pragma unroll
-                for (int r = 0; r < UN; ++r)
-                    if (w[r] != ~0ull) body(sl, w[r], base + i0 + 16u * (u32)r);
+                block(sl0, c0, ns, w);
             }
         }
     };
@@ -1377,30 +1434,48 @@ __global__ void __launch_bounds__(SEL_NT) k_bkt_select(const GateArg *__restrict
             m.sub.count = m.l1.count;
         }
         __syncthreads();
+        // the weights of the subset under a prefix: from lo up to below hi (where
+        // the key decides, of those with the prefix's weight)
+        auto bounds = [&](int vshift, u128 vpre, u64 &lo, u64 &hi) {
+            const int sh = vshift < 64 ? 0 : vshift - 64;
+            const u64 top = (u64)(vshift < 64 ? vpre >> (64 - vshift) : vpre);
+            lo = ((u64)e << 52) | ((((1ull << (52 - sh)) - 1) - top) << sh);
+            hi = lo + (1ull << sh);
+        };
         auto each = [&](int vshift, u128 vpre, bool keyed, auto f) {
             if (!slabs) {
-                recompute([&](u32, u64 w, u64 k, bool valid) {
-                    const u128 v = rank_key(w, k);
-                    if (valid && (int)(w >> 52) == e && (v >> vshift) == vpre) f(v);
+                recompute([](u32) {},
+                          [&](u32, u64 w, u64 k, const AT &, bool valid) {
+                              const u128 v = rank_key(w, k);
+                              if (valid && (int)(w >> 52) == e && (v >> vshift) == vpre) f(v);
+                          },
+                          [](u32) {});
+                return;
+            }
+            u64 lo, hi;
+            bounds(vshift, vpre, lo, hi);
+            if (vshift == 116) {
+                entries([&](u32, u32 c0, u32 ns, const u64 (&w)[S]) {
+#pragma unroll
+                    for (int i = 0; i < S; ++i)
+                        if (sts_readlane(ns, i) > c0 && (u32)(w[i] >> 52) == (u32)e) f.first(w[i]);
                 });
                 return;
             }
-            const bool key_decides = vshift < 64;
-            const u64 hi = (u64)(key_decides ? vpre >> (64 - vshift) : vpre); // the prefix's part in the weight
-            const int hsh = key_decides ? 0 : vshift - 64;
-            entries([&](u32, u64 w, u64 i) {
-                const u64 vh = ((1ull << 52) - 1) - (w & ((1ull << 52) - 1));
-                if ((int)(w >> 52) != e || (vh >> hsh) != hi) return;
-                u128 v = (u128)vh << 64;
-                if (keyed || key_decides) {
-                    v |= (u128)b.side_key[i];
-                    if ((v >> vshift) != vpre) return;
+            entries([&](u32 sl0, u32 i0, u32, const u64 (&w)[S]) {
+                u32 in = 0;
+#pragma unroll
+                for (int i = 0; i < S; ++i) in |= w[i] - lo < hi - lo ? 1u << i : 0u;
+                while (in) { // a few: the first level took most
+                    const u64 at = ((u64)(sl0 + (u32)__builtin_ctz(in) * (NT / 64)) << shift) + i0 + lane;
+                    in &= in - 1;
+                    const u128 v = rank_key(b.side_w[at], keyed ? b.side_key[at] : 0ull);
+                    if (vshift >= 64 || (v >> vshift) == vpre) f(v);
                 }
-                f(v);
             });
         };
         const u128 R = make128(m.l1.R_lo, m.l1.R_hi);
-        bool ok = narrow_cut<NT, true>(each, e, K, R, m.sub, m.u.raw, m.cut, STS_FINAL_SORT);
+        bool ok = narrow_cut<NT, true>(each, e, K, R, m.sub, m.raw, m.cut, STS_FINAL_SORT, true);
         const int vshift = m.sub.vshift;
         const u128 vpre = m.sub.vpre;
         const u32 count = (u32)m.sub.count;
@@ -1420,57 +1495,68 @@ __global__ void __launch_bounds__(SEL_NT) k_bkt_select(const GateArg *__restrict
                 } else if (x == e && p == vpre) {
                     const u32 slot = atomicAdd(&m.cut.n, 1u);
                     if (slot < STS_FINAL_SORT) {
-                        m.u.last.v[slot] = rank_key(w, k);
-                        m.u.last.share[slot] = sl;
+                        m.last[slot] = rank_key(w, k);
+                        m.last_share[slot] = sl;
                     }
                 }
             };
             if (slabs) {
-                for (u32 sl = g16; sl < nsl; sl += NT / 16) { // 16 lanes a share
-                    const u32 ns = b.t_side[sl];
-                    const u64 base = (u64)sl << shift;
-                    u32 before = l16 == 0 ? b.t_above[sl] : 0u;
-                    for (u32 i0 = l16; i0 < ns; i0 += 16 * UN) {
-                        u64 w[UN];
+                // by the weight's high word; what that leaves open (the subset,
+                // as a rule) by all of it
+                u64 lo, hi;
+                bounds(vshift, vpre, lo, hi);
+                const u32 lo32 = (u32)(lo >> 32), top32 = (u32)((hi - 1) >> 32);
+                entries([&](u32 sl0, u32 i0, u32 ns, const u64 (&w)[S]) {
+                    u32 above = 0; // of lane i: the i-th share's
+                    u32 near = 0;
 #pragma unroll
-                        for (int r = 0; r < UN; ++r) {
-                            const u32 i = i0 + 16u * (u32)r;
-                            w[r] = i < ns ? b.side_w[base + i] : 0ull; // ranked last
-                        }
-#pragma unroll
-                        for (int r = 0; r < UN; ++r) {
-                            // the key only of the terms it could matter for
-                            const bool near = (int)(w[r] >> 52) == e &&
-                                              (vshift < 64 || (rank_key(w[r], 0) >> vshift) == vpre);
-                            const u64 k = near && i0 + 16u * (u32)r < ns ? b.side_key[base + i0 + 16u * (u32)r] : 0ull;
-                            if (i0 + 16u * (u32)r < ns) sort_out(sl, w[r], k, before);
-                        }
+                    for (int i = 0; i < S; ++i) {
+                        if (sts_readlane(ns, i) <= i0) continue;
+                        const u32 h = (u32)(w[i] >> 32);
+                        const u32 n = (u32)__popcll(wballot((int)h > (int)top32));
+                        above = lane == (u32)i ? n : above;
+                        near |= h - lo32 <= top32 - lo32 ? 1u << i : 0u;
                     }
-#pragma unroll
-                    for (int d = 8; d > 0; d >>= 1) before += __shfl_xor(before, d, 64);
-                    if (l16 == 0) m.kept[sl] = before;
-                }
-            } else {
-                recompute([&](u32 sl, u64 w, u64 k, bool valid) {
-                    u32 before = 0;
-                    if (valid) sort_out(sl, w, k, before);
-                    const u64 mk = wballot(before != 0);
-                    if (lane == 0) m.kept[sl] += (u32)__popcll(mk); // the share is this wave's
+                    if (lane < (u32)S && above) atomicAdd(&m.kept[sl0 + lane * (NT / 64)], above);
+                    while (near) {
+                        const u32 i = (u32)__builtin_ctz(near);
+                        near &= near - 1;
+                        const u32 sl = sl0 + i * (NT / 64);
+                        const u64 at = ((u64)sl << shift) + i0 + lane;
+                        u32 before = 0;
+                        sort_out(sl, b.side_w[at], b.side_key[at], before);
+                        if (before) atomicAdd(&m.kept[sl], 1u);
+                    }
                 });
+            } else {
+                for (u32 sl = t; sl < nsl; sl += NT) m.kept[sl] = 0;
+                __syncthreads();
+                recompute([](u32) {},
+                          [&](u32 sl, u64 w, u64 k, const AT &, bool valid) {
+                              u32 before = 0;
+                              if (valid) sort_out(sl, w, k, before);
+                              const u64 mk = wballot(before != 0);
+                              if (lane == 0) m.kept[sl] += (u32)__popcll(mk); // the share is this wave's
+                          },
+                          [](u32) {});
             }
             __syncthreads();
             ok = m.cut.n == count;
-            const u32 rank = rank_cut<NT>(m.u.last.v, count, e, K, R, m.sub, m.cut);
+            const u32 rank = rank_cut<NT>(m.last, count, e, K, R, m.sub, m.cut);
             ok = ok && m.cut.hit != 0xffffffffu;
-            if (ok && rank <= m.cut.hit) atomicAdd(&m.kept[m.u.last.share[t]], 1u);
+            if (ok && rank <= m.cut.hit) atomicAdd(&m.kept[m.last_share[t]], 1u);
         } else {
             ok = false; // no subset is larger once every bit of V is fixed
         }
-        if (!ok) { // uniform
-            if (t == 0) atomicOr(&ctl->flags, STS_F_UNRESOLVED);
-            return;
+        if (!ok) { // uniform; an internal inconsistency: reported, and no term kept
+            for (u32 sl = t; sl < nsl; sl += NT) m.kept[sl] = 0;
+            if (t == 0) {
+                atomicOr(&ctl->flags, STS_F_UNRESOLVED);
+                ctl->thr_wbits = ~0ull;
+                ctl->thr_key = 0;
+            }
         }
-        if (wv == NT / 64 - 1) finish_cut(ctl, m.cut, e, m.l1.S, m.l1.total, m.l1.W, l10);
+        if (ok && wv == NT / 64 - 1) finish_cut(ctl, m.cut, e, m.l1.S, m.l1.total, m.l1.W, l10);
     } else {
         for (u32 sl = t; sl < nsl; sl += NT) m.kept[sl] = b.w_all[sl];
     }

@@ -360,17 +360,39 @@ __device__ __forceinline__ u32 sts_xcd_tile(u32 b, u32 tiles)
     return x * q + (x < r ? x : r) + i;
 }
 
-// inclusive scan over the 64 lanes of a wave
-template <typename T>
-__device__ __forceinline__ T wave_incl_scan(T v)
+// a lane's value moved by a DPP control word; 0 where it has no source lane
+template <int CTRL, int ROWS = 0xf, typename T> __device__ __forceinline__ T sts_dpp(T v)
 {
-    const int lane = sts_lane();
+    int w[sizeof(T) / 4];
+    __builtin_memcpy(w, &v, sizeof(T));
 #pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        T o = __shfl_up(v, d, 64);
-        if (lane >= d) v += o;
-    }
+    for (u32 i = 0; i < sizeof(T) / 4; ++i) w[i] = __builtin_amdgcn_update_dpp(0, w[i], CTRL, ROWS, 0xf, false);
+    __builtin_memcpy(&v, w, sizeof(T));
     return v;
+}
+// lane i's value in every lane, i uniform
+template <typename T> __device__ __forceinline__ T sts_readlane(T v, int lane)
+{
+    int w[sizeof(T) / 4];
+    __builtin_memcpy(w, &v, sizeof(T));
+#pragma unroll
+    for (u32 i = 0; i < sizeof(T) / 4; ++i) w[i] = __builtin_amdgcn_readlane(w[i], lane);
+    __builtin_memcpy(&v, w, sizeof(T));
+    return v;
+}
+// inclusive sum over the lanes of a row of 16, or of the wave (no LDS traffic)
+template <typename T> __device__ __forceinline__ T row_incl_scan(T v)
+{
+    v += sts_dpp<0x111>(v); // from the lanes 1, 2, 4 and 8 below in the row
+    v += sts_dpp<0x112>(v);
+    v += sts_dpp<0x114>(v);
+    return v + sts_dpp<0x118>(v);
+}
+template <typename T> __device__ __forceinline__ T wave_incl_scan(T v)
+{
+    v = row_incl_scan(v);
+    v += sts_dpp<0x142, 0xa>(v);        // a row's last lane to the row above, rows 1 and 3
+    return v + sts_dpp<0x143, 0xc>(v);  // lane 31 to rows 2 and 3
 }
 
 // exclusive scan over a workgroup of NT threads (NT/64 waves); returns the
@@ -378,19 +400,15 @@ __device__ __forceinline__ T wave_incl_scan(T v)
 template <typename T, int NT>
 __device__ __forceinline__ T block_excl_scan(T v, T *scratch, T *total)
 {
+    static_assert(NT / 64 <= 16, "a wave total per lane of a row");
     const int lane = sts_lane();
-    const int w = threadIdx.x >> 6;
+    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     T inc = wave_incl_scan(v);
     if (lane == 63) scratch[w] = inc;
     __syncthreads();
-    T base = 0, tot = 0;
-#pragma unroll
-    for (int i = 0; i < NT / 64; ++i) {
-        const T s = scratch[i];
-        if (i < w) base += s;
-        tot += s;
-    }
+    const T tots = row_incl_scan(lane < NT / 64 ? scratch[lane] : (T)0);
     __syncthreads();
+    const T base = w > 0 ? sts_readlane(tots, w - 1) : (T)0, tot = sts_readlane(tots, NT / 64 - 1);
     *total = tot;
     return base + inc - v;
 }

@@ -143,41 +143,6 @@ __device__ inline void sub_store(const Sub &s, DevCtl *ctl)
     ctl->sub_count = s.count;
 }
 
-// Pick the first digit (ascending = rank order) where the rule is met, over
-// 2048 bins held in (cnt[], hi[], lo[]) - global (agent loads) or LDS - by NT
-// threads, and narrow *sub to it. K, R: the rule (R all ones = no p-mass).
-// Returns false if no digit qualifies.
-// inclusive scan of (count, mass) pairs over a workgroup of NT threads, in
-// place: wave scans, then the wave totals through LDS (one barrier; sc, sm
-// hold NT / 64 entries and are not read again before the caller's next
-// barrier)
-template <int NT>
-__device__ __forceinline__ void block_scan_cm(u64 &c, u128 &m, u64 *sc, u128 *sm)
-{
-    const int lane = sts_lane(), w = (int)threadIdx.x >> 6;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const u64 oc = __shfl_up(c, d, 64);
-        const u64 ol = __shfl_up((u64)m, d, 64), oh = __shfl_up((u64)(m >> 64), d, 64);
-        if (lane >= d) {
-            c += oc;
-            m += make128(ol, oh);
-        }
-    }
-    if (lane == 63) {
-        sc[w] = c;
-        sm[w] = m;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < NT / 64; ++i) {
-        if (i < w) {
-            c += sc[i];
-            m += sm[i];
-        }
-    }
-}
-
 // bins in three arrays (count, mantissa sum >> 26, & (2^26 - 1)), in device
 // memory that other workgroups wrote (agent loads) or in LDS
 struct AgentBins {
@@ -197,64 +162,88 @@ struct WideBins {
     }
 };
 
-// bins(d, count, mass): the 2048 bins
+// Pick the first digit (ascending = rank order) where the rule is met, over
+// 2048 bins - bins(d, count, mass) - by a workgroup of NT threads, and narrow
+// *sub to it. K, R: the rule (R all ones = no p-mass). Returns false if no
+// digit qualifies. Four waves do the work, each thread on some neighbouring
+// bins: the arithmetic of a workgroup that is alone on its CU costs its waves
+// times the instructions (with two bins per thread of 16 waves the pick took
+// 4.4 us instead of PICK_US). s_m, s_c: 4 entries.
 template <int NT, typename BINS>
 __device__ bool pick_digit(const BINS &bins, u64 K, u128 R, int dw, Sub *sub, u128 *s_m, u64 *s_c, u32 *s_hit)
 {
-    constexpr int PER = STS_NBIN / NT;
-    const int t = threadIdx.x;
-    u64 c[PER];
-    u128 ms[PER];
-    u64 cc = 0;
-    u128 mm = 0;
+    constexpr int PT = NT < 256 ? NT : 256, PER = STS_NBIN / PT, LG = 3;
+    static_assert(PER == 1 << LG, "a row of lanes takes a thread's bins");
+    const int t = threadIdx.x, lane = sts_lane(), wv = __builtin_amdgcn_readfirstlane(t >> 6);
+    // the subset as it is before this level (one thread narrows it after the barrier)
+    const u64 cnt0 = sub->cnt_before;
+    const u128 m0 = sub->mb;
+    // met by the terms up to a point of the ranking (some of them in the subset)
+    auto met = [&](u64 c, u128 m) { return c > 0 && ((K > 0 && cnt0 + c >= K) || m0 + m >= R); };
+    u64 c = 0;
+    u128 m = 0;
+    if (t < PT) {
 #pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        bins((u32)(PER * t + k), c[k], ms[k]);
-        cc += c[k];
-        mm += ms[k];
+        for (int k = 0; k < PER; ++k) {
+            u64 ck;
+            u128 mk;
+            bins((u32)(PER * t + k), ck, mk);
+            c += ck;
+            m += mk;
+        }
+        c = wave_incl_scan(c);
+        m = wave_incl_scan(m);
+        if (lane == 63) {
+            s_c[wv] = c;
+            s_m[wv] = m;
+        }
     }
-    const u64 own_c = cc;
-    const u128 own_m = mm;
-    if (t == 0) *s_hit = 0xffffffffu;
-    block_scan_cm<NT>(cc, mm, s_c, s_m);
-    // exclusive prefix of this thread's bins, from the subset's start
-    u64 cnt = sub->cnt_before + (cc - own_c);
-    u128 m = sub->mb + (mm - own_m);
-    u32 hit = 0xffffffffu;
-    u64 cnt_hit = 0;
-    u128 m_hit = 0;
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        if (hit == 0xffffffffu && c[k]) {
-            const bool hk = K > 0 && cnt + c[k] >= K;
-            const bool hp = m + ms[k] >= R;
-            if (hk || hp) {
-                hit = (u32)(PER * t + k);
-                cnt_hit = cnt;
-                m_hit = m;
-            } else {
-                cnt += c[k];
-                m += ms[k];
+    if (t == 0) *s_hit = 0;
+    __syncthreads();
+    // the wave, the lane and the bin that reach it first: the rule only grows
+    // along the ranking
+    if (t < PT) {
+        const u64 tc = row_incl_scan(lane < PT / 64 ? s_c[lane] : 0ull);
+        const u128 tm = row_incl_scan(lane < PT / 64 ? s_m[lane] : (u128)0);
+        u64 cb = 0;
+        u128 mb = 0;
+        if (wv > 0) {
+            cb = sts_readlane(tc, wv - 1);
+            mb = sts_readlane(tm, wv - 1);
+        }
+        const u64 hits = __ballot(met(cb + c, mb + m));
+        if (hits && !met(cb, mb)) { // uniform: this wave
+            const int L = __builtin_ctzll(hits);
+            if (L > 0) { // the terms before lane L
+                cb += sts_readlane(c, L - 1);
+                mb += sts_readlane(m, L - 1);
+            }
+            const u32 d = (u32)(PER * ((wv << 6) + L)) + (u32)(lane & (PER - 1));
+            u64 ck;
+            u128 mk;
+            bins(d, ck, mk);
+            u64 cs = ck;
+            u128 ms = mk;
+            cs += sts_dpp<0x111>(cs);
+            ms += sts_dpp<0x111>(ms);
+            cs += sts_dpp<0x112>(cs);
+            ms += sts_dpp<0x112>(ms);
+            cs += sts_dpp<0x114>(cs);
+            ms += sts_dpp<0x114>(ms);
+            const u64 first = __ballot(met(cb + cs, mb + ms)); // of lanes 0 to PER - 1; not 0
+            if (lane == __builtin_ctzll(first)) {
+                const u128 vpre = (sub->vpre << dw) | (u128)d;
+                sub->cnt_before = cnt0 + cb + cs - ck;
+                sub->mb = m0 + mb + ms - mk;
+                sub->vpre = vpre;
+                sub->vshift -= dw;
+                sub->count = ck;
+                *s_hit = 1;
             }
         }
     }
-    if (hit != 0xffffffffu) atomicMin(s_hit, hit);
     __syncthreads();
-    const u32 first = *s_hit;
-    if (first == 0xffffffffu) {
-        __syncthreads();
-        return false;
-    }
-    if (hit == first) {
-        const int k = (int)first - PER * t;
-        sub->vpre = (sub->vpre << dw) | (u128)first;
-        sub->vshift -= dw;
-        sub->cnt_before = cnt_hit;
-        sub->mb = m_hit;
-        sub->count = c[k];
-    }
-    __syncthreads();
-    return true;
+    return *s_hit != 0;
 }
 
 // within-exponent rank key: ascending V = descending weight, then ascending key
@@ -292,8 +281,8 @@ struct Level1Cut {
 template <int NT> struct Level1Smem {
     unsigned short e[STS_NBIN]; // the non-empty bins in rank order: exponent field,
     u64 c[STS_NBIN];   // count,
-    __attribute__((aligned(16))) u64 lo[STS_NBIN]; // mantissa sum (low, high words)
-    u64 hi[STS_NBIN];
+    // mantissa sum, as the three limbs that it takes from limb (unit bit / 64) on
+    __attribute__((aligned(16))) u64 p[3][STS_NBIN];
     u32 scan[NT / 64];
     u64 bw[NT / 64], bk[NT / 64];
     u64 w[6];
@@ -301,14 +290,13 @@ template <int NT> struct Level1Smem {
     u32 fine, hit2;
     u64 R_lo, R_hi;
     u64 chunk[4][64]; // exact mass of each quarter of the bin list (a limb per lane)
-    u64 chunk_c[4];   // and its count
     Level1Cut cut;
 };
 
 // the exponent bins in device memory
 template <int NT> struct DeviceBins {
     u64 *h1;
-    __device__ __forceinline__ void load(int e, u64 &c, u64 &hi, u64 &lo) const
+    __device__ __forceinline__ void load(int, int e, u64 &c, u64 &hi, u64 &lo) const
     {
         c = h1[e];
         hi = h1[STS_NBIN + e];
@@ -320,11 +308,28 @@ template <int NT> struct DeviceBins {
     }
 };
 
+// the same, the loads issued beforehand
+template <int NT> struct EarlyBins : DeviceBins<NT> {
+    u64 c[STS_NBIN / NT], hi[STS_NBIN / NT], lo[STS_NBIN / NT];
+    __device__ __forceinline__ EarlyBins(u64 *h1) : DeviceBins<NT>{h1}
+    {
+#pragma unroll
+        for (int k = 0; k < STS_NBIN / NT; ++k)
+            DeviceBins<NT>::load(k, 2047 - STS_NBIN / NT * (int)threadIdx.x - k, c[k], hi[k], lo[k]);
+    }
+    __device__ __forceinline__ void load(int k, int, u64 &ck, u64 &hk, u64 &lk) const
+    {
+        ck = c[k];
+        hk = hi[k];
+        lk = lo[k];
+    }
+};
+
 // predicted: 0 no window, 1 a window of the tiled passes, 3 a bucketed step
 // whose histogram pass ran (no window; the side buffer, if the extraction
 // pass fills it, is packed densely)
-// bins: load(e, count, mantissa sum >> 26, & (2^26 - 1)) of exponent field e,
-// and clear(t) by every thread when all are read
+// bins: load(k, e, count, mantissa sum >> 26, & (2^26 - 1)) of exponent field e,
+// the thread's k-th, and clear(t) by every thread when all are read
 template <int NT, typename BINS>
 __device__ void pick_level1(const PassBufs &b, int groups, int peak_only, int predicted, Level1Smem<NT> &sm,
                             const BINS &bins)
@@ -345,7 +350,7 @@ __device__ void pick_level1(const PassBufs &b, int groups, int peak_only, int pr
 #pragma unroll
     for (int k = 0; k < NB; ++k) {
         const int e = 2047 - NB * t - k;
-        bins.load(e, c[k], hi[k], lo[k]);
+        bins.load(k, e, c[k], hi[k], lo[k]);
     }
     // the per-workgroup peaks too (reduced below)
     constexpr int BPT = (STS_MAX_GROUPS + NT - 1) / NT;
@@ -396,8 +401,11 @@ __device__ void pick_level1(const PassBufs &b, int groups, int peak_only, int pr
         sm.e[at] = (unsigned short)(2047 - NB * t - k);
         sm.c[at] = c[k];
         const u128 ms = ((u128)hi[k] << 26) + (u128)lo[k];
-        sm.lo[at] = (u64)ms;
-        sm.hi[at] = (u64)(ms >> 64);
+        const int off = unit_bit(2047 - NB * t - k) & 63;
+        const u128 ml = ms << off;
+        sm.p[0][at] = (u64)ml;
+        sm.p[1][at] = (u64)(ml >> 64);
+        sm.p[2][at] = off ? (u64)(ms >> 64) >> (64 - off) : 0ull;
         ++at;
     }
     // peak: reduce the per-workgroup bests (written by the identity pass of
@@ -428,30 +436,55 @@ __device__ void pick_level1(const PassBufs &b, int groups, int peak_only, int pr
     }
     __syncthreads();
 
-    // exact sums of the listed bins in four chunks, one wave each (a chain of
-    // exact additions per bin, a quarter as long as over all bins; the wave
-    // that goes on walks the chunks, so that more of them would not pay)
+    // this lane's limb of bin j
+    auto piece = [&](u32 j) {
+        const u32 k = (u32)(t & 63) - ((u32)unit_bit((int)sm.e[j]) >> 6);
+        return k < 3u ? sm.p[k][j] : 0ull;
+    };
+    // exact sum of bins j0 to j1: limbs and their carries are added up
+    // separately, and the carries resolved once at the end
+    auto add_bins = [&](u64 start, u32 j0, u32 j1) {
+        u64 acc = start;
+        u32 carry = 0;
+#pragma unroll 4
+        for (u32 j = j0; j < j1; ++j) {
+            const u64 v = piece(j);
+            acc += v;
+            carry += acc < v ? 1u : 0u;
+        }
+        const u32 in = __shfl_up(carry, 1, 64);
+        return wl_add(acc, (t & 63) ? (u64)in : 0ull);
+    };
+    // in four chunks, one wave each
     const u32 chunk = (nbins + NC - 1) / NC;
     if (t < 64 * NC) {
         const int q = t >> 6;
-        const u32 j0 = (u32)q * chunk, j1 = j0 + chunk < nbins ? j0 + chunk : nbins;
-        u64 C = 0, nc = 0;
-        for (u32 j = j0; j < j1; ++j) {
-            C = wl_add(C, wl_piece(sm.lo[j], sm.hi[j], unit_bit((int)sm.e[j])));
-            nc += sm.c[j];
-        }
-        sm.chunk[q][t & 63] = C;
-        if ((t & 63) == 0) sm.chunk_c[q] = nc;
+        const u32 j0 = (u32)q * chunk < nbins ? (u32)q * chunk : nbins, j1 = j0 + chunk < nbins ? j0 + chunk : nbins;
+        sm.chunk[q][t & 63] = add_bins(0, j0, j1);
     }
     __syncthreads();
 
     if (t < 64) { // one wave: the total, the target and the cut's bin
         const int lane = t;
-        u64 W = 0, total_c = 0;
+        u64 W = 0;
 #pragma unroll
-        for (int q = 0; q < NC; ++q) {
-            W = wl_add(W, sm.chunk[q][lane]);
-            total_c += sm.chunk_c[q];
+        for (int q = 0; q < NC; ++q) W = wl_add(W, sm.chunk[q][lane]);
+        // the counts, and the masses as doubles in units of the first bin's
+        // lowest limb (a total off by less than 2^-40 of it)
+        auto approx = [&](u32 j) {
+            if (j >= nbins) return 0.0;
+            const int sh = (unit_bit((int)sm.e[j]) >> 6) - (unit_bit((int)sm.e[0]) >> 6); // <= 0
+            const double m = (double)sm.p[0][j] + 0x1p64 * ((double)sm.p[1][j] + 0x1p64 * (double)sm.p[2][j]);
+            return sh < -15 ? 0.0 : ldexp(m, 64 * sh);
+        };
+        const double p = ctl->p;
+        const bool p_on = p > 0.0 && p < 1.0, by_mass = p_on && !peak_only;
+        u64 total_c = 0;
+        double total_m = 0.0;
+        for (u32 j0 = 0; j0 < nbins; j0 += 64) {
+            const u32 j = j0 + (u32)lane;
+            total_c += sts_readlane(wave_incl_scan(j < nbins ? sm.c[j] : 0ull), 63);
+            if (by_mass) total_m += sts_readlane(wave_incl_scan(approx(j)), 63);
         }
         const double Wd = wl_to_double(W);
         if (peak_only) {
@@ -469,8 +502,6 @@ __device__ void pick_level1(const PassBufs &b, int groups, int peak_only, int pr
             }
         } else {
             const u64 K = ctl->K;
-            const double p = ctl->p;
-            const bool p_on = p > 0.0 && p < 1.0;
             // p-mass target T = ceil(p * W), exactly
             u64 T = 0;
             if (p_on) {
@@ -489,31 +520,39 @@ __device__ void pick_level1(const PassBufs &b, int groups, int peak_only, int pr
                 ctl->tot_updates += *b.n_in;
                 ctl->tot_cand += total_c;
             }
-            // the first bin in rank order where the rule is met: the first
-            // chunk through which it is met (the rule only grows along the
-            // ranking), then that chunk's bins
-            u64 S = 0, cnt = 0;
-            u32 hit = 0xffffffffu;
-            for (int q = 0; q < NC; ++q) {
-                const u64 inc_q = wl_add(S, sm.chunk[q][lane]);
-                const bool met_q = (K > 0 && cnt + sm.chunk_c[q] >= K) || (p_on && wl_cmp(inc_q, T) >= 0);
-                if (met_q) {
-                    const u32 j0 = (u32)q * chunk, j1 = j0 + chunk < nbins ? j0 + chunk : nbins;
-                    for (u32 j = j0; j < j1; ++j) {
-                        const u64 inc = wl_add(S, wl_piece(sm.lo[j], sm.hi[j], unit_bit((int)sm.e[j])));
-                        const bool hk = K > 0 && cnt + sm.c[j] >= K;
-                        const bool hp = p_on && wl_cmp(inc, T) >= 0;
-                        if (hk || hp) {
-                            hit = j;
-                            break;
-                        }
-                        S = inc;
-                        cnt += sm.c[j];
-                    }
+            // The first bin in rank order where the rule is met: the first
+            // that meets it on the count or may meet it on the mass, judged by
+            // doubles (error far below the margin); from there on exactly
+            const double T_low = p * total_m * (1.0 - 0x1p-30);
+            u32 hit = nbins;
+            u64 cnt = 0;
+            double m0 = 0.0;
+            for (u32 j0 = 0; j0 < nbins && hit == nbins; j0 += 64) {
+                const u32 j = j0 + (u32)lane;
+                const u64 cj = j < nbins ? sm.c[j] : 0ull;
+                const u64 ci = cnt + wave_incl_scan(cj);
+                const double mi = p_on ? m0 + wave_incl_scan(approx(j)) : 0.0;
+                const u64 may = __ballot(j < nbins && ((K > 0 && ci >= K) || (p_on && mi >= T_low)));
+                const int L = may ? __builtin_ctzll(may) : 63;
+                if (may) hit = j0 + (u32)L;
+                cnt = sts_readlane(may ? ci - cj : ci, L);
+                m0 = sts_readlane(mi, L);
+            }
+            u64 S = 0;
+            if (hit < nbins) {
+                u32 j0 = 0;
+                for (int q = 0; q < NC && j0 + chunk <= hit; ++q, j0 += chunk) S = wl_add(S, sm.chunk[q][lane]);
+                S = add_bins(S, j0 < hit ? j0 : hit, hit);
+            }
+            for (;; ++hit) {
+                if (hit >= nbins) {
+                    hit = 0xffffffffu;
                     break;
                 }
-                S = inc_q;
-                cnt += sm.chunk_c[q];
+                const u64 inc = wl_add(S, piece(hit));
+                if ((K > 0 && cnt + sm.c[hit] >= K) || (p_on && wl_cmp(inc, T) >= 0)) break;
+                S = inc;
+                cnt += sm.c[hit];
             }
             if (lane == 0) {
                 sm.cut.keep_all = hit == 0xffffffffu;
@@ -627,8 +666,8 @@ __device__ void pick_level1(const PassBufs &b, int groups, int peak_only, int pr
         // level 2 from the window's bins (the side pass then has nothing to
         // do); the bin lists above are done with, so their LDS serves the pick
         const u128 R = make128(sm.R_lo, sm.R_hi);
-        u128 *s_m = reinterpret_cast<u128 *>(sm.lo);
-        u64 *s_c2 = sm.hi;
+        u128 *s_m = reinterpret_cast<u128 *>(sm.p[0]);
+        u64 *s_c2 = sm.p[1];
         const bool ok = pick_digit<NT>(AgentBins{b.h2w}, ctl->K, R, 11, &sm.sub,
                                         s_m, s_c2, &sm.hit2);
         if (ok && t <= STS_SUB_REGIONS) st_agent(&b.sub_cnt[t * 32], 0u);
@@ -650,9 +689,9 @@ __device__ void pick_level1(const PassBufs &b, int groups, int peak_only, int pr
 // STS_FINAL_SORT terms are left, then find the exact cut among them.
 // each(vshift, vpre, keyed, f) calls f(V) for every term of the subset whose V
 // lies under the prefix (all threads take part; V's key half may be 0 unless
-// keyed). raw: STS_NBIN * 24 bytes of LDS, or * 12 when there are so few terms
+// keyed). raw: STS_NBIN * 24 bytes of LDS, or THIN_BINS * 12 when there are so few terms
 // (below 2^22) that 64 bits hold a bin's sum of the 41 mantissa bits that the
-// first level leaves open.
+// first level leaves open; cleared: the caller has zeroed it.
 // ---------------------------------------------------------------------------
 struct CutSmem {
     u128 m[1024 / 64];
@@ -673,6 +712,11 @@ __device__ __forceinline__ u64 digit_mant(u32 d, int e)
 
 constexpr u64 LOW41 = (1ull << 41) - 1;
 
+// LDS places of the thin bins: one free per eight, since a thread picks among
+// eight neighbouring bins
+constexpr int THIN_BINS = STS_NBIN + STS_NBIN / 8;
+__device__ __forceinline__ u32 thin_at(u32 d) { return d + (d >> 3); }
+
 // bins of one level: sums of the low 41 mantissa bits, and counts; the high
 // bits come from the bin (first level) or are common to the subset
 struct ThinBins {
@@ -683,35 +727,59 @@ struct ThinBins {
     u64 high;
     __device__ __forceinline__ void operator()(u32 d, u64 &c, u128 &m) const
     {
-        c = cnt[d];
-        m = (u128)(first ? digit_mant(d, e) : high) * c + (u128)low[d];
+        const u32 n = cnt[thin_at(d)];
+        c = n;
+        // (below 2^22 terms: the first level's product, in units of 2^41, fits 64 bits)
+        const u128 top = first ? (u128)((u64)((e ? 4095u : 2047u) - d) * n) << 41 : (u128)high * n;
+        m = top + (u128)low[thin_at(d)];
+    }
+};
+
+// what a level's pass does with every term
+template <bool THIN> struct Binner {
+    u64 *h;
+    u32 *hc;
+    int shift, dw, e;
+    __device__ __forceinline__ void operator()(const u128 v) const
+    {
+        const u32 d = (u32)((v >> shift) & (u128)((1u << dw) - 1));
+        const u64 mant = mant_of_v(v, e);
+        if (THIN) {
+            atomicAdd((unsigned long long *)&h[thin_at(d)], mant & LOW41);
+            atomicAdd(&hc[thin_at(d)], 1u);
+        } else {
+            atomicAdd((unsigned long long *)&h[d], 1ull);
+            atomicAdd((unsigned long long *)&h[STS_NBIN + d], mant >> 26);
+            atomicAdd((unsigned long long *)&h[2 * STS_NBIN + d], mant & ((1ull << 26) - 1));
+        }
+    }
+    // the same of a weight at the first level (shift 105, 11 bits)
+    __device__ __forceinline__ void first(u64 w) const
+    {
+        static_assert(THIN, "thin bins");
+        const u32 d = thin_at(2047u - ((u32)(w >> 41) & 2047u));
+        atomicAdd((unsigned long long *)&h[d], w & LOW41);
+        atomicAdd(&hc[d], 1u);
     }
 };
 
 template <int NT, bool THIN, typename E>
-__device__ bool narrow_cut(E &&each, int e, u64 K, u128 R, Sub &sub, unsigned char *raw, CutSmem &sm, u32 enough)
+__device__ bool narrow_cut(E &&each, int e, u64 K, u128 R, Sub &sub, unsigned char *raw, CutSmem &sm, u32 enough,
+                           bool cleared = false)
 {
     const int t = threadIdx.x;
     u64 *h = reinterpret_cast<u64 *>(raw);
-    u32 *hc = reinterpret_cast<u32 *>(h + STS_NBIN);
+    u32 *hc = reinterpret_cast<u32 *>(h + THIN_BINS);
     while (sub.count > enough && sub.vshift > 0) {
         const int vshift = sub.vshift;
         const int dw = vshift < 11 ? vshift : 11;
         const u128 vpre = sub.vpre;
-        for (int i = t; i < (THIN ? STS_NBIN * 3 / 2 : 3 * STS_NBIN); i += NT) h[i] = 0;
-        __syncthreads();
-        each(vshift, vpre, vshift - dw < 64, [&](const u128 v) {
-            const u32 d = (u32)((v >> (vshift - dw)) & (u128)((1u << dw) - 1));
-            const u64 mant = mant_of_v(v, e);
-            if (THIN) {
-                atomicAdd((unsigned long long *)&h[d], mant & LOW41);
-                atomicAdd(&hc[d], 1u);
-            } else {
-                atomicAdd((unsigned long long *)&h[d], 1ull);
-                atomicAdd((unsigned long long *)&h[STS_NBIN + d], mant >> 26);
-                atomicAdd((unsigned long long *)&h[2 * STS_NBIN + d], mant & ((1ull << 26) - 1));
-            }
-        });
+        if (!cleared) {
+            for (int i = t; i < (THIN ? THIN_BINS * 3 / 2 : 3 * STS_NBIN); i += NT) h[i] = 0;
+            __syncthreads();
+        }
+        cleared = false;
+        each(vshift, vpre, vshift - dw < 64, Binner<THIN>{h, hc, vshift - dw, dw, e});
         __syncthreads();
         bool ok;
         if (THIN) {

@@ -24,7 +24,7 @@ constexpr int SLOTS = 2 * STS_TINY_MAX;
 // exponent bins in LDS: sums of mantissa >> 26; & (2^26 - 1), plus count << 44
 struct LdsBins {
     u64 *s_hi, *s_lo;
-    __device__ __forceinline__ void load(int e, u64 &c, u64 &hi, u64 &lo) const
+    __device__ __forceinline__ void load(int, int e, u64 &c, u64 &hi, u64 &lo) const
     {
         c = s_lo[e] >> 44;
         hi = s_hi[e];
@@ -41,7 +41,7 @@ template <typename AT> struct TinySmem {
             unsigned long long slot[SLOTS]; // a group: the index + 1 of its member j at bit 16 j
         } g;
         Level1Smem<NT> l1;
-        __attribute__((aligned(16))) unsigned char raw[STS_NBIN * 12];
+        __attribute__((aligned(16))) unsigned char raw[THIN_BINS * 12];
     } u;
     u64 hi[STS_NBIN], lo[STS_NBIN];
     Level1Cut l1;
