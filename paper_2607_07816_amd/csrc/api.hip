@@ -285,6 +285,7 @@ PassBufs pass_bufs(sts_ctx *c, int in, int out)
     PassBufs b;
     std::memset(&b, 0, sizeof(b));
     b.gate = c->gate_dev;
+    b.gate_dst = c->dgate;
     b.keys = c->keys[in];
     b.amps = c->amps[in];
     b.n_in = &c->ctl->cnt[in];
@@ -648,6 +649,7 @@ sts_status materialise(sts_ctx *c)
     if (!c->pending) return STS_OK;
     const u64 cb = sat_shl(c->n_bound, c->gate.m);
     u64 bound = cb;
+    if (c->bkt_pending) STS_TRY(c, launch_set_gate(c->gate, c->dgate, c->stream));
     if (c->tiny_pending) {
         if (cb <= c->cap) {
             const int dst = (c->cur + 1) % 3;
@@ -885,15 +887,15 @@ sts_status sts_apply_gate(sts_ctx *c, int m, const int *qubits, const double *U)
         c->pending = c->tiny_pending = true;
         return STS_OK;
     }
-    STS_TRY(c, launch_set_gate(g, c->dgate, c->stream));
     c->gate_dev = c->dgate;
-    if (use_buckets(c, m)) {
+    if (use_buckets(c, m)) { // (the gate goes to the device with the next call's first kernel)
         st = bucketize(c);
         if (st != STS_OK) return st;
         c->gate = g;
         c->pending = c->bkt_pending = true;
         return STS_OK;
     }
+    STS_TRY(c, launch_set_gate(g, c->dgate, c->stream));
     c->bucketed = false;
     st = sort_state(c, &c->dgate->notmask, &sorted, &hb);
     if (st != STS_OK) return st;
@@ -921,18 +923,19 @@ static sts_status truncate_buckets(sts_ctx *c)
     if (!small && c->p == 0.0 && c->K && cb < c->K) {
         // nothing can be cut: the histogram for the statistics, then the write
         b.whole = 1;
+        STS_TRY(c, launch_set_gate(c->gate, c->dgate, c->stream));
         STS_LAUNCH(c, STS_K_GROUP_HIST, launch_bucket_pass(STS_BKT_HIST, c->prec, m, b, tiles, c->stream));
         STS_LAUNCH(c, STS_K_PICK1, launch_pick1(b, 0, 0, 0, c->stream));
         return bucket_write(c, b, out, nb);
     }
     if (small) {
-        STS_LAUNCH(c, STS_K_GROUP_HIST, launch_bucket_pass(STS_BKT_SMALL, c->prec, m, b, tiles, c->stream));
+        STS_LAUNCH(c, STS_K_GROUP_HIST, launch_bucket_pass(STS_BKT_SMALL, c->prec, m, b, tiles, c->stream, &c->gate));
         STS_LAUNCH(c, STS_K_FINAL, launch_bucket_pass(STS_BKT_SELECT, c->prec, m, b, tiles, c->stream));
         b.emit_copies = 1;
     } else {
         // a window from a sample; the histogram pass and its pick run only
         // when it missed
-        STS_LAUNCH(c, STS_K_SAMPLE, launch_bucket_pass(STS_BKT_SAMPLE, c->prec, m, b, tiles, c->stream));
+        STS_LAUNCH(c, STS_K_SAMPLE, launch_bucket_pass(STS_BKT_SAMPLE, c->prec, m, b, tiles, c->stream, &c->gate));
         STS_LAUNCH(c, STS_K_GROUP_HIST, launch_bucket_pass(STS_BKT_WEIGH, c->prec, m, b, tiles, c->stream));
         STS_LAUNCH(c, STS_K_PICK1, launch_pick_window(b, bucket_groups(c, true), c->stream));
         b.recover = 1;
@@ -1303,9 +1306,10 @@ const char *sts_strerror(sts_status s)
 // launches the same kernels with the same grids whenever the context starts
 // it from the same term buffer with the same size bound: every size the
 // kernels use is read from device memory, and the gate itself from the
-// context's device copy, written by one k_set_gate launch. Such a step is
-// captured into a HIP graph once and afterwards replayed with only that
-// launch's argument changed to the new gate.
+// context's device copy, written by the one launch that is given it: the
+// step's first kernel, or k_set_gate. Such a step is captured into a HIP graph
+// once and afterwards replayed with only that launch's argument changed to the
+// new gate.
 // ---------------------------------------------------------------------------
 struct StepGraph {
     int m, cur;
@@ -1389,7 +1393,7 @@ sts_status step_replayed(sts_ctx *c, StepGraphs *gs, int m, const int *qubits, c
         e.bucketed_after = c->bucketed;
         e.hb_after = c->hb;
         e.bdc_after = c->bdc;
-        // the one launch that writes the gate
+        // the one launch that is given the gate
         size_t nn = 0;
         hipError_t he = hipGraphGetNodes(graph, nullptr, &nn);
         std::vector<hipGraphNode_t> nodes(nn);
@@ -1399,7 +1403,9 @@ sts_status step_replayed(sts_ctx *c, StepGraphs *gs, int m, const int *qubits, c
             if (hipGraphNodeGetType(nodes[i], &t) != hipSuccess || t != hipGraphNodeTypeKernel) continue;
             hipKernelNodeParams p{};
             if (hipGraphKernelNodeGetParams(nodes[i], &p) == hipSuccess &&
-                (p.func == set_gate_kernel() || p.func == tiny_kernel(c->prec, m)))
+                (p.func == set_gate_kernel() || p.func == tiny_kernel(c->prec, m) ||
+                 (m <= 2 && (p.func == bucket_first_kernel(STS_BKT_SMALL, c->prec, m) ||
+                             p.func == bucket_first_kernel(STS_BKT_SAMPLE, c->prec, m)))))
                 e.set_node = nodes[i];
         }
         if (he == hipSuccess && !e.set_node) he = hipErrorNotFound;

@@ -4,8 +4,10 @@
 
 #include "kernels.h"
 
-hipError_t bucket_c128_pass(int kind, int m, const PassBufs &b, int tiles, hipStream_t s);
-hipError_t bucket_c64_pass(int kind, int m, const PassBufs &b, int tiles, hipStream_t s);
+hipError_t bucket_c128_pass(int kind, int m, const PassBufs &b, int tiles, hipStream_t s, const GateArg *first);
+const void *bucket_c128_first(int kind, int m);
+hipError_t bucket_c64_pass(int kind, int m, const PassBufs &b, int tiles, hipStream_t s, const GateArg *first);
+const void *bucket_c64_first(int kind, int m);
 hipError_t tiny_c128(const GateArg &g, const PassBufs &b, hipStream_t s);
 hipError_t tiny_c64(const GateArg &g, const PassBufs &b, hipStream_t s);
 const void *tiny_c128_kernel(int m);
@@ -127,9 +129,15 @@ hipError_t launch_tiny(int prec, const GateArg &g, const PassBufs &b, hipStream_
 
 const void *tiny_kernel(int prec, int m) { return prec == 0 ? tiny_c128_kernel(m) : tiny_c64_kernel(m); }
 
-hipError_t launch_bucket_pass(int kind, int prec, int m, const PassBufs &b, int tiles, hipStream_t s)
+hipError_t launch_bucket_pass(int kind, int prec, int m, const PassBufs &b, int tiles, hipStream_t s,
+                              const GateArg *first)
 {
-    return prec == 0 ? bucket_c128_pass(kind, m, b, tiles, s) : bucket_c64_pass(kind, m, b, tiles, s);
+    return prec == 0 ? bucket_c128_pass(kind, m, b, tiles, s, first) : bucket_c64_pass(kind, m, b, tiles, s, first);
+}
+
+const void *bucket_first_kernel(int kind, int prec, int m)
+{
+    return prec == 0 ? bucket_c128_first(kind, m) : bucket_c64_first(kind, m);
 }
 
 hipError_t launch_bucket_kept(const PassBufs &b, int tiles, hipStream_t s)

@@ -5,11 +5,11 @@
 
 #include "bucket_impl.h"
 
-hipError_t bucket_c64_pass(int kind, int m, const PassBufs &b, int tiles, hipStream_t s)
+hipError_t bucket_c64_pass(int kind, int m, const PassBufs &b, int tiles, hipStream_t s, const GateArg *first)
 {
     switch (m) {
-    case 1: return sts_bucket::launch_m<float2, 1>(kind, b, tiles, s);
-    case 2: return sts_bucket::launch_m<float2, 2>(kind, b, tiles, s);
+    case 1: return sts_bucket::launch_m<float2, 1>(kind, b, tiles, s, first);
+    case 2: return sts_bucket::launch_m<float2, 2>(kind, b, tiles, s, first);
     }
     return hipErrorInvalidValue;
 }
@@ -19,4 +19,9 @@ int bucket_c64_groups(int m, int tiles, bool weigh)
     using namespace sts_bucket;
     if (weigh) return m == 1 ? weigh_grid<float2, 1>(tiles) : weigh_grid<float2, 2>(tiles);
     return std::min(tiles, m == 1 ? hist_capacity_b<float2, 1>() : hist_capacity_b<float2, 2>());
+}
+
+const void *bucket_c64_first(int kind, int m)
+{
+    return m == 1 ? sts_bucket::first_kernel<float2, 1>(kind) : sts_bucket::first_kernel<float2, 2>(kind);
 }

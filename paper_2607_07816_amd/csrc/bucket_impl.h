@@ -534,6 +534,14 @@ __device__ __forceinline__ void slab_put(SlabOut &o, u64 *sk, u64 *sw, AT *sa, u
     o.c_ab += n_ab;
 }
 
+// the gate that a step's first kernel was given, into device memory
+__device__ __forceinline__ void put_gate(const GateArg &g, GateArg *dst)
+{
+    const u32 *src = reinterpret_cast<const u32 *>(&g);
+    u32 *d = reinterpret_cast<u32 *>(dst);
+    for (u32 i = threadIdx.x; i < sizeof(GateArg) / sizeof(u32); i += STS_WG) d[i] = src[i];
+}
+
 // a candidate's weight to the exponent bins
 __device__ __forceinline__ void bin_weight(const PassBufs &b, u64 *s_hi, u64 *s_lo, int hot_lo, u64 wb, bool direct)
 {
@@ -866,10 +874,12 @@ __global__ void __launch_bounds__(64 * WeighWaves<AT>::value, 1)
 // ---------------------------------------------------------------------------
 // sampling pass (as k_tile_sample): the gate on evenly spaced tiles
 // ---------------------------------------------------------------------------
+// (the gate comes by value and goes to device memory for the step's other
+// kernels: a launch of its own for that cost 5 us a step)
 template <typename AT, int M>
-__global__ void __launch_bounds__(STS_WG) k_bkt_sample(const GateArg *__restrict__ gp, PassBufs b)
+__global__ void __launch_bounds__(STS_WG) k_bkt_sample(GateArg g, PassBufs b)
 {
-    const GateArg &g = *gp;
+    if (blockIdx.x == 0) put_gate(g, b.gate_dst);
     const GateLoc<M> gl = gate_loc<M>(g);
     __shared__ BktSmem<AT, BW> s;
     __shared__ SampleSmem ss;
@@ -1589,9 +1599,9 @@ __global__ void __launch_bounds__(SEL_NT) k_bkt_select(const GateArg *__restrict
 }
 
 template <typename AT, int M>
-__global__ void __launch_bounds__(STS_WG) k_bkt_small(const GateArg *__restrict__ gp, PassBufs b)
+__global__ void __launch_bounds__(STS_WG) k_bkt_small(GateArg g, PassBufs b)
 {
-    const GateArg &g = *gp;
+    if (blockIdx.x == 0) put_gate(g, b.gate_dst);
     const GateLoc<M> gl = gate_loc<M>(g);
     __shared__ BktSmem<AT, BW> s;
     __shared__ u64 s_hi[TT_SLOTS], s_lo[TT_SLOTS];
@@ -1680,7 +1690,14 @@ template <typename AT, int M> int weigh_grid(int tiles)
     return std::min((tiles + per - 1) / per, weigh_capacity<AT, M>());
 }
 
-template <typename AT, int M> hipError_t launch_m(int kind, const PassBufs &b, int tiles, hipStream_t s)
+template <typename AT, int M> const void *first_kernel(int kind)
+{
+    return kind == STS_BKT_SAMPLE ? reinterpret_cast<const void *>(&k_bkt_sample<AT, M>)
+                                  : reinterpret_cast<const void *>(&k_bkt_small<AT, M>);
+}
+
+template <typename AT, int M>
+hipError_t launch_m(int kind, const PassBufs &b, int tiles, hipStream_t s, const GateArg *first)
 {
     // a pass that a truncated step launches in case its window missed is sized
     // to cost little when it exits at once: one workgroup per CU
@@ -1690,7 +1707,7 @@ template <typename AT, int M> hipError_t launch_m(int kind, const PassBufs &b, i
         hipLaunchKernelGGL((k_bkt_hist<AT, M>), dim3(std::min(tiles, cap)), dim3(STS_WG), 0, s, b.gate, b);
         break;
     case STS_BKT_SAMPLE:
-        hipLaunchKernelGGL((k_bkt_sample<AT, M>), dim3(STS_SAMPLE_TILES / 2), dim3(STS_WG), 0, s, b.gate, b);
+        hipLaunchKernelGGL((k_bkt_sample<AT, M>), dim3(STS_SAMPLE_TILES / 2), dim3(STS_WG), 0, s, *first, b);
         break;
     case STS_BKT_EXTRACT:
         hipLaunchKernelGGL((k_bkt_extract<AT, M>), dim3(std::min(tiles, cap)), dim3(STS_WG), 0, s, b.gate, b);
@@ -1707,7 +1724,7 @@ template <typename AT, int M> hipError_t launch_m(int kind, const PassBufs &b, i
         hipLaunchKernelGGL((k_bkt_copy<AT>), dim3(tiles), dim3(STS_WG), 0, s, b.gate, b);
         break;
     case STS_BKT_SMALL:
-        hipLaunchKernelGGL((k_bkt_small<AT, M>), dim3(std::min(tiles, 256)), dim3(STS_WG), 0, s, b.gate, b);
+        hipLaunchKernelGGL((k_bkt_small<AT, M>), dim3(std::min(tiles, 256)), dim3(STS_WG), 0, s, *first, b);
         break;
     case STS_BKT_SELECT:
         hipLaunchKernelGGL((k_bkt_select<AT, M>), dim3(1), dim3(SEL_NT), 0, s, b.gate, b);

@@ -29,7 +29,8 @@ struct GateArg {
 
 // Device buffers a grouping pass reads and writes.
 struct PassBufs {
-    const GateArg *gate;  // the gate (device memory: written by k_set_gate per gate)
+    const GateArg *gate;  // the gate (device memory, written per gate: by k_set_gate or the step's first kernel)
+    GateArg *gate_dst;    // where a first kernel that is given the gate writes it
     const u64 *keys;      // sorted input keys (or the state, m = 0)
     const void *amps;     // sorted input amplitudes
     const u64 *n_in;      // number of input terms (device)
@@ -203,7 +204,11 @@ const void *tiny_kernel(int prec, int m); // the kernel launch_tiny launches (to
 #define STS_BKT_SELECT 8
 #define STS_SEL_SHARES 1024 // most shares of a step whose selection is one workgroup
 #define STS_BKT_CHUNK 32 // tiles whose offsets are relative to one base
-hipError_t launch_bucket_pass(int kind, int prec, int m, const PassBufs &b, int tiles, hipStream_t s);
+// (first: the gate, for the two passes that a truncated step may begin with,
+// SAMPLE and SMALL; they put it into device memory for the others)
+hipError_t launch_bucket_pass(int kind, int prec, int m, const PassBufs &b, int tiles, hipStream_t s,
+                              const GateArg *first = nullptr);
+const void *bucket_first_kernel(int kind, int prec, int m); // the kernel of SAMPLE or SMALL
 int bucket_hist_groups(int prec, int m, int tiles, bool weigh); // workgroups of the histogram or weighing pass
 hipError_t launch_pick_window(const PassBufs &b, int groups, hipStream_t s);
 // survivors per share (when the window held the cut or nothing is cut), then every tile's output offset
