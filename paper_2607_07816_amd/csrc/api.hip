@@ -611,7 +611,7 @@ sts_status tiny_to_sorted(sts_ctx *c)
 // the pending one-launch step, its result in buffer dst
 sts_status tiny_step(sts_ctx *c, PassBufs &b, int dst, u64 bound)
 {
-    STS_LAUNCH(c, STS_K_FINAL, launch_tiny(c->prec, c->gate, b, c->stream));
+    STS_LAUNCH(c, STS_K_FINAL, launch_tiny(c->prec, c->gate, b, c->n_bound, c->stream));
     c->cur = dst;
     c->n_bound = bound;
     c->bucketed = false;
@@ -1403,8 +1403,9 @@ sts_status step_replayed(sts_ctx *c, StepGraphs *gs, int m, const int *qubits, c
             if (hipGraphNodeGetType(nodes[i], &t) != hipSuccess || t != hipGraphNodeTypeKernel) continue;
             hipKernelNodeParams p{};
             if (hipGraphKernelNodeGetParams(nodes[i], &p) == hipSuccess &&
-                (p.func == set_gate_kernel() || p.func == tiny_kernel(c->prec, m) ||
-                 (m <= 2 && (p.func == bucket_first_kernel(STS_BKT_SMALL, c->prec, m) ||
+                (p.func == set_gate_kernel() ||
+                 (m <= 2 && (is_tiny_kernel(p.func, c->prec, m) ||
+                             p.func == bucket_first_kernel(STS_BKT_SMALL, c->prec, m) ||
                              p.func == bucket_first_kernel(STS_BKT_SAMPLE, c->prec, m)))))
                 e.set_node = nodes[i];
         }

@@ -8,10 +8,10 @@ hipError_t bucket_c128_pass(int kind, int m, const PassBufs &b, int tiles, hipSt
 const void *bucket_c128_first(int kind, int m);
 hipError_t bucket_c64_pass(int kind, int m, const PassBufs &b, int tiles, hipStream_t s, const GateArg *first);
 const void *bucket_c64_first(int kind, int m);
-hipError_t tiny_c128(const GateArg &g, const PassBufs &b, hipStream_t s);
-hipError_t tiny_c64(const GateArg &g, const PassBufs &b, hipStream_t s);
-const void *tiny_c128_kernel(int m);
-const void *tiny_c64_kernel(int m);
+hipError_t tiny_c128(const GateArg &g, const PassBufs &b, u64 n_bound, hipStream_t s);
+hipError_t tiny_c64(const GateArg &g, const PassBufs &b, u64 n_bound, hipStream_t s);
+const void *tiny_c128_kernel(int m, int size);
+const void *tiny_c64_kernel(int m, int size);
 int bucket_c128_groups(int m, int tiles, bool weigh);
 int bucket_c64_groups(int m, int tiles, bool weigh);
 
@@ -122,12 +122,17 @@ int bucket_hist_groups(int prec, int m, int tiles, bool weigh)
     return prec == 0 ? bucket_c128_groups(m, tiles, weigh) : bucket_c64_groups(m, tiles, weigh);
 }
 
-hipError_t launch_tiny(int prec, const GateArg &g, const PassBufs &b, hipStream_t s)
+hipError_t launch_tiny(int prec, const GateArg &g, const PassBufs &b, u64 n_bound, hipStream_t s)
 {
-    return prec == 0 ? tiny_c128(g, b, s) : tiny_c64(g, b, s);
+    return prec == 0 ? tiny_c128(g, b, n_bound, s) : tiny_c64(g, b, n_bound, s);
 }
 
-const void *tiny_kernel(int prec, int m) { return prec == 0 ? tiny_c128_kernel(m) : tiny_c64_kernel(m); }
+bool is_tiny_kernel(const void *func, int prec, int m)
+{
+    for (int size = 0; size < 3; ++size)
+        if (func == (prec == 0 ? tiny_c128_kernel(m, size) : tiny_c64_kernel(m, size))) return true;
+    return false;
+}
 
 hipError_t launch_bucket_pass(int kind, int prec, int m, const PassBufs &b, int tiles, hipStream_t s,
                               const GateArg *first)

@@ -189,8 +189,8 @@ hipError_t launch_terms_out(const u64 *keys, const void *amps, int amp_bytes, co
 
 // steps of at most STS_TINY_MAX terms (tiny_impl.h): one launch, the gate passed by value
 #define STS_TINY_MAX 2048
-hipError_t launch_tiny(int prec, const GateArg &g, const PassBufs &b, hipStream_t s);
-const void *tiny_kernel(int prec, int m); // the kernel launch_tiny launches (to find its node in a captured graph)
+hipError_t launch_tiny(int prec, const GateArg &g, const PassBufs &b, u64 n_bound, hipStream_t s);
+bool is_tiny_kernel(const void *func, int prec, int m); // one that launch_tiny launches (to find its node in a captured graph)
 
 // bucketed steps (bucket_impl.h): gates of 1 and 2 qubits on a state in bucket order
 #define STS_BKT_HIST 0

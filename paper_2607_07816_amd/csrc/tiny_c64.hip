@@ -2,16 +2,16 @@
 // amplitudes.
 #include "tiny_impl.h"
 
-hipError_t tiny_c64(const GateArg &g, const PassBufs &b, hipStream_t s)
+hipError_t tiny_c64(const GateArg &g, const PassBufs &b, u64 n_bound, hipStream_t s)
 {
-    if (g.m == 1) hipLaunchKernelGGL((sts_tiny::k_tiny<float2, 1>), dim3(1), dim3(sts_tiny::NT), 0, s, g, b);
-    else if (g.m == 2) hipLaunchKernelGGL((sts_tiny::k_tiny<float2, 2>), dim3(1), dim3(sts_tiny::NT), 0, s, g, b);
-    else return hipErrorInvalidValue;
-    return hipGetLastError();
+    switch (g.m) {
+    case 1: return sts_tiny::launch<float2, 1>(g, b, n_bound, s);
+    case 2: return sts_tiny::launch<float2, 2>(g, b, n_bound, s);
+    }
+    return hipErrorInvalidValue;
 }
 
-const void *tiny_c64_kernel(int m)
+const void *tiny_c64_kernel(int m, int size)
 {
-    return m == 1 ? reinterpret_cast<const void *>(&sts_tiny::k_tiny<float2, 1>)
-                  : reinterpret_cast<const void *>(&sts_tiny::k_tiny<float2, 2>);
+    return m == 1 ? sts_tiny::kernel<float2, 1>(size) : sts_tiny::kernel<float2, 2>(size);
 }

@@ -17,9 +17,9 @@ namespace sts_tiny {
 using namespace sts_group;
 using namespace sts_select;
 
-constexpr int NT = 1024;
-constexpr int RPT = STS_TINY_MAX / NT;      // terms of a thread
-constexpr int SLOTS = 2 * STS_TINY_MAX;
+// Two terms per thread, in the smallest workgroup that holds the state: what
+// the one CU spends is its waves times the instructions of each.
+constexpr int RPT = 2;
 
 // exponent bins in LDS: sums of mantissa >> 26; & (2^26 - 1), plus count << 44
 struct LdsBins {
@@ -33,11 +33,12 @@ struct LdsBins {
     __device__ __forceinline__ void clear(int) const {}
 };
 
-template <typename AT> struct TinySmem {
+template <typename AT, int NT> struct TinySmem {
+    static constexpr int CAP = RPT * NT, SLOTS = 2 * CAP;
     union {
         struct {
-            AT amp[STS_TINY_MAX];
-            u64 key[STS_TINY_MAX];
+            AT amp[CAP];
+            u64 key[CAP];
             unsigned long long slot[SLOTS]; // a group: the index + 1 of its member j at bit 16 j
         } g;
         Level1Smem<NT> l1;
@@ -50,24 +51,25 @@ template <typename AT> struct TinySmem {
     u32 scan[NT / 64];
 };
 
-template <typename AT, int M>
+template <typename AT, int M, int NT>
 __global__ void __launch_bounds__(NT) k_tiny(GateArg g, PassBufs b)
 {
     typedef typename Scalar<AT>::T R;
     constexpr int NP = 1 << M;
-    __shared__ TinySmem<AT> s;
+    constexpr int CAP = TinySmem<AT, NT>::CAP, SLOTS = TinySmem<AT, NT>::SLOTS;
+    __shared__ TinySmem<AT, NT> s;
     DevCtl *ctl = b.ctl;
     const int t = threadIdx.x;
     const u64 nm = g.notmask;
     const u64 K = ctl->K;
     const double l10 = ctl->log10_cum;
-    const u32 n = (u32)*b.n_in; // at most STS_TINY_MAX (the host's bound)
+    const u32 n = (u32)*b.n_in; // at most CAP (the host's bound)
     const AT *amps = (const AT *)b.amps;
     u64 key[RPT];
 #pragma unroll
     for (int r = 0; r < RPT; ++r) {
         const u32 i = (u32)(r * NT + t);
-        if (i < n && i < STS_TINY_MAX) {
+        if (i < n && i < CAP) {
             key[r] = b.keys[i];
             s.u.g.key[i] = key[r];
             s.u.g.amp[i] = amps[i];
@@ -85,7 +87,7 @@ __global__ void __launch_bounds__(NT) k_tiny(GateArg g, PassBufs b)
 #pragma unroll
     for (int r = 0; r < RPT; ++r) {
         const u32 i = (u32)(r * NT + t);
-        if (i < n && i < STS_TINY_MAX) {
+        if (i < n && i < CAP) {
             const u64 rest = key[r] & nm;
             u32 j = 0;
 #pragma unroll
@@ -123,7 +125,7 @@ __global__ void __launch_bounds__(NT) k_tiny(GateArg g, PassBufs b)
         G.present = 0;
         group_clear<AT, M>(G);
         rest[r] = 0;
-        if (i < n && i < STS_TINY_MAX) {
+        if (i < n && i < CAP) {
             const unsigned long long word = s.u.g.slot[at[r]];
             bool lead = true;
 #pragma unroll
@@ -239,6 +241,22 @@ __global__ void __launch_bounds__(NT) k_tiny(GateArg g, PassBufs b)
         *b.n_out = base;
         if (base > b.out_cap) atomicOr(&ctl->flags, STS_F_OUT_OVERFLOW);
     }
+}
+
+template <typename AT, int M> const void *kernel(int size)
+{
+    return size == 0 ? reinterpret_cast<const void *>(&k_tiny<AT, M, 256>)
+                     : size == 1 ? reinterpret_cast<const void *>(&k_tiny<AT, M, 512>)
+                                 : reinterpret_cast<const void *>(&k_tiny<AT, M, 1024>);
+}
+
+template <typename AT, int M> hipError_t launch(const GateArg &g, const PassBufs &b, u64 n_bound, hipStream_t s)
+{
+    static_assert(STS_TINY_MAX == RPT * 1024, "the largest workgroup's terms");
+    if (n_bound <= RPT * 256) hipLaunchKernelGGL((k_tiny<AT, M, 256>), dim3(1), dim3(256), 0, s, g, b);
+    else if (n_bound <= RPT * 512) hipLaunchKernelGGL((k_tiny<AT, M, 512>), dim3(1), dim3(512), 0, s, g, b);
+    else hipLaunchKernelGGL((k_tiny<AT, M, 1024>), dim3(1), dim3(1024), 0, s, g, b);
+    return hipGetLastError();
 }
 
 } // namespace sts_tiny
