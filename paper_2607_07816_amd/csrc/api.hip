@@ -64,7 +64,9 @@ int bucket_bits(u64 n)
 constexpr u64 kBucketMax = 1ull << 28;
 // up to this size bound a step's selection is one workgroup's (k_bkt_select);
 // above, the step samples its window first and spreads the selection
-constexpr u64 kSelectMax = 1ull << 15;
+constexpr u64 kSelectMax = 1ull << 17;
+// up to this one that workgroup reads a window of two octaves; above, a sampled one
+constexpr u64 kSmallMax = 1ull << 15;
 
 Layout make_layout(u64 cap, int prec)
 {
@@ -110,7 +112,7 @@ Layout make_layout(u64 cap, int prec)
     L.tctr = take(16 * 4);
     L.dU = take(kULen * 8 + kULen * 4); // U in FP64, then its FP32 rounding
     L.sub_cnt = take((STS_SUB_REGIONS + 1) * 128);
-    L.wpart = take(7 * STS_MAX_GROUPS * 8);
+    L.wpart = take(9 * STS_MAX_GROUPS * 8);
     L.sbins = take(STS_SW_BANKS * (STS_SW_NB + 4) * 8);
     L.gate = take(2 * sizeof(GateArg)); // the current gate, and the identity
     L.total = o;
@@ -928,7 +930,13 @@ static sts_status truncate_buckets(sts_ctx *c)
         STS_LAUNCH(c, STS_K_PICK1, launch_pick1(b, 0, 0, 0, c->stream));
         return bucket_write(c, b, out, nb);
     }
-    if (small) {
+    if (small && c->n_bound > kSmallMax) {
+        b.fine_window = 1;
+        STS_LAUNCH(c, STS_K_SAMPLE, launch_bucket_pass(STS_BKT_SAMPLE, c->prec, m, b, tiles, c->stream, &c->gate));
+        STS_LAUNCH(c, STS_K_GROUP_HIST, launch_bucket_pass(STS_BKT_MID, c->prec, m, b, tiles, c->stream));
+        STS_LAUNCH(c, STS_K_FINAL, launch_bucket_pass(STS_BKT_SELECT_MID, c->prec, m, b, tiles, c->stream));
+        b.emit_copies = 1;
+    } else if (small) {
         STS_LAUNCH(c, STS_K_GROUP_HIST, launch_bucket_pass(STS_BKT_SMALL, c->prec, m, b, tiles, c->stream, &c->gate));
         STS_LAUNCH(c, STS_K_FINAL, launch_bucket_pass(STS_BKT_SELECT, c->prec, m, b, tiles, c->stream));
         b.emit_copies = 1;

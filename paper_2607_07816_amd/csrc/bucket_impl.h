@@ -913,7 +913,7 @@ __global__ void __launch_bounds__(STS_WG) k_bkt_sample(GateArg g, PassBufs b)
     }
     sample_flush(ss, acc, b, sts_lane() == 0 ? seen : 0u);
     if (!sts_last_block(&ctl->done[2], &ss.flag)) return;
-    sample_finish(ss, b, e_lo, *b.n_in);
+    sample_finish(ss, b, e_lo, *b.n_in, b.fine_window);
 }
 
 // ---------------------------------------------------------------------------
@@ -1300,11 +1300,19 @@ constexpr int SEL_NT = 512;
 constexpr int SEL_S = 32; // shares of which a wave holds up to 64 entries each
 
 constexpr int SEL_NW = SEL_NT / 64;
+constexpr u32 SEL_LIST = 8192; // entries of a sampled window that LDS holds
+constexpr int MID_GROUPS = 512; // most workgroups of k_bkt_mid
+__host__ __device__ __forceinline__ int mid_groups(u32 tiles) { return tiles < MID_GROUPS ? (int)tiles : MID_GROUPS; }
+
 
 template <typename AT> struct SelectSmem {
     union {
         sts_select::Level1Smem<SEL_NT> l1;
         BktSmem<AT, SEL_NW> bkt; // when candidates are computed again
+        struct {
+            u64 w[SEL_LIST];
+            unsigned short at[SEL_LIST]; // share << 5 | index in its slab
+        } list; // a sampled window's entries
     } u;
     __attribute__((aligned(16))) unsigned char raw[sts_select::THIN_BINS * 12];
     sts_select::Level1Cut l1;
@@ -1314,15 +1322,17 @@ template <typename AT> struct SelectSmem {
     u32 last_share[STS_FINAL_SORT];                         // and their shares
     u32 kept[STS_SEL_SHARES];
     u32 side[STS_SEL_SHARES]; // window entries of each share's slab
+    u32 first[STS_SEL_SHARES]; // its first entry in the list
     u32 full;                 // a slab could not hold them
     u64 scan[SEL_NW];
 };
 
-template <typename AT, int M>
+template <typename AT, int M, bool MID>
 __global__ void __launch_bounds__(SEL_NT) k_bkt_select(const GateArg *__restrict__ gp, PassBufs b)
 {
     using namespace sts_select;
     constexpr int NT = SEL_NT, S = SEL_S;
+    static_assert(STS_SEL_SHARES <= 1 << 11, "a share and an index below 32 in 16 bits");
     const GateArg &g = *gp;
     const GateLoc<M> gl = gate_loc<M>(g);
     __shared__ SelectSmem<AT> m;
@@ -1334,12 +1344,14 @@ __global__ void __launch_bounds__(SEL_NT) k_bkt_select(const GateArg *__restrict
     const int shift = b.slab_shift;
     // control words, read before the pick writes any
     const int e_prev = ctl->e_pred, e_w = small_window(ctl);
+    const bool sampled = MID && ctl->w_mode;
     const u32 over = ctl->w_over;
     const u64 K = ctl->K;
     const double l10 = ctl->log10_cum;
     // Every load the selection starts with is issued at once: the exponent
     // bins, the shares' counts, and the first 64 window entries of S shares
-    // per wave, which stay in registers for all passes over the entries
+    // per wave, which stay in registers for all passes over the entries (a
+    // sampled window's are few, and scattered: read again by each pass)
     const EarlyBins<NT> bins(b.h1);
     const u32 room = 1u << shift;
     const u32 sl_own = lane * (NT / 64) + (u32)wv; // the share whose count the lane holds
@@ -1348,7 +1360,7 @@ __global__ void __launch_bounds__(SEL_NT) k_bkt_select(const GateArg *__restrict
 #pragma unroll
     for (int i = 0; i < S; ++i) {
         const u32 sl = (u32)(i * (NT / 64) + wv);
-        wa[i] = sl < nsl && lane < room ? b.side_w[((u64)sl << shift) + lane] : ~0ull;
+        wa[i] = !MID && sl < nsl && lane < room ? b.side_w[((u64)sl << shift) + lane] : ~0ull;
     }
     for (u32 sl = t; sl < nsl; sl += NT) {
         m.side[sl] = std::min(b.t_side[sl], room);
@@ -1356,10 +1368,11 @@ __global__ void __launch_bounds__(SEL_NT) k_bkt_select(const GateArg *__restrict
     }
     for (int i = t; i < THIN_BINS * 3 / 2; i += NT) reinterpret_cast<u64 *>(m.raw)[i] = 0;
     ns0 = std::min(ns0, room);
-    pick_level1<NT>(b, 0, 0, 0, m.u.l1, bins);
+    pick_level1<NT>(b, sampled ? mid_groups(ntiles) : 0, 0, sampled ? 2 : 0, m.u.l1, bins);
 #pragma unroll
-    for (int i = 0; i < S; ++i)
-        if (lane >= sts_readlane(ns0, i)) wa[i] = ~0ull; // no weight has all bits set
+    for (int i = 0; i < S; ++i) { // no weight has all bits set
+        if (lane >= sts_readlane(ns0, i)) wa[i] = ~0ull;
+    }
     __syncthreads();
     if (t < (int)(sizeof(Level1Cut) / sizeof(u64)))
         reinterpret_cast<u64 *>(&m.l1)[t] = reinterpret_cast<const u64 *>(&m.u.l1.cut)[t];
@@ -1367,12 +1380,12 @@ __global__ void __launch_bounds__(SEL_NT) k_bkt_select(const GateArg *__restrict
     __syncthreads();
     const bool all = m.l1.keep_all;
     const int e = m.l1.e;
-    auto recompute = [&](auto begin, auto body, auto end) { // of every share and candidate
+    auto recompute = [&](auto begin, auto body, auto end) __attribute__((always_inline)) { // of every share and candidate
         for (u32 sl = (u32)wv; sl < nsl; sl += SEL_NW) {
             const Share sh = load_share(g.bkt, b.bd_in, sl >> 2, (int)(sl & 3u));
             begin(sl);
             share_groups<AT, M>(s.w[wv], s.ucol, gl, sh, b.keys, (const AT *)b.amps,
-                                [&](const auto &ox, const auto &oy, u64 rest, bool active) {
+                                [&](const auto &ox, const auto &oy, u64 rest, bool active) __attribute__((always_inline)) {
 #pragma unroll
                 for (int i = 0; i < (1 << M); ++i) {
                     AT o;
@@ -1386,21 +1399,71 @@ __global__ void __launch_bounds__(SEL_NT) k_bkt_select(const GateArg *__restrict
     };
     // whether the slabs hold every candidate of the cut's exponent and above;
     // when the window missed, they are filled again with those
-    const bool hit = all || e_prev < 0 || e == e_w || e == e_w + 1;
+    const bool hit = all || (MID ? !sampled || m.l1.in_window : e_prev < 0 || e == e_w || e == e_w + 1);
+    const bool win = MID && sampled && hit && !over; // the cut lies in the sampled window
+    // such a window has a few entries a share: they are listed in LDS, four
+    // lanes a share, so that the passes over them run without gaps
+    u32 listed = 0;
+    if (win && !all) {
+        constexpr u32 PER = STS_SEL_SHARES / NT; // neighbouring shares of a thread
+        u32 ns[PER], sum = 0, most = 0;
+#pragma unroll
+        for (u32 r = 0; r < PER; ++r) {
+            const u32 sl = (u32)t * PER + r;
+            ns[r] = sl < nsl ? m.side[sl] : 0u;
+            sum += ns[r];
+            most = std::max(most, ns[r]);
+        }
+        if (t == 0) m.full = 0;
+        __syncthreads(); // (the bins' lists are read: the list takes their place)
+        if (most >= 32) m.full = 1;
+        u32 total, first = block_excl_scan<u32, NT>(sum, reinterpret_cast<u32 *>(m.scan), &total);
+#pragma unroll
+        for (u32 r = 0; r < PER; ++r) {
+            m.first[(u32)t * PER + r] = first;
+            first += ns[r];
+        }
+        __syncthreads();
+        listed = total <= SEL_LIST && !m.full ? total : 0u;
+        if (listed) {
+            constexpr u32 LN = 4, ROUNDS = STS_SEL_SHARES / (NT / LN);
+            const u32 own = (u32)t / LN, l = (u32)t % LN;
+            u64 w[ROUNDS];
+#pragma unroll
+            for (u32 r = 0; r < ROUNDS; ++r) { // every share's load in flight at once
+                const u32 sl = own + r * (NT / LN);
+                w[r] = sl < nsl && l < room ? b.side_w[((u64)sl << shift) + l] : 0ull;
+            }
+#pragma unroll
+            for (u32 r = 0; r < ROUNDS; ++r) {
+                const u32 sl = own + r * (NT / LN);
+                const u32 n = sl < nsl ? m.side[sl] : 0u;
+                for (u32 i = l; i < n; i += LN) {
+                    const u32 at = m.first[sl] + i;
+                    m.u.list.w[at] = i < LN ? w[r] : b.side_w[((u64)sl << shift) + i];
+                    m.u.list.at[at] = (unsigned short)(sl << 5 | i);
+                }
+            }
+        }
+        __syncthreads();
+        if (t == 0) m.full = 0;
+        __syncthreads();
+    }
+
     if (!hit || over) { // uniform
         smem_begin<AT, M, SEL_NW>(s, g);
         __syncthreads();
     }
     if (!hit && !over) {
         SlabOut so;
-        recompute([&](u32) { so = SlabOut{0, 0, 0, true}; },
-                  [&](u32 sl, u64 w, u64 k, const AT &o, bool valid) {
+        recompute([&](u32) __attribute__((always_inline)) { so = SlabOut{0, 0, 0, true}; },
+                  [&](u32 sl, u64 w, u64 k, const AT &o, bool valid) __attribute__((always_inline)) {
                       const int x = (int)(w >> 52);
                       const u64 at = (u64)sl << shift;
                       slab_put<AT>(so, b.side_key + at, b.side_w + at, (AT *)b.side_amp + at, room, valid && x == e,
                                    valid && x > e, k, w, o);
                   },
-                  [&](u32 sl) {
+                  [&](u32 sl) __attribute__((always_inline)) {
                       if (lane == 0) {
                           b.t_above[sl] = m.kept[sl] = so.c_ab;
                           b.t_side[sl] = so.c_in;
@@ -1414,15 +1477,15 @@ __global__ void __launch_bounds__(SEL_NT) k_bkt_select(const GateArg *__restrict
     const bool slabs = !all && !m.full;
     // block(first share, first index, counts, w[S]) for 64 window entries of S
     // shares (NT / 64 apart) at a time: those held in registers, then others.
-    // counts: lane i's is the i-th share's, entries past it have all bits set
-    auto entries = [&](auto block) {
+    // counts: lane i's is the i-th share's, entries past it have all bits set.
+    auto entries = [&](auto block) __attribute__((always_inline)) {
         for (u32 sl0 = (u32)wv; sl0 < nsl; sl0 += (u32)(S * (NT / 64))) {
             const u32 sl = sl0 + lane * (NT / 64);
             const u32 ns = lane < (u32)S && sl < nsl ? m.side[sl] : 0u;
             for (u32 c0 = 0; wballot(ns > c0); c0 += 64) {
                 u64 w[S];
                 const u32 at = c0 + lane;
-                if (c0 == 0 && sl0 == (u32)wv && hit) {
+                if (!MID && c0 == 0 && sl0 == (u32)wv && hit) {
 #pragma unroll
                     for (int i = 0; i < S; ++i) w[i] = wa[i];
                 } else {
@@ -1437,25 +1500,29 @@ __global__ void __launch_bounds__(SEL_NT) k_bkt_select(const GateArg *__restrict
     };
     if (!all) {
         if (t == 0) {
-            m.sub.cnt_before = m.l1.cnt;
-            m.sub.mb = 0;
+            m.sub.cnt_before = win ? m.l1.w_cnt : m.l1.cnt;
+            m.sub.mb = win ? make128(m.l1.w_mb_lo, m.l1.w_mb_hi) : (u128)0;
             m.sub.vpre = 0;
             m.sub.vshift = 116;
-            m.sub.count = m.l1.count;
+            m.sub.count = win ? m.l1.w_count : m.l1.count;
         }
         __syncthreads();
         // the weights of the subset under a prefix: from lo up to below hi (where
         // the key decides, of those with the prefix's weight)
-        auto bounds = [&](int vshift, u128 vpre, u64 &lo, u64 &hi) {
+        auto bounds = [&](int vshift, u128 vpre, u64 &lo, u64 &hi) __attribute__((always_inline)) {
             const int sh = vshift < 64 ? 0 : vshift - 64;
             const u64 top = (u64)(vshift < 64 ? vpre >> (64 - vshift) : vpre);
             lo = ((u64)e << 52) | ((((1ull << (52 - sh)) - 1) - top) << sh);
             hi = lo + (1ull << sh);
         };
-        auto each = [&](int vshift, u128 vpre, bool keyed, auto f) {
+        auto place = [&](u32 i) __attribute__((always_inline)) { // of a listed entry in the side buffer
+            const u32 at = m.u.list.at[i];
+            return ((u64)(at >> 5) << shift) + (at & 31u);
+        };
+        auto each = [&](int vshift, u128 vpre, bool keyed, auto f) __attribute__((always_inline)) {
             if (!slabs) {
                 recompute([](u32) {},
-                          [&](u32, u64 w, u64 k, const AT &, bool valid) {
+                          [&](u32, u64 w, u64 k, const AT &, bool valid) __attribute__((always_inline)) {
                               const u128 v = rank_key(w, k);
                               if (valid && (int)(w >> 52) == e && (v >> vshift) == vpre) f(v);
                           },
@@ -1464,20 +1531,31 @@ __global__ void __launch_bounds__(SEL_NT) k_bkt_select(const GateArg *__restrict
             }
             u64 lo, hi;
             bounds(vshift, vpre, lo, hi);
+            if (listed) {
+                for (u32 i = t; i < listed; i += NT) {
+                    const u64 w = m.u.list.w[i];
+                    if (w - lo >= hi - lo) continue;
+                    const u64 k = keyed ? b.side_key[place(i)] : 0ull;
+                    const u128 v = rank_key(w, k);
+                    if (vshift >= 64 || (v >> vshift) == vpre) f(v);
+                }
+                return;
+            }
             if (vshift == 116) {
-                entries([&](u32, u32 c0, u32 ns, const u64 (&w)[S]) {
+                entries([&](u32, u32 c0, u32 ns, const u64 (&w)[S]) __attribute__((always_inline)) {
 #pragma unroll
                     for (int i = 0; i < S; ++i)
                         if (sts_readlane(ns, i) > c0 && (u32)(w[i] >> 52) == (u32)e) f.first(w[i]);
                 });
                 return;
             }
-            entries([&](u32 sl0, u32 i0, u32, const u64 (&w)[S]) {
+            entries([&](u32 sl0, u32 i0, u32, const u64 (&w)[S]) __attribute__((always_inline)) {
                 u32 in = 0;
 #pragma unroll
                 for (int i = 0; i < S; ++i) in |= w[i] - lo < hi - lo ? 1u << i : 0u;
                 while (in) { // a few: the first level took most
-                    const u64 at = ((u64)(sl0 + (u32)__builtin_ctz(in) * (NT / 64)) << shift) + i0 + lane;
+                    const u32 i = (u32)__builtin_ctz(in);
+                    const u64 at = ((u64)(sl0 + i * (NT / 64)) << shift) + i0 + lane;
                     in &= in - 1;
                     const u128 v = rank_key(b.side_w[at], keyed ? b.side_key[at] : 0ull);
                     if (vshift >= 64 || (v >> vshift) == vpre) f(v);
@@ -1497,7 +1575,7 @@ __global__ void __launch_bounds__(SEL_NT) k_bkt_select(const GateArg *__restrict
         if (ok && count <= STS_FINAL_SORT) {
             // list the subset and, in the same pass, count the survivors
             // ranked before it, share by share
-            auto sort_out = [&](u32 sl, u64 w, u64 k, u32 &before) {
+            auto sort_out = [&](u32 sl, u64 w, u64 k, u32 &before) __attribute__((always_inline)) {
                 const int x = (int)(w >> 52);
                 const u128 p = rank_key(w, k) >> vshift;
                 if (x > e || (x == e && p < vpre)) {
@@ -1516,16 +1594,25 @@ __global__ void __launch_bounds__(SEL_NT) k_bkt_select(const GateArg *__restrict
                 u64 lo, hi;
                 bounds(vshift, vpre, lo, hi);
                 const u32 lo32 = (u32)(lo >> 32), top32 = (u32)((hi - 1) >> 32);
-                entries([&](u32 sl0, u32 i0, u32 ns, const u64 (&w)[S]) {
+                if (listed) {
+                    for (u32 i = t; i < listed; i += NT) {
+                        const u64 w = m.u.list.w[i];
+                        if (w < lo) continue;
+                        const u32 sl = (u32)m.u.list.at[i] >> 5;
+                        u32 before = w >= hi ? 1u : 0u;
+                        if (!before) sort_out(sl, w, b.side_key[place(i)], before);
+                        if (before) atomicAdd(&m.kept[sl], 1u);
+                    }
+                } else entries([&](u32 sl0, u32 i0, u32 ns, const u64 (&w)[S]) __attribute__((always_inline)) {
                     u32 above = 0; // of lane i: the i-th share's
                     u32 near = 0;
 #pragma unroll
                     for (int i = 0; i < S; ++i) {
                         if (sts_readlane(ns, i) <= i0) continue;
                         const u32 h = (u32)(w[i] >> 32);
+                        near |= h - lo32 <= top32 - lo32 ? 1u << i : 0u;
                         const u32 n = (u32)__popcll(wballot((int)h > (int)top32));
                         above = lane == (u32)i ? n : above;
-                        near |= h - lo32 <= top32 - lo32 ? 1u << i : 0u;
                     }
                     if (lane < (u32)S && above) atomicAdd(&m.kept[sl0 + lane * (NT / 64)], above);
                     while (near) {
@@ -1542,7 +1629,7 @@ __global__ void __launch_bounds__(SEL_NT) k_bkt_select(const GateArg *__restrict
                 for (u32 sl = t; sl < nsl; sl += NT) m.kept[sl] = 0;
                 __syncthreads();
                 recompute([](u32) {},
-                          [&](u32 sl, u64 w, u64 k, const AT &, bool valid) {
+                          [&](u32 sl, u64 w, u64 k, const AT &, bool valid) __attribute__((always_inline)) {
                               u32 before = 0;
                               if (valid) sort_out(sl, w, k, before);
                               const u64 mk = wballot(before != 0);
@@ -1598,13 +1685,13 @@ __global__ void __launch_bounds__(SEL_NT) k_bkt_select(const GateArg *__restrict
     }
 }
 
-template <typename AT, int M>
-__global__ void __launch_bounds__(STS_WG) k_bkt_small(GateArg g, PassBufs b)
+template <typename AT, int M, bool MID>
+__device__ __forceinline__ void small_pass(const GateArg &g, const PassBufs &b)
 {
-    if (blockIdx.x == 0) put_gate(g, b.gate_dst);
     const GateLoc<M> gl = gate_loc<M>(g);
     __shared__ BktSmem<AT, BW> s;
     __shared__ u64 s_hi[TT_SLOTS], s_lo[TT_SLOTS];
+    __shared__ u64 s_win[9]; // as pick_level1 takes them
     DevCtl *ctl = b.ctl;
     smem_begin<AT, M, BW>(s, g);
     for (int i = threadIdx.x; i < TT_SLOTS; i += STS_WG) {
@@ -1616,8 +1703,25 @@ __global__ void __launch_bounds__(STS_WG) k_bkt_small(GateArg g, PassBufs b)
     const u32 nsl = bkt_tiles(g.bkt) << 2;
     const int e_prev = ctl->e_pred;
     const int e_w = small_window(ctl);
-    // the window, in the weight's high word; without a previous cut, everything
-    const u32 wL = uni(e_prev >= 0 ? (u32)e_w << 20 : 0u), wH = uni(e_prev >= 0 ? (u32)(e_w + 2) << 20 : ~0u);
+    // the window, in the weight's high word (whose bits decide it); without a
+    // previous cut or a sample's window, everything
+    const bool sampled = MID && ctl->w_mode;
+    u32 wL = 0u, wH = ~0u;
+    if (sampled) {
+        wL = (u32)(ctl->w_lo >> 32);
+        wH = (u32)(ctl->w_hi >> 32) + 1u;
+    } else if (!MID && e_prev >= 0) {
+        wL = (u32)e_w << 20;
+        wH = (u32)(e_w + 2) << 20;
+    }
+    wL = uni(wL);
+    wH = uni(wH);
+    // the sampled window's (upper) exponent, and mantissa sums in it above the
+    // window and inside, and inside in the exponent below
+    const u32 e_beg = uni(((wH - 1u) >> 20) << 20), e_end = e_beg + (1u << 20);
+    u64 ab_hi = 0, ab_lo = 0, in_hi = 0, in_lo = 0, un_hi = 0, un_lo = 0;
+    u32 n_ab = 0, n_in = 0, n_un = 0;
+    if (threadIdx.x < 9) s_win[threadIdx.x] = 0;
     const int shift = b.slab_shift;
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int hot_lo = (e_prev >= 0 ? e_prev : TT_EBASE + 116) - (TT_HOT - 4);
@@ -1644,6 +1748,20 @@ __global__ void __launch_bounds__(STS_WG) k_bkt_small(GateArg g, PassBufs b)
                 const u32 hw = (u32)(wb >> 32);
                 if (cand) bin_weight(b, s_hi, s_lo, hot_lo, wb, direct);
                 so.c_all += (u32)__popcll(wballot(cand));
+                if (sampled && cand && hw >= wL && hw < e_end) { // uniform, then of some lanes
+                    const u64 mant = sts_mant(wb);
+                    const bool un = hw < e_beg, in = hw < wH && !un, ab = hw >= wH;
+                    const u64 h = mant >> 26, l = mant & ((1ull << 26) - 1);
+                    in_hi += in ? h : 0ull;
+                    in_lo += in ? l : 0ull;
+                    ab_hi += ab ? h : 0ull;
+                    ab_lo += ab ? l : 0ull;
+                    if (un) { // (seldom of any lane)
+                        un_hi += h;
+                        un_lo += l;
+                        ++n_un;
+                    }
+                }
                 slab_put<AT>(so, sk, sw, sa, 1u << shift, cand && hw >= wL && hw < wH, cand && hw >= wH,
                              rest | pattern_bits<M>(gl, i), wb, o);
             }
@@ -1652,11 +1770,35 @@ __global__ void __launch_bounds__(STS_WG) k_bkt_small(GateArg g, PassBufs b)
             b.w_all[sl] = so.c_all;
             b.t_above[sl] = so.c_ab;
             b.t_side[sl] = so.c_in;
+            n_ab += so.c_ab;
+            n_in += so.c_in;
             if (!so.fits) atomicOr(&ctl->w_over, 1u);
         }
     }
+    if (sampled) {
+        const bool l0 = sts_lane() == 0; // (the counts are the wave's)
+        u64 v[9] = {l0 ? n_ab : 0u, ab_hi, ab_lo, (l0 ? n_in : 0u) - (u64)n_un, in_hi, in_lo, n_un, un_hi, un_lo};
+#pragma unroll
+        for (int f = 0; f < 9; ++f) {
+            v[f] = wave_incl_scan(v[f]);
+            if (sts_lane() == 63) atomicAdd((unsigned long long *)&s_win[f], (unsigned long long)v[f]);
+        }
+    }
     __syncthreads();
+    if (sampled && threadIdx.x < 9) b.wpart[threadIdx.x * STS_MAX_GROUPS + blockIdx.x] = s_win[threadIdx.x];
     flush_bins(b, s_hi, s_lo, hot_lo);
+}
+
+template <typename AT, int M> __global__ void __launch_bounds__(STS_WG) k_bkt_small(GateArg g, PassBufs b)
+{
+    if (blockIdx.x == 0) put_gate(g, b.gate_dst);
+    small_pass<AT, M, false>(g, b);
+}
+
+template <typename AT, int M>
+__global__ void __launch_bounds__(STS_WG) k_bkt_mid(const GateArg *__restrict__ gp, PassBufs b)
+{
+    small_pass<AT, M, true>(*gp, b);
 }
 
 // ---------------------------------------------------------------------------
@@ -1701,13 +1843,13 @@ hipError_t launch_m(int kind, const PassBufs &b, int tiles, hipStream_t s, const
 {
     // a pass that a truncated step launches in case its window missed is sized
     // to cost little when it exits at once: one workgroup per CU
-    const int cap = b.materialise || b.whole ? hist_capacity_b<AT, M>() : 256;
+    const int cap = b.materialise || b.whole || b.emit_copies ? hist_capacity_b<AT, M>() : 256;
     switch (kind) {
     case STS_BKT_HIST:
         hipLaunchKernelGGL((k_bkt_hist<AT, M>), dim3(std::min(tiles, cap)), dim3(STS_WG), 0, s, b.gate, b);
         break;
     case STS_BKT_SAMPLE:
-        hipLaunchKernelGGL((k_bkt_sample<AT, M>), dim3(STS_SAMPLE_TILES / 2), dim3(STS_WG), 0, s, *first, b);
+        hipLaunchKernelGGL((k_bkt_sample<AT, M>), dim3(b.fine_window ? tiles : STS_SAMPLE_TILES / 2), dim3(STS_WG), 0, s, *first, b);
         break;
     case STS_BKT_EXTRACT:
         hipLaunchKernelGGL((k_bkt_extract<AT, M>), dim3(std::min(tiles, cap)), dim3(STS_WG), 0, s, b.gate, b);
@@ -1727,7 +1869,13 @@ hipError_t launch_m(int kind, const PassBufs &b, int tiles, hipStream_t s, const
         hipLaunchKernelGGL((k_bkt_small<AT, M>), dim3(std::min(tiles, 256)), dim3(STS_WG), 0, s, *first, b);
         break;
     case STS_BKT_SELECT:
-        hipLaunchKernelGGL((k_bkt_select<AT, M>), dim3(1), dim3(SEL_NT), 0, s, b.gate, b);
+        hipLaunchKernelGGL((k_bkt_select<AT, M, false>), dim3(1), dim3(SEL_NT), 0, s, b.gate, b);
+        break;
+    case STS_BKT_MID:
+        hipLaunchKernelGGL((k_bkt_mid<AT, M>), dim3(mid_groups((u32)tiles)), dim3(STS_WG), 0, s, b.gate, b);
+        break;
+    case STS_BKT_SELECT_MID:
+        hipLaunchKernelGGL((k_bkt_select<AT, M, true>), dim3(1), dim3(SEL_NT), 0, s, b.gate, b);
         break;
     case STS_BKT_EMIT:
         hipLaunchKernelGGL((k_bkt_emit<AT, M>), dim3(std::min(tiles, cap)), dim3(STS_WG), 0, s, b.gate, b);

@@ -1042,6 +1042,7 @@ struct SampleSmem {
     u64 scan_c[STS_WG / 64];
     double scan_m[STS_WG / 64];
     u32 flag, hit, cab, inputs;
+    int at_k, at_p;
     float mab, mbe;
 };
 
@@ -1123,7 +1124,8 @@ __device__ __forceinline__ void sample_flush(SampleSmem &s, SampleAcc &a, const 
 }
 
 // the last workgroup: the window from the sample of a state of n terms
-__device__ __forceinline__ void sample_finish(SampleSmem &s, const PassBufs &b, int e_lo, u64 n)
+// fine: every term was sampled, so the cut lies in the bin that is found
+__device__ __forceinline__ void sample_finish(SampleSmem &s, const PassBufs &b, int e_lo, u64 n, bool fine = false)
 {
     DevCtl *ctl = b.ctl;
     const u32 *gc = reinterpret_cast<const u32 *>(b.sbins);
@@ -1162,8 +1164,16 @@ __device__ __forceinline__ void sample_finish(SampleSmem &s, const PassBufs &b, 
     // sample; the mass target is p of the sample's own total
     const double kt = K > 0 && sampled > 0 ? (double)K * (double)sampled / (double)n : 0.0;
     const double mt = p * mtot;
-    if (t == 0) s.hit = 0xffffffffu;
+    if (t == 0) {
+        s.hit = 0xffffffffu;
+        s.at_k = s.at_p = -1;
+    }
     __syncthreads();
+    if (fine && c) {
+        // where each rule is met
+        if (K > 0 && (double)cex < kt && (double)(cex + c) >= kt) s.at_k = f;
+        if (p_on && mex < mt && mex + m >= mt) s.at_p = f;
+    }
     const bool met_above = (K > 0 && (double)c_above >= kt) || (p_on && m_above >= mt);
     const bool met = c && ((K > 0 && (double)(cex + c) >= kt) || (p_on && mex + m >= mt));
     if (sampled > 0 && !met_above && met) atomicMin(&s.hit, (u32)t);
@@ -1174,6 +1184,20 @@ __device__ __forceinline__ void sample_finish(SampleSmem &s, const PassBufs &b, 
         const int ex = e_lo + (fb >> STS_SW_FB);
         if (r == 0xffffffffu || ex < STS_FINE_MIN || ex > 2000) {
             ctl->w_mode = 0;
+        } else if (fine) {
+            // the cut is where a rule is met first: by count exactly there, by
+            // mass (single-precision sums) up to a quarter bin from it
+            const int k = s.at_k, m = s.at_p;
+            const int lo = std::max(k < 0 ? 0 : 4 * k, m < 0 ? 0 : 4 * m - 1);
+            const int hi = std::min(std::max(k < 0 ? 0 : 4 * k + 3, m < 0 ? 0 : 4 * m + 4), 4 * STS_SW_NB - 1);
+            auto edge = [&](int q) { // least weight of quarter bin q
+                return ((u64)(e_lo + (q >> (STS_SW_FB + 2))) << 52) +
+                       ((u64)(q & ((4 << STS_SW_FB) - 1)) << (50 - STS_SW_FB));
+            };
+            ctl->w_lo = edge(lo);
+            ctl->w_hi = edge(hi + 1) - 1;
+            ctl->e_w = (int)(ctl->w_hi >> 52);
+            ctl->w_mode = 1;
         } else {
             const int sub = fb & ((1 << STS_SW_FB) - 1);
             const int lo_sub = sub > 0 ? sub - 1 : 0;

@@ -65,7 +65,7 @@ struct PassBufs {
     int copy;             // histogram pass: also keep every candidate above the window, with
                           // the window's amplitudes, in the tile's slab; emit pass: when the
                           // window held the cut, copy the survivors out of the slabs
-    u64 *wpart;           // [7][STS_MAX_GROUPS] (the weighing pass: its sums); histogram passes [6][...]: per histogram workgroup, the count of candidates
+    u64 *wpart;           // [9][STS_MAX_GROUPS] (the weighing pass: its sums); histogram passes [6][...]: per histogram workgroup, the count of candidates
                           // above the window and the mantissa sums (>> 26, & (2^26-1)) of those in
                           // the window's exponent; then the count and sums of those inside it
     // bucketed steps: the input's and the output's bucket tables (first and one past the last
@@ -76,6 +76,7 @@ struct PassBufs {
     u32 *w_kept;
     u64 *t_base;          // output offset of every STS_BKT_CHUNK tiles (t_off is relative to it)
     int slab_shift;
+    int fine_window;      // the sample's window is for k_bkt_mid
     int emit_copies;      // write pass: also copies the survivors when the window held the cut
     int recover;          // histogram pass: only after a sampled window that missed
     int whole;            // the passes launched are known to run
@@ -202,7 +203,9 @@ bool is_tiny_kernel(const void *func, int prec, int m); // one that launch_tiny 
 #define STS_BKT_COPY 6
 #define STS_BKT_SMALL 7
 #define STS_BKT_SELECT 8
-#define STS_SEL_SHARES 1024 // most shares of a step whose selection is one workgroup
+#define STS_BKT_MID 9
+#define STS_BKT_SELECT_MID 10
+#define STS_SEL_SHARES 2048 // most shares of a step whose selection is one workgroup
 #define STS_BKT_CHUNK 32 // tiles whose offsets are relative to one base
 // (first: the gate, for the two passes that a truncated step may begin with,
 // SAMPLE and SMALL; they put it into device memory for the others)

@@ -170,7 +170,7 @@ struct WideBins {
 // times the instructions (with two bins per thread of 16 waves the pick took
 // 4.4 us instead of PICK_US). s_m, s_c: 4 entries.
 template <int NT, typename BINS>
-__device__ bool pick_digit(const BINS &bins, u64 K, u128 R, int dw, Sub *sub, u128 *s_m, u64 *s_c, u32 *s_hit)
+__device__ __forceinline__ bool pick_digit(const BINS &bins, u64 K, u128 R, int dw, Sub *sub, u128 *s_m, u64 *s_c, u32 *s_hit)
 {
     constexpr int PT = NT < 256 ? NT : 256, PER = STS_NBIN / PT, LG = 3;
     static_assert(PER == 1 << LG, "a row of lanes takes a thread's bins");
@@ -274,6 +274,8 @@ struct Level1Cut {
     u64 total;        // candidates
     double W;
     u64 cnt, count;   // terms ranked before e's, and e's
+    int in_window;    // the window holds the cut:
+    u64 w_cnt, w_count, w_mb_lo, w_mb_hi; // terms ranked before its own, its own, and the mass in e before them
     u64 R_lo, R_hi;   // mass to reach inside e, in its units (all ones: off)
     u64 S[STS_NL];    // exact mass ranked before e's terms
 };
@@ -285,7 +287,7 @@ template <int NT> struct Level1Smem {
     __attribute__((aligned(16))) u64 p[3][STS_NBIN];
     u32 scan[NT / 64];
     u64 bw[NT / 64], bk[NT / 64];
-    u64 w[6];
+    u64 w[9];
     Sub sub;   // level 2 of a sampled window that holds the cut
     u32 fine, hit2;
     u64 R_lo, R_hi;
@@ -325,13 +327,13 @@ template <int NT> struct EarlyBins : DeviceBins<NT> {
     }
 };
 
-// predicted: 0 no window, 1 a window of the tiled passes, 3 a bucketed step
+// predicted: 0 no window, 1 a window of the tiled passes, 2 one without level-2 bins, 3 a bucketed step
 // whose histogram pass ran (no window; the side buffer, if the extraction
 // pass fills it, is packed densely)
 // bins: load(k, e, count, mantissa sum >> 26, & (2^26 - 1)) of exponent field e,
 // the thread's k-th, and clear(t) by every thread when all are read
 template <int NT, typename BINS>
-__device__ void pick_level1(const PassBufs &b, int groups, int peak_only, int predicted, Level1Smem<NT> &sm,
+__device__ __forceinline__ void pick_level1(const PassBufs &b, int groups, int peak_only, int predicted, Level1Smem<NT> &sm,
                             const BINS &bins)
 {
     constexpr int NB = STS_NBIN / NT, NW = NT / 64;
@@ -340,9 +342,10 @@ __device__ void pick_level1(const PassBufs &b, int groups, int peak_only, int pr
     DevCtl *ctl = b.ctl;
     // the exponent of the window the histogram pass copied (predicted steps)
     const int w_mode = ctl->w_mode;
-    const bool win = predicted == 1;
+    const bool win = predicted == 1 || predicted == 2;
     const int e_w = win ? (w_mode ? ctl->e_w : ctl->e_pred) : -1;
-    if (t < 6) sm.w[t] = 0;
+    const int e_w2 = predicted == 2 ? (int)(ctl->w_lo >> 52) : -1; // (e_w itself as a rule)
+    if (t < 9) sm.w[t] = 0;
     if (t == 0) sm.fine = 0;
 
     // own bins: every load issued before any is used
@@ -358,35 +361,37 @@ __device__ void pick_level1(const PassBufs &b, int groups, int peak_only, int pr
 #pragma unroll
     for (int r = 0; r < BPT; ++r) {
         const int i = t + NT * r;
-        bwv[r] = i < groups ? b.best[i] : 0ull;
-        bkv[r] = i < groups ? b.best[STS_MAX_GROUPS + i] : ~0ull;
+        bwv[r] = peak_only && i < groups ? b.best[i] : 0ull;
+        bkv[r] = peak_only && i < groups ? b.best[STS_MAX_GROUPS + i] : ~0ull;
     }
     // the window sums of the histogram workgroups: count of candidates above
     // the window and mantissa sums of those in its exponent, then count and
     // sums of those inside it
     // (loaded whenever the pass predicted, before the control block says
     // whether a window was copied)
-    u64 v[6] = {0, 0, 0, 0, 0, 0};
+    // (predicted == 2: then count and sums of those inside it in the exponent below)
+    u64 v[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+    const int fields = predicted == 2 ? 9 : 6;
     if (win) {
 #pragma unroll
         for (int r = 0; r < STS_MAX_GROUPS / NT; ++r) { // every load issued before any is used
             const int i = t + NT * r;
             if (i < groups) {
 #pragma unroll
-                for (int f = 0; f < 6; ++f) v[f] += b.wpart[f * STS_MAX_GROUPS + i];
+                for (int f = 0; f < 9; ++f)
+                    if (f < fields) v[f] += b.wpart[f * STS_MAX_GROUPS + i];
             }
         }
     }
     if (e_w >= 0) {
 #pragma unroll
-        for (int f = 0; f < 6; ++f) {
-#pragma unroll
-            for (int d = 32; d > 0; d >>= 1) v[f] += __shfl_xor(v[f], d, 64);
-        }
+        for (int f = 0; f < 9; ++f)
+            if (f < fields) v[f] = wave_incl_scan(v[f]); // (lane 63: the sum)
         __syncthreads(); // sm.w cleared
-        if ((t & 63) == 0) {
+        if ((t & 63) == 63) {
 #pragma unroll
-            for (int f = 0; f < 6; ++f) atomicAdd((unsigned long long *)&sm.w[f], (unsigned long long)v[f]);
+            for (int f = 0; f < 9; ++f)
+                if (f < fields && v[f]) atomicAdd((unsigned long long *)&sm.w[f], (unsigned long long)v[f]);
         }
     }
     // list the non-empty bins in rank order
@@ -591,6 +596,11 @@ __device__ void pick_level1(const PassBufs &b, int groups, int peak_only, int pr
                     const u64 Sw = wl_add(Sa, wl_piece((u64)mw, (u64)(mw >> 64), ub));
                     const bool met_w = (K > 0 && cnt + ca + cw >= K) || (p_on && wl_cmp(Sw, T) >= 0);
                     in_window = !met_a && met_w;
+                } else if (predicted == 2 && e == e_w2) { // the window's part in the exponent below
+                    cw = sm.w[6];
+                    const u128 mw = ((u128)sm.w[7] << 26) + (u128)sm.w[8];
+                    const u64 Sw = wl_add(S, wl_piece((u64)mw, (u64)(mw >> 64), ub));
+                    in_window = (K > 0 && cnt + cw >= K) || (p_on && wl_cmp(Sw, T) >= 0);
                 }
                 // remaining mass to reach inside the bin, in its units (rounded up)
                 u64 R_lo = ~0ull, R_hi = ~0ull;
@@ -615,10 +625,15 @@ __device__ void pick_level1(const PassBufs &b, int groups, int peak_only, int pr
                     sm.cut.e = e;
                     sm.cut.cnt = cnt;
                     sm.cut.count = sm.c[hit];
+                    sm.cut.in_window = in_window;
+                    sm.cut.w_cnt = cnt + ca;
+                    sm.cut.w_count = cw;
+                    sm.cut.w_mb_lo = (u64)ma;
+                    sm.cut.w_mb_hi = (u64)(ma >> 64);
                     sm.cut.R_lo = R_lo;
                     sm.cut.R_hi = R_hi;
                 }
-                if (lane == 0 && in_window && w_mode && win) {
+                if (lane == 0 && in_window && w_mode && predicted == 1) {
                     // the histogram pass binned this window for level 2: the
                     // whole workgroup picks its digit below
                     sm.fine = 1;
@@ -645,7 +660,7 @@ __device__ void pick_level1(const PassBufs &b, int groups, int peak_only, int pr
                 }
             }
             if (lane == 0) {
-                ctl->w2_mode = win && w_mode; // the histogram pass binned the window for level 2
+                ctl->w2_mode = predicted == 1 && w_mode; // the histogram pass binned the window for level 2
                 ctl->w_mode = 0;                     // a window serves one step
                 if (predicted == 3) {
                     ctl->w_over = 0;
@@ -697,6 +712,8 @@ struct CutSmem {
     u128 m[1024 / 64];
     u64 c[1024 / 64];
     u32 hit, n;
+    u32 rank[STS_FINAL_SORT]; // of the last terms
+    u64 mass[STS_FINAL_SORT];
     u64 thr_w, thr_k;  // the cut's term
     u64 mk_lo, mk_hi;  // mantissa sum ranked up to it inside its exponent
     u64 L;
@@ -764,7 +781,7 @@ template <bool THIN> struct Binner {
 };
 
 template <int NT, bool THIN, typename E>
-__device__ bool narrow_cut(E &&each, int e, u64 K, u128 R, Sub &sub, unsigned char *raw, CutSmem &sm, u32 enough,
+__device__ __forceinline__ bool narrow_cut(E &&each, int e, u64 K, u128 R, Sub &sub, unsigned char *raw, CutSmem &sm, u32 enough,
                            bool cleared = false)
 {
     const int t = threadIdx.x;
@@ -797,28 +814,37 @@ __device__ bool narrow_cut(E &&each, int e, u64 K, u128 R, Sub &sub, unsigned ch
 // the cut among the m <= STS_FINAL_SORT terms listed in sv (a handful as a
 // rule): every term counts and weighs the ones before it by itself; their
 // mantissas add up below 2^63. Returns this thread's rank (m or more: no term)
-template <int NT> __device__ u32 rank_cut(const u128 *sv, u32 m, int e, u64 K, u128 R, const Sub &sub, CutSmem &sm)
+// The threads of a term share the comparisons (its partial sums meet in LDS).
+template <int NT> __device__ __forceinline__ u32 rank_cut(const u128 *sv, u32 m, int e, u64 K, u128 R, const Sub &sub, CutSmem &sm)
 {
-    const u32 t = threadIdx.x;
-    static_assert(STS_FINAL_SORT <= NT, "one term per thread");
-    u128 v = 0;
-    u32 rank = ~0u;
-    u64 mass = 0; // of the terms up to this one
-    bool met = false;
-    if (t < m) {
-        v = sv[t];
-        rank = 0;
-        for (u32 i = 0; i < m; ++i) {
-            const u128 o = sv[i];
+    constexpr u32 PARTS = NT / STS_FINAL_SORT;
+    static_assert(PARTS >= 1 && NT % STS_FINAL_SORT == 0, "whole parts");
+    const u32 t = threadIdx.x, i = t % STS_FINAL_SORT, part = t / STS_FINAL_SORT;
+    if (t < STS_FINAL_SORT) {
+        sm.rank[t] = 0;
+        sm.mass[t] = 0;
+    }
+    __syncthreads();
+    if (i < m) {
+        const u128 v = sv[i];
+        u32 rank = 0;
+        u64 mass = 0; // of the terms up to this one
+        for (u32 j = part; j < m; j += PARTS) {
+            const u128 o = sv[j];
             rank += o < v ? 1u : 0u;
             mass += o <= v ? mant_of_v(o, e) : 0ull;
         }
-        met = (K > 0 && sub.cnt_before + rank + 1 >= K) || sub.mb + (u128)mass >= R;
-        if (met) atomicMin(&sm.hit, rank);
+        if (rank) atomicAdd(&sm.rank[i], rank);
+        if (mass) atomicAdd((unsigned long long *)&sm.mass[i], (unsigned long long)mass);
     }
     __syncthreads();
+    const u32 rank = t < m ? sm.rank[t] : ~0u;
+    const u64 mass = t < m ? sm.mass[t] : 0ull;
+    const bool met = t < m && ((K > 0 && sub.cnt_before + rank + 1 >= K) || sub.mb + (u128)mass >= R);
+    if (met) atomicMin(&sm.hit, rank);
+    __syncthreads();
     if (met && rank == sm.hit) {
-        const u128 mk = sub.mb + (u128)mass;
+        const u128 v = sv[t], mk = sub.mb + (u128)mass;
         sm.thr_w = ((u64)e << 52) | (((1ull << 52) - 1) - (u64)(v >> 64));
         sm.thr_k = (u64)v;
         sm.mk_lo = (u64)mk;
@@ -857,7 +883,7 @@ __device__ __forceinline__ void finish_cut(DevCtl *ctl, CutSmem &sm, int e, cons
 // all of it, up to the cut's term in sm (false: the cut could not be resolved,
 // an internal inconsistency); finish_cut by one wave follows
 template <int NT, bool THIN, typename E>
-__device__ bool resolve_cut(E &&each, int e, u64 K, u128 R, Sub &sub, unsigned char *raw, CutSmem &sm)
+__device__ __forceinline__ bool resolve_cut(E &&each, int e, u64 K, u128 R, Sub &sub, unsigned char *raw, CutSmem &sm)
 {
     if (!narrow_cut<NT, THIN>(each, e, K, R, sub, raw, sm, STS_FINAL_SORT)) return false;
     u128 *sv = reinterpret_cast<u128 *>(raw);
