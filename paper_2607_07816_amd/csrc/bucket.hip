@@ -17,7 +17,7 @@ int bucket_c64_groups(int m, int tiles, bool weigh);
 
 namespace {
 
-constexpr int KT = 1024;
+constexpr int KT = 256;
 
 // The survivors of every share and the output offset of every tile. When the
 // window held the cut, a share's survivors are its entries above the window
@@ -39,39 +39,49 @@ __global__ void __launch_bounds__(KT) k_bkt_kept(PassBufs b)
     const bool all = !b.materialise && ctl->keep_all, hit = !b.materialise && !ctl->keep_all && ctl->pred_hit;
     const u32 lane = (u32)sts_lane(), sub = lane >> 4, l16 = lane & 15u;
     const u32 t0 = blockIdx.x * STS_BKT_CHUNK;
-    for (u32 k = threadIdx.x >> 6; k < STS_BKT_CHUNK; k += KT / 64) {
-        const u32 tile = t0 + k;
-        u32 c = 0;
-        if (tile < ntiles) {
-            const u32 sl = (tile << 2) + sub;
-            if (hit) {
-                const u32 ns = b.t_side[sl];
-                const u64 base = (u64)sl << shift;
-                if (l16 == 0) c = b.t_above[sl];
-                for (u32 i0 = l16; i0 < ns; i0 += UN * 16) {
-                    u64 w[UN], key[UN];
+    // a wave's tiles at a time, their loads in flight together
+    constexpr u32 PW = STS_BKT_CHUNK / (KT / 64);
+    const u32 k0 = threadIdx.x >> 6;
+    u32 c[PW], ns[PW];
 #pragma unroll
-                    for (int r = 0; r < UN; ++r) {
-                        const u32 i = i0 + 16u * (u32)r;
-                        w[r] = b.side_w[base + (i < ns ? i : 0u)];
-                        key[r] = b.side_key[base + (i < ns ? i : 0u)];
-                    }
+    for (u32 q = 0; q < PW; ++q) {
+        const u32 tile = t0 + k0 + q * (KT / 64), sl = (tile << 2) + sub;
+        const bool in = tile < ntiles;
+        ns[q] = in && hit ? b.t_side[sl] : 0u;
+        c[q] = !in ? 0u : hit ? (l16 == 0 ? b.t_above[sl] : 0u) : all ? b.w_all[sl] : b.w_kept[sl];
+    }
+    if (hit) {
+        u64 w[PW][UN];
 #pragma unroll
-                    for (int r = 0; r < UN; ++r) {
-                        const u32 i = i0 + 16u * (u32)r;
-                        c += (i < ns && (w[r] > thr_w || (w[r] == thr_w && key[r] <= thr_k))) ? 1u : 0u;
-                    }
-                }
+        for (u32 q = 0; q < PW; ++q) {
+            const u64 base = (u64)(((t0 + k0 + q * (KT / 64)) << 2) + sub) << shift;
 #pragma unroll
-                for (int d = 8; d > 0; d >>= 1) c += __shfl_xor(c, d, 64);
-            } else {
-                c = all ? b.w_all[sl] : b.w_kept[sl];
+            for (int r = 0; r < UN; ++r) {
+                const u32 i = l16 + 16u * (u32)r;
+                w[q][r] = i < ns[q] ? b.side_w[base + i] : 0ull;
             }
-            if (l16 == 0 && (hit || all)) b.w_kept[sl] = c;
-            c += __shfl_xor(c, 16, 64);
-            c += __shfl_xor(c, 32, 64);
         }
-        if (lane == 0) s_tile[k] = c;
+#pragma unroll
+        for (u32 q = 0; q < PW; ++q) {
+            const u64 base = (u64)(((t0 + k0 + q * (KT / 64)) << 2) + sub) << shift;
+            // (the key decides between equal weights only, and is read for those)
+            auto count = [&](u32 i, u64 x) {
+                if (i < ns[q] && (x > thr_w || (x == thr_w && b.side_key[base + i] <= thr_k))) ++c[q];
+            };
+#pragma unroll
+            for (int r = 0; r < UN; ++r) count(l16 + 16u * (u32)r, w[q][r]);
+            for (u32 i = l16 + 16u * UN; i < ns[q]; i += 16) count(i, b.side_w[base + i]);
+#pragma unroll
+            for (int d = 8; d > 0; d >>= 1) c[q] += __shfl_xor(c[q], d, 64);
+        }
+    }
+#pragma unroll
+    for (u32 q = 0; q < PW; ++q) {
+        const u32 tile = t0 + k0 + q * (KT / 64), sl = (tile << 2) + sub;
+        if (tile < ntiles && l16 == 0 && (hit || all)) b.w_kept[sl] = c[q];
+        c[q] += __shfl_xor(c[q], 16, 64);
+        c[q] += __shfl_xor(c[q], 32, 64);
+        if (lane == 0) s_tile[k0 + q * (KT / 64)] = c[q];
     }
     __syncthreads();
     if (threadIdx.x < 64) {
@@ -83,12 +93,21 @@ __global__ void __launch_bounds__(KT) k_bkt_kept(PassBufs b)
     }
     if (!sts_last_block(&ctl->done[3], &s_flag)) return;
     u64 carry = 0;
-    for (u32 i0 = 0; i0 < gridDim.x; i0 += KT) {
-        const u32 i = i0 + threadIdx.x;
-        const u64 v = i < gridDim.x ? ld_agent(&b.t_base[i]) : 0ull;
+    constexpr u32 PT = 8; // chunks of a thread at a time
+    for (u32 i0 = 0; i0 < gridDim.x; i0 += KT * PT) {
+        const u32 i = i0 + threadIdx.x * PT;
+        u64 v[PT], sum = 0;
+#pragma unroll
+        for (u32 q = 0; q < PT; ++q) v[q] = i + q < gridDim.x ? ld_agent(&b.t_base[i + q]) : 0ull;
+#pragma unroll
+        for (u32 q = 0; q < PT; ++q) sum += v[q];
         u64 total;
-        const u64 run = block_excl_scan<u64, KT>(v, s_scratch, &total) + carry;
-        if (i < gridDim.x) st_agent(&b.t_base[i], run);
+        u64 run = block_excl_scan<u64, KT>(sum, s_scratch, &total) + carry;
+#pragma unroll
+        for (u32 q = 0; q < PT; ++q) {
+            if (i + q < gridDim.x) st_agent(&b.t_base[i + q], run);
+            run += v[q];
+        }
         carry += total;
     }
     if (threadIdx.x == 0) {

@@ -1182,8 +1182,7 @@ __device__ __forceinline__ void copy_share(const BktPlan &p, const PassBufs &b, 
             if (at < cap) {
                 ok[at] = kk[r];
                 const AT o = out_amp(aa[r], rescale, scale);
-                __builtin_nontemporal_store(o.x, &oa[at].x);
-                __builtin_nontemporal_store(o.y, &oa[at].y);
+                oa[at] = o;
             }
         }
         return;
