@@ -110,10 +110,8 @@ inline BktPlan bkt_plan(int hb, int delta, int m, const int *q, int pm, const in
     for (int t = 0; t < m; ++t) add(lin_dir(q[t]) >> (32 - hb));
     // the wave's two dimensions are reduced against each other, so that their
     // coordinates are read off their pivots
-    int fixed = n;
     for (int t = 0; t < pm; ++t) add(lin_dir(pq[t]) >> (32 - hb));
     for (int i = 0; i < hb; ++i) add(1u << i);
-    (void)fixed;
     if ((p.E[0] >> pv[1]) & 1u) p.E[0] ^= p.E[1];
     // coordinates of each key bit
     for (int t = 0; t < 64; ++t) {

@@ -2,7 +2,7 @@
 
 A step of 1- and 2-qubit gates takes one launch up to 2048 terms (in three
 workgroup sizes: up to 512, 1024 and 2048), a selection by one workgroup up to
-2^17 (from 2^15 with a window found beforehand), and a chain of launches above;
+2^17 (from 2^14 with a window found beforehand), and a chain of launches above;
 from 2049 terms on the state stays in the order of a linear hash of its keys.
 FP64 sequences are compared with the oracle bit for bit, complex64 steps within
 the per-step tolerances of the window tests.
@@ -61,7 +61,8 @@ def same(S, keys, amps, n, gs, K, p, cap=None):
     check(kg, ag, stats, ko, ao, info, "c128")
 
 
-EDGES = [1, 2, 511, 513, 1024, 1025, 2047, 2048, 2049, 4097, (1 << 15) - 1, (1 << 15) + 1, 1 << 17, (1 << 17) + 1]
+EDGES = [1, 2, 511, 513, 1024, 1025, 2047, 2048, 2049, 4097, 1 << 14, (1 << 14) + 1, (1 << 15) - 1,
+         (1 << 15) + 1, 1 << 17, (1 << 17) + 1]
 
 
 @pytest.mark.parametrize("p", [0.0, 0.99])
