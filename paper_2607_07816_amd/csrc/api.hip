@@ -1,8 +1,18 @@
 // api.hip - the C ABI of libsts: context, device memory, and the order in
 // which the kernels of a gate step run.
 //
-// A gate step (sts_apply_gate then sts_truncate) runs, on the context's
-// stream and without host synchronisation:
+// A gate step (sts_apply_gate then sts_truncate) runs on the context's stream
+// and without host synchronisation. Which kernels depends on the size bound:
+//   up to 2048 terms (gates of 1 and 2 qubits): one launch (tiny_impl.h);
+//   more, gates of 1 and 2 qubits: the state is kept in the order of a linear
+//   hash of its keys (linhash.h), in which a gate's partners and new terms
+//   share four buckets, so that nothing is sorted (bucket_impl.h):
+//     up to 2^17 terms: weigh all candidates (above 2^14 after a pass that
+//     finds the window), select in one workgroup, write;
+//     above: sample a window, weigh, decide and pick, list and resolve the
+//     last terms, count and place the survivors, write; further passes that
+//     exit at once unless the window missed;
+//   gates of 3 qubits and more, and the one step of sts_step_static:
 //   1. 1..4 radix digit passes (per-tile counts, per-digit scan, scatter):
 //      group the state by the hash bucket of the bits outside the gate
 //      (radix.hip);
@@ -12,10 +22,10 @@
 //   4. extraction pass: copy the candidates of the cut's exponent to the side
 //      buffer (group.hip);
 //   5. level-2 histogram + pick over the side buffer, then the final levels
-//      and an LDS sort of the last <= 4096 candidates (select.hip);
+//      and the ranking of the last <= 128 candidates (select.hip);
 //   6. write pass: recompute once more and write the survivors, rescaled
 //      (group.hip).
-// Without a truncation rule (or when the next gate arrives first) step 6
+// Without a truncation rule (or when the next gate arrives first) the write
 // alone runs, keeping every nonzero candidate.
 #include <algorithm>
 #include <array>
@@ -571,11 +581,6 @@ int slab_shift(const sts_ctx *c)
 
 int bucket_tiles(const sts_ctx *c) { return 1 << (c->gate.bkt.hb - STS_BKT_DIMS); }
 
-int bucket_groups(const sts_ctx *c, bool weigh)
-{
-    return bucket_hist_groups(c->prec, c->gate.m, bucket_tiles(c), weigh);
-}
-
 // the passes that write the pending bucketed step's survivors to buffer dst
 sts_status bucket_write(sts_ctx *c, const PassBufs &b, int dst, u64 bound)
 {
@@ -951,7 +956,7 @@ static sts_status truncate_buckets(sts_ctx *c)
         // when it missed
         STS_LAUNCH(c, STS_K_SAMPLE, launch_bucket_pass(STS_BKT_SAMPLE, c->prec, m, b, tiles, c->stream, &c->gate));
         STS_LAUNCH(c, STS_K_GROUP_HIST, launch_bucket_pass(STS_BKT_WEIGH, c->prec, m, b, tiles, c->stream));
-        STS_LAUNCH(c, STS_K_PICK1, launch_pick_window(b, bucket_groups(c, true), c->stream));
+        STS_LAUNCH(c, STS_K_PICK1, launch_pick_window(b, bucket_weigh_groups(c->prec, m, tiles), c->stream));
         b.recover = 1;
         STS_LAUNCH(c, STS_K_GROUP_HIST, launch_bucket_pass(STS_BKT_HIST, c->prec, m, b, tiles, c->stream));
         STS_LAUNCH(c, STS_K_GROUP_EXTRACT, launch_bucket_pass(STS_BKT_EXTRACT, c->prec, m, b, tiles, c->stream));

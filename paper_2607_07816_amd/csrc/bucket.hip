@@ -12,8 +12,8 @@ hipError_t tiny_c128(const GateArg &g, const PassBufs &b, u64 n_bound, hipStream
 hipError_t tiny_c64(const GateArg &g, const PassBufs &b, u64 n_bound, hipStream_t s);
 const void *tiny_c128_kernel(int m, int size);
 const void *tiny_c64_kernel(int m, int size);
-int bucket_c128_groups(int m, int tiles, bool weigh);
-int bucket_c64_groups(int m, int tiles, bool weigh);
+int bucket_c128_groups(int m, int tiles);
+int bucket_c64_groups(int m, int tiles);
 
 namespace {
 
@@ -25,7 +25,9 @@ constexpr int KT = 256;
 // share, a wave per tile); when nothing is cut, all its candidates; otherwise
 // the counting pass has them. A workgroup has STS_BKT_CHUNK tiles, whose
 // offsets are relative to the chunk's base; the last workgroup scans the
-// chunks' sums.
+// chunks' sums. Bound by the round trips to memory (a count, then a few window
+// entries): a wave's eight tiles are loaded together, 24 us at 2^24 complex64
+// terms, where two tiles one after the other, keys included, took 31.
 __global__ void __launch_bounds__(KT) k_bkt_kept(PassBufs b)
 {
     __shared__ u32 s_flag;
@@ -136,9 +138,9 @@ __global__ void __launch_bounds__(256) k_bkt_bounds(const u64 *__restrict__ keys
 
 } // namespace
 
-int bucket_hist_groups(int prec, int m, int tiles, bool weigh)
+int bucket_weigh_groups(int prec, int m, int tiles)
 {
-    return prec == 0 ? bucket_c128_groups(m, tiles, weigh) : bucket_c64_groups(m, tiles, weigh);
+    return prec == 0 ? bucket_c128_groups(m, tiles) : bucket_c64_groups(m, tiles);
 }
 
 hipError_t launch_tiny(int prec, const GateArg &g, const PassBufs &b, u64 n_bound, hipStream_t s)

@@ -14,11 +14,10 @@ hipError_t bucket_c64_pass(int kind, int m, const PassBufs &b, int tiles, hipStr
     return hipErrorInvalidValue;
 }
 
-int bucket_c64_groups(int m, int tiles, bool weigh)
+int bucket_c64_groups(int m, int tiles)
 {
     using namespace sts_bucket;
-    if (weigh) return m == 1 ? weigh_grid<float2, 1>(tiles) : weigh_grid<float2, 2>(tiles);
-    return std::min(tiles, m == 1 ? hist_capacity_b<float2, 1>() : hist_capacity_b<float2, 2>());
+    return m == 1 ? weigh_grid<float2, 1>(tiles) : weigh_grid<float2, 2>(tiles);
 }
 
 const void *bucket_c64_first(int kind, int m)

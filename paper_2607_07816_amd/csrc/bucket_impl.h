@@ -658,7 +658,11 @@ __device__ __forceinline__ void flush_fine(u64 *s_acc, FineSums &f, double k1, d
 
 // One workgroup per CU, whose waves' tables fill the LDS (16 waves for
 // complex64, 12 for complex128): the pass waits on chains of LDS round trips,
-// and more waves hide more of them. Four waves have one tile.
+// and more waves hide more of them. Four waves have one tile. Bound by vector
+// instructions (about 1660 a wave and share of 256 terms, 55% of its time):
+// 323 us at 2^24 complex64 terms, where the sorted path took 345 for its three
+// scatters, 83 for their counts and 321 for the histogram; with 12 waves and
+// no register spills 341.
 template <typename AT> struct WeighWaves {
     static constexpr int value = sizeof(AT) == 8 ? 16 : 12;
 };
@@ -1210,6 +1214,10 @@ __device__ __forceinline__ void copy_share(const BktPlan &p, const PassBufs &b, 
     }
 }
 
+// Bound by memory: 536 MB in 120 us (4.5 TB/s) at 2^24 complex64 terms. The
+// slabs are read past the caches, the survivors are not written past them: with
+// non-temporal amplitude stores the copy took 143 us and the next weighing pass 323
+// instead of 330.
 template <typename AT>
 __global__ void __launch_bounds__(STS_WG) k_bkt_copy(const GateArg *__restrict__ gp, PassBufs b)
 {
@@ -1282,18 +1290,28 @@ __global__ void __launch_bounds__(STS_WG) k_bkt_emit(const GateArg *__restrict__
 
 // ---------------------------------------------------------------------------
 // Small steps (at most STS_SEL_SHARES shares). The weighing pass bins the
-// weights as the histogram pass does and copies a window of two octaves (of
-// all weights when there is no previous cut) and the candidates above it to
-// the slabs. One workgroup then does the whole selection: the level-1 pick
-// over the exponent bins, the further levels over the slabs' entries of the
-// cut's exponent, and the survivors' offsets. Several short launches in a
-// chain cost more than one workgroup's passes over some thousands of entries.
-// (Selecting in the weighing pass's last workgroup instead of a launch of its
-// own was slower: 48 us instead of 12 + 29 at 4096 terms; the fences of that
-// handover cost more than the launch.) A window that missed the cut is not
-// recovered by further launches either: the selection then computes the
-// candidates again and fills the slabs with those of the cut's exponent and
+// weights as the histogram pass does and copies a window of weights and the
+// candidates above it to the slabs: two octaves around the previous cut
+// (k_bkt_small; everything without a previous cut), or, of larger states, the
+// bin that the sampling pass, run on all terms, found (k_bkt_mid, which also
+// sums the mass above it). One workgroup then does the whole selection: the
+// level-1 pick over the exponent bins, the further levels over the window's
+// entries of the cut's exponent, and the survivors' offsets. Several short
+// launches in a chain cost more than one workgroup's passes over some thousands
+// of entries. (Selecting in the weighing pass's last workgroup instead of a
+// launch of its own was slower: 48 us instead of 12 + 29 at 4096 terms; the
+// fences of that handover cost more than the launch.) A window that missed the
+// cut is not recovered by further launches either: the selection then computes
+// the candidates again and fills the slabs with those of the cut's exponent and
 // above (for every pass over them if a slab cannot hold its share's).
+//
+// The selection is bound by what its waves issue on one CU and by round trips
+// to memory, so its first loads go out together, entries are kept on the chip
+// (a two-octave window's in registers, a found one's in an LDS list), and 512
+// threads do the work: 31 us at 16,384 terms, 43 with 1024 threads that read the
+// entries again for each pass; 33 us at 100,003 terms, where the chain of
+// launches it replaced took 55. A miss: 200 us at 16,384 terms, 620 when the
+// candidates were computed again for each pass.
 // ---------------------------------------------------------------------------
 constexpr int SEL_NT = 512;
 constexpr int SEL_S = 32; // shares of which a wave holds up to 64 entries each

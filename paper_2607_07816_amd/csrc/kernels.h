@@ -212,7 +212,7 @@ bool is_tiny_kernel(const void *func, int prec, int m); // one that launch_tiny 
 hipError_t launch_bucket_pass(int kind, int prec, int m, const PassBufs &b, int tiles, hipStream_t s,
                               const GateArg *first = nullptr);
 const void *bucket_first_kernel(int kind, int prec, int m); // the kernel of SAMPLE or SMALL
-int bucket_hist_groups(int prec, int m, int tiles, bool weigh); // workgroups of the histogram or weighing pass
+int bucket_weigh_groups(int prec, int m, int tiles); // workgroups of the weighing pass
 hipError_t launch_pick_window(const PassBufs &b, int groups, hipStream_t s);
 // survivors per share (when the window held the cut or nothing is cut), then every tile's output offset
 hipError_t launch_bucket_kept(const PassBufs &b, int tiles, hipStream_t s);
