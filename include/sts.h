@@ -113,8 +113,8 @@ sts_status sts_init(sts_ctx **out, int n_qubits, uint64_t max_terms, double mass
  * qubits, and 4-qubit gates on a state holding at most about half of
  * cap_terms, run on the LDS-tiled kernels; other 4- and 5-qubit gates run on
  * slower untiled ones (same results). The result is
- * formed lazily: the grouping work runs now, and the new amplitudes are
- * produced by the following sts_truncate (so candidates are never stored),
+ * formed lazily: the terms are grouped now where that takes a sort (3 qubits
+ * and more), and the new amplitudes are produced by the following sts_truncate (so candidates are never stored),
  * or by the next call that needs them. Returns STS_E_ARG for bad arguments.
  * Whether a gate's un-truncated result must fit in cap_terms is known only
  * when the next call arrives (an sts_truncate never forms it), so its

@@ -591,9 +591,10 @@ sts_status bucket_write(sts_ctx *c, const PassBufs &b, int dst, u64 bound)
                        launch_bucket_pass(STS_BKT_COUNT, c->prec, c->gate.m, b, tiles, c->stream));
         STS_LAUNCH(c, STS_K_TILE_KEPT, launch_bucket_kept(b, tiles, c->stream));
     }
-    if (!b.materialise && !b.emit_copies && !b.whole)
+    const bool copied = !b.materialise && !b.emit_copies && !b.whole;
+    if (copied)
         STS_LAUNCH(c, STS_K_GROUP_EMIT, launch_bucket_pass(STS_BKT_COPY, c->prec, c->gate.m, b, tiles, c->stream));
-    STS_LAUNCH(c, STS_K_GROUP_EMIT, launch_bucket_pass(STS_BKT_EMIT, c->prec, c->gate.m, b, tiles, c->stream));
+    STS_LAUNCH(c, copied ? STS_K_GROUP_EXTRACT : STS_K_GROUP_EMIT, launch_bucket_pass(STS_BKT_EMIT, c->prec, c->gate.m, b, tiles, c->stream));
     c->cur = dst;
     c->n_bound = bound;
     c->hb = c->gate.bkt.hb + c->gate.bkt.delta;
@@ -957,8 +958,8 @@ static sts_status truncate_buckets(sts_ctx *c)
         STS_LAUNCH(c, STS_K_SAMPLE, launch_bucket_pass(STS_BKT_SAMPLE, c->prec, m, b, tiles, c->stream, &c->gate));
         STS_LAUNCH(c, STS_K_GROUP_HIST, launch_bucket_pass(STS_BKT_WEIGH, c->prec, m, b, tiles, c->stream));
         STS_LAUNCH(c, STS_K_PICK1, launch_pick_window(b, bucket_weigh_groups(c->prec, m, tiles), c->stream));
-        b.recover = 1;
-        STS_LAUNCH(c, STS_K_GROUP_HIST, launch_bucket_pass(STS_BKT_HIST, c->prec, m, b, tiles, c->stream));
+        b.recover = 1; // (timed apart from the passes that do the work)
+        STS_LAUNCH(c, STS_K_SIDE_HIST, launch_bucket_pass(STS_BKT_HIST, c->prec, m, b, tiles, c->stream));
         STS_LAUNCH(c, STS_K_GROUP_EXTRACT, launch_bucket_pass(STS_BKT_EXTRACT, c->prec, m, b, tiles, c->stream));
         const int sg =
             (int)std::min<u64>(std::max<u64>(ceil_div(std::min(cb, c->scap), 256), 1), STS_SIDE_GROUPS);

@@ -30,7 +30,9 @@ _PKG = os.path.dirname(os.path.abspath(__file__))
 SHORT_NAMES = ("k_radix_pass", "k_radix_count", "k_radix_hist", "k_radix_scan", "k_tile_hist", "k_tile_extract", "k_tile_emit",
                "k_tile_compact", "k_group_hist", "k_group_compact", "k_group_extract", "k_group_emit", "k_pick1",
                "k_side_hist", "k_side_extract", "k_final", "k_tile_kept", "k_tile_scan", "k_init_state",
-               "k_set_n", "k_tile_sample", "k_fill_zero", "k_ctl_begin", "k_terms_out")
+               "k_set_n", "k_bkt_weigh", "k_bkt_sample", "k_bkt_hist", "k_bkt_extract", "k_bkt_count", "k_bkt_copy",
+               "k_bkt_emit", "k_bkt_select", "k_bkt_small", "k_bkt_mid", "k_bkt_kept", "k_pick_window", "k_tiny",
+               "k_tile_sample", "k_fill_zero", "k_ctl_begin", "k_terms_out")
 
 
 def short(name: str) -> str:
