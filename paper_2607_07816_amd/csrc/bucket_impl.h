@@ -1831,10 +1831,14 @@ template <typename F> int resident_groups(F kernel, int threads)
     return std::min((per_cu > 0 ? per_cu : 1) * (cus > 0 ? cus : 1), STS_MAX_GROUPS);
 }
 
-template <typename AT, int M> int hist_capacity_b()
+// of the histogram, extraction, counting and emission passes
+template <typename AT, int M> int pass_capacity(int kind)
 {
-    static const int cap = resident_groups(k_bkt_hist<AT, M>, STS_WG);
-    return cap;
+    static const int hist = resident_groups(k_bkt_hist<AT, M>, STS_WG);
+    static const int extract = resident_groups(k_bkt_extract<AT, M>, STS_WG);
+    static const int count = resident_groups(k_bkt_count<AT, M>, STS_WG);
+    static const int emit = resident_groups(k_bkt_emit<AT, M>, STS_WG);
+    return kind == STS_BKT_HIST ? hist : kind == STS_BKT_EXTRACT ? extract : kind == STS_BKT_COUNT ? count : emit;
 }
 
 template <typename AT, int M> int weigh_capacity()
@@ -1858,15 +1862,19 @@ template <typename AT, int M> const void *first_kernel(int kind)
 template <typename AT, int M>
 hipError_t launch_m(int kind, const PassBufs &b, int tiles, hipStream_t s, const GateArg *first)
 {
-    // a pass that a truncated step launches in case its window missed is sized
-    // to cost little when it exits at once: one workgroup per CU
-    const int cap = b.materialise || b.whole || b.emit_copies ? hist_capacity_b<AT, M>() : 256;
+    // a pass over tiles by all the workgroups that are resident at once, also
+    // where it is launched in case a window missed (exiting at once takes as long
+    // in one workgroup per CU, and a miss at 2^24 terms 4.4 instead of 2.4 ms)
+    const int cap = pass_capacity<AT, M>(kind);
+    // the sample's tiles: at 2^24 terms twice as many halve the misses for 1 us
+    // of 550, at 2^20 they cost as much as they save
+    const int sample = b.fine_window ? tiles : tiles >= 1 << 14 ? STS_SAMPLE_TILES : STS_SAMPLE_TILES / 2;
     switch (kind) {
     case STS_BKT_HIST:
         hipLaunchKernelGGL((k_bkt_hist<AT, M>), dim3(std::min(tiles, cap)), dim3(STS_WG), 0, s, b.gate, b);
         break;
     case STS_BKT_SAMPLE:
-        hipLaunchKernelGGL((k_bkt_sample<AT, M>), dim3(b.fine_window ? tiles : STS_SAMPLE_TILES / 2), dim3(STS_WG), 0, s, *first, b);
+        hipLaunchKernelGGL((k_bkt_sample<AT, M>), dim3(sample), dim3(STS_WG), 0, s, *first, b);
         break;
     case STS_BKT_EXTRACT:
         hipLaunchKernelGGL((k_bkt_extract<AT, M>), dim3(std::min(tiles, cap)), dim3(STS_WG), 0, s, b.gate, b);
