@@ -37,22 +37,14 @@ __global__ void __launch_bounds__(256) k_pick1(PassBufs b, int groups, int peak_
 // the exact total W, the exact mass above the window, and the window's level-2
 // bins. Decides exactly whether the window holds the cut; if so picks level 2,
 // if nothing is cut says so, and otherwise asks for the histogram pass.
+// A chain of latencies: 12 us at 2^20 complex128 terms, 16 at 2^24 complex64
+// ones; limbs and carries of the exponent bins are added apart (12.9 and 17 us with a
+// carry resolved for every bin).
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ u128 wave_sum128(u128 v)
-{
-#pragma unroll
-    for (int d = 32; d > 0; d >>= 1) {
-        const u64 lo = __shfl_xor((u64)v, d, 64), hi = __shfl_xor((u64)(v >> 64), d, 64);
-        v += make128(lo, hi);
-    }
-    return v;
-}
-
 __global__ void __launch_bounds__(256) k_pick_window(PassBufs b, int groups)
 {
     __shared__ unsigned short s_e[STS_NBIN]; // the non-empty exponent bins in rank order
-    __shared__ __attribute__((aligned(16))) u64 s_lo[STS_NBIN];
-    __shared__ u64 s_hi[STS_NBIN];
+    __shared__ __attribute__((aligned(16))) u64 s_p[3][STS_NBIN]; // their mantissa sums, as the limbs from (unit bit / 64) on
     __shared__ u32 s_scan[4];
     __shared__ u64 s_cnt[4][3];
     __shared__ u64 s_sum[4][6]; // per wave: total, above, window (low and high words)
@@ -122,20 +114,20 @@ __global__ void __launch_bounds__(256) k_pick_window(PassBufs b, int groups)
         if (!c[k]) continue;
         s_e[at] = (unsigned short)(2047 - 8 * t - k);
         const u128 ms = ((u128)hi[k] << 26) + (u128)lo[k];
-        s_lo[at] = (u64)ms;
-        s_hi[at] = (u64)(ms >> 64);
+        const int off = unit_bit(2047 - 8 * t - k) & 63;
+        const u128 ml = ms << off;
+        s_p[0][at] = (u64)ml;
+        s_p[1][at] = (u64)(ml >> 64);
+        s_p[2][at] = off ? (u64)(ms >> 64) >> (64 - off) : 0ull;
         ++at;
     }
-    tot = wave_sum128(tot);
-    abv = wave_sum128(abv);
-    win = wave_sum128(win);
-#pragma unroll
-    for (int d = 32; d > 0; d >>= 1) {
-        c_all += __shfl_xor(c_all, d, 64);
-        c_ab += __shfl_xor(c_ab, d, 64);
-        c_in += __shfl_xor(c_in, d, 64);
-    }
-    if (lane == 0) {
+    tot = wave_incl_scan(tot); // (lane 63: the sum)
+    abv = wave_incl_scan(abv);
+    win = wave_incl_scan(win);
+    c_all = wave_incl_scan(c_all);
+    c_ab = wave_incl_scan(c_ab);
+    c_in = wave_incl_scan(c_in);
+    if (lane == 63) {
         s_cnt[q][0] = c_all;
         s_cnt[q][1] = c_ab;
         s_cnt[q][2] = c_in;
@@ -152,12 +144,25 @@ __global__ void __launch_bounds__(256) k_pick_window(PassBufs b, int groups)
         // register range, then those below
         const u32 chunk = (nbins + 3) / 4;
         const u32 j0 = (u32)q * chunk, j1 = j0 + chunk < nbins ? j0 + chunk : nbins;
+        // limbs and their carries apart; the carries are resolved at the end
         u64 A = 0, B = 0;
+        u32 cA = 0, cB = 0;
+#pragma unroll 4
         for (u32 j = j0; j < j1; ++j) {
-            const u64 v = wl_piece(s_lo[j], s_hi[j], unit_bit((int)s_e[j]));
-            if ((int)s_e[j] >= L) A = wl_add(A, v);
-            else B = wl_add(B, v);
+            const int f = (int)s_e[j];
+            const u32 k = (u32)lane - ((u32)unit_bit(f) >> 6);
+            const u64 v = k < 3u ? s_p[k][j] : 0ull;
+            if (f >= L) { // uniform
+                A += v;
+                cA += A < v ? 1u : 0u;
+            } else {
+                B += v;
+                cB += B < v ? 1u : 0u;
+            }
         }
+        const u32 upA = __shfl_up(cA, 1, 64), upB = __shfl_up(cB, 1, 64);
+        A = wl_add(A, lane ? (u64)upA : 0ull);
+        B = wl_add(B, lane ? (u64)upB : 0ull);
         s_part[q][0][lane] = A;
         s_part[q][1][lane] = B;
     }
@@ -257,7 +262,7 @@ __global__ void __launch_bounds__(256) k_pick_window(PassBufs b, int groups)
         for (int i = t; i < 3 * STS_NBIN; i += 256) h1[i] = 0;
     if (s_fine) { // uniform: the bin lists above are done with, so their LDS serves the pick
         const bool ok = pick_digit<256>(AgentBins{b.h2w}, ctl->K,
-                                        make128(s_R_lo, s_R_hi), 11, &s_sub, reinterpret_cast<u128 *>(s_lo), s_hi,
+                                        make128(s_R_lo, s_R_hi), 11, &s_sub, reinterpret_cast<u128 *>(s_p[0]), s_p[1],
                                         &s_hit2);
         if (ok && t <= STS_SUB_REGIONS) st_agent(&b.sub_cnt[t * 32], 0u);
         if (t == 0) {
