@@ -479,11 +479,13 @@ sts_status sort_state(sts_ctx *c, const u64 *notmask, int *sorted, int *hb_out)
 }
 
 // sort n terms by key, from *k and *a through the buffers kb and ab in turn (the
-// input stays as it is unless no pass is needed); *k and *a: where they end up
+// input stays as it is unless no pass is needed); *k and *a: where they end up.
+// 8-bit digits at every size: a load and a read of 100,000 terms of 24 qubits
+// took 440 us, 478 with 11-bit digits and one pass fewer (of 48 qubits 561 and 576)
 sts_status sort_by_key(sts_ctx *c, u64 n, int prec, u64 **k, void **a, std::array<u64 *, 2> kb,
                        std::array<void *, 2> ab, const u64 *count)
 {
-    const int shape = n <= (1ull << 18) ? STS_RADIX_11x8 : STS_RADIX_8x16;
+    const int shape = STS_RADIX_8x16;
     const int bits = sts_radix_bits(shape);
     const int tiles = (int)ceil_div(n, sts_radix_tile(shape));
     for (int p = 0; p * bits < c->n_qubits; ++p) {

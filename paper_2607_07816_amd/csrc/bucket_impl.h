@@ -876,10 +876,15 @@ __global__ void __launch_bounds__(64 * WeighWaves<AT>::value, 1)
 }
 
 // ---------------------------------------------------------------------------
-// sampling pass (as k_tile_sample): the gate on evenly spaced tiles
-// ---------------------------------------------------------------------------
+// sampling pass (as k_tile_sample): the gate on evenly spaced tiles, one per
+// workgroup, or on all of them for a fine window, which then holds the cut for
+// certain (by count; by mass up to its single-precision sums). A chain of
+// latencies - a share's tables, bins to device memory, the last workgroup's
+// scans: 23 us on the 512 tiles of 100,003 terms, 16 on 128 of them, 24 on 256
+// tiles of 2^24 terms.
 // (the gate comes by value and goes to device memory for the step's other
 // kernels: a launch of its own for that cost 5 us a step)
+// ---------------------------------------------------------------------------
 template <typename AT, int M>
 __global__ void __launch_bounds__(STS_WG) k_bkt_sample(GateArg g, PassBufs b)
 {
@@ -1806,6 +1811,9 @@ __device__ __forceinline__ void small_pass(const GateArg &g, const PassBufs &b)
     flush_bins(b, s_hi, s_lo, hot_lo);
 }
 
+// Both are as long as one share's chain of LDS round trips and the flush of the
+// bins: 11 us at 4,096 to 16,384 terms, k_bkt_mid 18 at 100,003 (k_bkt_weigh, whose
+// tables fill a CU's LDS, took 27 there).
 template <typename AT, int M> __global__ void __launch_bounds__(STS_WG) k_bkt_small(GateArg g, PassBufs b)
 {
     if (blockIdx.x == 0) put_gate(g, b.gate_dst);

@@ -380,7 +380,9 @@ template <typename T> __device__ __forceinline__ T sts_readlane(T v, int lane)
     __builtin_memcpy(&v, w, sizeof(T));
     return v;
 }
-// inclusive sum over the lanes of a row of 16, or of the wave (no LDS traffic)
+// inclusive sum over the lanes of a row of 16, or of the wave (moves inside the
+// registers: shuffles through LDS made the scans of a full CU's waves several
+// times as long)
 template <typename T> __device__ __forceinline__ T row_incl_scan(T v)
 {
     v += sts_dpp<0x111>(v); // from the lanes 1, 2, 4 and 8 below in the row

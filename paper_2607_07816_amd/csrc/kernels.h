@@ -67,7 +67,8 @@ struct PassBufs {
                           // window held the cut, copy the survivors out of the slabs
     u64 *wpart;           // [9][STS_MAX_GROUPS] (the weighing pass: its sums); histogram passes [6][...]: per histogram workgroup, the count of candidates
                           // above the window and the mantissa sums (>> 26, & (2^26-1)) of those in
-                          // the window's exponent; then the count and sums of those inside it
+                          // the window's exponent; then the count and sums of those inside it (k_bkt_mid:
+                          // in that exponent, then of those in the one below)
     // bucketed steps: the input's and the output's bucket tables (first and one past the last
     // term of each bucket), per share the candidates and the survivors, log2 of a share's slab
     const uint2 *bd_in;
@@ -151,7 +152,7 @@ inline u64 sts_radix_tile(int shape) { return (shape & 1) ? 2048ull : 4096ull; }
 // what a sort orders by: the mixed masked key (grouping), the bucket hash of linhash.h, the key
 #define STS_SORT_BY_MIX 0
 #define STS_SORT_BY_BUCKET 1 // (shapes 8x16 and 11x8)
-#define STS_SORT_BY_KEY 2    // (shapes 8x16 and 11x8)
+#define STS_SORT_BY_KEY 2    // (shape 8x16)
 
 // one step of a sort pass: what = 0 digit counts per tile, 1 their scan (one
 // workgroup per digit), 2 the scatter

@@ -1,4 +1,6 @@
 // radix.hip - grouping a state by the bits outside a gate's qubits.
+// (The same passes put a state into bucket order, by the hash of linhash.h, and
+// terms for the host into key order.)
 //
 // Every term whose key differs from another only on the gate's qubits must
 // meet it (Sec. IV.A: the 2^m amplitudes of a tuple share the bits outside
@@ -341,15 +343,18 @@ hipError_t launch_radix(int what, int by, int shape, int prec, const u64 *kin, c
                         const u64 *n_in, u64 *n_out, const u64 *notmask, int shift, u32 *counts, u64 *prefix,
                         u64 *totals, u64 tiles_cap, int tiles, hipStream_t s)
 {
-    if (by != BY_MIX) { // these sorts take two of the shapes
+    if (by == BY_KEY) {
+        if (shape != STS_RADIX_8x16) return hipErrorInvalidValue;
+        return radix_launch<8, 16, BY_KEY>(what, prec, kin, ain, kout, aout, n_in, n_out, notmask, shift, counts, prefix,
+                                           totals, tiles_cap, tiles, s);
+    }
+    if (by == BY_LIN) { // takes two of the shapes
         if (shape == STS_RADIX_8x16)
-            return (by == BY_LIN ? radix_launch<8, 16, BY_LIN> : radix_launch<8, 16, BY_KEY>)(
-                what, prec, kin, ain, kout, aout, n_in, n_out, notmask, shift, counts, prefix, totals, tiles_cap, tiles,
-                s);
+            return radix_launch<8, 16, BY_LIN>(what, prec, kin, ain, kout, aout, n_in, n_out, notmask, shift, counts,
+                                               prefix, totals, tiles_cap, tiles, s);
         if (shape == STS_RADIX_11x8)
-            return (by == BY_LIN ? radix_launch<11, 8, BY_LIN> : radix_launch<11, 8, BY_KEY>)(
-                what, prec, kin, ain, kout, aout, n_in, n_out, notmask, shift, counts, prefix, totals, tiles_cap, tiles,
-                s);
+            return radix_launch<11, 8, BY_LIN>(what, prec, kin, ain, kout, aout, n_in, n_out, notmask, shift, counts,
+                                               prefix, totals, tiles_cap, tiles, s);
         return hipErrorInvalidValue;
     }
     switch (shape) {

@@ -777,6 +777,9 @@ __global__ void __launch_bounds__(64) k_set_gate(GateArg g, GateArg *dst)
     for (u32 i = threadIdx.x; i < sizeof(GateArg) / sizeof(u32); i += 64) d[i] = src[i];
 }
 
+// Terms from and to the host: one read of what the copy brought (bound by HBM, some
+// us); sorting and checking on the host took 34 of a hand-over's 35 ms at 300,007
+// terms.
 // range and finiteness of n terms from the host; complex64: their amplitudes
 // rounded to FP32 (nearest-even)
 __global__ void __launch_bounds__(256) k_load_check(const u64 *__restrict__ keys, const double2 *__restrict__ amps,
