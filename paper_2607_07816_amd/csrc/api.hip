@@ -931,6 +931,7 @@ static sts_status truncate_buckets(sts_ctx *c)
     u64 nb = c->K ? std::min<u64>(c->K, cb) : cb;
     sts_status st = STS_OK;
     const bool out_risk = nb > c->cap; // a cut limited by p-mass alone may keep more than cap terms
+    b.may_refuse = out_risk;
     if (out_risk) {
         st = save_ctl(c);
         if (st != STS_OK) return st;

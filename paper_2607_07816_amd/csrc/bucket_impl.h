@@ -1701,7 +1701,7 @@ __global__ void __launch_bounds__(SEL_NT) k_bkt_select(const GateArg *__restrict
     }
     if (t == 0) {
         *b.n_out = carry;
-        if (carry > b.out_cap) atomicOr(&ctl->flags, STS_F_OUT_OVERFLOW);
+        if (carry > b.out_cap && !b.may_refuse) atomicOr(&ctl->flags, STS_F_OUT_OVERFLOW);
         ctl->w_over = 0;
         ctl->pred_hit = slabs;
     }

@@ -79,6 +79,7 @@ struct PassBufs {
     int slab_shift;
     int fine_window;      // the sample's window is for k_bkt_mid
     int emit_copies;      // write pass: also copies the survivors when the window held the cut
+    int may_refuse;       // the host checks the result's size before it is written
     int recover;          // histogram pass: only after a sampled window that missed
     int whole;            // the passes launched are known to run
     u64 *sbins;           // sampling pass: STS_SW_BANKS x STS_SW_NB counts (u32), as many masses

@@ -75,6 +75,35 @@ def test_steps_at_the_edges(S, N, p):
     same(S, keys, amps, 40, gates(rng, 40, [2, 2, 1, 2, 3, 2, 1, 2]), N, p)
 
 
+@pytest.mark.parametrize("p", [0.5, 0.9])
+@pytest.mark.parametrize("N", [1500, 3000, 30011, 70001, 140003])
+def test_mass_alone(S, N, p):
+    # no top-k: the rule is the mass, in a capacity that does not hold every
+    # candidate; a result that does not fit is refused and changes nothing
+    rng = np.random.default_rng([N, 3])
+    keys, amps = random_state(rng, 40, N)
+    refused = 0
+    with S.State(40, K=0, p=p, precision="c128", capacity=3 * N) as st:
+        st.load_terms(keys, amps)
+        for qs, U in gates(rng, 40, [2, 1, 2]):
+            ko, ao, info = oracle(keys, amps, [(qs, U)], 0, p)
+            st.apply_gate(qs, U)
+            if len(ko) > 3 * N:
+                with pytest.raises(S.CapacityError):
+                    st.truncate()
+                refused += 1
+            else:
+                st.truncate()
+                keys, amps = ko, ao
+                stats = st.stats()
+                assert stats["kept_fraction"] == info["fraction"] and stats["W"] == info["W"]
+        kg, ag = st.read_terms()
+    say(f"N={N} p={p}: {refused} refused")
+    ko, ao = CO.sorted_terms(keys, amps)
+    assert np.array_equal(kg, ko)
+    assert np.array_equal(ag.view(np.uint64), ao.view(np.uint64))
+
+
 @pytest.mark.parametrize("N", [700, 2049, 30011, 70001, 140003])
 def test_c64_steps(S, N):
     rng = np.random.default_rng(N)
