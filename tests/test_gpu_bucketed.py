@@ -190,6 +190,28 @@ def test_nothing_cut_and_no_truncation(S, N):
     assert np.array_equal(ag.view(np.uint64), ao.view(np.uint64))
 
 
+@pytest.mark.parametrize("N", [1500, 3000, 50000, 150000])
+def test_untruncated_gate_beyond_the_capacity(S, N):
+    # reported by the next call, the gate discarded; the state goes on from the terms before it
+    rng = np.random.default_rng(N)
+    keys, amps = random_state(rng, 40, N)
+    (q2, U2), (q1, U1) = gates(rng, 40, [2, 1])
+    with S.State(40, K=0, p=0.0, precision="c128", capacity=3 * N) as st:
+        st.load_terms(keys, amps)
+        for _ in range(2):
+            st.apply_gate(q2, U2)
+            with pytest.raises(S.CapacityError):
+                st.num_terms()
+            k, a = st.read_terms()
+            assert np.array_equal(k, np.sort(keys)) and np.array_equal(a, amps[np.argsort(keys)])
+        st.apply_gate(q1, U1)
+        kg, ag = st.read_terms()
+    ko, ao, _ = CO.step(keys, amps, q1, U1, 0, 0.0, False, CO.host_threads())
+    ko, ao = CO.sorted_terms(ko, ao)
+    assert np.array_equal(kg, ko)
+    assert np.array_equal(ag.view(np.uint64), ao.view(np.uint64))
+
+
 def test_growth_through_every_size(S):
     # from one term to 2^17 and more: every path in turn, the bucket tables refined on the way
     rng = np.random.default_rng(5)
