@@ -10,10 +10,11 @@
 // CU hide each other's chains of LDS round trips.
 //
 // A share larger than the LDS tables (the hash is uneven there) is taken in
-// several rounds, each with the groups whose second hash has one prefix; the
-// prefix grows until the round fits, so any distribution of keys is handled.
+// several parts, each with the groups whose second hash has one prefix
+// (parts.h); every part scans the whole share.
 #pragma once
 #include "group_impl.h"
+#include "parts.h"
 #include "select_impl.h"
 
 namespace sts_bucket {
@@ -451,18 +452,15 @@ __device__ __forceinline__ void share_parts(WaveSmem<AT> &s, const AT *ucol, con
                                             F &&body)
 {
     bool first = true;
-    int depth = 0;
-    u64 pre = 0;
-    if (t.n > BW_CAP)
-        while ((t.n >> depth) > BW_CAP * 3 / 4) ++depth;
-    for (;;) {
+    PartWalk part;
+    part.begin(t.n, BW_CAP);
+    do {
         u32 cnt = t.n;
-        if (depth) {
-            cnt = uni(stage_part<AT>(s, t, keys, amps, g.nm, depth, pre));
-            if (cnt > BW_CAP) { // split the prefix (at 64 bits a part is one group)
-                ++depth;
-                pre <<= 1;
-                continue;
+        if (part.depth) {
+            cnt = uni(stage_part<AT>(s, t, keys, amps, g.nm, part.depth, part.pre));
+            while (cnt > BW_CAP) {
+                part.split();
+                cnt = uni(stage_part<AT>(s, t, keys, amps, g.nm, part.depth, part.pre));
             }
         }
         wave_sync();
@@ -470,11 +468,7 @@ __device__ __forceinline__ void share_parts(WaveSmem<AT> &s, const AT *ucol, con
             if (first) grouped();
             first = false;
         }, body);
-        if (depth == 0) break;
-        ++pre;
-        if (depth < 64 && pre == (1ull << depth)) break;
-        if (depth == 64 && pre == 0) break;
-    }
+    } while (part.next());
 }
 
 template <typename AT, int M, typename F>

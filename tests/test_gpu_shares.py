@@ -1,0 +1,73 @@
+"""Shares that overflow a wave's tables in unkind ways (needs the GPU): many
+terms of one share whose mixed masked keys share a long prefix, so that its
+parts are many and small. FP64, compared with the oracle bit for bit."""
+import functools
+
+import numpy as np
+import pytest
+
+from paper_2607_07816_amd import circuits as C
+from tests.test_gpu_bucketed import MASK64, S, lin_hash, same  # noqa: F401 (S: a fixture)
+
+pytestmark = [pytest.mark.gpu, pytest.mark.timeout(300)]
+
+
+def unmix(h):
+    """The inverse of sts_mix64 (common.h), the SplitMix64 finaliser."""
+    def unshift(x, s):
+        y = x.copy()
+        for _ in range(64 // s + 1):
+            y = x ^ (y >> np.uint64(s))
+        return y
+    with np.errstate(over="ignore"):
+        x = unshift(h, 31)
+        x = x * np.uint64(pow(0x94d049bb133111eb, -1, 1 << 64))
+        x = unshift(x, 27)
+        x = x * np.uint64(pow(0xbf58476d1ce4e5b9, -1, 1 << 64))
+        return unshift(x, 30)
+
+
+def mix(x):
+    with np.errstate(over="ignore"):
+        x = (x ^ (x >> np.uint64(30))) * np.uint64(0xbf58476d1ce4e5b9)
+        x = (x ^ (x >> np.uint64(27))) * np.uint64(0x94d049bb133111eb)
+    return x ^ (x >> np.uint64(31))
+
+
+@functools.lru_cache(maxsize=None)
+def clustered_keys(count, bits, hb, gate):
+    """`count` keys of 64 bits, zero on the gate's qubits, in one bucket of
+    2^hb, whose mixed keys have `bits` leading bits in common."""
+    rng = np.random.default_rng([count, bits, hb])
+    mask = np.uint64(MASK64 ^ sum(1 << q for q in gate))
+    bucket, out = None, np.zeros(0, dtype=np.uint64)
+    prefix = int(rng.integers(0, 1 << 62)) >> (62 - bits)
+    while len(out) < count:
+        low = rng.integers(0, 1 << (64 - bits), size=1 << 22, dtype=np.uint64)
+        k = unmix(np.uint64(prefix << (64 - bits)) | low)
+        k = k[k & ~mask == 0]
+        b = lin_hash(k) >> np.uint64(32 - hb)
+        bucket = b[0] if bucket is None else bucket
+        out = np.unique(np.concatenate([out, k[b == bucket]]))
+    return rng.permutation(out)[:count]
+
+
+def test_unmix():
+    x = np.random.default_rng(1).integers(0, 1 << 63, size=1000, dtype=np.uint64)
+    assert np.array_equal(unmix(mix(x)), x)
+
+
+@pytest.mark.parametrize("p", [0.0, 0.9])
+@pytest.mark.parametrize("N,hb,bits", [(3000, 8, 30), (20000, 11, 30), (150000, 14, 28), (150000, 14, 10)])
+def test_clustered_share(S, N, hb, bits, p):
+    # one share of 330 clustered terms and the buckets' usual ones, cut by the next gate's truncation
+    rng = np.random.default_rng([N, bits])
+    gate = (3, 40)
+    heavy = clustered_keys(330, bits, hb, gate)
+    keys = np.unique(np.concatenate([heavy, rng.integers(0, MASK64, size=N - 330, dtype=np.uint64)]))
+    amps = rng.standard_normal(len(keys)) + 1j * rng.standard_normal(len(keys))
+    amps /= np.linalg.norm(amps)
+    other = tuple(int(q) for q in rng.choice(64, size=2, replace=False))
+    gs = [(gate, C.haar_unitary(rng, 4)), (other, C.haar_unitary(rng, 4)), (gate[:1], C.haar_unitary(rng, 2))]
+    print(f"N={N} hb={hb} bits={bits} p={p}", flush=True)
+    same(S, keys, amps, 64, gs, len(keys), p, cap=2 * len(keys))
