@@ -661,6 +661,11 @@ template <typename AT> struct WeighWaves {
     static constexpr int value = sizeof(AT) == 8 ? 16 : 12;
 };
 constexpr int WEIGH_COLD = 64; // exponent fields with LDS bins, from L - 38
+// Most rounds of 64 groups that a share may take: one of BW_BINNED terms in
+// parts of usual size takes at most some 30, one in many small parts more, and
+// is left to the histogram pass. A lane's sums then stay exact between flushes.
+constexpr u32 WEIGH_ROUNDS = 64;
+static_assert(WEIGH_ROUNDS * BW_FLUSH * 4 <= 1 << 12, "four weights a round, sums of up to 2^12 of them");
 
 template <typename AT, int M>
 __global__ void __launch_bounds__(64 * WeighWaves<AT>::value, 1)
@@ -757,8 +762,8 @@ __global__ void __launch_bounds__(64 * WeighWaves<AT>::value, 1)
     uint2 d2 = runs(tile + step);
     for (u32 it = 0; it < rounds; ++it, tile += step) {
         if (it && it % BW_FLUSH == 0) {
-            // a lane has added at most 16 * 32 * 4 weights, and the bins at
-            // most 16 * 16 * BW_BINNED * 4
+            // a lane has added at most BW_FLUSH * WEIGH_ROUNDS * 4 weights (or
+            // the sums are not used), and the bins at most 16 * 16 * BW_BINNED * 4
             __syncthreads();
             flush();
             __syncthreads();
@@ -785,7 +790,9 @@ __global__ void __launch_bounds__(64 * WeighWaves<AT>::value, 1)
             advance();
             continue;
         }
+        u32 taken = 0;
         share_parts<AT, M>(s.w[wv], s.ucol, gl, sh, keys, amps, advance, [&](const auto &ox, const auto &oy, u64 rest, bool active) {
+            ++taken;
 #pragma unroll
             for (int i = 0; i < (1 << M); ++i) {
                 AT o;
@@ -852,7 +859,7 @@ __global__ void __launch_bounds__(64 * WeighWaves<AT>::value, 1)
             b.t_above[sl] = c_ab;
             b.t_side[sl] = c_in;
         }
-        if (!fits) over = true;
+        if (!fits || taken > WEIGH_ROUNDS) over = true;
         n_all += c_all;
         n_above += c_ab;
         n_win += c_in;

@@ -86,3 +86,50 @@ def test_every_term_once_in_few_parts(lib, spread, cluster, bits, at):
     assert 0 < parts <= limit
     assert scans.value <= parts + limit
     assert (seen == 1).all()
+
+
+BINNED, ROUNDS = 640, 64  # BW_BINNED and WEIGH_ROUNDS of csrc/bucket_impl.h
+
+
+def rounds_of(sizes):
+    return sum(-(-s // 64) + 1 for s in sizes)  # one round more than full ones, for the groups of several members
+
+
+def part_sizes(h, cap):
+    """The parts of the walk, from their definition: halves of what does not fit."""
+    even = 0
+    while len(h) > cap and len(h) >> even > cap * 3 // 4:
+        even += 1
+    out, todo = [], [(even, p) for p in range(1 << even)]
+    while todo:
+        d, p = todo.pop()
+        c = sum(1 for x in h if x >> (64 - d) == p)
+        if c > cap:
+            todo += [(d + 1, 2 * p), (d + 1, 2 * p + 1)]
+        else:
+            out.append(c)
+    return out
+
+
+@pytest.mark.parametrize("n", [321, 480, 500, BINNED])
+def test_rounds_of_usual_shares(lib, n):
+    # evenly spread shares of every size that the weighing pass sums stay far below its bound
+    for seed in range(5):
+        rng = np.random.default_rng([n, seed])
+        h = [int(x) for x in rng.integers(0, (1 << 64) - 1, size=n, dtype=np.uint64)]
+        assert rounds_of(part_sizes(h, CAP)) <= ROUNDS // 2
+
+
+def test_the_most_parts_of_a_summed_share(lib):
+    # a term beside the cluster at every bit of its prefix: a part a bit, which the bound on the rounds catches
+    n = BINNED
+    side = [1 << (63 - d) for d in range(50)]
+    rng = np.random.default_rng(0)
+    h = side + [int(x) for x in rng.permutation(1 << 13)[:n - len(side)]]
+    arr = np.array(h, dtype=np.uint64)
+    seen, scans = np.zeros(n, dtype=np.uint32), ctypes.c_long(0)
+    parts = lib.walk(n, CAP, arr.ctypes.data_as(ctypes.c_void_p), seen.ctypes.data_as(ctypes.c_void_p), ctypes.byref(scans),
+                     ctypes.c_long(1 << 20))
+    assert parts == len(part_sizes(h, CAP)) <= 66
+    assert (seen == 1).all()
+    assert rounds_of(part_sizes(h, CAP)) > ROUNDS  # more than a lane's sums are counted on for
