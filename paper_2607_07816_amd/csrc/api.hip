@@ -82,6 +82,14 @@ constexpr u64 kSelectMax = 1ull << 17;
 // terms 51 us instead of 54, at 32,768 69 and 59.
 constexpr u64 kSmallMax = 1ull << 14;
 
+// Terms from the host of which a quarter has this many in one bucket (of 2 to
+// 16 on average, and up to 36 by chance) take the sort: a share of four buckets
+// of 160 terms and more no longer fits a wave's tables twice, and larger ones are
+// scanned once for each of their parts. Steps of 60,000 terms with 117 in a bucket:
+// 62 us bucketed, 154 sorted; with 234: 1610 and 176. Of 150,000 with 146: 136 and
+// 192, with 293 262 and 190. Of 2^20 with 128: 396 and 236, with 1024 8650 and 245.
+constexpr u32 kCrowded = 48;
+
 Layout make_layout(u64 cap, int prec)
 {
     const u64 asz = prec == STS_C128 ? 16 : 8;
@@ -191,6 +199,7 @@ struct sts_ctx {
     u32 *w_all = nullptr, *w_kept = nullptr;
     u64 *t_base = nullptr;
     uint2 *bd[2] = {nullptr, nullptr}; // bucket tables
+    bool crowded = false;   // loaded terms that crowd in few buckets: not kept in bucket order
     bool bucketed = false;  // the state in buffer cur is in bucket order:
     int hb = 0, bdc = 0;    // 2^hb buckets, table bd[bdc]
     bool one_step = false;    // sts_step_static
@@ -508,7 +517,7 @@ bool use_tiny(const sts_ctx *c, int m) { return m <= 2 && c->n_bound <= STS_TINY
 // costs what the sort does, and no later step gains from it)
 bool use_buckets(const sts_ctx *c, int m)
 {
-    return !c->one_step && m <= 2 && c->cap <= kBucketMax && c->n_bound > STS_TINY_MAX;
+    return !c->one_step && !c->crowded && m <= 2 && c->cap <= kBucketMax && c->n_bound > STS_TINY_MAX;
 }
 
 // whether the state's buckets suit its size bound: neither so few that a
@@ -1166,14 +1175,16 @@ sts_status sts_load_terms(sts_ctx *c, uint64_t n, const uint64_t *keys, const do
         double *wide = c->prec == STS_C128 ? (double *)c->amps[dst] : (double *)c->side_amp;
         STS_TRY(c, hipMemcpyAsync(c->keys[dst], keys, n * 8, hipMemcpyHostToDevice, c->stream));
         STS_TRY(c, hipMemcpyAsync(wide, amps, n * 16, hipMemcpyHostToDevice, c->stream));
-        STS_TRY(c, launch_load_check(c->prec, c->keys[dst], wide, n, lim, (float2 *)c->amps[dst], c->ctl, c->stream));
+        u64 *counts = c->cap <= kBucketMax ? (u64 *)c->bd[c->bdc ^ 1] : nullptr; // (the next bucketed step's table)
+        STS_TRY(c, launch_load_check(c->prec, c->keys[dst], wide, n, lim, (float2 *)c->amps[dst], bucket_bits(n), counts,
+                                     c->ctl, c->stream));
         STS_TRY(c, launch_set_n(&c->ctl->cnt[dst], n, c->stream));
         u64 *k = c->keys[dst];
         void *w = c->keys[dst]; // moved along with the keys, not used
         st = sort_by_key(c, n, STS_C64, &k, &w, {c->side_key, c->side_key + c->cap}, {c->side_w, c->side_w + c->cap},
                          &c->ctl->cnt[dst]);
         if (st != STS_OK) return st;
-        STS_TRY(c, launch_load_unique(k, n, c->ctl, c->stream));
+        STS_TRY(c, launch_load_unique(k, n, bucket_bits(n), counts, c->ctl, c->stream));
         st = sync_ctl(c); // also: the caller's arrays have been read
         if (st != STS_OK) return st;
         if (c->hctl->load_flags) {
@@ -1184,6 +1195,7 @@ sts_status sts_load_terms(sts_ctx *c, uint64_t n, const uint64_t *keys, const do
     // the state is replaced: any pending gate is dropped
     c->pending = c->bkt_pending = c->tiny_pending = false;
     c->bucketed = false;
+    c->crowded = n && c->hctl->load_most >= kCrowded;
     c->cur = dst;
     STS_TRY(c, launch_set_n(&c->ctl->cnt[c->cur], n, c->stream));
     c->n_bound = n;

@@ -48,6 +48,7 @@ struct DevCtl {
     alignas(128) u32 done[4]; // last-workgroup counters, one per kernel kind
     alignas(128) u32 flags;   // STS_F_* below
     u32 load_flags;      // sts_load_terms: the terms are not acceptable
+    u32 load_most;       // most in one bucket, of a quarter of them
     u32 w_over;          // bucketed histogram pass: a share's slab was too small for its window entries
     // truncation rule
     alignas(128) u64 K;  // top-k (0 = off)

@@ -178,11 +178,12 @@ hipError_t launch_init_state(int prec, u64 *keys, void *amps, u64 *n_out, hipStr
 hipError_t launch_set_n(u64 *n_out, u64 n, hipStream_t s);
 hipError_t launch_set_gate(const GateArg &g, GateArg *dst, hipStream_t s);
 const void *set_gate_kernel(); // the kernel launch_set_gate launches (to find its node in a captured graph)
-// terms from the host: range and finiteness (ctl->load_flags), and FP32 rounding of complex64 amplitudes
-hipError_t launch_load_check(int prec, const u64 *keys, const double *amps, u64 n, u64 limit, float2 *amps32,
-                             DevCtl *ctl, hipStream_t s);
-// ctl->load_flags if two neighbours of the n sorted keys are equal
-hipError_t launch_load_unique(const u64 *sorted, u64 n, DevCtl *ctl, hipStream_t s);
+// terms from the host: range and finiteness (ctl->load_flags), FP32 rounding of complex64 amplitudes, and the
+// terms in each of the 2^hb buckets, of a quarter of them (counts, cleared here, or null)
+hipError_t launch_load_check(int prec, const u64 *keys, const double *amps, u64 n, u64 limit, float2 *amps32, int hb,
+                             u64 *counts, DevCtl *ctl, hipStream_t s);
+// ctl->load_flags if two neighbours of the n sorted keys are equal; ctl->load_most: the most terms in one bucket
+hipError_t launch_load_unique(const u64 *sorted, u64 n, int hb, const u64 *counts, DevCtl *ctl, hipStream_t s);
 // n complex64 amplitudes to FP64 pairs
 hipError_t launch_widen(const float2 *in, double2 *out, u64 n, hipStream_t s);
 hipError_t launch_fill_zero(u64 *p, u64 n, hipStream_t s);

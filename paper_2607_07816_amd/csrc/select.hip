@@ -777,29 +777,54 @@ __global__ void __launch_bounds__(64) k_set_gate(GateArg g, GateArg *dst)
     for (u32 i = threadIdx.x; i < sizeof(GateArg) / sizeof(u32); i += 64) d[i] = src[i];
 }
 
+// before the terms' buckets are counted
+__global__ void __launch_bounds__(256) k_load_clear(u32 *counts, u64 n, DevCtl *ctl)
+{
+    for (u64 i = (u64)blockIdx.x * 256 + threadIdx.x; i < n; i += (u64)gridDim.x * 256) counts[i] = 0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) ctl->load_most = 0;
+}
+
 // Terms from and to the host: one read of what the copy brought (bound by HBM, some
 // us); sorting and checking on the host took 34 of a hand-over's 35 ms at 300,007
 // terms.
 // range and finiteness of n terms from the host; complex64: their amplitudes
-// rounded to FP32 (nearest-even)
+// rounded to FP32 (nearest-even); and how many of a quarter
+// of them lie in each bucket
 __global__ void __launch_bounds__(256) k_load_check(const u64 *__restrict__ keys, const double2 *__restrict__ amps,
-                                                    u64 n, u64 limit, float2 *amps32, DevCtl *ctl)
+                                                    u64 n, u64 limit, float2 *amps32, int hb, u32 *counts, DevCtl *ctl)
 {
     bool bad = false;
     for (u64 i = (u64)blockIdx.x * 256 + threadIdx.x; i < n; i += (u64)gridDim.x * 256) {
         const double2 a = amps[i];
-        bad |= keys[i] > limit || !isfinite(a.x) || !isfinite(a.y);
+        const u64 key = keys[i];
+        bad |= key > limit || !isfinite(a.x) || !isfinite(a.y);
         if (amps32) amps32[i] = make_float2((float)a.x, (float)a.y);
+        // (a quarter of the terms, by another hash: 5 us at 300,007 terms, 15 for all)
+        if (counts && sts_mix64(key) >> 62 == 0) {
+            u32 v = 0;
+            for (int j = 0; j < hb; ++j) v |= sts_parity(key, k_lin_masks[32 - hb + j]) << j;
+            atomicAdd(&counts[v], 1u);
+        }
     }
     if (bad) atomicOr(&ctl->load_flags, 1u);
 }
 
-__global__ void __launch_bounds__(256) k_load_unique(const u64 *__restrict__ keys, u64 n, DevCtl *ctl)
+__global__ void __launch_bounds__(256) k_load_unique(const u64 *__restrict__ keys, u64 n, const u32 *__restrict__ counts,
+                                                     u64 buckets, DevCtl *ctl)
 {
     bool bad = false;
     for (u64 i = (u64)blockIdx.x * 256 + threadIdx.x + 1; i < n; i += (u64)gridDim.x * 256)
         bad |= keys[i] == keys[i - 1];
     if (bad) atomicOr(&ctl->load_flags, 1u);
+    u32 most = 0;
+    for (u64 i = (u64)blockIdx.x * 256 + threadIdx.x; i < buckets; i += (u64)gridDim.x * 256)
+        most = counts[i] > most ? counts[i] : most;
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) {
+        const u32 o = __shfl_xor(most, d, 64);
+        most = o > most ? o : most;
+    }
+    if (sts_lane() == 0 && most) atomicMax(&ctl->load_most, most);
 }
 
 __global__ void __launch_bounds__(256) k_widen(const float2 *__restrict__ in, double2 *__restrict__ out, u64 n)
@@ -924,17 +949,20 @@ hipError_t launch_set_n(u64 *n_out, u64 n, hipStream_t s)
 
 static dim3 stream_grid(u64 n) { return dim3((unsigned)std::max<u64>(1, std::min<u64>((n + 255) / 256, 2048))); }
 
-hipError_t launch_load_check(int prec, const u64 *keys, const double *amps, u64 n, u64 limit, float2 *amps32,
-                             DevCtl *ctl, hipStream_t s)
+hipError_t launch_load_check(int prec, const u64 *keys, const double *amps, u64 n, u64 limit, float2 *amps32, int hb,
+                             u64 *counts, DevCtl *ctl, hipStream_t s)
 {
+    if (counts) hipLaunchKernelGGL(k_load_clear, stream_grid(1ull << hb), dim3(256), 0, s, (u32 *)counts, 1ull << hb,
+                                   ctl);
     hipLaunchKernelGGL(k_load_check, stream_grid(n), dim3(256), 0, s, keys, (const double2 *)amps, n, limit,
-                       prec == 0 ? nullptr : amps32, ctl);
+                       prec == 0 ? nullptr : amps32, hb, (u32 *)counts, ctl);
     return hipGetLastError();
 }
 
-hipError_t launch_load_unique(const u64 *sorted, u64 n, DevCtl *ctl, hipStream_t s)
+hipError_t launch_load_unique(const u64 *sorted, u64 n, int hb, const u64 *counts, DevCtl *ctl, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_load_unique, stream_grid(n), dim3(256), 0, s, sorted, n, ctl);
+    hipLaunchKernelGGL(k_load_unique, stream_grid(n), dim3(256), 0, s, sorted, n, (const u32 *)counts,
+                       counts ? 1ull << hb : 0ull, ctl);
     return hipGetLastError();
 }
 

@@ -7,7 +7,8 @@ import numpy as np
 import pytest
 
 from paper_2607_07816_amd import circuits as C
-from tests.test_gpu_bucketed import MASK64, S, lin_hash, same  # noqa: F401 (S: a fixture)
+from tests.test_gpu_bucketed import MASK64, S, lin_hash, oracle, run, same  # noqa: F401 (S: a fixture)
+from tests.test_gpu_window import check
 
 pytestmark = [pytest.mark.gpu, pytest.mark.timeout(300)]
 
@@ -52,6 +53,23 @@ def clustered_keys(count, bits, hb, gate):
     return rng.permutation(out)[:count]
 
 
+def span_of_kernel(bits, rng, count):
+    """`count` keys of 64 bits whose bucket hash has its top `bits` bits zero."""
+    dirs = lin_hash(np.uint64(1) << np.arange(64, dtype=np.uint64)) >> np.uint64(32 - bits)
+    rows = [(int(d), 1 << q) for q, d in enumerate(dirs)]  # (hash, key): eliminate the hash bits
+    for b in range(bits):
+        pivot = next((r for r in rows if r[0] >> b & 1), None)
+        if pivot:
+            rows.remove(pivot)
+            rows = [(h ^ pivot[0], k ^ pivot[1]) if h >> b & 1 else (h, k) for h, k in rows]
+    basis = np.array([k for h, k in rows if h == 0], dtype=np.uint64)
+    out = np.zeros(0, dtype=np.uint64)
+    while len(out) < count:
+        pick = rng.integers(0, 2, size=(2 * count, len(basis)), dtype=np.uint64)
+        out = np.unique(np.concatenate([out, np.bitwise_xor.reduce(pick * basis[None, :], axis=1)]))
+    return rng.permutation(out)[:count]
+
+
 def test_unmix():
     x = np.random.default_rng(1).integers(0, 1 << 63, size=1000, dtype=np.uint64)
     assert np.array_equal(unmix(mix(x)), x)
@@ -71,3 +89,35 @@ def test_clustered_share(S, N, hb, bits, p):
     gs = [(gate, C.haar_unitary(rng, 4)), (other, C.haar_unitary(rng, 4)), (gate[:1], C.haar_unitary(rng, 2))]
     print(f"N={N} hb={hb} bits={bits} p={p}", flush=True)
     same(S, keys, amps, 64, gs, len(keys), p, cap=2 * len(keys))
+
+
+@pytest.mark.parametrize("p", [0.0, 0.9])
+@pytest.mark.parametrize("N,bits", [(1 << 16, 16), (1 << 16, 12), (60000, 4), (60000, 3), (150000, 4), (150000, 3),
+                                    (20000, 3), (1500, 16)])
+def test_terms_that_crowd_in_few_buckets(S, N, bits, p):
+    # all terms in 2^-bits of the buckets: from some 160 in each on their steps are sorted, those with fewer
+    # take their shares in parts. (65536 terms of one bucket took seconds a step bucketed.)
+    rng = np.random.default_rng([N, bits])
+    keys = span_of_kernel(bits, rng, N)
+    amps = rng.standard_normal(N) + 1j * rng.standard_normal(N)
+    amps /= np.linalg.norm(amps)
+    print(f"N={N} bits={bits} p={p}", flush=True)
+    same(S, keys, amps, 64, [((int(a), int(b)), C.haar_unitary(rng, 4)) for a, b in rng.choice(64, size=(3, 2), replace=False)],
+         N, p, cap=4 * N)
+
+
+def test_crowded_terms_and_then_others(S):
+    # the order follows the terms that were loaded last; refused terms leave it
+    rng = np.random.default_rng(7)
+    N = 1 << 14
+    crowded, spread = span_of_kernel(14, rng, N), np.unique(rng.integers(0, MASK64, size=N, dtype=np.uint64))
+    amps = rng.standard_normal(N) + 1j * rng.standard_normal(N)
+    gs = [((5, 50), C.haar_unitary(rng, 4)), ((9,), C.haar_unitary(rng, 2))]
+    with S.State(64, K=N, p=0.0, precision="c128", capacity=N) as st:
+        for keys in (crowded, spread, crowded):
+            st.load_terms(keys, amps[:len(keys)])
+            with pytest.raises(Exception):
+                st.load_terms(np.concatenate([keys, keys[:1]])[1:], np.full(len(keys), np.nan))
+            ko, ao, info = oracle(keys, amps[:len(keys)], gs, N, 0.0)
+            kg, ag, stats = run(st, gs)
+            check(kg, ag, stats, ko, ao, info, "c128")
