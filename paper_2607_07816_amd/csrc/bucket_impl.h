@@ -630,7 +630,7 @@ __global__ void __launch_bounds__(STS_WG) k_bkt_hist(const GateArg *__restrict__
 // weighing pass of a sampled step (large states): the window [w_lo, w_hi] is
 // set, so the exact masses needed are only the total's, the mass above the
 // window and the window's own level-2 bins. The first two are summed in
-// registers: a weight of the exponent fields [L, L + 28), L = e_w - 15, is a
+// registers: a weight of the exponent fields [L, L + FINE_EXPS), L <= e_w, is a
 // multiple of u = 2^(L - 1075) below 2^80 u, and is split exactly into a
 // multiple of 2^40 u (by adding and subtracting 1.5 * 2^92 u) and a rest of
 // at most 2^39 u; sums of up to 2^12 of either stay exact in binary64. Weights
@@ -660,7 +660,12 @@ __device__ __forceinline__ void flush_fine(u64 *s_acc, FineSums &f, double k1, d
 template <typename AT> struct WeighWaves {
     static constexpr int value = sizeof(AT) == 8 ? 16 : 12;
 };
-constexpr int WEIGH_COLD = 64; // exponent fields with LDS bins, from L - 38
+constexpr int FINE_EXPS = 28; // exponent fields that the registers sum, from L
+// LDS bins for the rest of [TT_EBASE, TT_EBASE + TT_NB), the histogram pass's
+// range. (Bins in device memory, where every workgroup adds to the same few words,
+// took 5300 us at 2^20 terms whose cut lies 2^16 below most weights, and LDS bins
+// 245; those from L - 38 to L + 25 only, 2800 us where small weights lie lower.)
+constexpr int WEIGH_COLD = TT_NB - FINE_EXPS;
 // Most rounds of 64 groups that a share may take: one of BW_BINNED terms in
 // parts of usual size takes at most some 30, one in many small parts more, and
 // is left to the histogram pass. A lane's sums then stay exact between flushes.
@@ -694,16 +699,14 @@ __global__ void __launch_bounds__(64 * WeighWaves<AT>::value, 1)
     const u64 *keys = b.keys;
     const AT *amps = (const AT *)b.amps;
     const u32 ntiles = bkt_tiles(g.bkt);
-    const int e_w = ctl->e_w;
     const u64 w_lo = ctl->w_lo, w_hi = ctl->w_hi;
     const u32 d_lo = uni((u32)((((1ull << 52) - 1) - (w_hi & ((1ull << 52) - 1))) >> 41));
     const u32 d_top = 2047u - d_lo;
     // the window's edges are multiples of 2^47 in the weight bits: the high
     // words decide
     const u32 wL = uni((u32)(w_lo >> 32)), wH = uni((u32)((w_hi + 1) >> 32));
-    const int L = (int)uni((u32)sts_fine_low(e_w));
-    const u32 rL = (u32)L << 20, rN = 28u << 20;
-    const int e_cold = L - 38;
+    const int L = (int)uni((u32)ctl->w_L);
+    const u32 rL = (u32)L << 20, rN = (u32)FINE_EXPS << 20;
     const double C = __longlong_as_double((long long)(((u64)(L + 40) << 52) | (1ull << 51)));
     const double k1 = __longlong_as_double((long long)((u64)(2058 - L) << 52));
     const double k2 = __longlong_as_double((long long)((u64)(2098 - L) << 52));
@@ -725,7 +728,7 @@ __global__ void __launch_bounds__(64 * WeighWaves<AT>::value, 1)
             const u64 lo = s_lo[i];
             if (lo >> 44) {
                 const u128 tot = ((u128)s_hi[i] << 20) + (u128)(lo & ((1ull << 44) - 1));
-                const int e = e_cold + i; // counted bins only: a field of the binary64 range
+                const int e = TT_EBASE + i + (TT_EBASE + i < L ? 0 : FINE_EXPS);
                 atomicAdd(&b.h1[e], lo >> 44);
                 atomicAdd(&b.h1[STS_NBIN + e], (u64)(tot >> 26));
                 atomicAdd(&b.h1[2 * STS_NBIN + e], (u64)tot & ((1ull << 26) - 1));
@@ -809,7 +812,7 @@ __global__ void __launch_bounds__(64 * WeighWaves<AT>::value, 1)
                 if (m_far) { // uniform: some weights are too far from the window for the sums
                     if (cand && hw - rL >= rN) {
                         w = 0.0;
-                        const int e_ = (int)(wb >> 52), bin = e_ - e_cold;
+                        const int e_ = (int)(wb >> 52), bin = e_ - TT_EBASE - (e_ < L ? 0 : FINE_EXPS);
                         const u64 mant = sts_mant(wb);
                         if ((unsigned)bin < (unsigned)WEIGH_COLD) {
                             atomicAdd(&s_hi[bin], mant >> 20);

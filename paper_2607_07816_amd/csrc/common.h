@@ -66,6 +66,7 @@ struct DevCtl {
     // the sampling pass (w_mode = 1), else the octave of e_pred
     int w_mode;
     int e_w;
+    int w_L;             // lowest exponent field that the weighing pass sums in registers
     u64 w_lo, w_hi;
     int need_full;       // bucketed step: the sampled window missed; the histogram pass runs after all
     int level;           // last resolved level
@@ -95,10 +96,9 @@ struct DevCtl {
 #define STS_F_UNRESOLVED 4u
 #define STS_F_INEXACT 8u
 
-// lowest exponent field whose weights the weighing pass sums in registers
-// (a window is set only where it is at least STS_FINE_MIN - 15: see there)
+// lowest exponent field of a window: the weighing pass sums weights from at
+// most 15 fields below it in registers
 #define STS_FINE_MIN 100
-__host__ __device__ inline int sts_fine_low(int e_w) { return e_w - 15; }
 
 // --------------------------------------------------------------------------
 // hashing: a bijective 64-bit mixer (splitmix64 finalisation). Equal hashes

@@ -1041,14 +1041,14 @@ struct SampleSmem {
     float m[STS_SW_NB];
     u64 scan_c[STS_WG / 64];
     double scan_m[STS_WG / 64];
-    u32 flag, hit, cab, inputs;
+    u32 flag, hit, cab, eab, inputs;
     int at_k, at_p;
     float mab, mbe;
 };
 
 // a thread's candidates outside the bins
 struct SampleAcc {
-    u32 c_above = 0;
+    u32 c_above = 0, e_above = 0; // (e_above: the sum of their rows)
     float m_above = 0.f, m_below = 0.f;
 };
 
@@ -1060,6 +1060,7 @@ __device__ __forceinline__ void sample_begin(SampleSmem &s)
     s.m[threadIdx.x] = 0.f;
     if (threadIdx.x == 0) {
         s.cab = 0;
+        s.eab = 0;
         s.inputs = 0;
         s.mab = 0.f;
         s.mbe = 0.f;
@@ -1072,6 +1073,7 @@ __device__ __forceinline__ void sample_add(SampleSmem &s, SampleAcc &a, u64 wb, 
     const int row = (int)(wb >> 52) - e_lo;
     if (row >= STS_SW_EXPS) {
         ++a.c_above;
+        a.e_above += (u32)row;
         a.m_above += w;
     } else if (row < 0) {
         a.m_below += w;
@@ -1093,17 +1095,19 @@ __device__ __forceinline__ void sample_flush(SampleSmem &s, SampleAcc &a, const 
     u32 *gc = reinterpret_cast<u32 *>(b.sbins);                                   // [bank][bin] counts
     float *gm = reinterpret_cast<float *>(b.sbins + STS_SW_BANKS * STS_SW_NB / 2); // [bank][bin] masses
     // per bank: [0] inputs sampled, [1] count above the bins, [2] (float) mass
-    // above, [3] (float) mass below
+    // above, and their rows' sum in the upper half, [3] (float) mass below
     u64 *bt = b.sbins + STS_SW_BANKS * STS_SW_NB + 4 * bank;
 #pragma unroll
     for (int d = 32; d > 0; d >>= 1) {
         a.c_above += __shfl_xor(a.c_above, d, 64);
+        a.e_above += __shfl_xor(a.e_above, d, 64);
         a.m_above += __shfl_xor(a.m_above, d, 64);
         a.m_below += __shfl_xor(a.m_below, d, 64);
     }
     if (inputs) atomicAdd(&s.inputs, inputs);
     if ((threadIdx.x & 63) == 0) {
         atomicAdd(&s.cab, a.c_above);
+        atomicAdd(&s.eab, a.e_above);
         atomicAdd(&s.mab, a.m_above);
         atomicAdd(&s.mbe, a.m_below);
     }
@@ -1118,6 +1122,7 @@ __device__ __forceinline__ void sample_flush(SampleSmem &s, SampleAcc &a, const 
         if (s.cab) {
             atomicAdd(&bt[1], (u64)s.cab);
             atomicAdd(reinterpret_cast<float *>(&bt[2]), s.mab);
+            atomicAdd(reinterpret_cast<u32 *>(&bt[2]) + 1, s.eab);
         }
         if (s.mbe != 0.f) atomicAdd(reinterpret_cast<float *>(&bt[3]), s.mbe);
     }
@@ -1142,7 +1147,7 @@ __device__ __forceinline__ void sample_finish(SampleSmem &s, const PassBufs &b, 
         c += ld_agent(&gc[k * STS_SW_NB + f]);
         m += (double)__int_as_float((int)ld_agent(reinterpret_cast<const u32 *>(&gm[k * STS_SW_NB + f])));
     }
-    u64 sampled = 0, c_above = 0;
+    u64 sampled = 0, c_above = 0, e_above = 0;
     double m_above = 0.0, m_below = 0.0;
 #pragma unroll
     for (int k = 0; k < STS_SW_BANKS; ++k) {
@@ -1150,6 +1155,7 @@ __device__ __forceinline__ void sample_finish(SampleSmem &s, const PassBufs &b, 
         sampled += ld_agent(&bt[0]);
         c_above += ld_agent(&bt[1]);
         m_above += (double)__int_as_float((int)ld_agent(reinterpret_cast<const u32 *>(&bt[2])));
+        e_above += ld_agent(reinterpret_cast<const u32 *>(&bt[2]) + 1);
         m_below += (double)__int_as_float((int)ld_agent(reinterpret_cast<const u32 *>(&bt[3])));
     }
     u64 ctot;
@@ -1203,6 +1209,11 @@ __device__ __forceinline__ void sample_finish(SampleSmem &s, const PassBufs &b, 
             const int lo_sub = sub > 0 ? sub - 1 : 0;
             const int hi_sub = sub + 1 < (1 << STS_SW_FB) ? sub + 1 : sub;
             ctl->e_w = ex;
+            // what the weighing pass sums in registers: from 15 exponent fields
+            // below the window on; higher up, but not above the window, where most
+            // weights lie above the bins (24 fields below their mean one)
+            const int bulk = c_above > ctot ? e_lo + (int)(e_above / c_above) : 0;
+            ctl->w_L = std::min(std::max(ex - 15, bulk - 24), ex);
             ctl->w_lo = ((u64)ex << 52) | ((u64)lo_sub << (52 - STS_SW_FB));
             ctl->w_hi = ((u64)ex << 52) + ((u64)(hi_sub + 1) << (52 - STS_SW_FB)) - 1;
             ctl->w_mode = 1;

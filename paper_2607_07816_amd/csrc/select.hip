@@ -75,7 +75,7 @@ __global__ void __launch_bounds__(256) k_pick_window(PassBufs b, int groups)
             }
         return;
     }
-    const int L = sts_fine_low(e);
+    const int L = ctl->w_L;
     // every load issued before any is used: the workgroups' sums,
     u64 c_all = 0, c_ab = 0, c_in = 0;
     u128 tot = 0, abv = 0; // units of 2^(L - 1075); the low parts may be negative

@@ -1,0 +1,57 @@
+"""Cuts far from where most weights lie, and steps that cut nothing (needs the
+GPU): gates close to a permutation, whose cut lies in the tail of the kept
+weights, and gates that do not branch, on states around and above 2^17 terms.
+FP64, compared with the oracle bit for bit."""
+import numpy as np
+import pytest
+
+from oracle import c_oracle as CO
+from paper_2607_07816_amd import circuits as C
+from tests.helpers import random_state
+from tests.test_gpu_bucketed import S, oracle, run  # noqa: F401 (S: a fixture)
+from tests.test_gpu_window import check
+
+pytestmark = [pytest.mark.gpu, pytest.mark.timeout(300)]
+
+CZ = np.diag([1, 1, 1, -1]).astype(np.complex128)
+
+
+def rx(theta):
+    c, s = np.cos(theta), np.sin(theta)
+    return np.array([[c, -1j * s], [-1j * s, c]])
+
+
+def pick(rng, n, m):
+    return tuple(int(q) for q in rng.choice(n, size=m, replace=False))
+
+
+def steps(S, keys, amps, n, gs, K, p, cap):
+    """Every step of `gs` on one context, each compared with the oracle's."""
+    with S.State(n, K=K, p=p, precision="c128", capacity=cap) as st:
+        st.load_terms(keys, amps)
+        for i, (qs, U) in enumerate(gs):
+            keys, amps, info = oracle(keys, amps, [(qs, U)], K, p)
+            kg, ag, stats = run(st, [(qs, U)])
+            print(f"step {i} {qs}", flush=True)
+            check(kg, ag, stats, keys, amps, info, "c128")
+
+
+@pytest.mark.parametrize("p", [0.0, 0.99999])
+@pytest.mark.parametrize("theta", [1e-2, 1e-3, 1e-4, 1e-7, 1e-12, 1e-40])
+@pytest.mark.parametrize("N", [40000, 150000])
+def test_gates_close_to_a_permutation(S, N, theta, p):
+    rng = np.random.default_rng([N, int(-np.log10(theta))])
+    keys, amps = random_state(rng, 40, N)
+    gs = [(pick(rng, 40, 2), C.haar_unitary(rng, 4))] + \
+         [(pick(rng, 40, 2), CZ @ np.kron(rx(theta), rx(theta))), (pick(rng, 40, 1), rx(theta))] * 2
+    steps(S, keys, amps, 40, gs, N, p, N)
+
+
+@pytest.mark.parametrize("exponents", [(-3, 3), (-60, 60), (-150, 100)])
+def test_weights_of_any_size(S, exponents):
+    # amplitudes spread over many octaves, on both sides of the cut
+    rng = np.random.default_rng(exponents[1])
+    N = 150000
+    keys, amps = random_state(rng, 40, N)
+    amps = amps * 2.0 ** rng.integers(exponents[0], exponents[1], size=N)
+    steps(S, keys, amps, 40, [(pick(rng, 40, m), C.haar_unitary(rng, 1 << m)) for m in (2, 1, 2, 2)], N, 0.0, N)
