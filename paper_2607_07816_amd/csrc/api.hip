@@ -602,7 +602,7 @@ sts_status bucket_write(sts_ctx *c, const PassBufs &b, int dst, u64 bound)
                        launch_bucket_pass(STS_BKT_COUNT, c->prec, c->gate.m, b, tiles, c->stream));
         STS_LAUNCH(c, STS_K_TILE_KEPT, launch_bucket_kept(b, tiles, c->stream));
     }
-    const bool copied = !b.materialise && !b.emit_copies && !b.whole;
+    const bool copied = !b.materialise && !b.emit_copies;
     if (copied)
         STS_LAUNCH(c, STS_K_GROUP_EMIT, launch_bucket_pass(STS_BKT_COPY, c->prec, c->gate.m, b, tiles, c->stream));
     STS_LAUNCH(c, copied ? STS_K_GROUP_EXTRACT : STS_K_GROUP_EMIT, launch_bucket_pass(STS_BKT_EMIT, c->prec, c->gate.m, b, tiles, c->stream));
@@ -946,15 +946,14 @@ static sts_status truncate_buckets(sts_ctx *c)
         if (st != STS_OK) return st;
     }
     const bool small = c->n_bound <= kSelectMax && tiles * 4 <= STS_SEL_SHARES;
+    b.keep = 1;
+    b.recover = 1;
     if (!small && c->p == 0.0 && c->K && cb < c->K) {
         // nothing can be cut: the histogram for the statistics, then the write
         b.whole = 1;
         STS_TRY(c, launch_set_gate(c->gate, c->dgate, c->stream));
         STS_LAUNCH(c, STS_K_GROUP_HIST, launch_bucket_pass(STS_BKT_HIST, c->prec, m, b, tiles, c->stream));
-        STS_LAUNCH(c, STS_K_PICK1, launch_pick1(b, 0, 0, 0, c->stream));
-        return bucket_write(c, b, out, nb);
-    }
-    if (small && c->n_bound > kSmallMax) {
+    } else if (small && c->n_bound > kSmallMax) {
         b.fine_window = 1;
         STS_LAUNCH(c, STS_K_SAMPLE, launch_bucket_pass(STS_BKT_SAMPLE, c->prec, m, b, tiles, c->stream, &c->gate));
         STS_LAUNCH(c, STS_K_GROUP_HIST, launch_bucket_pass(STS_BKT_MID, c->prec, m, b, tiles, c->stream));
@@ -970,7 +969,7 @@ static sts_status truncate_buckets(sts_ctx *c)
         STS_LAUNCH(c, STS_K_SAMPLE, launch_bucket_pass(STS_BKT_SAMPLE, c->prec, m, b, tiles, c->stream, &c->gate));
         STS_LAUNCH(c, STS_K_GROUP_HIST, launch_bucket_pass(STS_BKT_WEIGH, c->prec, m, b, tiles, c->stream));
         STS_LAUNCH(c, STS_K_PICK1, launch_pick_window(b, bucket_weigh_groups(c->prec, m, tiles), c->stream));
-        b.recover = 1; // (timed apart from the passes that do the work)
+        // (timed apart from the passes that do the work)
         STS_LAUNCH(c, STS_K_SIDE_HIST, launch_bucket_pass(STS_BKT_HIST, c->prec, m, b, tiles, c->stream));
         STS_LAUNCH(c, STS_K_GROUP_EXTRACT, launch_bucket_pass(STS_BKT_EXTRACT, c->prec, m, b, tiles, c->stream));
         const int sg =

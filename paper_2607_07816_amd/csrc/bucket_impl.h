@@ -565,24 +565,31 @@ __device__ __forceinline__ int small_window(const DevCtl *ctl)
 // ---------------------------------------------------------------------------
 // histogram pass: exponent histogram with exact mantissa sums of all new
 // weights (persistent grid). With b.recover it runs only after a sampled
-// window that missed, and its last workgroup does the level-1 pick.
+// window that missed (or where nothing can be cut, b.whole), and its last
+// workgroup does the level-1 pick. With b.keep it also puts every candidate, with
+// its weight, into the share's slab, from which the following passes then read:
+// none of them multiplies again unless a slab was too small. The pick's tables
+// take the place of the waves' (two workgroups per CU instead of one).
 // ---------------------------------------------------------------------------
+template <typename AT> union HistSmem {
+    struct {
+        BktSmem<AT, BW> s;
+        u64 hi[TT_SLOTS], lo[TT_SLOTS];
+    } pass;
+    sts_select::Level1Smem<STS_WG> l1;
+};
+
 template <typename AT, int M>
 __global__ void __launch_bounds__(STS_WG) k_bkt_hist(const GateArg *__restrict__ gp, PassBufs b)
 {
     const GateArg &g = *gp;
     const GateLoc<M> gl = gate_loc<M>(g);
-    __shared__ BktSmem<AT, BW> s;
-    __shared__ union {
-        struct {
-            u64 hi[TT_SLOTS], lo[TT_SLOTS];
-        } bins;
-        sts_select::Level1Smem<STS_WG> l1;
-    } u;
+    __shared__ HistSmem<AT> u;
     __shared__ u32 s_flag;
-    u64 *const s_hi = u.bins.hi, *const s_lo = u.bins.lo;
+    BktSmem<AT, BW> &s = u.pass.s;
+    u64 *const s_hi = u.pass.hi, *const s_lo = u.pass.lo;
     DevCtl *ctl = b.ctl;
-    if (b.recover && !ctl->need_full) return; // uniform
+    if (b.recover && !b.whole && !ctl->need_full) return; // uniform
     smem_begin<AT, M, BW>(s, g);
     for (int i = threadIdx.x; i < TT_SLOTS; i += STS_WG) {
         s_hi[i] = 0;
@@ -592,6 +599,13 @@ __global__ void __launch_bounds__(STS_WG) k_bkt_hist(const GateArg *__restrict__
     const int e_prev = ctl->e_pred;
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int hot_lo = (e_prev >= 0 ? e_prev : TT_EBASE + 116) - (TT_HOT - 4);
+    const int shift = b.slab_shift;
+    if (b.keep && blockIdx.x == 0 && threadIdx.x == 0) {
+        ctl->side_dense = 0;
+        ctl->side_ntiles = (u64)ntiles << 2;
+        ctl->side_slab_shift = shift;
+        ctl->side_spt_log2 = 2;
+    }
     __syncthreads();
     int since_flush = 0;
     for (u32 tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
@@ -605,7 +619,9 @@ __global__ void __launch_bounds__(STS_WG) k_bkt_hist(const GateArg *__restrict__
         ++since_flush;
         const Share sh = load_share(g.bkt, b.bd_in, tile, wv);
         const bool direct = sh.n > BW_BINNED;
-        u32 c_all = 0;
+        const u32 sl = (tile << 2) + (u32)wv;
+        const u64 slab = (u64)sl << shift;
+        SlabOut so = {0, 0, 0, true};
         share_groups<AT, M>(s.w[wv], s.ucol, gl, sh, b.keys, (const AT *)b.amps,
                             [&](const auto &ox, const auto &oy, u64 rest, bool active) {
 #pragma unroll
@@ -614,11 +630,22 @@ __global__ void __launch_bounds__(STS_WG) k_bkt_hist(const GateArg *__restrict__
                 o.x = ox[i];
                 o.y = oy[i];
                 const bool cand = active && nonzero(o);
-                if (cand) bin_weight(b, s_hi, s_lo, hot_lo, weight_bits(o), direct);
-                c_all += (u32)__popcll(wballot(cand));
+                const u64 wb = weight_bits(o);
+                if (cand) bin_weight(b, s_hi, s_lo, hot_lo, wb, direct);
+                so.c_all += (u32)__popcll(wballot(cand));
+                if (b.keep) // uniform
+                    slab_put<AT>(so, b.side_key + slab, b.side_w + slab, (AT *)b.side_amp + slab, 1u << shift, cand, false,
+                                 rest | pattern_bits<M>(gl, i), wb, o);
             }
         });
-        if (sts_lane() == 0) b.w_all[(tile << 2) + (u32)wv] = c_all;
+        if (sts_lane() == 0) {
+            b.w_all[sl] = so.c_all;
+            if (b.keep) {
+                b.t_above[sl] = 0;
+                b.t_side[sl] = so.c_in;
+                if (!so.fits) atomicOr(&ctl->w_over, 1u);
+            }
+        }
     }
     __syncthreads();
     flush_bins(b, s_hi, s_lo, hot_lo);
@@ -931,10 +958,25 @@ __global__ void __launch_bounds__(STS_WG) k_bkt_sample(GateArg g, PassBufs b)
 
 // ---------------------------------------------------------------------------
 // the passes of a step whose window missed the cut (they exit at once when it
-// held it): the candidates of the cut's exponent to the side buffer, densely
-// packed (one claim per tile), with their level-2 bins, picked by the last
-// workgroup; and the survivors per share
+// held it): the level-2 bins of the cut's exponent, picked by the last workgroup;
+// and the survivors per share. Both read the weights in the slabs; where a slab
+// was too small for its candidates, these are computed again and those of the
+// cut's exponent go to the side buffer, densely packed (one claim per tile)
 // ---------------------------------------------------------------------------
+// f(weight, index) of the n entries of a slab, a wave's loads in flight together
+template <typename F> __device__ __forceinline__ void slab_weights(const u64 *__restrict__ w, u32 n, F &&f)
+{
+    constexpr int UN = 8;
+    for (u32 i0 = (u32)sts_lane(); i0 < n; i0 += 64 * UN) {
+        u64 x[UN];
+#pragma unroll
+        for (int r = 0; r < UN; ++r) x[r] = i0 + 64u * (u32)r < n ? w[i0 + 64u * (u32)r] : ~0ull;
+#pragma unroll
+        for (int r = 0; r < UN; ++r)
+            if (x[r] != ~0ull) f(x[r], i0 + 64u * (u32)r); // (no weight has all bits set)
+    }
+}
+
 template <typename AT, int M>
 __global__ void __launch_bounds__(STS_WG) k_bkt_extract(const GateArg *__restrict__ gp, PassBufs b)
 {
@@ -961,8 +1003,41 @@ __global__ void __launch_bounds__(STS_WG) k_bkt_extract(const GateArg *__restric
     const AT *amps = (const AT *)b.amps;
     const u32 ntiles = bkt_tiles(g.bkt);
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const bool slabs = ctl->slab_all;
+    auto flush = [&]() {
+        for (int i = threadIdx.x; i < STS_NBIN; i += STS_WG) {
+            const u32 c = s_num[i];
+            if (!c) continue;
+            const u128 tot = (u128)digit_mant((u32)i, e_star) * c + (u128)s_low[i];
+            atomicAdd(&b.h2w[i], (u64)c);
+            atomicAdd(&b.h2w[STS_NBIN + i], (u64)(tot >> 26));
+            atomicAdd(&b.h2w[2 * STS_NBIN + i], (u64)tot & ((1ull << 26) - 1));
+            s_low[i] = 0;
+            s_num[i] = 0;
+        }
+    };
     __syncthreads();
-    for (u32 tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+    u32 since = 0;
+    for (u32 tile = blockIdx.x; slabs && tile < ntiles; tile += gridDim.x) {
+        if (++since > 1u << 8) { // (a tile has four slabs of at most 2^12 entries: sums stay below 2^64)
+            __syncthreads();
+            flush();
+            since = 1;
+            __syncthreads();
+        }
+        const u32 sl = (tile << 2) + (u32)wv;
+        slab_weights(b.side_w + ((u64)sl << b.slab_shift), b.t_side[sl], [&](u64 w, u32) {
+            if ((int)(w >> 52) != e_star) return;
+            const u32 d = 2047u - ((u32)(w >> 41) & 2047u);
+            atomicAdd(&s_low[d], w & LOW41);
+            atomicAdd(&s_num[d], 1u);
+        });
+    }
+    if (slabs) {
+        __syncthreads();
+        flush();
+    }
+    for (u32 tile = blockIdx.x; !slabs && tile < ntiles; tile += gridDim.x) {
         const Share sh = load_share(g.bkt, b.bd_in, tile, wv);
         u32 cnt = 0;
         share_groups<AT, M>(s.w[wv], s.ucol, gl, sh, keys, amps, [&](const auto &ox, const auto &oy, u64, bool active) {
@@ -1009,16 +1084,7 @@ __global__ void __launch_bounds__(STS_WG) k_bkt_extract(const GateArg *__restric
             }
         });
         __syncthreads();
-        for (int i = threadIdx.x; i < STS_NBIN; i += STS_WG) {
-            const u32 c = s_num[i];
-            if (!c) continue;
-            const u128 tot = (u128)digit_mant((u32)i, e_star) * c + (u128)s_low[i];
-            atomicAdd(&b.h2w[i], (u64)c);
-            atomicAdd(&b.h2w[STS_NBIN + i], (u64)(tot >> 26));
-            atomicAdd(&b.h2w[2 * STS_NBIN + i], (u64)tot & ((1ull << 26) - 1));
-            s_low[i] = 0;
-            s_num[i] = 0;
-        }
+        flush();
     }
     if (!sts_last_block(&ctl->done[1], &s_flag)) return;
     if (threadIdx.x == 0) {
@@ -1057,10 +1123,23 @@ __global__ void __launch_bounds__(STS_WG) k_bkt_count(const GateArg *__restrict_
     DevCtl *ctl = b.ctl;
     const bool all = b.materialise;
     if (!all && (ctl->pred_hit || ctl->keep_all)) return; // uniform
-    smem_begin<AT, M, BW>(s, g);
     const u64 thr_w = ctl->thr_wbits, thr_k = ctl->thr_key;
     const u32 ntiles = bkt_tiles(g.bkt);
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    if (!all && ctl->slab_all) { // uniform
+        for (u32 tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+            const u32 sl = (tile << 2) + (u32)wv;
+            const u64 slab = (u64)sl << b.slab_shift;
+            u32 cnt = 0;
+            slab_weights(b.side_w + slab, b.t_side[sl], [&](u64 w, u32 i) {
+                cnt += w > thr_w || (w == thr_w && b.side_key[slab + i] <= thr_k) ? 1u : 0u;
+            });
+            cnt = wave_incl_scan(cnt);
+            if (sts_lane() == 63) b.w_kept[sl] = cnt;
+        }
+        return;
+    }
+    smem_begin<AT, M, BW>(s, g);
     __syncthreads();
     for (u32 tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
         const Share sh = load_share(g.bkt, b.bd_in, tile, wv);
@@ -1139,7 +1218,8 @@ __device__ __forceinline__ u32 share_base(const PassBufs &b, u32 tile, int wv)
 }
 
 // when the window held the cut, the survivors are in the wave's slab: all
-// entries above the window, and the window's by the threshold
+// entries above the window, and the window's by the threshold; or every candidate
+// is there, as the window's
 template <typename AT>
 __device__ __forceinline__ void copy_share(const BktPlan &p, const PassBufs &b, u32 tile, int wv, u32 *cnt, u64 thr_w,
                                            u64 thr_k, bool rescale, double scale)
@@ -1202,25 +1282,42 @@ __device__ __forceinline__ void copy_share(const BktPlan &p, const PassBufs &b, 
     }
     // a large share: count, then place
     for (int phase = 0; phase < 2; ++phase) {
-        for (u32 j0 = 0; j0 < n; j0 += 64) {
-            const u32 j = j0 + lane;
-            bool keep = false;
-            u64 k = 0;
-            u32 i = 0;
-            if (j < n) {
-                i = place(j);
-                k = sk[i];
-                keep = j < na || survives<AT>(sw[i], k, false, thr_w, thr_k);
+        for (u32 j0 = 0; j0 < n; j0 += UN * 64) {
+            u64 kk[UN], ww[UN];
+            AT aa[UN];
+#pragma unroll
+            for (int r = 0; r < UN; ++r) {
+                const u32 j = j0 + (u32)r * 64 + lane;
+                ww[r] = ~0ull;
+                if (j < n) {
+                    const u32 i = place(j);
+                    kk[r] = sk[i];
+                    if (j >= na) ww[r] = sw[i];
+                    if (phase) aa[r] = sa[i];
+                }
             }
-            const u32 at = sub_rank(keep, keep ? sub_bucket(p, k) : 0u, bits, cnt);
-            if (phase && keep && at < cap) {
-                ok[at] = k;
-                oa[at] = out_amp(sa[i], rescale, scale);
+#pragma unroll
+            for (int r = 0; r < UN; ++r) {
+                const u32 j = j0 + (u32)r * 64 + lane;
+                if (j0 + (u32)r * 64 >= n) break; // uniform
+                const bool keep = j < n && survives<AT>(ww[r], kk[r], false, thr_w, thr_k);
+                const u32 at = sub_rank(keep, keep ? sub_bucket(p, kk[r]) : 0u, bits, cnt);
+                if (phase && keep && at < cap) {
+                    ok[at] = kk[r];
+                    oa[at] = out_amp(aa[r], rescale, scale);
+                }
             }
         }
         wave_sync();
         if (phase == 0) sub_starts(p, b, tile, wv, base, cnt);
     }
+}
+
+// whether the survivors are in the slabs
+__device__ __forceinline__ bool in_slabs(const DevCtl *ctl)
+{
+    const int keep_all = ctl->keep_all, hit = ctl->pred_hit, every = ctl->slab_all;
+    return keep_all ? every : hit || every;
 }
 
 // Bound by memory: 536 MB in 120 us (4.5 TB/s) at 2^24 complex64 terms. The
@@ -1233,12 +1330,13 @@ __global__ void __launch_bounds__(STS_WG) k_bkt_copy(const GateArg *__restrict__
     __shared__ u32 s_cnt[BW][BW_SUBS];
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const DevCtl *ctl = b.ctl;
-    const int keep_all = ctl->keep_all, hit = ctl->pred_hit;
-    if (keep_all || !hit) return; // uniform
-    copy_share<AT>(gp->bkt, b, blockIdx.x, wv, s_cnt[wv], ctl->thr_wbits, ctl->thr_key, ctl->dropped, ctl->scale);
+    const int all = ctl->keep_all;
+    if (!in_slabs(ctl)) return; // uniform
+    copy_share<AT>(gp->bkt, b, blockIdx.x, wv, s_cnt[wv], all ? 0ull : ctl->thr_wbits, all ? ~0ull : ctl->thr_key,
+                   ctl->dropped, ctl->scale);
 }
 
-// otherwise (also when nothing is cut) they are computed again
+// otherwise they are computed again
 template <typename AT, int M>
 __global__ void __launch_bounds__(STS_WG) k_bkt_emit(const GateArg *__restrict__ gp, PassBufs b)
 {
@@ -1249,13 +1347,13 @@ __global__ void __launch_bounds__(STS_WG) k_bkt_emit(const GateArg *__restrict__
     __shared__ u32 s_cnt[BW][BW_SUBS];
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const DevCtl *ctl = b.ctl;
-    const int keep_all = ctl->keep_all, dropped = ctl->dropped, hit = ctl->pred_hit;
+    const int keep_all = ctl->keep_all, dropped = ctl->dropped;
     const u64 thr_w = ctl->thr_wbits, thr_k = ctl->thr_key;
     const double scale = ctl->scale;
     const bool all = b.materialise || keep_all;
     const bool rescale = !all && dropped;
     const u32 cap = (u32)b.out_cap, ntiles = bkt_tiles(p);
-    if (!all && hit) { // uniform: the copy's part (of a small step; else k_bkt_copy does it)
+    if (!b.materialise && in_slabs(ctl)) { // uniform: the copy's part (of a small step; else k_bkt_copy does it)
         if (b.emit_copies)
             for (u32 tile = blockIdx.x; tile < ntiles; tile += gridDim.x)
                 copy_share<AT>(p, b, tile, wv, s_cnt[wv], thr_w, thr_k, rescale, scale);
@@ -1707,6 +1805,7 @@ __global__ void __launch_bounds__(SEL_NT) k_bkt_select(const GateArg *__restrict
         *b.n_out = carry;
         if (carry > b.out_cap && !b.may_refuse) atomicOr(&ctl->flags, STS_F_OUT_OVERFLOW);
         ctl->w_over = 0;
+        ctl->slab_all = 0;
         ctl->pred_hit = slabs;
     }
 }

@@ -81,7 +81,8 @@ struct PassBufs {
     int emit_copies;      // write pass: also copies the survivors when the window held the cut
     int may_refuse;       // the host checks the result's size before it is written
     int recover;          // histogram pass: only after a sampled window that missed
-    int whole;            // the passes launched are known to run
+    int whole;            // the histogram pass is known to run
+    int keep;             // and puts every candidate into its share's slab
     u64 *sbins;           // sampling pass: STS_SW_BANKS x STS_SW_NB counts (u32), as many masses
                           // (float), then 4 totals per bank
 };

@@ -58,7 +58,10 @@ __global__ void __launch_bounds__(256) k_pick_window(PassBufs b, int groups)
     const int w_mode = ctl->w_mode, e = ctl->e_w;
     const u32 over = ctl->w_over;
     const u64 w_hi = ctl->w_hi;
-    if (t == 0) s_fine = 0;
+    if (t == 0) {
+        s_fine = 0;
+        ctl->slab_all = 0;
+    }
     __syncthreads(); // the control words are read
     if (!w_mode || over) { // uniform: the histogram pass has to do the step
         if (t == 0) {
@@ -533,11 +536,11 @@ __global__ void __launch_bounds__(256) k_side_extract(PassBufs b)
                 if (w[r] != ~0ull) {
                     if (vshift >= 64) { // the fixed part lies in the weight half of V
                         const u64 vh = ((1ull << 52) - 1) - (w[r] & ((1ull << 52) - 1));
-                        take = (vh >> (vshift - 64)) == (u64)vpre;
+                        take = (int)(w[r] >> 52) == e && (vh >> (vshift - 64)) == (u64)vpre;
                         if (take) k = b.side_key[i];
                     } else {
                         k = b.side_key[i];
-                        take = (rank_key(w[r], k) >> vshift) == vpre;
+                        take = (int)(w[r] >> 52) == e && (rank_key(w[r], k) >> vshift) == vpre;
                     }
                 }
                 const u64 mask = __ballot(take);
@@ -649,7 +652,7 @@ __global__ void __launch_bounds__(FT) k_final(PassBufs b)
 #pragma unroll
             for (int r = 0; r < FB; ++r) {
                 const u128 v = rank_key(w[r], k[r]);
-                if (ok[r] && (v >> vshift) == vpre) body(v);
+                if (ok[r] && (int)(w[r] >> 52) == e && (v >> vshift) == vpre) body(v);
             }
         }
     };

@@ -333,8 +333,8 @@ template <int NT> struct EarlyBins : DeviceBins<NT> {
 };
 
 // predicted: 0 no window, 1 a window of the tiled passes, 2 one without level-2 bins, 3 a bucketed step
-// whose histogram pass ran (no window; the side buffer, if the extraction
-// pass fills it, is packed densely)
+// whose histogram pass ran (no window; the slabs hold every candidate, or the side
+// buffer, if the extraction pass fills it, is packed densely)
 // bins: load(k, e, count, mantissa sum >> 26, & (2^26 - 1)) of exponent field e,
 // the thread's k-th, and clear(t) by every thread when all are read
 template <int NT, typename BINS>
@@ -668,10 +668,12 @@ __device__ __forceinline__ void pick_level1(const PassBufs &b, int groups, int p
                 ctl->w2_mode = predicted == 1 && w_mode; // the histogram pass binned the window for level 2
                 ctl->w_mode = 0;                     // a window serves one step
                 if (predicted == 3) {
+                    const bool every = b.keep && !ld_agent(&ctl->w_over);
+                    ctl->slab_all = every;
                     ctl->w_over = 0;
                     ctl->need_full = 0;
-                    // the extraction pass packs its candidates densely
-                    if (hit != 0xffffffffu && !ctl->pred_hit) {
+                    // else the extraction pass packs its candidates densely
+                    if (hit != 0xffffffffu && !every) {
                         ctl->side_dense = 1;
                         ctl->side_n = 0;
                     }

@@ -5,7 +5,6 @@ FP64, compared with the oracle bit for bit."""
 import numpy as np
 import pytest
 
-from oracle import c_oracle as CO
 from paper_2607_07816_amd import circuits as C
 from tests.helpers import random_state
 from tests.test_gpu_bucketed import S, oracle, run  # noqa: F401 (S: a fixture)
@@ -33,6 +32,8 @@ def steps(S, keys, amps, n, gs, K, p, cap):
             keys, amps, info = oracle(keys, amps, [(qs, U)], K, p)
             kg, ag, stats = run(st, [(qs, U)])
             print(f"step {i} {qs}", flush=True)
+            if info is None:  # no rule: the oracle weighs nothing
+                info = dict(fraction=1.0, W=stats["W"])
             check(kg, ag, stats, keys, amps, info, "c128")
 
 
@@ -55,3 +56,19 @@ def test_weights_of_any_size(S, exponents):
     keys, amps = random_state(rng, 40, N)
     amps = amps * 2.0 ** rng.integers(exponents[0], exponents[1], size=N)
     steps(S, keys, amps, 40, [(pick(rng, 40, m), C.haar_unitary(rng, 1 << m)) for m in (2, 1, 2, 2)], N, 0.0, N)
+
+
+@pytest.mark.parametrize("prec", ["c64", "c128"])
+def test_uncut_steps_of_shares_beyond_their_slabs(S, prec):
+    # growing by four at each gate into the whole capacity, from a state that leaves some slabs too small
+    rng = np.random.default_rng(11)
+    N = 140000
+    keys, amps = random_state(rng, 40, N)
+    gs = [(pick(rng, 40, 2), C.haar_unitary(rng, 4)), (pick(rng, 40, 1), C.haar_unitary(rng, 2))]
+    with S.State(40, K=8 * N, p=0.0, precision=prec, capacity=8 * N) as st:
+        st.load_terms(keys, amps)
+        kg, ag, stats = run(st, gs)
+    if prec == "c64":
+        amps = amps.astype(np.complex64).astype(np.complex128)
+    ko, ao, info = oracle(keys, amps, gs, 8 * N, 0.0)
+    check(kg, ag, stats, ko, ao, info, prec)
