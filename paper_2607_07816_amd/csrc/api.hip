@@ -528,6 +528,9 @@ bool buckets_suit(const sts_ctx *c)
     return c->bucketed && c->hb >= ideal - 1 && c->hb <= ideal + 2;
 }
 
+// the most terms that the qubits allow
+u64 all_keys(const sts_ctx *c) { return c->n_qubits < 64 ? 1ull << c->n_qubits : ~0ull; }
+
 // the size bound after a gate of m qubits and the cut that follows it
 u64 bound_after(const sts_ctx *c, int m)
 {
@@ -948,7 +951,7 @@ static sts_status truncate_buckets(sts_ctx *c)
     const bool small = c->n_bound <= kSelectMax && tiles * 4 <= STS_SEL_SHARES;
     b.keep = 1;
     b.recover = 1;
-    if (!small && c->p == 0.0 && c->K && cb < c->K) {
+    if (!small && c->p == 0.0 && (c->K == 0 || std::min(cb, all_keys(c)) <= c->K)) {
         // nothing can be cut: the histogram for the statistics, then the write
         b.whole = 1;
         STS_TRY(c, launch_set_gate(c->gate, c->dgate, c->stream));

@@ -530,6 +530,9 @@ __device__ __forceinline__ void pick_level1(const PassBufs &b, int groups, int p
                 ctl->tot_updates += *b.n_in;
                 ctl->tot_cand += total_c;
             }
+            // after the histogram pass of a bucketed step: no more candidates than K
+            // are no cut (of the least of them, which changes nothing)
+            const bool uncut = predicted == 3 && !p_on && total_c <= K;
             // The first bin in rank order where the rule is met: the first
             // that meets it on the count or may meet it on the mass, judged by
             // doubles (error far below the margin); from there on exactly
@@ -537,7 +540,7 @@ __device__ __forceinline__ void pick_level1(const PassBufs &b, int groups, int p
             u32 hit = nbins;
             u64 cnt = 0;
             double m0 = 0.0;
-            for (u32 j0 = 0; j0 < nbins && hit == nbins; j0 += 64) {
+            for (u32 j0 = 0; j0 < nbins && hit == nbins && !uncut; j0 += 64) {
                 const u32 j = j0 + (u32)lane;
                 const u64 cj = j < nbins ? sm.c[j] : 0ull;
                 const u64 ci = cnt + wave_incl_scan(cj);

@@ -58,6 +58,35 @@ def test_weights_of_any_size(S, exponents):
     steps(S, keys, amps, 40, [(pick(rng, 40, m), C.haar_unitary(rng, 1 << m)) for m in (2, 1, 2, 2)], N, 0.0, N)
 
 
+def permutations(rng, n, count):
+    """Gates that do not branch."""
+    X = np.array([[0, 1], [1, 0]], dtype=np.complex128)
+    cx = np.eye(4, dtype=np.complex128)[[0, 3, 2, 1]]
+    one = [lambda: np.diag(np.exp(1j * rng.uniform(0, 6, 2))), lambda: X]
+    two = [lambda: CZ, lambda: cx]
+    return [(pick(rng, n, m), (one if m == 1 else two)[i // 2 % 2]()) for i, m in enumerate((1, 2) * count)][:count]
+
+
+@pytest.mark.parametrize("K", [0, 1 << 18])
+@pytest.mark.parametrize("n,N", [(18, 1 << 18), (18, 140000), (17, 1 << 17)])
+def test_every_key_fits(S, n, N, K):
+    # K at least every key of the qubits, no p-mass: nothing is ever cut
+    rng = np.random.default_rng([n, N])
+    keys, amps = random_state(rng, n, N)
+    steps(S, keys, amps, n, [(pick(rng, n, m), C.haar_unitary(rng, 1 << m)) for m in (2, 1, 2, 2)], K, 0.0, 1 << 18)
+
+
+@pytest.mark.parametrize("p", [0.0, 0.9999])
+@pytest.mark.parametrize("K", [150000, 150001, 149990, 600000])
+def test_gates_that_do_not_branch(S, K, p):
+    # as many candidates as K, one fewer, some more; then a gate that branches, and again
+    rng = np.random.default_rng(K)
+    N = 150000
+    keys, amps = random_state(rng, 40, N)
+    haar = [(pick(rng, 40, 2), C.haar_unitary(rng, 4))]
+    steps(S, keys, amps, 40, permutations(rng, 40, 4) + haar + permutations(rng, 40, 3) + haar + haar, K, p, max(K, N))
+
+
 @pytest.mark.parametrize("prec", ["c64", "c128"])
 def test_uncut_steps_of_shares_beyond_their_slabs(S, prec):
     # growing by four at each gate into the whole capacity, from a state that leaves some slabs too small
