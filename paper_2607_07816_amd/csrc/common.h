@@ -69,7 +69,7 @@ struct DevCtl {
     int w_L;             // lowest exponent field that the weighing pass sums in registers
     u64 w_lo, w_hi;
     int need_full;       // bucketed step: the sampled window missed; the histogram pass runs after all
-    int slab_all;        // and has put every candidate into the slabs
+    int slab_all;        // and has put every candidate that may survive into the slabs
     int level;           // last resolved level
     u64 cnt_before;      // terms ranked before the current subset
     u64 mb_lo, mb_hi;    // mantissa sum (units 2^(max(e*,1)-1075)) ranked before the subset inside e*

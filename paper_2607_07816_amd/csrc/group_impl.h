@@ -1129,8 +1129,10 @@ __device__ __forceinline__ void sample_flush(SampleSmem &s, SampleAcc &a, const 
 }
 
 // the last workgroup: the window from the sample of a state of n terms
-// fine: every term was sampled, so the cut lies in the bin that is found
-__device__ __forceinline__ void sample_finish(SampleSmem &s, const PassBufs &b, int e_lo, u64 n, bool fine = false)
+// fine: every term was sampled, so the cut lies in the bin that is found;
+// least: sampled candidates in the window below which there is none
+__device__ __forceinline__ void sample_finish(SampleSmem &s, const PassBufs &b, int e_lo, u64 n, bool fine = false,
+                                              u32 least = 0)
 {
     DevCtl *ctl = b.ctl;
     const u32 *gc = reinterpret_cast<const u32 *>(b.sbins);
@@ -1174,6 +1176,7 @@ __device__ __forceinline__ void sample_finish(SampleSmem &s, const PassBufs &b, 
         s.hit = 0xffffffffu;
         s.at_k = s.at_p = -1;
     }
+    s.c[f] = c; // (the workgroup's own bins are flushed)
     __syncthreads();
     if (fine && c) {
         // where each rule is met
@@ -1208,6 +1211,8 @@ __device__ __forceinline__ void sample_finish(SampleSmem &s, const PassBufs &b, 
             const int sub = fb & ((1 << STS_SW_FB) - 1);
             const int lo_sub = sub > 0 ? sub - 1 : 0;
             const int hi_sub = sub + 1 < (1 << STS_SW_FB) ? sub + 1 : sub;
+            u32 in = 0;
+            for (int q = lo_sub - sub; q <= hi_sub - sub; ++q) in += s.c[fb + q];
             ctl->e_w = ex;
             // what the weighing pass sums in registers: from 15 exponent fields
             // below the window on; higher up, but not above the window, where most
@@ -1216,7 +1221,7 @@ __device__ __forceinline__ void sample_finish(SampleSmem &s, const PassBufs &b, 
             ctl->w_L = std::min(std::max(ex - 15, bulk - 24), ex);
             ctl->w_lo = ((u64)ex << 52) | ((u64)lo_sub << (52 - STS_SW_FB));
             ctl->w_hi = ((u64)ex << 52) + ((u64)(hi_sub + 1) << (52 - STS_SW_FB)) - 1;
-            ctl->w_mode = 1;
+            ctl->w_mode = in >= least ? 1 : 0;
         }
     }
     for (int i = t; i < STS_SW_BANKS * (STS_SW_NB + 4); i += STS_WG) st_agent(&b.sbins[i], 0ull);

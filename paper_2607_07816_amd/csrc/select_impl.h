@@ -349,6 +349,7 @@ __device__ __forceinline__ void pick_level1(const PassBufs &b, int groups, int p
     const int w_mode = ctl->w_mode;
     const bool win = predicted == 1 || predicted == 2;
     const int e_w = win ? (w_mode ? ctl->e_w : ctl->e_pred) : -1;
+    const int e_floor = predicted == 3 ? slab_floor(b, ctl->e_pred) : 0; // (read before the cut's is written)
     const int e_w2 = predicted == 2 ? (int)(ctl->w_lo >> 52) : -1; // (e_w itself as a rule)
     if (t < 9) sm.w[t] = 0;
     if (t == 0) sm.fine = 0;
@@ -671,7 +672,8 @@ __device__ __forceinline__ void pick_level1(const PassBufs &b, int groups, int p
                 ctl->w2_mode = predicted == 1 && w_mode; // the histogram pass binned the window for level 2
                 ctl->w_mode = 0;                     // a window serves one step
                 if (predicted == 3) {
-                    const bool every = b.keep && !ld_agent(&ctl->w_over);
+                    const bool every = b.keep && !ld_agent(&ctl->w_over) &&
+                                       (hit != 0xffffffffu ? (int)sm.e[hit] >= e_floor : e_floor == 0);
                     ctl->slab_all = every;
                     ctl->w_over = 0;
                     ctl->need_full = 0;
