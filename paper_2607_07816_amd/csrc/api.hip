@@ -605,7 +605,7 @@ sts_status bucket_write(sts_ctx *c, const PassBufs &b, int dst, u64 bound)
                        launch_bucket_pass(STS_BKT_COUNT, c->prec, c->gate.m, b, tiles, c->stream));
         STS_LAUNCH(c, STS_K_TILE_KEPT, launch_bucket_kept(b, tiles, c->stream));
     }
-    const bool copied = !b.materialise && !b.emit_copies;
+    const bool copied = !b.emit_copies;
     if (copied)
         STS_LAUNCH(c, STS_K_GROUP_EMIT, launch_bucket_pass(STS_BKT_COPY, c->prec, c->gate.m, b, tiles, c->stream));
     STS_LAUNCH(c, copied ? STS_K_GROUP_EXTRACT : STS_K_GROUP_EMIT, launch_bucket_pass(STS_BKT_EMIT, c->prec, c->gate.m, b, tiles, c->stream));
@@ -701,7 +701,10 @@ sts_status materialise(sts_ctx *c)
     const int dst = (c->cur + 1) % 3;
     PassBufs b = pass_bufs(c, c->cur, dst);
     b.materialise = 1;
-    if (c->bkt_pending) return bucket_write(c, b, dst, std::min(bound, c->cap));
+    if (c->bkt_pending) {
+        b.slab_shift = slab_shift(c);
+        return bucket_write(c, b, dst, std::min(bound, c->cap));
+    }
     if (use_tiles(c, c->gate.m)) {
         const int tt = (int)std::max<u64>(ceil_div(c->n_bound, 2048), 1);
         STS_LAUNCH(c, STS_K_GROUP_EXTRACT,

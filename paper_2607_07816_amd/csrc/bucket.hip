@@ -114,6 +114,10 @@ __global__ void __launch_bounds__(KT) k_bkt_kept(PassBufs b)
     }
     if (threadIdx.x == 0) {
         *b.n_out = carry;
+        if (b.materialise) { // (the count has put the new terms into the slabs)
+            ctl->slab_all = !ctl->w_over;
+            ctl->w_over = 0;
+        }
         if (carry > b.out_cap) atomicOr(&ctl->flags, STS_F_OUT_OVERFLOW);
     }
 }

@@ -970,7 +970,10 @@ __global__ void __launch_bounds__(STS_WG) k_bkt_sample(GateArg g, PassBufs b)
 // held it): the level-2 bins of the cut's exponent, picked by the last workgroup;
 // and the survivors per share. Both read the weights in the slabs; where a slab
 // was too small for its candidates, these are computed again and those of the
-// cut's exponent go to the side buffer, densely packed (one claim per tile)
+// cut's exponent go to the side buffer, densely packed (one claim per tile).
+// A gate without a truncation has the count only, which puts the new terms into
+// the slabs for the copy (347 us at 2^22 complex64 terms when they were computed
+// three times, 251 with the sort)
 // ---------------------------------------------------------------------------
 // f(weight, index) of the n entries of a slab, a wave's loads in flight together
 template <typename F> __device__ __forceinline__ void slab_weights(const u64 *__restrict__ w, u32 n, F &&f)
@@ -1152,7 +1155,10 @@ __global__ void __launch_bounds__(STS_WG) k_bkt_count(const GateArg *__restrict_
     __syncthreads();
     for (u32 tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
         const Share sh = load_share(g.bkt, b.bd_in, tile, wv);
+        const u32 sl = (tile << 2) + (u32)wv;
+        const u64 slab = (u64)sl << b.slab_shift;
         u32 cnt = 0;
+        SlabOut so = {0, 0, 0, true};
         share_groups<AT, M>(s.w[wv], s.ucol, gl, sh, b.keys, (const AT *)b.amps, [&](const auto &ox, const auto &oy, u64 rest, bool active) {
 #pragma unroll
             for (int i = 0; i < (1 << M); ++i) {
@@ -1160,11 +1166,21 @@ __global__ void __launch_bounds__(STS_WG) k_bkt_count(const GateArg *__restrict_
                 o.x = ox[i];
                 o.y = oy[i];
                 const u64 key = rest | pattern_bits<M>(gl, i);
-                cnt += (u32)__popcll(
-                    wballot(active && nonzero(o) && survives<AT>(weight_bits(o), key, all, thr_w, thr_k)));
+                const bool take = active && nonzero(o) && survives<AT>(weight_bits(o), key, all, thr_w, thr_k);
+                cnt += (u32)__popcll(wballot(take));
+                if (all) // uniform
+                    slab_put<AT>(so, b.side_key + slab, b.side_w + slab, (AT *)b.side_amp + slab, 1u << b.slab_shift, false,
+                                 take, key, 0, o);
             }
         });
-        if (sts_lane() == 0) b.w_kept[(tile << 2) + (u32)wv] = cnt;
+        if (sts_lane() == 0) {
+            b.w_kept[sl] = cnt;
+            if (all) {
+                b.t_above[sl] = so.c_ab;
+                b.t_side[sl] = 0;
+                if (!so.fits) atomicOr(&ctl->w_over, 1u);
+            }
+        }
     }
 }
 
@@ -1323,10 +1339,10 @@ __device__ __forceinline__ void copy_share(const BktPlan &p, const PassBufs &b, 
 }
 
 // whether the survivors are in the slabs
-__device__ __forceinline__ bool in_slabs(const DevCtl *ctl)
+__device__ __forceinline__ bool in_slabs(const PassBufs &b, const DevCtl *ctl)
 {
     const int keep_all = ctl->keep_all, hit = ctl->pred_hit, every = ctl->slab_all;
-    return keep_all ? every : hit || every;
+    return b.materialise || keep_all ? every : hit || every;
 }
 
 // Bound by memory: 536 MB in 120 us (4.5 TB/s) at 2^24 complex64 terms. The
@@ -1339,10 +1355,10 @@ __global__ void __launch_bounds__(STS_WG) k_bkt_copy(const GateArg *__restrict__
     __shared__ u32 s_cnt[BW][BW_SUBS];
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const DevCtl *ctl = b.ctl;
-    const int all = ctl->keep_all;
-    if (!in_slabs(ctl)) return; // uniform
+    const bool all = b.materialise || ctl->keep_all;
+    if (!in_slabs(b, ctl)) return; // uniform
     copy_share<AT>(gp->bkt, b, blockIdx.x, wv, s_cnt[wv], all ? 0ull : ctl->thr_wbits, all ? ~0ull : ctl->thr_key,
-                   ctl->dropped, ctl->scale);
+                   !all && ctl->dropped, ctl->scale);
 }
 
 // otherwise they are computed again
@@ -1362,7 +1378,7 @@ __global__ void __launch_bounds__(STS_WG) k_bkt_emit(const GateArg *__restrict__
     const bool all = b.materialise || keep_all;
     const bool rescale = !all && dropped;
     const u32 cap = (u32)b.out_cap, ntiles = bkt_tiles(p);
-    if (!b.materialise && in_slabs(ctl)) { // uniform: the copy's part (of a small step; else k_bkt_copy does it)
+    if (in_slabs(b, ctl)) { // uniform: the copy's part (of a small step; else k_bkt_copy does it)
         if (b.emit_copies)
             for (u32 tile = blockIdx.x; tile < ntiles; tile += gridDim.x)
                 copy_share<AT>(p, b, tile, wv, s_cnt[wv], thr_w, thr_k, rescale, scale);

@@ -6,6 +6,7 @@ import functools
 import numpy as np
 import pytest
 
+from oracle import c_oracle as CO
 from paper_2607_07816_amd import circuits as C
 from tests.test_gpu_bucketed import MASK64, S, lin_hash, oracle, run, same  # noqa: F401 (S: a fixture)
 from tests.test_gpu_window import check
@@ -121,3 +122,26 @@ def test_crowded_terms_and_then_others(S):
             ko, ao, info = oracle(keys, amps[:len(keys)], gs, N, 0.0)
             kg, ag, stats = run(st, gs)
             check(kg, ag, stats, ko, ao, info, "c128")
+
+
+@pytest.mark.parametrize("N,bits", [(150000, 3), (60000, 3), (150000, 0)])
+def test_untruncated_gates_of_crowded_terms(S, N, bits):
+    # the new terms of some shares exceed their slabs: they are computed again for the write
+    rng = np.random.default_rng([N, bits, 5])
+    keys = span_of_kernel(bits, rng, N) if bits else np.unique(rng.integers(0, MASK64, size=N, dtype=np.uint64))
+    amps = rng.standard_normal(N) + 1j * rng.standard_normal(N)
+    gs = [((int(a), int(b)), C.haar_unitary(rng, 4)) for a, b in rng.choice(64, size=(2, 2), replace=False)]
+    ko, ao = keys, amps
+    with S.State(64, K=0, p=0.0, precision="c128", capacity=4 * N) as st:
+        st.load_terms(keys, amps)
+        for i, (qs, U) in enumerate(gs):
+            if i:  # back to N terms
+                kg, ag = ko[::4], ao[::4]
+                st.load_terms(kg, ag)
+                ko, ao = kg, ag
+            ko, ao, _ = CO.step(ko, ao, qs, U, 0, 0.0, False, CO.host_threads())
+            ko, ao = CO.sorted_terms(ko, ao)
+            st.apply_gate(qs, U)
+            kg, ag = st.read_terms()
+            assert np.array_equal(kg, ko)
+            assert np.array_equal(ag.view(np.uint64), ao.view(np.uint64))
