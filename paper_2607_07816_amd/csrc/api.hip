@@ -596,7 +596,7 @@ int slab_shift(const sts_ctx *c)
 int bucket_tiles(const sts_ctx *c) { return 1 << (c->gate.bkt.hb - STS_BKT_DIMS); }
 
 // the passes that write the pending bucketed step's survivors to buffer dst
-sts_status bucket_write(sts_ctx *c, const PassBufs &b, int dst, u64 bound)
+sts_status bucket_write(sts_ctx *c, PassBufs b, int dst, u64 bound)
 {
     const int tiles = bucket_tiles(c);
     if (!b.emit_copies) { // else k_bkt_select has the offsets
@@ -604,6 +604,7 @@ sts_status bucket_write(sts_ctx *c, const PassBufs &b, int dst, u64 bound)
             STS_LAUNCH(c, STS_K_GROUP_EXTRACT,
                        launch_bucket_pass(STS_BKT_COUNT, c->prec, c->gate.m, b, tiles, c->stream));
         STS_LAUNCH(c, STS_K_TILE_KEPT, launch_bucket_kept(b, tiles, c->stream));
+        if (b.materialise && c->n_bound <= kSelectMax) b.emit_copies = 1; // a launch less
     }
     const bool copied = !b.emit_copies;
     if (copied)
