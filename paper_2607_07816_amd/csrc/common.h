@@ -382,6 +382,13 @@ template <typename T> __device__ __forceinline__ T sts_readlane(T v, int lane)
     __builtin_memcpy(&v, w, sizeof(T));
     return v;
 }
+// the first active lane's value in every lane
+__device__ __forceinline__ u64 sts_firstlane(u64 v)
+{
+    const u32 lo = (u32)__builtin_amdgcn_readfirstlane((int)(u32)v);
+    const u32 hi = (u32)__builtin_amdgcn_readfirstlane((int)(u32)(v >> 32));
+    return ((u64)hi << 32) | lo;
+}
 // inclusive sum over the lanes of a row of 16, or of the wave (moves inside the
 // registers: shuffles through LDS made the scans of a full CU's waves several
 // times as long)

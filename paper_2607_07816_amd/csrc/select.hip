@@ -311,11 +311,6 @@ __device__ __forceinline__ SideView side_view(const PassBufs &b, const DevCtl *c
     return v;
 }
 
-__device__ __forceinline__ bool side_valid(const SideView &v, u64 f)
-{
-    return v.dense || (f & ((1ull << v.shift) - 1)) < (u64)v.cnt[f >> v.shift];
-}
-
 // The same entries as a list of chunks: the tiles of the tiled layout (each
 // the runs of its 1 or 4 slabs), or runs of 8192 entries of the dense one.
 // Workgroups walk chunks; threads walk the entries of a chunk.
@@ -616,33 +611,64 @@ __global__ void __launch_bounds__(FT) k_final(PassBufs b)
     const u64 *src_w = small ? b.sub_w : b.side_w;
     const u64 *src_k = small ? b.sub_key : b.side_key;
     const SideView view = side_view(b, ctl);
+    const bool slabs = !small && !view.dense;
     const u64 n = small ? (u64)s_regpre[STS_SUB_REGIONS] : view.flat;
-    // physical index of visited entry f (false: an empty slot of the side buffer)
-    auto entry = [&](u64 f, u64 &i) -> bool {
-        if (small) {
-            int lo = 0; // the last region r with pre[r] <= f (then f < pre[r + 1])
+    // physical index of visited entry f of the regions
+    auto entry = [&](u64 f) -> u64 {
+        if (!small) return f;
+        int lo = 0; // the last region r with pre[r] <= f (then f < pre[r + 1])
 #pragma unroll
-            for (int step = STS_SUB_REGIONS / 2; step > 0; step >>= 1)
-                if (s_regpre[lo + step] <= f) lo += step;
-            i = (u64)lo * region_len + (f - s_regpre[lo]);
-            return true;
-        }
-        i = f;
-        return side_valid(view, f);
+        for (int step = STS_SUB_REGIONS / 2; step > 0; step >>= 1)
+            if (s_regpre[lo + step] <= f) lo += step;
+        return (u64)lo * region_len + (f - s_regpre[lo]);
     };
     // body(V) for every visited entry whose V lies under the prefix: FB
     // entries per thread at a time, their loads in flight together (a loop
     // of one entry at a time waits on a load per entry)
     auto each_in_subset = [&](int vshift, u128 vpre, bool, auto body) {
+        auto take = [&](u64 w, u64 k) {
+            const u128 v = rank_key(w, k);
+            if ((int)(w >> 52) == e && (v >> vshift) == vpre) body(v);
+        };
+        if (slabs) { // a wave's slabs, the counts of 64 of them read together
+            const u64 room = 1ull << view.shift, nsl = (view.flat + room - 1) >> view.shift;
+            for (u64 s0 = (u64)(t >> 6) * 64; s0 < nsl; s0 += FT) {
+                const u64 sl = s0 + (u64)sts_lane();
+                u64 ns = sl < nsl ? std::min((u64)view.cnt[sl], room) : 0ull;
+                if (sl < nsl) ns = std::min(ns, view.flat - (sl << view.shift));
+                if (!__ballot(ns != 0)) continue;
+#pragma unroll 1
+                for (int j = 0; j < 64; j += FB) { // FB slabs at a time
+                    u32 nr[FB], most = 0;
+#pragma unroll
+                    for (int r = 0; r < FB; ++r) {
+                        nr[r] = sts_readlane((u32)ns, j + r);
+                        most = nr[r] > most ? nr[r] : most;
+                    }
+                    for (u32 i = (u32)sts_lane(); i < most; i += 64) {
+                        u64 w[FB], k[FB];
+#pragma unroll
+                        for (int r = 0; r < FB; ++r) {
+                            const u64 at = i < nr[r] ? ((s0 + (u64)(j + r)) << view.shift) + i : 0ull; // (or a harmless load)
+                            w[r] = src_w[at];
+                            k[r] = src_k[at];
+                        }
+#pragma unroll
+                        for (int r = 0; r < FB; ++r)
+                            if (i < nr[r]) take(w[r], k[r]);
+                    }
+                }
+            }
+            return;
+        }
         for (u64 f0 = t; f0 < n; f0 += (u64)FT * FB) {
             u64 w[FB], k[FB], at[FB];
             bool ok[FB];
 #pragma unroll
             for (int r = 0; r < FB; ++r) {
                 const u64 f = f0 + (u64)FT * r;
-                u64 i = 0;
-                ok[r] = f < n && entry(f, i);
-                at[r] = ok[r] ? i : 0ull; // entry 0 exists: a harmless load
+                ok[r] = f < n;
+                at[r] = ok[r] ? entry(f) : 0ull; // entry 0 exists: a harmless load
             }
 #pragma unroll
             for (int r = 0; r < FB; ++r) {
@@ -650,10 +676,8 @@ __global__ void __launch_bounds__(FT) k_final(PassBufs b)
                 k[r] = src_k[at[r]];
             }
 #pragma unroll
-            for (int r = 0; r < FB; ++r) {
-                const u128 v = rank_key(w[r], k[r]);
-                if (ok[r] && (int)(w[r] >> 52) == e && (v >> vshift) == vpre) body(v);
-            }
+            for (int r = 0; r < FB; ++r)
+                if (ok[r]) take(w[r], k[r]);
         }
     };
     const u64 K = ctl->K;

@@ -764,11 +764,17 @@ struct ThinBins {
     }
 };
 
+// A subset of more terms than this after a level is one of equal weights as a
+// rule. At 2^21 equal weights k_final took 67 ms when every lane added for
+// itself, 23 ms so.
+constexpr u64 TIES = 4096;
+
 // what a level's pass does with every term
 template <bool THIN> struct Binner {
     u64 *h;
     u32 *hc;
     int shift, dw, e;
+    bool many; // the subset is still large after a level
     __device__ __forceinline__ void operator()(const u128 v) const
     {
         const u32 d = (u32)((v >> shift) & (u128)((1u << dw) - 1));
@@ -777,9 +783,17 @@ template <bool THIN> struct Binner {
             atomicAdd((unsigned long long *)&h[thin_at(d)], mant & LOW41);
             atomicAdd(&hc[thin_at(d)], 1u);
         } else {
-            atomicAdd((unsigned long long *)&h[d], 1ull);
-            atomicAdd((unsigned long long *)&h[STS_NBIN + d], mant >> 26);
-            atomicAdd((unsigned long long *)&h[2 * STS_NBIN + d], mant & ((1ull << 26) - 1));
+            u64 n = 1;
+            if (many) { // uniform: equal weights as a rule, which would queue on one bin; one lane adds for all
+                const u64 here = __ballot(true);
+                if (__ballot(d == (u32)__builtin_amdgcn_readfirstlane((int)d) && mant == sts_firstlane(mant)) == here) {
+                    if (sts_lanes_below(here) != 0) return;
+                    n = (u64)__popcll(here);
+                }
+            }
+            atomicAdd((unsigned long long *)&h[d], n);
+            atomicAdd((unsigned long long *)&h[STS_NBIN + d], (mant >> 26) * n);
+            atomicAdd((unsigned long long *)&h[2 * STS_NBIN + d], (mant & ((1ull << 26) - 1)) * n);
         }
     }
     // the same of a weight at the first level (shift 105, 11 bits)
@@ -808,7 +822,7 @@ __device__ __forceinline__ bool narrow_cut(E &&each, int e, u64 K, u128 R, Sub &
             __syncthreads();
         }
         cleared = false;
-        each(vshift, vpre, vshift - dw < 64, Binner<THIN>{h, hc, vshift - dw, dw, e});
+        each(vshift, vpre, vshift - dw < 64, Binner<THIN>{h, hc, vshift - dw, dw, e, sub.count > TIES});
         __syncthreads();
         bool ok;
         if (THIN) {

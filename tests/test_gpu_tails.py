@@ -101,3 +101,14 @@ def test_uncut_steps_of_shares_beyond_their_slabs(S, prec):
         amps = amps.astype(np.complex64).astype(np.complex128)
     ko, ao, info = oracle(keys, amps, gs, 8 * N, 0.0)
     check(kg, ag, stats, ko, ao, info, prec)
+
+
+@pytest.mark.parametrize("N,values", [(140000, 1), (300000, 1), (300000, 3)])
+def test_cut_among_many_equal_weights(S, N, values):
+    # more terms of the cut's weight than the selection's buffer holds (65,536): the keys decide
+    rng = np.random.default_rng([N, values])
+    keys, _ = random_state(rng, 40, N)
+    amps = rng.choice([1.0, 1.5, 1j], size=N)[:N].astype(np.complex128) if values > 1 else np.ones(N, dtype=np.complex128)
+    amps = amps * 2.0 ** -9
+    H = np.array([[1, 1], [1, -1]], dtype=np.complex128)
+    steps(S, keys, amps, 40, permutations(rng, 40, 2) + [(pick(rng, 40, 1), H * 0.5), (pick(rng, 40, 1), H)], N // 2 + 1, 0.0, N)
