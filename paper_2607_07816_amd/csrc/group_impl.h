@@ -1041,14 +1041,15 @@ struct SampleSmem {
     float m[STS_SW_NB];
     u64 scan_c[STS_WG / 64];
     double scan_m[STS_WG / 64];
-    u32 flag, hit, cab, eab, inputs;
+    u64 cab;
+    u32 flag, hit, inputs;
     int at_k, at_p;
     float mab, mbe;
 };
 
 // a thread's candidates outside the bins
 struct SampleAcc {
-    u32 c_above = 0, e_above = 0; // (e_above: the sum of their rows)
+    u64 c_above = 0; // count, and the sum of their rows in the upper half
     float m_above = 0.f, m_below = 0.f;
 };
 
@@ -1060,7 +1061,6 @@ __device__ __forceinline__ void sample_begin(SampleSmem &s)
     s.m[threadIdx.x] = 0.f;
     if (threadIdx.x == 0) {
         s.cab = 0;
-        s.eab = 0;
         s.inputs = 0;
         s.mab = 0.f;
         s.mbe = 0.f;
@@ -1072,8 +1072,7 @@ __device__ __forceinline__ void sample_add(SampleSmem &s, SampleAcc &a, u64 wb, 
     const float w = (float)__longlong_as_double((long long)wb);
     const int row = (int)(wb >> 52) - e_lo;
     if (row >= STS_SW_EXPS) {
-        ++a.c_above;
-        a.e_above += (u32)row;
+        a.c_above += ((u64)(u32)row << 32) + 1ull;
         a.m_above += w;
     } else if (row < 0) {
         a.m_below += w;
@@ -1094,20 +1093,15 @@ __device__ __forceinline__ void sample_flush(SampleSmem &s, SampleAcc &a, const 
     const int bank = (int)(blockIdx.x % STS_SW_BANKS);
     u32 *gc = reinterpret_cast<u32 *>(b.sbins);                                   // [bank][bin] counts
     float *gm = reinterpret_cast<float *>(b.sbins + STS_SW_BANKS * STS_SW_NB / 2); // [bank][bin] masses
-    // per bank: [0] inputs sampled, [1] count above the bins, [2] (float) mass
-    // above, and their rows' sum in the upper half, [3] (float) mass below
+    // per bank: [0] inputs sampled, [1] count above the bins, and the sum of their
+    // rows in the upper half, [2] (float) mass above, [3] (float) mass below
     u64 *bt = b.sbins + STS_SW_BANKS * STS_SW_NB + 4 * bank;
-#pragma unroll
-    for (int d = 32; d > 0; d >>= 1) {
-        a.c_above += __shfl_xor(a.c_above, d, 64);
-        a.e_above += __shfl_xor(a.e_above, d, 64);
-        a.m_above += __shfl_xor(a.m_above, d, 64);
-        a.m_below += __shfl_xor(a.m_below, d, 64);
-    }
+    a.c_above = wave_incl_scan(a.c_above); // (lane 63: the sum)
+    a.m_above = wave_incl_scan(a.m_above);
+    a.m_below = wave_incl_scan(a.m_below);
     if (inputs) atomicAdd(&s.inputs, inputs);
-    if ((threadIdx.x & 63) == 0) {
+    if ((threadIdx.x & 63) == 63) {
         atomicAdd(&s.cab, a.c_above);
-        atomicAdd(&s.eab, a.e_above);
         atomicAdd(&s.mab, a.m_above);
         atomicAdd(&s.mbe, a.m_below);
     }
@@ -1120,9 +1114,8 @@ __device__ __forceinline__ void sample_flush(SampleSmem &s, SampleAcc &a, const 
     if (threadIdx.x == 0) {
         if (s.inputs) atomicAdd(&bt[0], (u64)s.inputs);
         if (s.cab) {
-            atomicAdd(&bt[1], (u64)s.cab);
+            atomicAdd(&bt[1], s.cab);
             atomicAdd(reinterpret_cast<float *>(&bt[2]), s.mab);
-            atomicAdd(reinterpret_cast<u32 *>(&bt[2]) + 1, s.eab);
         }
         if (s.mbe != 0.f) atomicAdd(reinterpret_cast<float *>(&bt[3]), s.mbe);
     }
@@ -1155,9 +1148,10 @@ __device__ __forceinline__ void sample_finish(SampleSmem &s, const PassBufs &b, 
     for (int k = 0; k < STS_SW_BANKS; ++k) {
         const u64 *bt = gt + 4 * k;
         sampled += ld_agent(&bt[0]);
-        c_above += ld_agent(&bt[1]);
+        const u64 ab = ld_agent(&bt[1]);
+        c_above += ab & 0xffffffffull;
+        e_above += ab >> 32;
         m_above += (double)__int_as_float((int)ld_agent(reinterpret_cast<const u32 *>(&bt[2])));
-        e_above += ld_agent(reinterpret_cast<const u32 *>(&bt[2]) + 1);
         m_below += (double)__int_as_float((int)ld_agent(reinterpret_cast<const u32 *>(&bt[3])));
     }
     u64 ctot;
