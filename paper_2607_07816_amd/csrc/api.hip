@@ -135,7 +135,7 @@ Layout make_layout(u64 cap, int prec)
     L.dU = take(kULen * 8 + kULen * 4); // U in FP64, then its FP32 rounding
     L.sub_cnt = take((STS_SUB_REGIONS + 1) * 128);
     L.wpart = take(9 * STS_MAX_GROUPS * 8);
-    L.sbins = take(STS_SW_BANKS * (STS_SW_NB + 4) * 8);
+    L.sbins = take(STS_SW_WORDS * 8);
     L.gate = take(2 * sizeof(GateArg)); // the current gate, and the identity
     L.total = o;
     return L;

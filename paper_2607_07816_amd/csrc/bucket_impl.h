@@ -911,7 +911,7 @@ __global__ void __launch_bounds__(64 * WeighWaves<AT>::value, 1)
 // ---------------------------------------------------------------------------
 // sampling pass (as k_tile_sample): the gate on evenly spaced tiles, one per
 // workgroup, or on all of them for a fine window, which then holds the cut for
-// certain (by count; by mass up to its single-precision sums). A chain of
+// certain (by count; by mass up to the rounding of its sums). A chain of
 // latencies - a share's tables, bins to device memory, the last workgroup's
 // scans: 23 us on the 512 tiles of 100,003 terms, 16 on 128 of them, 24 on 256
 // tiles of 2^24 terms.
@@ -937,7 +937,7 @@ __global__ void __launch_bounds__(STS_WG) k_bkt_sample(GateArg g, PassBufs b)
     if (e_prev < 0) return; // uniform: nothing to centre the bins on
     smem_begin<AT, M, BW>(s, g);
     SampleAcc acc;
-    sample_begin(ss);
+    sample_begin(ss, acc, ctl);
     __syncthreads();
     const u32 ntiles = bkt_tiles(g.bkt);
     const u32 stride = ntiles > gridDim.x ? ntiles / gridDim.x : 1;

@@ -1025,8 +1025,8 @@ __global__ void __launch_bounds__(STS_WG, M >= 4 ? 3 : 5) k_tile_hist(const Gate
 // sampling pass (large states): the gate on the first STS_SAMPLE_SPAN inputs
 // of STS_SAMPLE_TILES evenly spaced tiles, the candidates' weights counted in
 // fine bins (exponent field and the top STS_SW_FB fraction bits, over the
-// STS_SW_EXPS exponents around the previous cut) with their masses summed in
-// FP32. The last workgroup scales the sample to the whole input, estimates
+// STS_SW_EXPS exponents around the previous cut) with their masses summed
+// there. The last workgroup scales the sample to the whole input, estimates
 // the bin where this step's cut falls (the rule of Sec. III applied to the
 // sample) and sets the window the histogram pass copies to the side buffer:
 // that bin and its two neighbours inside the same exponent field. The
@@ -1034,36 +1034,40 @@ __global__ void __launch_bounds__(STS_WG, M >= 4 ? 3 : 5) k_tile_hist(const Gate
 // exactly, and a window that misses it costs the extraction pass. Without a
 // previous cut the pass does nothing (the histogram pass then predicts
 // nothing).
+// Masses are needed for a p-mass rule only. Every sum is of whole numbers, or
+// in a fixed order: the window, and with it the order of the survivors,
+// is the same in every run.
 // ---------------------------------------------------------------------------
 // a sampling workgroup's bins and totals
 struct SampleSmem {
-    u32 c[STS_SW_NB];
-    float m[STS_SW_NB];
+    u64 cm[STS_SW_NB]; // counts, and below bit 44 the sums of mantissa >> 29
     u64 scan_c[STS_WG / 64];
     double scan_m[STS_WG / 64];
+    float mab[STS_WG / 64], mbe[STS_WG / 64]; // per wave
+    double above[STS_WG / 64], below[STS_WG / 64];
     u64 cab;
     u32 flag, hit, inputs;
     int at_k, at_p;
-    float mab, mbe;
 };
 
 // a thread's candidates outside the bins
 struct SampleAcc {
     u64 c_above = 0; // count, and the sum of their rows in the upper half
     float m_above = 0.f, m_below = 0.f;
+    bool mass = false;
 };
 
+__device__ __forceinline__ bool by_mass(const DevCtl *ctl) { return ctl->p > 0.0 && ctl->p < 1.0; }
+
 // clear the bins (the caller's barrier follows)
-__device__ __forceinline__ void sample_begin(SampleSmem &s)
+__device__ __forceinline__ void sample_begin(SampleSmem &s, SampleAcc &a, const DevCtl *ctl)
 {
     static_assert(STS_SW_NB == STS_WG, "one bin per thread in the last workgroup");
-    s.c[threadIdx.x] = 0;
-    s.m[threadIdx.x] = 0.f;
+    a.mass = by_mass(ctl);
+    s.cm[threadIdx.x] = 0;
     if (threadIdx.x == 0) {
         s.cab = 0;
         s.inputs = 0;
-        s.mab = 0.f;
-        s.mbe = 0.f;
     }
 }
 
@@ -1078,46 +1082,47 @@ __device__ __forceinline__ void sample_add(SampleSmem &s, SampleAcc &a, u64 wb, 
         a.m_below += w;
     } else {
         const int f = (row << STS_SW_FB) | (int)((wb >> (52 - STS_SW_FB)) & ((1u << STS_SW_FB) - 1));
-        atomicAdd(&s.c[f], 1u);
-        atomicAdd(&s.m[f], w);
+        atomicAdd(&s.cm[f], (1ull << 44) | (sts_mant(wb) >> 29)); // (2^17 candidates of a bank at most)
     }
 }
+
+// the banks of the bins in device memory are followed by two totals of each
+__device__ __forceinline__ u64 *sample_totals(const PassBufs &b) { return b.sbins + STS_SW_BANKS * STS_SW_NB; }
 
 // add the workgroup's bins to one of STS_SW_BANKS copies in device memory
 // (atomics on one address from every workgroup would queue behind each
 // other); `inputs`: the inputs this thread speaks for. Workgroup totals of
 // the out-of-range parts (wave sums, then LDS), then one global atomic per
-// non-empty bin and per total, on the workgroup's bank.
+// non-empty bin and per total, on the workgroup's bank; its masses out of range
+// have a word of their own.
 __device__ __forceinline__ void sample_flush(SampleSmem &s, SampleAcc &a, const PassBufs &b, u32 inputs)
 {
     const int bank = (int)(blockIdx.x % STS_SW_BANKS);
-    u32 *gc = reinterpret_cast<u32 *>(b.sbins);                                   // [bank][bin] counts
-    float *gm = reinterpret_cast<float *>(b.sbins + STS_SW_BANKS * STS_SW_NB / 2); // [bank][bin] masses
     // per bank: [0] inputs sampled, [1] count above the bins, and the sum of their
-    // rows in the upper half, [2] (float) mass above, [3] (float) mass below
-    u64 *bt = b.sbins + STS_SW_BANKS * STS_SW_NB + 4 * bank;
+    // rows in the upper half
+    u64 *bt = sample_totals(b) + 2 * bank;
     a.c_above = wave_incl_scan(a.c_above); // (lane 63: the sum)
-    a.m_above = wave_incl_scan(a.m_above);
-    a.m_below = wave_incl_scan(a.m_below);
+    if (a.mass) {
+        a.m_above = wave_incl_scan(a.m_above);
+        a.m_below = wave_incl_scan(a.m_below);
+    }
     if (inputs) atomicAdd(&s.inputs, inputs);
     if ((threadIdx.x & 63) == 63) {
         atomicAdd(&s.cab, a.c_above);
-        atomicAdd(&s.mab, a.m_above);
-        atomicAdd(&s.mbe, a.m_below);
+        s.mab[threadIdx.x >> 6] = a.m_above;
+        s.mbe[threadIdx.x >> 6] = a.m_below;
     }
     __syncthreads();
-    const u32 cb = s.c[threadIdx.x];
-    if (cb) {
-        atomicAdd(&gc[bank * STS_SW_NB + threadIdx.x], cb);
-        atomicAdd(&gm[bank * STS_SW_NB + threadIdx.x], s.m[threadIdx.x]);
-    }
+    const u64 cb = s.cm[threadIdx.x];
+    if (cb) atomicAdd(&b.sbins[bank * STS_SW_NB + threadIdx.x], cb);
     if (threadIdx.x == 0) {
         if (s.inputs) atomicAdd(&bt[0], (u64)s.inputs);
-        if (s.cab) {
-            atomicAdd(&bt[1], s.cab);
-            atomicAdd(reinterpret_cast<float *>(&bt[2]), s.mab);
+        if (s.cab) atomicAdd(&bt[1], s.cab);
+        if (a.mass) {
+            const float mab = (s.mab[0] + s.mab[1]) + (s.mab[2] + s.mab[3]);
+            const float mbe = (s.mbe[0] + s.mbe[1]) + (s.mbe[2] + s.mbe[3]);
+            b.wpart[blockIdx.x] = ((u64)__float_as_uint(mab) << 32) | __float_as_uint(mbe);
         }
-        if (s.mbe != 0.f) atomicAdd(reinterpret_cast<float *>(&bt[3]), s.mbe);
     }
 }
 
@@ -1128,40 +1133,55 @@ __device__ __forceinline__ void sample_finish(SampleSmem &s, const PassBufs &b, 
                                               u32 least = 0)
 {
     DevCtl *ctl = b.ctl;
-    const u32 *gc = reinterpret_cast<const u32 *>(b.sbins);
-    const float *gm = reinterpret_cast<const float *>(b.sbins + STS_SW_BANKS * STS_SW_NB / 2);
-    const u64 *gt = b.sbins + STS_SW_BANKS * STS_SW_NB;
+    const u64 *gt = sample_totals(b);
+    const u64 K = ctl->K;
+    const double p = ctl->p;
+    const bool p_on = by_mass(ctl);
     // thread t owns bin STS_SW_NB-1-t, so rank order (weight descending) is
     // thread order
     const int t = threadIdx.x;
     const int f = STS_SW_NB - 1 - t;
     u32 c = 0;
-    double m = 0.0;
+    u64 q = 0;
 #pragma unroll
     for (int k = 0; k < STS_SW_BANKS; ++k) {
-        c += ld_agent(&gc[k * STS_SW_NB + f]);
-        m += (double)__int_as_float((int)ld_agent(reinterpret_cast<const u32 *>(&gm[k * STS_SW_NB + f])));
+        const u64 v = ld_agent(&b.sbins[k * STS_SW_NB + f]);
+        c += (u32)(v >> 44);
+        q += v & ((1ull << 44) - 1);
     }
     u64 sampled = 0, c_above = 0, e_above = 0;
-    double m_above = 0.0, m_below = 0.0;
 #pragma unroll
     for (int k = 0; k < STS_SW_BANKS; ++k) {
-        const u64 *bt = gt + 4 * k;
+        const u64 *bt = gt + 2 * k;
         sampled += ld_agent(&bt[0]);
         const u64 ab = ld_agent(&bt[1]);
         c_above += ab & 0xffffffffull;
         e_above += ab >> 32;
-        m_above += (double)__int_as_float((int)ld_agent(reinterpret_cast<const u32 *>(&bt[2])));
-        m_below += (double)__int_as_float((int)ld_agent(reinterpret_cast<const u32 *>(&bt[3])));
+    }
+    double above = 0.0, below = 0.0;
+    if (p_on) { // uniform
+        for (u32 g = (u32)t; g < gridDim.x; g += STS_WG) {
+            const u64 v = ld_agent(&b.wpart[g]);
+            above += (double)__uint_as_float((u32)(v >> 32));
+            below += (double)__uint_as_float((u32)v);
+        }
+        above = wave_incl_scan(above); // (lane 63: the sum)
+        below = wave_incl_scan(below);
+        if ((t & 63) == 63) {
+            s.above[t >> 6] = above;
+            s.below[t >> 6] = below;
+        }
     }
     u64 ctot;
-    double mtot;
     const u64 cex = block_excl_scan<u64, STS_WG>((u64)c, s.scan_c, &ctot) + c_above;
-    const double mex = block_excl_scan<double, STS_WG>(m, s.scan_m, &mtot) + m_above;
-    mtot += m_above + m_below;
-    const u64 K = ctl->K;
-    const double p = ctl->p;
-    const bool p_on = p > 0.0 && p < 1.0;
+    double m = 0.0, mex = 0.0, mtot = 0.0, m_above = 0.0;
+    if (p_on) { // in units of 2^(e_lo - 1046)
+        m = ldexp((double)q, f >> STS_SW_FB);
+        m_above = ldexp((s.above[0] + s.above[1]) + (s.above[2] + s.above[3]), 1046 - e_lo);
+        const double m_below = ldexp((s.below[0] + s.below[1]) + (s.below[2] + s.below[3]), 1046 - e_lo);
+        mex = block_excl_scan<double, STS_WG>(m, s.scan_m, &mtot) + m_above;
+        mtot += m_above + m_below;
+    }
     // the rule scaled to the sample: K of n terms is K * sampled / n of the
     // sample; the mass target is p of the sample's own total
     const double kt = K > 0 && sampled > 0 ? (double)K * (double)sampled / (double)n : 0.0;
@@ -1170,7 +1190,7 @@ __device__ __forceinline__ void sample_finish(SampleSmem &s, const PassBufs &b, 
         s.hit = 0xffffffffu;
         s.at_k = s.at_p = -1;
     }
-    s.c[f] = c; // (the workgroup's own bins are flushed)
+    s.cm[f] = c; // (the workgroup's own bins are flushed)
     __syncthreads();
     if (fine && c) {
         // where each rule is met
@@ -1189,7 +1209,7 @@ __device__ __forceinline__ void sample_finish(SampleSmem &s, const PassBufs &b, 
             ctl->w_mode = 0;
         } else if (fine) {
             // the cut is where a rule is met first: by count exactly there, by
-            // mass (single-precision sums) up to a quarter bin from it
+            // mass (sums rounded to 2^-24) up to a quarter bin from it
             const int k = s.at_k, m = s.at_p;
             const int lo = std::max(k < 0 ? 0 : 4 * k, m < 0 ? 0 : 4 * m - 1);
             const int hi = std::min(std::max(k < 0 ? 0 : 4 * k + 3, m < 0 ? 0 : 4 * m + 4), 4 * STS_SW_NB - 1);
@@ -1206,7 +1226,7 @@ __device__ __forceinline__ void sample_finish(SampleSmem &s, const PassBufs &b, 
             const int lo_sub = sub > 0 ? sub - 1 : 0;
             const int hi_sub = sub + 1 < (1 << STS_SW_FB) ? sub + 1 : sub;
             u32 in = 0;
-            for (int q = lo_sub - sub; q <= hi_sub - sub; ++q) in += s.c[fb + q];
+            for (int q = lo_sub - sub; q <= hi_sub - sub; ++q) in += (u32)s.cm[fb + q];
             ctl->e_w = ex;
             // what the weighing pass sums in registers: from 15 exponent fields
             // below the window on; higher up, but not above the window, where most
@@ -1218,7 +1238,7 @@ __device__ __forceinline__ void sample_finish(SampleSmem &s, const PassBufs &b, 
             ctl->w_mode = in >= least ? 1 : 0;
         }
     }
-    for (int i = t; i < STS_SW_BANKS * (STS_SW_NB + 4); i += STS_WG) st_agent(&b.sbins[i], 0ull);
+    for (int i = t; i < STS_SW_WORDS; i += STS_WG) st_agent(&b.sbins[i], 0ull);
 }
 
 template <typename AT, int M>
@@ -1234,13 +1254,13 @@ __global__ void __launch_bounds__(STS_WG) k_tile_sample(const GateArg *__restric
     const int e_prev = ctl->e_pred;
     if (e_prev < 0) return; // uniform: nothing to centre the bins on
     const int e_lo = e_prev - STS_SW_EXPS / 2; // exponent field of bin row 0
-    sample_begin(ss);
+    SampleAcc acc;
+    sample_begin(ss, acc, ctl);
     const u64 *keys = b.keys;
     const AT *amps = (const AT *)b.amps;
     const u64 ntiles = (n + TT_TG - 1) / TT_TG;
     const u64 stride = ntiles > gridDim.x ? ntiles / gridDim.x : 1;
     const u64 tile = (u64)blockIdx.x * stride;
-    SampleAcc acc;
     u32 inputs = 0;
     __syncthreads();
     if (tile < ntiles) {

@@ -65,7 +65,7 @@ struct PassBufs {
     int copy;             // histogram pass: also keep every candidate above the window, with
                           // the window's amplitudes, in the tile's slab; emit pass: when the
                           // window held the cut, copy the survivors out of the slabs
-    u64 *wpart;           // [9][STS_MAX_GROUPS] (the weighing pass: its sums); histogram passes [6][...]: per histogram workgroup, the count of candidates
+    u64 *wpart;           // [9][STS_MAX_GROUPS] (the sampling pass: masses out of its bins; the weighing pass: its sums); histogram passes [6][...]: per histogram workgroup, the count of candidates
                           // above the window and the mantissa sums (>> 26, & (2^26-1)) of those in
                           // the window's exponent; then the count and sums of those inside it (k_bkt_mid:
                           // in that exponent, then of those in the one below)
@@ -83,8 +83,8 @@ struct PassBufs {
     int recover;          // histogram pass: only after a sampled window that missed
     int whole;            // the histogram pass is known to run
     int keep;             // and puts the candidates into their share's slab
-    u64 *sbins;           // sampling pass: STS_SW_BANKS x STS_SW_NB counts (u32), as many masses
-                          // (float), then 4 totals per bank
+    u64 *sbins;           // sampling pass: STS_SW_BANKS x STS_SW_NB counts and masses, then 2 totals
+                          // per bank
 };
 
 // The slabs of one tile in the tiled side-buffer layout: 2^spl (1 or 4)
@@ -251,6 +251,7 @@ inline u64 sts_compact_groups(u64 n, int m)
 #define STS_SW_EXPS 8                            // exponent fields the sampling bins cover
 #define STS_SW_NB (STS_SW_EXPS << STS_SW_FB)     // sampling bins (256)
 #define STS_SW_BANKS 16                          // copies of the sampling bins in device memory
+#define STS_SW_WORDS (STS_SW_BANKS * (STS_SW_NB + 2)) // their words
 #define STS_SAMPLE_TILES 256                     // tiles the sampling pass runs the gate on
 #define STS_SAMPLE_SPAN 512                      // inputs of each, from the tile's start
 #define STS_SAMPLE_MIN (1ull << 22)              // terms from which a step samples first

@@ -112,3 +112,18 @@ def test_cut_among_many_equal_weights(S, N, values):
     amps = amps * 2.0 ** -9
     H = np.array([[1, 1], [1, -1]], dtype=np.complex128)
     steps(S, keys, amps, 40, permutations(rng, 40, 2) + [(pick(rng, 40, 1), H * 0.5), (pick(rng, 40, 1), H)], N // 2 + 1, 0.0, N)
+
+
+@pytest.mark.parametrize("N", [40000, 150000])
+def test_runs_repeat_bit_for_bit(S, N):
+    # complex64 sums of 3-qubit groups follow the state's order, which a p-mass rule's window shapes
+    rng = np.random.default_rng(N)
+    keys, amps = random_state(rng, 40, N)
+    gs = [(pick(rng, 40, m), C.haar_unitary(rng, 1 << m)) for m in (2, 3, 1, 2, 3, 2, 4, 2)]
+    out = []
+    for _ in range(3):
+        with S.State(40, K=N, p=0.97, precision="c64", capacity=2 * N) as st:
+            st.load_terms(keys, amps)
+            kg, ag, stats = run(st, gs)
+            out.append((kg.tobytes(), ag.tobytes(), stats["W"]))
+    assert out[0] == out[1] == out[2]
