@@ -197,7 +197,10 @@ __global__ void __launch_bounds__(NT) k_tiny(GateArg g, PassBufs b)
                 }
         };
         if (!resolve_cut<NT, true>(each, e, K, make128(s.l1.R_lo, s.l1.R_hi), s.sub, s.u.raw, s.cut)) { // uniform
-            if (t == 0) atomicOr(&ctl->flags, STS_F_UNRESOLVED);
+            if (t == 0) { // (an internal inconsistency: reported, and no term kept)
+                atomicOr(&ctl->flags, STS_F_UNRESOLVED);
+                *b.n_out = 0;
+            }
             return;
         }
         thr_w = s.cut.thr_w;
