@@ -184,12 +184,17 @@ typedef enum {
     STS_K_RADIX_HIST = 0,   /* per-tile digit counts of a grouping-sort pass */
     STS_K_RADIX_SCAN = 1,   /* their scan into per-tile digit offsets        */
     STS_K_RADIX_PASS = 2,   /* one scatter pass of the grouping sort         */
-    STS_K_GROUP_HIST = 3,   /* gate + weight histogram pass                  */
+    STS_K_GROUP_HIST = 3,   /* gate + weight histogram or weighing pass      */
     STS_K_PICK1 = 4,        /* exponent-level cut                            */
-    STS_K_GROUP_EXTRACT = 5,/* gate + copy of the cut's exponent             */
-    STS_K_SIDE_HIST = 6,    /* mantissa-level cut                            */
-    STS_K_FINAL = 7,        /* last levels and LDS sort                      */
-    STS_K_GROUP_EMIT = 8,   /* gate + survivor write                         */
+    STS_K_GROUP_EXTRACT = 5,/* gate + copy of the cut's exponent; bucketed
+                               steps: the extraction, the survivor count and
+                               the recomputing write, which exit at once
+                               where the window held the cut                 */
+    STS_K_SIDE_HIST = 6,    /* mantissa-level cut; bucketed steps: the
+                               histogram pass of a missed window             */
+    STS_K_FINAL = 7,        /* last levels and the exact cut; the selection
+                               of a step by one workgroup; a one-launch step */
+    STS_K_GROUP_EMIT = 8,   /* survivor write                                */
     STS_K_SIDE_EXTRACT = 9, /* copy of the mantissa-level subset             */
     STS_K_TILE_KEPT = 10,   /* survivors per tile                            */
     STS_K_TILE_SCAN = 11,   /* output offsets per tile                       */

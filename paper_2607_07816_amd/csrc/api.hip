@@ -509,8 +509,8 @@ sts_status sort_by_key(sts_ctx *c, u64 n, int prec, u64 **k, void **a, std::arra
 }
 
 // whether a gate of m qubits on the current state is a one-launch step: at
-// 2,048 terms, the most that one workgroup's LDS and registers hold, 35 us
-// instead of 43 as a bucketed step, at 1,024 21
+// 2,048 terms, the most that one workgroup's LDS and registers hold, 33 us
+// (with the gap to the next step) instead of 43 as a bucketed step, at 1,024 21
 bool use_tiny(const sts_ctx *c, int m) { return m <= 2 && c->n_bound <= STS_TINY_MAX; }
 
 // whether it is a bucketed step (not the one step of sts_step_static: putting its terms in bucket order

@@ -698,22 +698,15 @@ __device__ __forceinline__ void flush_one(const PassBufs &b, int e, u64 hi, u64 
     }
 }
 
-// add the LDS bins of single exponents to the global histogram and clear them
-template <int NT = STS_WG> __device__ __forceinline__ void flush_cold(const PassBufs &b, u64 *s_hi, u64 *s_lo)
+// add the LDS bins to the global exponent histogram and clear them
+__device__ __forceinline__ void flush_bins(const PassBufs &b, u64 *s_hi, u64 *s_lo, int hot_lo)
 {
-    for (int i = threadIdx.x; i < TT_NB; i += NT) {
+    for (int i = threadIdx.x; i < TT_NB; i += STS_WG) {
         const u64 hi = s_hi[i], lo = s_lo[i];
         s_hi[i] = 0;
         s_lo[i] = 0;
         flush_one(b, TT_EBASE + i, hi, lo);
     }
-}
-
-// add the LDS bins to the global exponent histogram and clear them
-template <int NT = STS_WG>
-__device__ __forceinline__ void flush_bins(const PassBufs &b, u64 *s_hi, u64 *s_lo, int hot_lo)
-{
-    flush_cold<NT>(b, s_hi, s_lo);
     if (threadIdx.x < TT_HOT) {
         u64 hi = 0, lo = 0;
         const int at = TT_NB + (int)threadIdx.x * TT_HPER;

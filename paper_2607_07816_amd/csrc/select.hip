@@ -12,7 +12,7 @@
 //              buffer of that exponent's candidates,
 //   level 3+ - further 11-bit digits of V inside one workgroup (level 3 from
 //              a histogram built while the level-2 subset is copied out),
-//              until at most 512 terms remain; those are sorted in LDS.
+//              until at most 128 terms remain, whose ranks are counted.
 // Masses are exact: each bin carries the exact integer sum of its weights'
 // mantissas, levels >= 2 share one exponent, and level 1 prefixes are exact
 // integers on the 2^-1074 grid. Every decision therefore equals the one made
@@ -433,8 +433,8 @@ __global__ void __launch_bounds__(256) k_side_hist(PassBufs b, u64 *h2)
 {
     __shared__ u64 s_hi[STS_NBIN];
     __shared__ u64 s_lo[STS_NBIN];
-    __shared__ u128 s_m[256];
-    __shared__ u64 s_c[256];
+    __shared__ u128 s_m[4]; // a wave's each
+    __shared__ u64 s_c[4];
     __shared__ u32 s_hit, s_flag;
     __shared__ Sub s_sub;
     DevCtl *ctl = b.ctl;
