@@ -227,7 +227,7 @@ def main():
     # counter summaries exist for the headline configuration only (unfused
     # 48-qubit circuit, the precision in the file name)
     profile_tag = f"peaked48_K2e24_{prec}" if args.workload == "48q" and not args.fuse else None
-    traffic_gbs = measured_traffic(dom, avg_s, profile_tag)
+    traffic_gbs = measured_traffic(SUMMARY_OF.get(dom, dom), avg_s, profile_tag)
 
     key, prob = st.peak()
     log(f"state peak {key:#x} prob {prob:.4f} (hidden {circuit.hidden:#x})")
@@ -262,7 +262,7 @@ def main():
             "candidates_per_step": timed_cand / max(timed_steps, 1),
         },
         "roofline": {
-            "bound": "hbm",
+            "bound": BOUND_OF.get(dom, "hbm") if profile_tag else "hbm",
             "kernel": dom,
             "achieved": achieved,
             "peak": HBM_PEAK_GBS,
@@ -490,6 +490,13 @@ def bench_serve(args):
         "cpu_baseline": None,
     }
     print(json.dumps(line), flush=True)
+
+
+# The headline step is one of a bucketed state, whose weighing pass is timed as
+# group_hist: its counter summary is named after the pass, and it is bound by
+# the instructions it issues (the counters beside it), at a fifth of HBM's rate.
+SUMMARY_OF = {"group_hist": "weigh_pass"}
+BOUND_OF = {"group_hist": "instruction issue"}
 
 
 def measured_traffic(kind: str, avg_s: float, tag):

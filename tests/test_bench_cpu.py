@@ -41,3 +41,17 @@ def test_traffic_summary_matches_configuration():
         assert abs(got - float(rec["traffic_bytes_per_launch"]) / 1e-4 / 1e9) < 1e-6
     else:
         assert got is None
+
+
+def test_the_headline_kernel_has_a_traffic_summary():
+    # the weighing pass is timed as group_hist; its summary is found, and used while the sources are those it was taken on
+    b = _bench()
+    from paper_2607_07816_amd import profsum
+    name = b.SUMMARY_OF["group_hist"]
+    rec = profsum.read_traffic(os.path.join(ROOT, "profiles", f"{name}_peaked48_K2e24_c64_hbm_traffic.txt"))
+    assert rec["kernel"] == "k_bkt_weigh"
+    got = b.measured_traffic(name, 1e-4, "peaked48_K2e24_c64")
+    if rec.get("source_digest") == profsum.source_digest():
+        assert abs(got - float(rec["traffic_bytes_per_launch"]) / 1e-4 / 1e9) < 1e-6
+    else:
+        assert got is None
