@@ -106,13 +106,14 @@ __device__ __forceinline__ uint2 load_runs(const BktPlan &p, const uint2 *__rest
     return bd[bkt_rep(p, tile) ^ bkt_comb(p, ((u32)sts_lane() & 3u) | ((u32)wv << 2))];
 }
 
-__device__ __forceinline__ Share share_of(uint2 d)
+// the share whose runs four lanes hold, from lane `at` on
+__device__ __forceinline__ Share share_of(uint2 d, int at = 0)
 {
     u32 beg[4], cnt[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        beg[i] = (u32)__builtin_amdgcn_readlane((int)d.x, i);
-        cnt[i] = (u32)__builtin_amdgcn_readlane((int)d.y, i) - beg[i];
+        beg[i] = (u32)__builtin_amdgcn_readlane((int)d.x, at + i);
+        cnt[i] = (u32)__builtin_amdgcn_readlane((int)d.y, at + i) - beg[i];
     }
     Share s;
     s.p1 = cnt[0];
@@ -475,6 +476,7 @@ template <typename AT, int M, typename F>
 __device__ __forceinline__ void share_groups(WaveSmem<AT> &s, const AT *ucol, const GateLoc<M> &g, const Share &t,
                                              const u64 *__restrict__ keys, const AT *__restrict__ amps, F &&body)
 {
+    if (t.n == 0) return;
     if (t.n <= BW_CAP) {
         Staged<AT> st;
         stage_load<AT>(st, t, keys, amps);
@@ -609,6 +611,11 @@ __global__ void __launch_bounds__(STS_WG) k_bkt_hist(const GateArg *__restrict__
     }
     __syncthreads();
     int since_flush = 0;
+    // the runs of 16 shares are loaded together (a state far below its size bound
+    // has many empty ones, each of which would wait for a load: 92 us for 65,536
+    // of them)
+    uint2 next = make_uint2(0, 0);
+    int held = 0;
     for (u32 tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
         if (since_flush == BW_FLUSH) {
             // a tile adds at most 4 * BW_BINNED * 4 candidates to the bins
@@ -618,7 +625,11 @@ __global__ void __launch_bounds__(STS_WG) k_bkt_hist(const GateArg *__restrict__
             __syncthreads();
         }
         ++since_flush;
-        const Share sh = load_share(g.bkt, b.bd_in, tile, wv);
+        if ((held & 15) == 0) {
+            const u32 t = tile + ((u32)sts_lane() >> 2) * gridDim.x;
+            next = load_runs(g.bkt, b.bd_in, t < ntiles ? t : 0u, wv);
+        }
+        const Share sh = share_of(next, 4 * (held++ & 15));
         const bool direct = sh.n > BW_BINNED;
         const u32 sl = (tile << 2) + (u32)wv;
         const u64 slab = (u64)sl << shift;
@@ -975,6 +986,20 @@ __global__ void __launch_bounds__(STS_WG) k_bkt_sample(GateArg g, PassBufs b)
 // the slabs for the copy (347 us at 2^22 complex64 terms when they were computed
 // three times, 251 with the sort)
 // ---------------------------------------------------------------------------
+// the entries of a wave's slabs, one tile after the other: the counts of 64 tiles
+// are loaded together
+struct SlabCounts {
+    u32 held = 0, c = 0;
+    __device__ __forceinline__ u32 next(const PassBufs &b, u32 tile, u32 ntiles, int wv)
+    {
+        if ((held & 63u) == 0) {
+            const u32 t = tile + (u32)sts_lane() * gridDim.x;
+            c = t < ntiles ? b.t_side[(t << 2) + (u32)wv] : 0u;
+        }
+        return (u32)__builtin_amdgcn_readlane((int)c, (int)(held++ & 63u));
+    }
+};
+
 // f(weight, index) of the n entries of a slab, a wave's loads in flight together
 template <typename F> __device__ __forceinline__ void slab_weights(const u64 *__restrict__ w, u32 n, F &&f)
 {
@@ -1030,6 +1055,7 @@ __global__ void __launch_bounds__(STS_WG) k_bkt_extract(const GateArg *__restric
     };
     __syncthreads();
     u32 since = 0;
+    SlabCounts counts;
     for (u32 tile = blockIdx.x; slabs && tile < ntiles; tile += gridDim.x) {
         if (++since > 1u << 8) { // (a tile has four slabs of at most 2^12 entries: sums stay below 2^64)
             __syncthreads();
@@ -1038,7 +1064,7 @@ __global__ void __launch_bounds__(STS_WG) k_bkt_extract(const GateArg *__restric
             __syncthreads();
         }
         const u32 sl = (tile << 2) + (u32)wv;
-        slab_weights(b.side_w + ((u64)sl << b.slab_shift), b.t_side[sl], [&](u64 w, u32) {
+        slab_weights(b.side_w + ((u64)sl << b.slab_shift), counts.next(b, tile, ntiles, wv), [&](u64 w, u32) {
             if ((int)(w >> 52) != e_star) return;
             const u32 d = 2047u - ((u32)(w >> 41) & 2047u);
             atomicAdd(&s_low[d], w & LOW41);
@@ -1139,11 +1165,12 @@ __global__ void __launch_bounds__(STS_WG) k_bkt_count(const GateArg *__restrict_
     const u32 ntiles = bkt_tiles(g.bkt);
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     if (!all && ctl->slab_all) { // uniform
+        SlabCounts counts;
         for (u32 tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
             const u32 sl = (tile << 2) + (u32)wv;
             const u64 slab = (u64)sl << b.slab_shift;
             u32 cnt = 0;
-            slab_weights(b.side_w + slab, b.t_side[sl], [&](u64 w, u32 i) {
+            slab_weights(b.side_w + slab, counts.next(b, tile, ntiles, wv), [&](u64 w, u32 i) {
                 cnt += w > thr_w || (w == thr_w && b.side_key[slab + i] <= thr_k) ? 1u : 0u;
             });
             cnt = wave_incl_scan(cnt);
@@ -1255,6 +1282,13 @@ __device__ __forceinline__ void copy_share(const BktPlan &p, const PassBufs &b, 
     const u32 sl = (tile << 2) + (u32)wv;
     cnt[lane] = 0;
     const u32 na = uni(b.t_above[sl]), ns = uni(b.t_side[sl]), n = na + ns;
+    if (n == 0) { // empty buckets may begin anywhere
+        if (lane < 4u << p.delta) {
+            const u32 in = bkt_rep(p, tile) ^ bkt_comb(p, (lane & 3u) | ((u32)wv << 2));
+            b.bd_out[(in << p.delta) | (lane >> 2)] = make_uint2(0, 0);
+        }
+        return;
+    }
     const u32 base = uni(share_base(b, tile, wv));
     wave_sync();
     const u32 cap = (u32)b.out_cap;
