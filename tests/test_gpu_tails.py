@@ -5,6 +5,7 @@ FP64, compared with the oracle bit for bit."""
 import numpy as np
 import pytest
 
+from paper_2607_07816_amd import batch as B
 from paper_2607_07816_amd import circuits as C
 from tests.helpers import random_state
 from tests.test_gpu_bucketed import S, oracle, run  # noqa: F401 (S: a fixture)
@@ -127,3 +128,48 @@ def test_runs_repeat_bit_for_bit(S, N):
             kg, ag, stats = run(st, gs)
             out.append((kg.tobytes(), ag.tobytes(), stats["W"]))
     assert out[0] == out[1] == out[2]
+
+
+@pytest.mark.parametrize("p", [0.0, 0.9])
+@pytest.mark.parametrize("N", [1, 300, 5000])
+def test_few_terms_under_a_large_bound(S, N, p):
+    # gates that do not branch raise the size bound fourfold each: most shares of the later steps are empty
+    rng = np.random.default_rng(N)
+    keys, amps = random_state(rng, 40, N)
+    cz = [(pick(rng, 40, 2), CZ) for _ in range(9 if N < 1000 else 5)]
+    haar = [(pick(rng, 40, m), C.haar_unitary(rng, 1 << m)) for m in (2, 1, 2)]
+    # (no read between them: it would tell the host the true size)
+    with S.State(40, K=1 << 19, p=p, precision="c128", capacity=1 << 19) as st:
+        st.load_terms(keys, amps)
+        kg, ag, stats = run(st, cz + haar)
+    ko, ao, info = oracle(keys, amps, cz + haar, 1 << 19, p)
+    check(kg, ag, stats, ko, ao, info, "c128")
+
+
+def test_uncut_result_beyond_the_capacity(S):
+    # no rule at all: refused as before, and the state goes on from the terms before the gate
+    rng = np.random.default_rng(3)
+    N = 150000
+    keys, amps = random_state(rng, 40, N)
+    g2, g1 = (pick(rng, 40, 2), C.haar_unitary(rng, 4)), (pick(rng, 40, 1), C.haar_unitary(rng, 2))
+    with S.State(40, K=0, p=0.0, precision="c128", capacity=3 * N) as st:
+        st.load_terms(keys, amps)
+        for _ in range(2):
+            st.apply_gate(*g2)
+            with pytest.raises(S.CapacityError):
+                st.truncate()
+        kg, ag, stats = run(st, [g1])
+    ko, ao, info = oracle(keys, amps, [g1], 0, 0.0)
+    check(kg, ag, stats, ko, ao, dict(fraction=1.0, W=stats["W"]), "c128")
+
+
+@pytest.mark.parametrize("prec", ["c128", "c64"])
+def test_replayed_steps_of_full_states(S, prec):
+    # every key held, steps captured once and replayed: the same terms as launched ones, bit for bit
+    items = [(c, 1 << 18, 0.0) for c, _ in C.batch_workload(2, 9, n_range=(18, 18), depth_range=(4, 4), logk_range=(9, 9))]
+    plain, _ = B.run_batch(items, prec, 2, 0, want_terms=True)
+    for graph in (1, 8):
+        res, _ = B.run_batch(items, prec, 2, graph, want_terms=True)
+        for a, b in zip(plain, res):
+            assert a["status"] == b["status"] == 0 and len(a["keys"]) == 1 << 18
+            assert np.array_equal(a["keys"], b["keys"]) and np.array_equal(a["amps"], b["amps"])
