@@ -693,10 +693,10 @@ __device__ __forceinline__ void flush_fine(u64 *s_acc, FineSums &f, double k1, d
 // One workgroup per CU, whose waves' tables fill the LDS (16 waves for
 // complex64, 12 for complex128): the pass waits on chains of LDS round trips,
 // and more waves hide more of them. Four waves have one tile. Bound by vector
-// instructions (about 1660 a wave and share of 256 terms, 55% of its time):
-// 323 us at 2^24 complex64 terms, where the sorted path took 345 for its three
-// scatters, 83 for their counts and 321 for the histogram; with 12 waves and
-// no register spills 341.
+// instructions (about 1730 a wave and share of 256 terms, 59% of its time):
+// 313 us at 2^24 complex64 terms, where the sorted path took 345 for its three
+// scatters, 83 for their counts and 321 for the histogram. (With 12 waves and
+// no register spills 341 when it took 323.)
 template <typename AT> struct WeighWaves {
     static constexpr int value = sizeof(AT) == 8 ? 16 : 12;
 };
@@ -924,7 +924,7 @@ __global__ void __launch_bounds__(64 * WeighWaves<AT>::value, 1)
 // workgroup, or on all of them for a fine window, which then holds the cut for
 // certain (by count; by mass up to the rounding of its sums). A chain of
 // latencies - a share's tables, bins to device memory, the last workgroup's
-// scans: 23 us on the 512 tiles of 100,003 terms, 16 on 128 of them, 24 on 256
+// scans: 24 us on the 512 tiles of 100,003 terms, 16 on 128 of them, 24 on 256
 // tiles of 2^24 terms.
 // (the gate comes by value and goes to device memory for the step's other
 // kernels: a launch of its own for that cost 5 us a step)
@@ -2034,7 +2034,8 @@ hipError_t launch_m(int kind, const PassBufs &b, int tiles, hipStream_t s, const
 {
     // a pass over tiles by all the workgroups that are resident at once, also
     // where it is launched in case a window missed (exiting at once takes as long
-    // in one workgroup per CU, and a miss at 2^24 terms 4.4 instead of 2.4 ms)
+    // in one workgroup per CU, and a miss at 2^24 terms took 4.4 instead of 2.4 ms
+    // when each of them computed the candidates again; now it adds 1.0 ms)
     const int cap = pass_capacity<AT, M>(kind);
     // the sample's tiles: at 2^24 terms twice as many halve the misses for 1 us
     // of 550, at 2^20 they cost as much as they save

@@ -91,14 +91,15 @@ def kernel_rows(path: str, last: float = 0.5):
     return sorted(rows, key=lambda r: -r[2])
 
 
-def counter_means(path: str, counter: str):
+def counter_means(path: str, counter: str, last: float = 1.0):
     """{short kernel name: (mean value per dispatch, dispatches)} for one
     counter over each kernel's largest-grid dispatches (the steady-state
     launches of the library's kernels; the calibration copy among the
-    runtime's small blits)."""
+    runtime's small blits). `last`: of these, the last fraction only (the
+    persistent kernels have their largest grid while the state still grows)."""
     cur = _db(path).cursor()
     q = """select dispatch_id, kernel_name, grid_size, sum(value) from counters_collection
-           where counter_name = ? group by dispatch_id"""
+           where counter_name = ? group by dispatch_id order by dispatch_id"""
     rows = [(d, short(k), g, v) for d, k, g, v in cur.execute(q, (counter,))]
     best = {}
     for _, k, g, _ in rows:
@@ -107,7 +108,11 @@ def counter_means(path: str, counter: str):
     for _, k, g, v in rows:
         if g == best[k]:
             vals[k].append(v)
-    return {k: (sum(v) / len(v), len(v)) for k, v in vals.items()}
+    out = {}
+    for k, v in vals.items():
+        tail = v[int(len(v) * (1.0 - last)):] or v
+        out[k] = (sum(tail) / len(tail), len(tail))
+    return out
 
 
 def cmd_trace(args):
@@ -133,8 +138,8 @@ def _copy_entry(means):
 
 
 def cmd_traffic(args):
-    f = counter_means(args.fetch, "FETCH_SIZE")
-    w = counter_means(args.write, "WRITE_SIZE")
+    f = counter_means(args.fetch, "FETCH_SIZE", args.last)
+    w = counter_means(args.write, "WRITE_SIZE", args.last)
     ck_f, (copy_f, _) = _copy_entry(f)
     ck_w, (copy_w, _) = _copy_entry(w)
     scale_f = args.copy_bytes / (copy_f * 1024.0)
@@ -175,12 +180,13 @@ def cmd_counters(args):
     for db in args.db:
         cur = _db(db).cursor()
         for (c,) in cur.execute("select distinct counter_name from counters_collection").fetchall():
-            for k, (v, n) in counter_means(db, c).items():
+            for k, (v, n) in counter_means(db, c, args.last).items():
                 vals[k][c] = (v, n)
     kernels = [k for k in sorted(vals) if any(k.startswith(p) for p in args.kernel)]
     if not kernels:
         raise SystemExit(f"none of {args.kernel} in {sorted(vals)}")
-    out = ["# rocprofv3 counters per dispatch (mean over each kernel's largest-grid dispatches)"]
+    out = ["# rocprofv3 counters per dispatch (mean over each kernel's largest-grid dispatches"
+           + (f", the last {args.last:.0%})" if args.last < 1.0 else ")")]
     for i, cmd in enumerate(args.command):
         out.append(f"# command {i + 1}: {cmd}")
     out.append(f"# library source digest: {source_digest()}")
@@ -221,10 +227,12 @@ def main(argv=None):
     c.add_argument("--command", default="")
     c.add_argument("--command-fetch", default="")
     c.add_argument("--command-write", default="")
+    c.add_argument("--last", type=float, default=1.0)
     q = sub.add_parser("counters")
     q.add_argument("db", nargs="+")
     q.add_argument("--kernel", action="append", required=True, help="kernel name prefix (repeatable)")
     q.add_argument("--command", action="append", default=[], help="command of each pass (repeatable)")
+    q.add_argument("--last", type=float, default=1.0)
     args = ap.parse_args(argv)
     {"trace": cmd_trace, "traffic": cmd_traffic, "counters": cmd_counters}[args.mode](args)
 

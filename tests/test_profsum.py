@@ -74,3 +74,12 @@ def test_counters_per_dispatch_and_wave(tmp_path, capsys):
     # steady dispatch only (grid 800): 3200 instructions over 32 waves
     assert "3200" in line and "100.0 per wave" in line
     assert "# command 2: y" in out
+
+
+def test_only_the_last_dispatches(tmp_path):
+    # a persistent kernel has the same grid while the state grows: the last fraction is the steady state
+    db = tmp_path / "c_results.db"
+    _make_db(db, "SQ_WAVES", [(i, "void k_bkt_weigh<float2>(PassBufs)", 256, [float(v)]) for i, v in
+                              enumerate([1, 2, 4, 8, 8, 8], 1)])
+    assert profsum.counter_means(str(db), "SQ_WAVES")["k_bkt_weigh<c64>"] == (31 / 6, 6)
+    assert profsum.counter_means(str(db), "SQ_WAVES", 0.5)["k_bkt_weigh<c64>"] == (8.0, 3)
