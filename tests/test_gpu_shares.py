@@ -145,3 +145,37 @@ def test_untruncated_gates_of_crowded_terms(S, N, bits):
             kg, ag = st.read_terms()
             assert np.array_equal(kg, ko)
             assert np.array_equal(ag.view(np.uint64), ao.view(np.uint64))
+
+
+@pytest.mark.parametrize("prec", ["c128", "c64"])
+@pytest.mark.parametrize("n", [8, 9, 40, 64])
+def test_few_terms_to_and_from_the_host(S, n, prec):
+    # up to 1,024 terms and 512 per 8 qubits the host orders and checks them, the device more
+    line = 1024 + 512 * -(-n // 8)
+    rng = np.random.default_rng(n)
+    for N in sorted({min(N, 1 << n) for N in (1, 2, 255, 1000, line, line + 1)}):
+        ends = np.array([0, (1 << n) - 1], np.uint64)
+        keys = np.unique(np.concatenate([ends, rng.integers(0, ends[1], size=4 * N, dtype=np.uint64, endpoint=True)]))
+        keys = rng.permutation(keys)[:N]
+        amps = rng.standard_normal(len(keys)) + 1j * rng.standard_normal(len(keys))
+        want = np.argsort(keys)
+        rounded = amps if prec == "c128" else amps.astype(np.complex64).astype(np.complex128)
+        with S.State(n, K=0, p=0.0, precision=prec, capacity=8192) as st:
+            st.load_terms(keys, amps)
+            for bad in ("twice", "range", "nan", "inf"):
+                k, a = keys.copy(), amps.copy()
+                if bad == "twice":
+                    if len(k) < 2:
+                        continue
+                    k[-1] = k[0]
+                elif bad == "range":
+                    if n == 64:
+                        continue
+                    k[len(k) // 2] = np.uint64(1 << n)
+                else:
+                    a[-1] = complex(0.0, np.nan) if bad == "nan" else complex(np.inf, 0.0)
+                with pytest.raises(Exception):
+                    st.load_terms(k, a)
+            for _ in range(2):
+                kg, ag = st.read_terms()
+                assert np.array_equal(kg, keys[want]) and np.array_equal(ag, rounded[want])
